@@ -330,15 +330,15 @@ int compress_impl(const calidrop_params* p, const void* q_win, const void* k, co
                          win_lse);
       if ((rc = launch_status("rowlse_import"))) return rc;
     } else {
-      if (L.RB == 256) hipLaunchKernelGGL((cd::score_rowstats_direct_kernel<T, D, 4>), grid_s, dim3(256), 0, st, sa);
-      else hipLaunchKernelGGL((cd::score_rowstats_direct_kernel<T, D, 2>), grid_s, dim3(256), 0, st, sa);
+      if (L.RB == 256) hipLaunchKernelGGL((cd::score_rowstats_kernel<T, D, 2, 8>), grid_s, dim3(512), 0, st, sa);
+      else hipLaunchKernelGGL((cd::score_rowstats_kernel<T, D, 2, 4>), grid_s, dim3(256), 0, st, sa);
       if ((rc = launch_status("score_rowstats"))) return rc;
       if (L.NCH > 64) hipLaunchKernelGGL(cd::rowstats_merge_kernel<64>, dim3(static_cast<unsigned>((rows + 3) / 4)), dim3(256), 0, st, sa);
       else hipLaunchKernelGGL(cd::rowstats_merge_kernel<16>, dim3(static_cast<unsigned>((rows + 15) / 16)), dim3(256), 0, st, sa);
       if ((rc = launch_status("rowstats_merge"))) return rc;
     }
-    if (L.RB == 256) hipLaunchKernelGGL((cd::score_votes_kernel<T, D, 8>), grid_s, dim3(512), 0, st, sa);
-    else hipLaunchKernelGGL((cd::score_votes_kernel<T, D, 4>), grid_s, dim3(256), 0, st, sa);
+    if (L.RB == 256) hipLaunchKernelGGL((cd::score_votes_kernel<T, D, 2, 8>), grid_s, dim3(512), 0, st, sa);
+    else hipLaunchKernelGGL((cd::score_votes_kernel<T, D, 2, 4>), grid_s, dim3(256), 0, st, sa);
     if ((rc = launch_status("score_votes"))) return rc;
   }
 
@@ -623,9 +623,6 @@ int recal_packed_impl(const calidrop_params* p, const void* q_t, const void* k_e
   return launch_status("attend_finalize(recalibrate, packed)");
 }
 
-constexpr int kH2oRowTiles = CD_H2O_ROW_TILES;        // 16-row tiles per wave in the H2O scoring passes
-constexpr int kH2oBlock = 4 * 16 * kH2oRowTiles;      // stationary rows (or keys) per workgroup
-
 struct H2oLayout {
   size_t row_lse, vote, score, bitmap, q_last, part_o, part_ml, sel_hist, sel_cnt, total;
   int lse_stride, W32, NSEG;
@@ -674,12 +671,12 @@ int h2o_impl(const calidrop_params* p, int n_local, const void* q_full, const vo
   ha.vote = reinterpret_cast<float*>(ws + L.vote);
   ha.plane = vote_plane(total_tokens, p->n_kv_heads);
   ha.q_last = ws + L.q_last;
-  const int nblk = ceil_div(max_seq_len, kH2oBlock);
+  const int nblk = ceil_div(max_seq_len, cd::h2o_block<T>());     // blocks of stationary rows (or keys)
   // always launched: it also extracts Q_{-1}, which prompts within the budget need as C_q
-  hipLaunchKernelGGL((cd::h2o_rowlse_kernel<T, D, kH2oRowTiles>), dim3(nblk, p->batch * p->n_q_heads), dim3(256), 0, st, ha);
+  hipLaunchKernelGGL((cd::h2o_rowlse_kernel<T, D>), dim3(nblk, p->batch * p->n_q_heads), dim3(256), 0, st, ha);
   if ((rc = launch_status("h2o_rowlse"))) return rc;
   if (max_seq_len > p->budget) {
-    hipLaunchKernelGGL((cd::h2o_votes_kernel<T, D, kH2oRowTiles>), dim3((nblk + 1) / 2, bg, G), dim3(256), 0, st, ha);
+    hipLaunchKernelGGL((cd::h2o_votes_kernel<T, D>), dim3((nblk + 1) / 2, bg, G), dim3(256), 0, st, ha);
     if ((rc = launch_status("h2o_votes"))) return rc;
   }
   // selection: the votes are the scores (no pooling); the local window plays the part of the

@@ -14,11 +14,20 @@
 #include "cd_common.h"
 #include "cd_score.h"
 
+#include <type_traits>
+
 namespace cd {
 
-#ifndef CD_H2O_ROW_TILES
-#define CD_H2O_ROW_TILES 2     // 16-row tiles of stationary rows per wave (build-time tuning knob)
-#endif
+// Both passes run at the chip's power limit (the clock settles near 2 GHz), so what counts is the energy per
+// logit: with 64 stationary rows per wave a fragment read from LDS serves 4 row tiles instead of 2.  Together
+// with the stage loads overlapped and branch-free full stages, one layer of 32 query heads x 32768 rows:
+// both passes 8.7 -> 7.9 ms; 32 rows per wave 8.2 ms, 128 rows 8.0 ms, 32 x 32 x 16 matrix instructions 8.4 ms
+// (same cycles, lower clock).  A dense bf16 product of 8192 x 8192 reaches 1.33 PFLOP/s on the same card, at which
+// the 8.8 TFLOP of the two passes would take 6.6 ms without a single exponential.
+// fp32 keeps 32 rows: 64 would need all 256 registers.
+// 16-row tiles of stationary rows per wave, and stationary rows (or keys) per workgroup of 4 waves.
+template <typename T> constexpr int h2o_tiles() { return sizeof(T) == 2 ? 4 : 2; }
+template <typename T> constexpr int h2o_block() { return 4 * 16 * h2o_tiles<T>(); }
 
 struct H2oArgs {
   const void* q_full;        // packed like K with Hq heads: sequence b at token seq_off[b], inside [Hq][n_b][D]
@@ -34,11 +43,10 @@ struct H2oArgs {
   void* q_last;              // [batch][Hq][D]: the last prompt query of every head (Q_{-1})
 };
 
-// RT = 16-row tiles of stationary rows per wave (a workgroup holds 4 * 16 * RT of them).
-template <typename T, int D, int RT>
-__global__ __launch_bounds__(256) void h2o_rowlse_kernel(H2oArgs a) {
+template <typename T, int D>
+__global__ __launch_bounds__(256, 2) void h2o_rowlse_kernel(H2oArgs a) {
   using KS = KeyStream<T, D>;
-  constexpr int KT = KS::KT, NK = KS::NK, SK = KS::kStageKeys, EPL = KS::EPL, KD = KS::KD;
+  constexpr int RT = h2o_tiles<T>(), KT = KS::KT, NK = KS::NK, SK = KS::kStageKeys, EPL = KS::EPL, KD = KS::KD;
   constexpr int WR = 16 * RT, BR = 4 * WR;
   int vx, vh;                                    // row block and (sequence, query head) of this workgroup
   xcd_head_major(vx, vh);
@@ -75,6 +83,8 @@ __global__ __launch_bounds__(256) void h2o_rowlse_kernel(H2oArgs a) {
   float m[RT], l[RT];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) { m[rt] = -INFINITY; l[rt] = 0.f; }
+  typename KS::Frags fr;
+  fr.init(i, c);
 
   const int key_end = min(n, i0 + BR);           // no row of the block sees a key beyond its last row
   const int nstages = (key_end + SK - 1) / SK;
@@ -83,10 +93,10 @@ __global__ __launch_bounds__(256) void h2o_rowlse_kernel(H2oArgs a) {
   ks.issue(kbase, 0, n, s_k[0]);
 
   // S^T tile kt of a stage: keys 16 kt .. 16 kt + 15 against this wave's rows
-  auto mma_tile = [&](const char* lds, int kt, f32x4 (&acc)[RT]) {
+  auto mma_tile = [&](const char* lds, int kt, f32x4 (&acc)[RT]) __attribute__((always_inline)) {
     u32x4 kf[NK];
 #pragma unroll
-    for (int kk = 0; kk < NK; ++kk) kf[kk] = KS::frag(lds, kt, kk, i, c);
+    for (int kk = 0; kk < NK; ++kk) kf[kk] = fr.get(lds, kt, kk);
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
       acc[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -94,45 +104,39 @@ __global__ __launch_bounds__(256) void h2o_rowlse_kernel(H2oArgs a) {
       for (int kk = 0; kk < NK; ++kk) mma_step<T>(acc[rt], kf[kk], qf[rt][kk]);
     }
   };
-  // acc[rt][r] <-> key kfirst + r, row (rt, i)
-  auto softmax_tile = [&](const f32x4 (&acc)[RT], int kfirst, bool full, bool first) {
-    if (full) {
-      // The sum is taken against a reference m that need not be the row maximum: m + log2(sum of
-      // exp2(s - m)) is the same number for any m that keeps the terms in range.  The reference is
-      // the logit of key 0 (every row sees it); only when a sum outgrows 2^64 is the tile redone
-      // against its true maximum.  This saves the running-maximum arithmetic on every tile.
-      if (first) {
+  // A stage every row of the wave sees completely, as one straight run of code: fragment reads, matrix
+  // products and exponentials of neighbouring key tiles have no branch between them and are scheduled
+  // into each other.  The sum is taken against a reference m that need not be the row maximum:
+  // m + log2(sum of exp2(s - m)) is the same number for any m that keeps the terms in range.  The
+  // reference is the logit of key 0 (every row sees it).
+  auto stage_full = [&](const char* lds, auto first) __attribute__((always_inline)) {
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) m[rt] = __shfl(acc[rt][0] * a.sl2, i);     // lane (i, c = 0), r = 0: key 0
-      }
-      float l_old[RT];
-      bool big = false;
+    for (int kt = 0; kt < KT; ++kt) {
+      f32x4 t[RT];                    // t[rt][r] <-> key 4 c + r of the tile, row (rt, i)
+      mma_tile(lds, kt, t);
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
-        l_old[rt] = l[rt];
-        const float nm = -m[rt];
-        l[rt] += (fast_exp2(fmaf(acc[rt][0], a.sl2, nm)) + fast_exp2(fmaf(acc[rt][1], a.sl2, nm))) +
-                 (fast_exp2(fmaf(acc[rt][2], a.sl2, nm)) + fast_exp2(fmaf(acc[rt][3], a.sl2, nm)));
-        big |= !(l[rt] <= 0x1p+64f);
-      }
-      if (__any(big)) {
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-          const float tm = fmaxf(fmaxf(acc[rt][0], acc[rt][1]), fmaxf(acc[rt][2], acc[rt][3])) * a.sl2;
-          const float mn = fmaxf(m[rt], tm);
-          const float nm = -mn;
-          l[rt] = l_old[rt] * fast_exp2(m[rt] - mn) +
-                  ((fast_exp2(fmaf(acc[rt][0], a.sl2, nm)) + fast_exp2(fmaf(acc[rt][1], a.sl2, nm))) +
-                   (fast_exp2(fmaf(acc[rt][2], a.sl2, nm)) + fast_exp2(fmaf(acc[rt][3], a.sl2, nm))));
-          m[rt] = mn;
+        if constexpr (decltype(first)::value) {
+          if (kt == 0) m[rt] = __shfl(t[rt][0] * a.sl2, i);                 // lane (i, c = 0), result 0: key 0
         }
+        const float nm = -m[rt];
+        l[rt] += (fast_exp2(fmaf(t[rt][0], a.sl2, nm)) + fast_exp2(fmaf(t[rt][1], a.sl2, nm))) +
+                 (fast_exp2(fmaf(t[rt][2], a.sl2, nm)) + fast_exp2(fmaf(t[rt][3], a.sl2, nm)));
       }
-    } else {
+    }
+  };
+  // Any stage: per-row causal mask, running maximum.
+  auto stage_masked = [&](const char* lds, int key0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) {
+      f32x4 t[RT];
+      mma_tile(lds, kt, t);
+      const int kfirst = key0 + 16 * kt + 4 * c;
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
         float x[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) x[r] = (kfirst + r <= lim[rt]) ? acc[rt][r] * a.sl2 : -INFINITY;
+        for (int r = 0; r < 4; ++r) x[r] = (kfirst + r <= lim[rt]) ? t[rt][r] * a.sl2 : -INFINITY;
         const float tm = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
         const float mn = fmaxf(m[rt], tm);
         const float ms = (mn == -INFINITY) ? 0.f : mn;
@@ -142,31 +146,43 @@ __global__ __launch_bounds__(256) void h2o_rowlse_kernel(H2oArgs a) {
       }
     }
   };
-  // One stage.  The matrix products of tile kt+1 are issued before the softmax arithmetic of
-  // tile kt, so that the matrix cores and the vector ALU of this wave work at the same time.
-  auto compute = [&](const char* lds, int key0) {
+  auto compute = [&](const char* lds, int key0) __attribute__((always_inline)) {
     if (key0 > wrow0 + WR - 1 || wrow0 >= n) return;        // nothing of this stage is visible to the wave
     const bool full = key0 + SK - 1 <= wrow0 && wrow0 + WR <= n;   // every key visible to every (real) row
-    f32x4 acc[2][RT];
-    mma_tile(lds, 0, acc[0]);
+    bool masked = !full;
+    if (full) {
+      float l_old[RT];
 #pragma unroll
-    for (int kt = 0; kt < KT; ++kt) {
-      if (kt + 1 < KT) mma_tile(lds, kt + 1, acc[(kt + 1) & 1]);
-      softmax_tile(acc[kt & 1], key0 + 16 * kt + 4 * c, full, key0 == 0 && kt == 0);
+      for (int rt = 0; rt < RT; ++rt) l_old[rt] = l[rt];
+      if (key0 == 0) stage_full(lds, std::true_type{});
+      else stage_full(lds, std::false_type{});
+      // a sum that outgrew 2^64: the stage is redone against its running maximum
+      bool big = false;
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) big |= !(l[rt] <= 0x1p+64f);
+      masked = __any(big);
+      if (masked) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) l[rt] = l_old[rt];
+      }
     }
+    if (masked) stage_masked(lds, key0);
   };
 
   // stage s is computed from buffer s & 1 while the loads of stage s + 1 fill the other one; the
   // barrier both publishes stage s and says that everyone is done reading the buffer about to be
   // refilled
-  for (int s = 0; s < nstages; ++s) {
-    ks.wait_all();
-    __syncthreads();
-    if (s + 1 < nstages) ks.issue(kbase, (s + 1) * SK, n, s_k[(s + 1) & 1]);
-    compute(s_k[s & 1], s * SK);
+  auto step = [&](int st, const char* __restrict cur, char* __restrict nxt) __attribute__((always_inline)) {
+    if (st + 1 < nstages) ks.issue(kbase, (st + 1) * SK, n, nxt);
+    compute(cur, st * SK);
+  };
+  operands_ready();
+  for (int st = 0; st < nstages; ++st) {
+    stage_barrier();
+    step(st, s_k[st & 1], s_k[(st + 1) & 1]);
   }
 
-  // merge the four lanes that hold the same row (different keys); padding rows get +inf so that
+  // merge the lanes that hold the same row (different keys); padding rows get +inf so that
   // pass 2 turns them into probability 0
   float* out = a.row_lse + static_cast<int64_t>(b * a.Hq + hq) * a.lse_stride;
 #pragma unroll
@@ -178,10 +194,10 @@ __global__ __launch_bounds__(256) void h2o_rowlse_kernel(H2oArgs a) {
   }
 }
 
-template <typename T, int D, int RT>
-__global__ __launch_bounds__(256) void h2o_votes_kernel(H2oArgs a) {
+template <typename T, int D>
+__global__ __launch_bounds__(256, 2) void h2o_votes_kernel(H2oArgs a) {
   using KS = KeyStream<T, D>;
-  constexpr int KT = KS::KT, NK = KS::NK, SK = KS::kStageKeys, EPL = KS::EPL, KD = KS::KD;
+  constexpr int RT = h2o_tiles<T>(), KT = KS::KT, NK = KS::NK, SK = KS::kStageKeys, EPL = KS::EPL, KD = KS::KD;
   constexpr int WR = 16 * RT, BR = 4 * WR;
   // grid: x = pair of key blocks (block x and its mirror nblk-1-x: early keys are seen by many
   // rows, late keys by few, so every workgroup gets the same amount of work), y = (sequence, KV
@@ -208,6 +224,8 @@ __global__ __launch_bounds__(256) void h2o_votes_kernel(H2oArgs a) {
   __shared__ __attribute__((aligned(16))) float s_z[2][64];      // row log-sum-exp of the staged rows
   KeyStreamDirect<T, D> ks;
   ks.init();
+  typename KS::Frags fr;
+  fr.init(i, c);
 
   for (int job = 0; job < 2; ++job) {
     const int blk = job == 0 ? vx : nblk - 1 - vx;
@@ -232,61 +250,60 @@ __global__ __launch_bounds__(256) void h2o_votes_kernel(H2oArgs a) {
 
     // streamed rows: j0 .. n-1 of this query head, SK per stage, with their log-sum-exp
     const int nstages = (n - j0 + SK - 1) / SK;
-    auto issue = [&](int s) {                      // rows and their log-sum-exp, straight into LDS
-      const int q0 = j0 + s * SK;
-      ks.issue(qbase, q0, n, s_q[s & 1]);
-      if (threadIdx.x < SK) load_to_lds4(lse_row + q0 + threadIdx.x, &s_z[s & 1][0]);
+    auto issue = [&](int st, char* rows, float* z) __attribute__((always_inline)) {   // rows and their log-sum-exp, straight into LDS
+      const int q0 = j0 + st * SK;
+      ks.issue(qbase, q0, n, rows);
+      if (threadIdx.x < SK) load_to_lds4(lse_row + q0 + threadIdx.x, z);
     };
     __syncthreads();                               // the previous job is done with the buffers
-    issue(0);
+    issue(0, s_q[0], s_z[0]);
 
-    // S^T tile kt of a stage: rows 16 kt .. 16 kt + 15 of the stage against this wave's keys
-    auto mma_tile = [&](const char* lds, int kt, f32x4 (&acc)[RT]) {
-      u32x4 qf[NK];
-#pragma unroll
-      for (int kk = 0; kk < NK; ++kk) qf[kk] = KS::frag(lds, kt, kk, i, c);
-#pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        acc[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kk = 0; kk < NK; ++kk) mma_step<T>(acc[rt], qf[kk], kf[rt][kk]);
-      }
-    };
-    // the matrix products of tile kt+1 are issued before the exponentials of tile kt
-    auto compute = [&](int buf, int s) {
-      const int q0 = j0 + s * SK;
-      if (q0 + SK - 1 < wkey0 || wkey0 >= n) return;          // no row of the stage sees a key of this wave
-      const bool full = q0 >= wkey0 + WR - 1;                  // every row sees every key of the wave
-      const char* lds = s_q[buf];
-      f32x4 acc[2][RT];
-      mma_tile(lds, 0, acc[0]);
+    // one stage; with kFull every row sees every key of the wave and the stage is one straight run of
+    // code, in which the exponentials of a row tile are scheduled into the products of the next
+    auto stage = [&](const char* lds, const float* zs, int q0, auto full) __attribute__((always_inline)) {
 #pragma unroll
       for (int kt = 0; kt < KT; ++kt) {
-        if (kt + 1 < KT) mma_tile(lds, kt + 1, acc[(kt + 1) & 1]);
-        const f32x4 z = *reinterpret_cast<const f32x4*>(&s_z[buf][16 * kt + 4 * c]);   // rows q0+16kt+4c+r; +inf beyond n
-        const int qfirst = q0 + 16 * kt + 4 * c;
+        u32x4 qf[NK];
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk) qf[kk] = fr.get(lds, kt, kk);
+        f32x4 t[RT];                  // t[rt][r] <-> row 16 kt + 4 c + r of the stage, key (rt, i)
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
-          const f32x4& t = acc[kt & 1][rt];                    // t[r] <-> row qfirst + r, key (rt, i)
-          if (full) {
-            v[rt] += (fast_exp2(fmaf(t[0], a.sl2, -z[0])) + fast_exp2(fmaf(t[1], a.sl2, -z[1]))) +
-                     (fast_exp2(fmaf(t[2], a.sl2, -z[2])) + fast_exp2(fmaf(t[3], a.sl2, -z[3])));
-          } else {
-            float p[4];
+          t[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-              p[r] = (qfirst + r >= kpos[rt]) ? fast_exp2(fmaf(t[r], a.sl2, -z[r])) : 0.f;
-            v[rt] += (p[0] + p[1]) + (p[2] + p[3]);
+          for (int kk = 0; kk < NK; ++kk) mma_step<T>(t[rt], qf[kk], kf[rt][kk]);
+        }
+        const int q = 16 * kt + 4 * c;
+        const f32x4 z = *reinterpret_cast<const f32x4*>(zs + q);         // log-sum-exp of four rows; +inf beyond n
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+          float p[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            p[r] = fast_exp2(fmaf(t[rt][r], a.sl2, -z[r]));
+            if constexpr (!decltype(full)::value) p[r] = (q0 + q + r >= kpos[rt]) ? p[r] : 0.f;
           }
+          v[rt] += (p[0] + p[1]) + (p[2] + p[3]);
         }
       }
     };
+    auto compute = [&](const char* lds, const float* zs, int st) __attribute__((always_inline)) {
+      const int q0 = j0 + st * SK;
+      if (q0 + SK - 1 < wkey0 || wkey0 >= n) return;          // no row of the stage sees a key of this wave
+      if (q0 >= wkey0 + WR - 1) stage(lds, zs, q0, std::true_type{});
+      else stage(lds, zs, q0, std::false_type{});
+    };
 
-    for (int s = 0; s < nstages; ++s) {
-      ks.wait_all();
-      __syncthreads();
-      if (s + 1 < nstages) issue(s + 1);
-      compute(s & 1, s);
+    auto step = [&](int st, const char* __restrict cur, char* __restrict nxt, const float* __restrict z,
+                    float* __restrict z_nxt) __attribute__((always_inline)) {
+      if (st + 1 < nstages) issue(st + 1, nxt, z_nxt);
+      compute(cur, z, st);
+    };
+    operands_ready();
+    for (int st = 0; st < nstages; ++st) {
+      const int cb = st & 1, ob = cb ^ 1;
+      stage_barrier();
+      step(st, s_q[cb], s_q[ob], s_z[cb], s_z[ob]);
     }
 
 #pragma unroll

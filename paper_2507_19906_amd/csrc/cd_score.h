@@ -13,10 +13,11 @@
 #pragma once
 #include "cd_common.h"
 
+#include <type_traits>
+
 namespace cd {
 
 constexpr int kRowBlock = 128;     // query rows per workgroup, doubled for KV heads with more than 128 window rows
-#define CD_VOTES_WAVES 4          // waves per SIMD the bf16 vote kernel is compiled for
 constexpr int kMaxCalHeads = 8;    // largest GQA group whose calibration logits the vote pass exports
 constexpr int kMinChunkKeys = 256; // keys per workgroup in the scoring passes: a multiple of this
 
@@ -71,11 +72,19 @@ struct KeyStream {
   static_assert(CH == 8 || CH == 16 || CH == 32, "row size not covered by the LDS swizzle");
   __device__ __forceinline__ static int swz(int key) { return CH == 8 ? ((key >> 1) & 7) : (key & 15); }
 
-  // fragment of key tile kt for mma step kk: lane (i, c) gets key 16 kt + i, chunk 4 kk + c
-  __device__ __forceinline__ static u32x4 frag(const char* lds, int kt, int kk, int i, int c) {
-    const int key = 16 * kt + i;
-    return ld16(lds + key * (CH * 16) + (((4 * kk + c) ^ swz(key)) * 16));
-  }
+  // fragment of key tile kt for mma step kk: lane (i, c) gets key 16 kt + i, chunk 4 kk + c.  The swizzle of a
+  // key depends on its position inside its tile only, so a lane needs NK byte offsets for the whole
+  // stream; the tile is an immediate of the LDS read.
+  struct Frags {
+    uint32_t off[NK];
+    __device__ __forceinline__ void init(int i, int c) {
+#pragma unroll
+      for (int kk = 0; kk < NK; ++kk) off[kk] = i * (CH * 16) + (((4 * kk + c) ^ swz(i)) * 16);
+    }
+    __device__ __forceinline__ u32x4 get(const char* lds, int kt, int kk) const {
+      return ld16(lds + off[kk] + kt * (16 * CH * 16));
+    }
+  };
 };
 
 // The same stage layout filled by LDS-direct loads: every lane fetches the 16-byte chunk that
@@ -87,80 +96,67 @@ template <typename T, int D, int NT = 256>
 struct KeyStreamDirect {
   using KS = KeyStream<T, D, NT>;
   static constexpr int CH = KS::CH, NLD = KS::NLD, kStageKeys = KS::kStageKeys;
-  int goff[NLD];         // byte offset, inside an in-range stage, of the chunk for slot threadIdx.x + NT u
-  int lkey[NLD], lch[NLD];   // the slot's stage-local key and its global chunk index (for the clamped tail)
+  // Slot threadIdx.x + NT u holds key key0 + u kKeys: the bits of key0 (< kKeys) and u kKeys do not overlap,
+  // so the swizzle of the sum is the exclusive or of the two swizzles and a lane keeps one chunk index.
+  static constexpr int kKeys = NT / CH;
+  uint32_t key0, ch0;    // of slot threadIdx.x: its stage-local key, its global chunk index
 
   __device__ __forceinline__ void init() {
-#pragma unroll
-    for (int u = 0; u < NLD; ++u) {
-      const int slot = threadIdx.x + u * NT;
-      const int key = slot / CH, chp = slot % CH;
-      lkey[u] = key;
-      lch[u] = chp ^ KS::swz(key);
-      goff[u] = key * (CH * 16) + lch[u] * 16;
-    }
+    key0 = threadIdx.x / CH;
+    ch0 = (threadIdx.x % CH) ^ KS::swz(key0);
   }
   // kStream: the rows are read once and not again soon - non-temporal loads
   template <bool kStream = false>
-  __device__ __forceinline__ void issue(const T* kbase, int key0, int n, char* lds) const {
-    const char* base = reinterpret_cast<const char*>(kbase);
-    char* dst = lds + (threadIdx.x >> 6) * 1024;           // wave-uniform
-    if (key0 + kStageKeys <= n) {
-      const char* sbase = base + static_cast<int64_t>(key0) * (CH * 16);
+  __device__ __forceinline__ void issue(const T* kbase, int first_key, int n, char* lds) const {
+    const char* sbase = reinterpret_cast<const char*>(kbase) + static_cast<int64_t>(first_key) * (CH * 16);     // uniform
+    char* dst = lds + wave_index() * 1024;
+    // the loads themselves stand once, behind the choice of the offsets: two copies of them would be merged
+    // by the compiler and lose what it knows about the LDS they write (see stage_barrier)
+    uint32_t off[NLD];
+    if (first_key + kStageKeys <= n) {
 #pragma unroll
-      for (int u = 0; u < NLD; ++u) {
-        if constexpr (kStream) load_to_lds16_stream(sbase + goff[u], dst + u * (NT * 16));
-        else load_to_lds16(sbase + goff[u], dst + u * (NT * 16));
-      }
+      for (int u = 0; u < NLD; ++u) off[u] = (key0 + u * kKeys) * (CH * 16) + ((ch0 ^ KS::swz(u * kKeys)) * 16);
     } else {
 #pragma unroll
-      for (int u = 0; u < NLD; ++u) {
-        const int key = min(key0 + lkey[u], n - 1);          // the tail repeats the last row
-        load_to_lds16(base + static_cast<int64_t>(key) * (CH * 16) + lch[u] * 16, dst + u * (NT * 16));
-      }
+      for (int u = 0; u < NLD; ++u)                            // the tail repeats the last row
+        off[u] = min(key0 + u * kKeys, static_cast<uint32_t>(n - 1 - first_key)) * (CH * 16) + ((ch0 ^ KS::swz(u * kKeys)) * 16);
     }
-  }
-  // all LDS-direct loads this wave has issued have landed
-  __device__ __forceinline__ static void wait_all() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-};
-
-// Query fragments of the 32 rows a wave owns: lane (i, c) holds row 16 rt + i of the wave.
-template <typename T, int D>
-struct WaveQueries {
-  static constexpr int EPL = Elem<T>::kPer16B;
-  static constexpr int KD = Elem<T>::kStepK;
-  static constexpr int NK = D / KD;
-  u32x4 qf[2][NK];
-  int lim[2];        // last visible key position of row (rt, i), -1 for padding rows
-  bool any_rows;     // wave-uniform: this wave owns at least one real row
-
-  // row0: first row (inside the KV head) of the 32 rows of this wave
-  __device__ __forceinline__ void load(const ScoreArgs& a, int b, int g, int row0, int P, int i, int c) {
-    const T* q = static_cast<const T*>(a.q_win);
-    any_rows = row0 < a.R;
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
-      const int rho = row0 + rt * 16 + i;
-      const bool valid = rho < a.R;
-      const int hh = valid ? rho / a.w : 0;
-      const int wi = valid ? rho - hh * a.w : 0;
-      const T* qp = q + (static_cast<int64_t>(b * a.Hq + g * a.G + hh) * a.w + wi) * D + c * EPL;
-#pragma unroll
-      for (int kk = 0; kk < NK; ++kk) qf[rt][kk] = valid ? ld16(qp + kk * KD) : zero16();
-      lim[rt] = valid ? P + wi : -1;
+    for (int u = 0; u < NLD; ++u) {
+      if constexpr (kStream) load_to_lds16_stream(sbase + off[u], dst + u * (NT * 16));
+      else load_to_lds16(sbase + off[u], dst + u * (NT * 16));
     }
   }
 };
 
-// Pass 1 with the key stream loaded straight into LDS (no staging registers, one barrier per stage)
-// and the matrix products of the next key tile issued ahead of the exponentials of the current one.
-// A workgroup of 4 waves keeps 64 RT window-query rows stationary (RT = 2: 128 rows; RT = 4: 256 rows,
-// so that a KV head with up to 256 window rows - G*w - streams its keys once), 16 RT rows per wave.
-template <typename T, int D, int RT>
-__global__ __launch_bounds__(256) void score_rowstats_direct_kernel(ScoreArgs a) {
-  using KS = KeyStream<T, D>;
+// The stage barrier of the streaming kernels: every LDS-direct load this wave has issued has landed, its
+// LDS accesses are done, and so are everyone else's.
+//
+// Whatever follows the barrier inside a stage has to say which LDS it touches, or the compiler puts a wait for
+// the loads just issued in front of the first LDS access (it cannot tell the buffer being filled from the
+// one being read) and the double buffer hides nothing: the stage functions below therefore take every LDS
+// pointer they use as a __restrict parameter, and operands loaded ahead of the stage loop are waited for in
+// front of it (operands_ready), where the compiler sees it - the wait of the barrier it does not.
+__device__ __forceinline__ void stage_barrier() {
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void operands_ready() { __builtin_amdgcn_s_waitcnt(0x0F70); }     // vmcnt(0)
+
+// Pass 1: the key stream goes straight into LDS (no staging registers, one barrier per stage), the next
+// stage while the current one is computed.
+// Bound by HBM at 128 rows (32 layers x 32768 keys: 340 us = 6.3 TB/s, what a plain read of the same size
+// reaches), by the chip's power at 256 (131072 keys: 86 -> 75 us with the stage loads overlapped, 8 waves of
+// 32 rows and 2048 keys per workgroup; 4 waves of 64 rows: 82 us).
+// A workgroup of NR waves keeps 16 RT NR window-query rows stationary, 16 RT per wave (128 rows, or 256 so
+// that a KV head with up to 256 window rows - G*w - streams its keys once).
+template <typename T, int D, int RT, int NR>
+__global__ __launch_bounds__(NR * 64, sizeof(T) == 2 ? 4 : 2) void score_rowstats_kernel(ScoreArgs a) {
+  constexpr int NT = NR * 64;
+  using KS = KeyStream<T, D, NT>;
   constexpr int KT = KS::KT, NK = KS::NK, SK = KS::kStageKeys, EPL = KS::EPL, KD = KS::KD;
-  constexpr int WR = 16 * RT, RB = 4 * WR;
+  constexpr int WR = 16 * RT, RB = NR * WR;
   // every chunk of a (sequence, KV head, row block) behind the same L2, so that its query rows are fetched
   // from memory once and not once per XCD; when the rows do not divide over the XCDs, the chunk index is
   // rotated instead so that the chunks every sequence has do not all land on the same XCDs
@@ -183,7 +179,7 @@ __global__ __launch_bounds__(256) void score_rowstats_direct_kernel(ScoreArgs a)
   const T* kbase = static_cast<const T*>(a.k) + (static_cast<int64_t>(off0) * a.Hkv + static_cast<int64_t>(g) * n) * D;
 
   __shared__ __attribute__((aligned(16))) char s_k[2][KS::kStageBytes];
-  KeyStreamDirect<T, D> ks;
+  KeyStreamDirect<T, D, NT> ks;
   ks.init();
   if (a.keep_k) ks.template issue<false>(kbase, key_base, n, s_k[0]);
   else ks.template issue<true>(kbase, key_base, n, s_k[0]);
@@ -207,12 +203,14 @@ __global__ __launch_bounds__(256) void score_rowstats_direct_kernel(ScoreArgs a)
   float m[RT], l[RT];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) { m[rt] = -INFINITY; l[rt] = 0.f; }
+  typename KS::Frags fr;
+  fr.init(i, c);
 
   // S^T tile kt of a stage: keys 16 kt .. 16 kt + 15 against this wave's rows
-  auto mma_tile = [&](const char* lds, int kt, f32x4 (&acc)[RT]) {
+  auto mma_tile = [&](const char* lds, int kt, f32x4 (&acc)[RT]) __attribute__((always_inline)) {
     u32x4 kf[NK];
 #pragma unroll
-    for (int kk = 0; kk < NK; ++kk) kf[kk] = KS::frag(lds, kt, kk, i, c);
+    for (int kk = 0; kk < NK; ++kk) kf[kk] = fr.get(lds, kt, kk);
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
       acc[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -220,46 +218,38 @@ __global__ __launch_bounds__(256) void score_rowstats_direct_kernel(ScoreArgs a)
       for (int kk = 0; kk < NK; ++kk) mma_step<T>(acc[rt], kf[kk], qf[rt][kk]);
     }
   };
-  // acc[rt][r] <-> key kfirst + r, row (rt, i)
-  auto softmax_tile = [&](const f32x4 (&acc)[RT], int kfirst, bool full, bool first) {
-    if (full) {
-      // every key of the tile is a prefix key, visible to all rows.  The sum is taken against a reference
-      // that need not be the maximum (m + log2 sum exp2(s - m) is the same number for any m that keeps
-      // the terms in range): the logit of the chunk's first key.  Only when a sum outgrows 2^64 is the
-      // tile redone against its true maximum.
-      if (first) {
+  // A stage of prefix keys, visible to all rows, as one straight run of code (no branch between the
+  // fragment reads, matrix products and exponentials of neighbouring key tiles).  The sum is taken
+  // against a reference that need not be the maximum (m + log2 sum exp2(s - m) is the same number for
+  // any m that keeps the terms in range): the logit of the chunk's first key.
+  auto stage_full = [&](const char* lds, auto first) __attribute__((always_inline)) {
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) m[rt] = __shfl(acc[rt][0] * a.sl2, i);     // lane (i, c = 0), r = 0: first key
-      }
-      float l_old[RT];
-      bool big = false;
+    for (int kt = 0; kt < KT; ++kt) {
+      f32x4 t[RT];                               // t[rt][r] <-> key 4 c + r of the tile, row (rt, i)
+      mma_tile(lds, kt, t);
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
-        l_old[rt] = l[rt];
-        const float nm = -m[rt];
-        l[rt] += (fast_exp2(fmaf(acc[rt][0], a.sl2, nm)) + fast_exp2(fmaf(acc[rt][1], a.sl2, nm))) +
-                 (fast_exp2(fmaf(acc[rt][2], a.sl2, nm)) + fast_exp2(fmaf(acc[rt][3], a.sl2, nm)));
-        big |= !(l[rt] <= 0x1p+64f);
-      }
-      if (__any(big)) {
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-          const float tm = fmaxf(fmaxf(acc[rt][0], acc[rt][1]), fmaxf(acc[rt][2], acc[rt][3])) * a.sl2;
-          const float mn = fmaxf(m[rt], tm);
-          const float nm = -mn;
-          l[rt] = l_old[rt] * fast_exp2(m[rt] - mn) +
-                  ((fast_exp2(fmaf(acc[rt][0], a.sl2, nm)) + fast_exp2(fmaf(acc[rt][1], a.sl2, nm))) +
-                   (fast_exp2(fmaf(acc[rt][2], a.sl2, nm)) + fast_exp2(fmaf(acc[rt][3], a.sl2, nm))));
-          m[rt] = mn;
+        if constexpr (decltype(first)::value) {
+          if (kt == 0) m[rt] = __shfl(t[rt][0] * a.sl2, i);                 // lane (i, c = 0), r = 0: first key
         }
+        const float nm = -m[rt];
+        l[rt] += (fast_exp2(fmaf(t[rt][0], a.sl2, nm)) + fast_exp2(fmaf(t[rt][1], a.sl2, nm))) +
+                 (fast_exp2(fmaf(t[rt][2], a.sl2, nm)) + fast_exp2(fmaf(t[rt][3], a.sl2, nm)));
       }
-    } else {
-      // tile reaches into the window: causal mask per row, and the end of the sequence
+    }
+  };
+  // Any stage: causal mask per row, end of the sequence, running maximum.
+  auto stage_masked = [&](const char* lds, int key0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) {
+      f32x4 t[RT];
+      mma_tile(lds, kt, t);
+      const int kfirst = key0 + 16 * kt + 4 * c;
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
         float x[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) x[r] = (kfirst + r <= lim[rt]) ? acc[rt][r] * a.sl2 : -INFINITY;
+        for (int r = 0; r < 4; ++r) x[r] = (kfirst + r <= lim[rt]) ? t[rt][r] * a.sl2 : -INFINITY;
         const float tm = fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]));
         const float mn = fmaxf(m[rt], tm);
         const float ms = (mn == -INFINITY) ? 0.f : mn;
@@ -269,28 +259,41 @@ __global__ __launch_bounds__(256) void score_rowstats_direct_kernel(ScoreArgs a)
       }
     }
   };
-  auto compute = [&](const char* lds, int key0) {
+  auto compute = [&](const char* lds, int key0) __attribute__((always_inline)) {
     if (!any_rows) return;
-    const bool full = key0 + SK <= P;
-    f32x4 acc[2][RT];
-    mma_tile(lds, 0, acc[0]);
+    bool masked = key0 + SK > P;
+    if (!masked) {
+      float l_old[RT];
 #pragma unroll
-    for (int kt = 0; kt < KT; ++kt) {
-      if (kt + 1 < KT) mma_tile(lds, kt + 1, acc[(kt + 1) & 1]);
-      softmax_tile(acc[kt & 1], key0 + 16 * kt + 4 * c, full, key0 == key_base && kt == 0);
+      for (int rt = 0; rt < RT; ++rt) l_old[rt] = l[rt];
+      if (key0 == key_base) stage_full(lds, std::true_type{});
+      else stage_full(lds, std::false_type{});
+      // a sum that outgrew 2^64: the stage is redone against its running maximum
+      bool big = false;
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) big |= !(l[rt] <= 0x1p+64f);
+      masked = __any(big);
+      if (masked) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) l[rt] = l_old[rt];
+      }
     }
+    if (masked) stage_masked(lds, key0);
   };
 
   // stage s is computed from buffer s & 1 while the loads of stage s + 1 fill the other one; the
   // barrier both publishes stage s and says that everyone is done reading the buffer about to be refilled
-  for (int s = 0; s < nstages; ++s) {
-    ks.wait_all();
-    __syncthreads();
-    if (s + 1 < nstages) {
-      if (a.keep_k) ks.template issue<false>(kbase, key_base + (s + 1) * SK, n, s_k[(s + 1) & 1]);
-      else ks.template issue<true>(kbase, key_base + (s + 1) * SK, n, s_k[(s + 1) & 1]);
+  auto step = [&](int st, const char* __restrict cur, char* __restrict nxt) __attribute__((always_inline)) {
+    if (st + 1 < nstages) {
+      if (a.keep_k) ks.template issue<false>(kbase, key_base + (st + 1) * SK, n, nxt);
+      else ks.template issue<true>(kbase, key_base + (st + 1) * SK, n, nxt);
     }
-    compute(s_k[s & 1], key_base + s * SK);
+    compute(cur, key_base + st * SK);
+  };
+  operands_ready();
+  for (int st = 0; st < nstages; ++st) {
+    stage_barrier();
+    step(st, s_k[st & 1], s_k[(st + 1) & 1]);
   }
 
   // merge the four lanes that hold the same row (different keys) and write the chunk partial
@@ -351,11 +354,15 @@ __global__ __launch_bounds__(256) void rowlse_import_kernel(ScoreArgs a, const f
   a.row_lse[gr] = val;
 }
 
-// NW waves of 32 rows each: a row block of RB = 32 NW rows (4 waves: 128 rows, 8 waves: 256 rows).
-template <typename T, int D, int NW>
-__global__ __launch_bounds__(NW * 64, sizeof(T) == 2 ? CD_VOTES_WAVES : 2) void score_votes_kernel(ScoreArgs a) {
-  using KS = KeyStream<T, D, NW * 64>;
-  constexpr int KT = KS::KT, NK = KS::NK, SK = KS::kStageKeys, RB = 32 * NW;
+// NR waves of 16 RT rows each (RT = 2: 4 waves for a block of 128 rows, 8 for 256).  With the stage loads
+// overlapped and the stage free of branches: 448 -> 426 us for 32 layers x 32768 keys (HBM, 160 MiB of votes
+// and logits written into the read stream), 105 -> 80 us for 131072 keys at 256 rows.  64 rows per wave
+// (RT = 4, half the LDS reads) leaves too few waves: 440 us and 90 us or more.
+template <typename T, int D, int RT, int NR>
+__global__ __launch_bounds__(NR * 64, sizeof(T) == 2 ? 4 : 2) void score_votes_kernel(ScoreArgs a) {
+  constexpr int NT = NR * 64;
+  using KS = KeyStream<T, D, NT>;
+  constexpr int KT = KS::KT, NK = KS::NK, SK = KS::kStageKeys, RB = 16 * RT * NR, EPL = KS::EPL, KD = KS::KD;
   // grid: x = key chunk, y = (sequence, KV head, row block).  Workgroups are dealt to the 8 XCDs
   // round-robin in launch order: the launch index is re-read so that every chunk of a y sits behind the
   // same L2 (the stationary query rows are then fetched from memory once, not once per XCD); when y
@@ -382,98 +389,125 @@ __global__ __launch_bounds__(NW * 64, sizeof(T) == 2 ? CD_VOTES_WAVES : 2) void 
   float* vote = a.vote + static_cast<int64_t>(rb) * a.plane + head_tok;
 
   __shared__ __attribute__((aligned(16))) char s_k[2][KS::kStageBytes];
-  __shared__ float s_v[2][NW][2][SK];              // partial votes of a stage per wave and pair of row groups
-  __shared__ float s_z[2][kMaxCalHeads][SK];       // exported calibration logits of a stage, per head
-  WaveQueries<T, D> wq;
-  wq.load(a, b, g, rb * RB + wv * 32, P, i, c);
-  // S tiles are rows x keys here: lane (i, c) holds key i and rows 16 rt + 4 c + r of the wave
-  float lse[2][4];
+  __shared__ float s_v[2][NR * 2 * SK];              // partial votes of a stage per row wave and pair of row groups
+  __shared__ float s_z[2][kMaxCalHeads * SK];       // exported calibration logits of a stage, per head
+  const int row0 = rb * RB + wv * (16 * RT);       // first row of this wave
+  // the key stream goes straight into LDS (no staging registers: one more wave per SIMD fits)
+  KeyStreamDirect<T, D, NT> ks;
+  ks.init();
+  ks.template issue<true>(kbase, key_base, n, s_k[0]);
+  // stationary rows as operands: lane (i, c) holds piece c of row 16 rt + i
+  u32x4 qf[RT][NK];
 #pragma unroll
-  for (int rt = 0; rt < 2; ++rt)
+  for (int rt = 0; rt < RT; ++rt) {
+    const int rho = row0 + rt * 16 + i;
+    const bool valid = rho < a.R;
+    const int hh = valid ? rho / a.w : 0;
+    const int wi = valid ? rho - hh * a.w : 0;
+    const T* qp = static_cast<const T*>(a.q_win) + (static_cast<int64_t>(b * a.Hq + g * a.G + hh) * a.w + wi) * D + c * EPL;
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk) qf[rt][kk] = valid ? ld16(qp + kk * KD) : zero16();
+  }
+  // S tiles are rows x keys here: lane (i, c) holds key i and rows 16 rt + 4 c + r of the wave
+  float lse[RT][4];
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      lse[rt][r] = a.row_lse[static_cast<int64_t>(bg) * a.row_stride + rb * RB + wv * 32 + rt * 16 + 4 * c + r];   // padding rows: +inf
+      lse[rt][r] = a.row_lse[static_cast<int64_t>(bg) * a.row_stride + row0 + rt * 16 + 4 * c + r];   // padding rows: +inf
 
   // Rows that are the last window query of a head (the default calibration query, Alg. 1
   // step 5) also export their logits, so that the calibration pass need not read K again.
   // (the export needs w % 4 == 0, so that such a row is always slot r = 3 of its lane)
-  int cal_head[2];                      // head in group whose last window row is this lane's (rt, r = 3), or -1
-  bool cal_lane = false;
+  int cal_head[RT];                     // head in group whose last window row is this lane's (rt, r = 3), or -1
 #pragma unroll
-  for (int rt = 0; rt < 2; ++rt) {
-    const int rho = rb * RB + wv * 32 + rt * 16 + 4 * c + 3;
-    const bool is_cal = a.cal_logit != nullptr && rho < a.R && (rho % a.w) == a.w - 1;
-    cal_head[rt] = is_cal ? rho / a.w : -1;
-    cal_lane |= is_cal;
+  for (int rt = 0; rt < RT; ++rt) {
+    const int rho = row0 + rt * 16 + 4 * c + 3;
+    cal_head[rt] = (a.cal_logit != nullptr && rho < a.R && (rho % a.w) == a.w - 1) ? rho / a.w : -1;
   }
-  const bool cal_wave = __any(cal_lane);
+  uint32_t cal_mask = 0;                // heads whose last window row is in this row block
+  if (a.cal_logit)
+    for (int hh = 0; hh < a.G; ++hh) cal_mask |= ((hh * a.w + a.w - 1) / RB == rb ? 1u : 0u) << hh;
   float* zrow = a.cal_logit ? a.cal_logit + static_cast<int64_t>(b * a.Hq + g * a.G) * a.zstride : nullptr;
 
-  // the key stream goes straight into LDS (no staging registers: one more wave per SIMD fits)
-  KeyStreamDirect<T, D, NW * 64> ks;
-  ks.init();
-  ks.template issue<true>(kbase, key_base, n, s_k[0]);
-
-  auto compute = [&](const char* lds, float (*sv)[2][SK], float (*sz)[SK]) {
+  // One stage, without a branch up to the export at its end, so that the fragment reads, matrix products
+  // and exponentials of neighbouring key tiles are scheduled into each other.
+  typename KS::Frags fr;
+  fr.init(i, c);
+  auto compute = [&](const char* lds, float* sv, float* sz) __attribute__((always_inline)) {
+    float vs[KT], zc[KT][RT];
 #pragma unroll
     for (int kt = 0; kt < KT; ++kt) {
       u32x4 kf[NK];
 #pragma unroll
-      for (int kk = 0; kk < NK; ++kk) kf[kk] = KS::frag(lds, kt, kk, i, c);
+      for (int kk = 0; kk < NK; ++kk) kf[kk] = fr.get(lds, kt, kk);
       float v = 0.f;
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt) {
+      for (int rt = 0; rt < RT; ++rt) {
         f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int kk = 0; kk < NK; ++kk) mma_step<T>(acc, wq.qf[rt][kk], kf[kk]);
+        for (int kk = 0; kk < NK; ++kk) mma_step<T>(acc, qf[rt][kk], kf[kk]);
 #pragma unroll
         for (int r = 0; r < 4; ++r) v += fast_exp2(fmaf(acc[r], a.sl2, -lse[rt][r]));
-        if (cal_wave && cal_head[rt] >= 0) sz[cal_head[rt]][16 * kt + i] = acc[3] * a.sl2;
+        zc[kt][rt] = acc[3];
       }
-      // only neighbouring row groups are added here (one lane swap); the rest of the sum is left to the
-      // flush: the full four-way reduction costs as many vector instructions per key tile as a third
-      // of the exponentials, and keeping all four shares would cost a workgroup per compute unit in LDS
-      {
-        float lo, hi;
-        pair16(v, lo, hi);
-        if ((c & 1) == 0) sv[wv][c >> 1][16 * kt + i] = lo + hi;
-      }
+      vs[kt] = v;
     }
+    // only neighbouring row groups are added here (one lane swap), the rest of the sum is left to the
+    // flush; both lanes of a pair hold the sum and store it to the same place
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) {
+      float lo, hi;
+      pair16(vs[kt], lo, hi);
+      sv[(2 * wv + (c >> 1)) * SK + 16 * kt + i] = lo + hi;
+    }
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+      if (cal_head[rt] >= 0) {
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt) sz[cal_head[rt] * SK + 16 * kt + i] = zc[kt][rt] * a.sl2;
+      }
   };
-  // after the stage barrier: add the partial votes in a fixed order (waves ascending, inside a wave
-  // (c0 + c1) + (c2 + c3), the inner sums already taken) and store; the second wave stores the exported logits, one coalesced row
-  // per head
-  auto flush = [&](const float (*sv)[2][SK], const float (*sz)[SK], int key0) {
+  // after the stage barrier: add the partial votes in a fixed order (row waves ascending, inside a wave
+  // (c0 + c1) + (c2 + c3), the inner sums already taken) and store; the second wave stores the exported
+  // logits, one coalesced row per head
+  auto flush = [&](const float* sv, const float* sz, int key0) __attribute__((always_inline)) {
     if (threadIdx.x < SK) {
       const int key = key0 + threadIdx.x;
       if (key < P) {
         float tot = 0.f;
 #pragma unroll
-        for (int ww = 0; ww < NW; ++ww)
-          tot += sv[ww][0][threadIdx.x] + sv[ww][1][threadIdx.x];
+        for (int ww = 0; ww < NR; ++ww)
+          tot += sv[2 * ww * SK + threadIdx.x] + sv[(2 * ww + 1) * SK + threadIdx.x];
         __builtin_nontemporal_store(tot, vote + key);    // written once, read by a later kernel: kept out of the caches the K stream uses
       }
-    } else if (zrow != nullptr && threadIdx.x >= 64 && threadIdx.x < 64 + SK) {
+    } else if (cal_mask != 0 && threadIdx.x >= 64 && threadIdx.x < 64 + SK) {
       const int t = threadIdx.x - 64;
       const int key = key0 + t;
       if (key < P)
-        for (int hh = 0; hh < a.G; ++hh)
-          if ((hh * a.w + a.w - 1) / RB == rb)             // heads whose last window row is in this row block
-            __builtin_nontemporal_store(sz[hh][t], zrow + static_cast<int64_t>(hh) * a.zstride + key);
+        for (uint32_t left = cal_mask; left; left &= left - 1u) {
+          const int hh = __ffs(left) - 1;
+          __builtin_nontemporal_store(sz[hh * SK + t], zrow + static_cast<int64_t>(hh) * a.zstride + key);
+        }
     }
   };
 
   // stage s is computed from buffer s & 1 while the loads of stage s + 1 fill the other one; the barrier
   // publishes stage s, says that everyone is done reading the buffer about to be refilled, and hands
   // the partial votes of stage s - 1 to the flush
-  for (int s = 0; s < nstages; ++s) {
-    ks.wait_all();
-    __syncthreads();
-    if (s + 1 < nstages) ks.template issue<true>(kbase, key_base + (s + 1) * SK, n, s_k[(s + 1) & 1]);
-    if (s > 0) flush(s_v[(s - 1) & 1], s_z[(s - 1) & 1], key_base + (s - 1) * SK);
-    compute(s_k[s & 1], s_v[s & 1], s_z[s & 1]);
+  auto step = [&](int st, const char* __restrict cur, char* __restrict nxt, float* __restrict sv, float* __restrict sz,
+                  const float* __restrict sv_prev, const float* __restrict sz_prev) __attribute__((always_inline)) {
+    if (st + 1 < nstages) ks.template issue<true>(kbase, key_base + (st + 1) * SK, n, nxt);
+    if (st > 0) flush(sv_prev, sz_prev, key_base + (st - 1) * SK);
+    compute(cur, sv, sz);
+  };
+  operands_ready();
+  for (int st = 0; st < nstages; ++st) {
+    const int cb = st & 1, ob = cb ^ 1;
+    stage_barrier();
+    step(st, s_k[cb], s_k[ob], s_v[cb], s_z[cb], s_v[ob], s_z[ob]);
   }
-  __syncthreads();
+  stage_barrier();
   flush(s_v[(nstages - 1) & 1], s_z[(nstages - 1) & 1], key_base + (nstages - 1) * SK);
 }
 

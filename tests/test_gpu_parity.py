@@ -80,6 +80,15 @@ def test_shapes_and_ragged_tails(wl):
     run_case(wl)
 
 
+@pytest.mark.parametrize("dtype,Hq,Hkv,D,w", [("bf16", 8, 2, 128, 32), ("bf16", 8, 1, 64, 32), ("fp32", 4, 2, 64, 16),
+                                              ("fp32", 16, 1, 128, 16)])
+def test_scoring_at_the_edges_of_its_key_stages(dtype, Hq, Hkv, D, w):
+    # prompts and prefixes that end one short of, at and one past a stage of 64 (fp32: 32) keys, and at the
+    # second and third stage; 128- and 256-row blocks
+    lens = sorted({e + d + s for e in (64, 128, 192) for d in (-1, 0, 1) for s in (0, w)} | {31 + w, 33 + w})
+    run_case(small(dtype, Hq, Hkv, D, [n for n in lens if n > 24 + w], w, w + 8, 5, T=1, name=f"stage_edges_{dtype}_{D}"))
+
+
 @pytest.mark.parametrize("dtype,D,budget", [("bf16", 128, 64), ("fp32", 64, 200), ("bf16", 64, 300),
                                             ("bf16", 128, 600)])
 def test_many_sequences_single_workgroup_decode(dtype, D, budget):
