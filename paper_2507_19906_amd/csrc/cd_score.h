@@ -19,7 +19,7 @@ namespace cd {
 
 constexpr int kRowBlock = 128;     // query rows per workgroup, doubled for KV heads with more than 128 window rows
 constexpr int kMaxCalHeads = 8;    // largest GQA group whose calibration logits the vote pass exports
-constexpr int kMinChunkKeys = 256; // keys per workgroup in the scoring passes: a multiple of this
+constexpr int kChunkUnit = 64;      // keys per workgroup in the scoring passes: a multiple of this
 
 struct ScoreArgs {
   const void* q_win;
