@@ -105,9 +105,12 @@ constexpr int kFusedMaxRowsFewPairs = 2048;
 
 // How the rows of a streaming-attention pass are split over workgroups.
 struct SplitPlan { int rows_per_split, NS; };
-SplitPlan plan_splits(int heads_kv_total, int max_rows) {
+// `prompt`: a pass over prompt rows.  Where that leaves only a few hundred workgroups with a few tiles per wave
+// each, they are halved down to one tile per wave: 8 KV heads of 8192 rows 7.9 -> 6.3 us at 128 rows instead of 256.
+// Longer splits stay at 32 (131072 rows: 44 us at 4096 rows, 45 us at 1024).
+SplitPlan plan_splits(int heads_kv_total, int max_rows, bool prompt = false) {
   const int kTargetGroups = 4096;                      // ~16 workgroups per compute unit
-  const int kMaxSplits = 32;                           // the merge of the partials is sequential
+  const int kMaxSplits = 32;
   const int kMinRows = cd::kTileRows * cd::kAttWaves;  // one tile per wave
   if (max_rows < 1) max_rows = 1;
   int want = ceil_div(kTargetGroups, heads_kv_total);
@@ -115,6 +118,8 @@ SplitPlan plan_splits(int heads_kv_total, int max_rows) {
   if (want > kMaxSplits) want = kMaxSplits;
   int rps = ceil_div(ceil_div(max_rows, want), kMinRows) * kMinRows;
   if (rps < kMinRows) rps = kMinRows;
+  if (prompt && rps <= 4 * kMinRows)
+    while (rps > kMinRows && static_cast<int64_t>(heads_kv_total) * ceil_div(max_rows, rps) <= 512) rps = ceil_div(rps / 2, kMinRows) * kMinRows;
   return SplitPlan{rps, ceil_div(max_rows, rps)};
 }
 
@@ -140,7 +145,7 @@ CompressLayout compress_layout(const calidrop_params* p, int64_t total_tokens, i
   }
   L.NCH = ceil_div(max_seq_len, L.chunk_keys);
   L.W32 = ceil_div(max_seq_len, 64) * 2;
-  L.sp = plan_splits(p->batch * p->n_kv_heads, max_seq_len);
+  L.sp = plan_splits(p->batch * p->n_kv_heads, max_seq_len, true);
   const size_t rows = static_cast<size_t>(p->batch) * p->n_kv_heads * L.NRB * L.RB;
   const size_t toks = static_cast<size_t>(total_tokens) * p->n_kv_heads;
   size_t off = 0;
@@ -206,8 +211,8 @@ void launch_bitmap(const cd::BitmapArgs& ba, int pairs, hipStream_t st) {
 // stream capture) only launch.
 constexpr size_t kSelMaxLdsBytes = (static_cast<size_t>(cd::kSelMaxLdsKeys) + cd::kSelMaxLdsKeys / 32 + 1) * sizeof(float);
 constexpr int kMaxDevices = 64;
-constexpr int kLdsSlots = 16;                             // kernels that ask for more than 48 KiB of dynamic LDS
-enum { kLdsSelect8 = 0, kLdsSelect16, kLdsSelect32, kLdsVotes };   // first slot of each family (votes: + variant)
+constexpr int kLdsSlots = 8;                              // kernels that ask for more than 48 KiB of dynamic LDS
+enum { kLdsSelect = 0 };                                  // three variants of the selection kernel
 std::atomic<uint8_t> g_lds_ready[kLdsSlots][kMaxDevices]; // zero-initialised: nothing raised yet
 
 // `bytes` is the largest size any call can ask of this kernel, so one setting per (slot, device) is enough.
@@ -240,33 +245,58 @@ int static_scratch_ptr(char** out) {
   return CALIDROP_OK;
 }
 
-// Pooling + selection + gather for scores already in sa.vote.  Heads whose pooled scores fit in
+// Where the gather of the retained rows runs.  In a small call it shares the launch of the streaming pass (a launch
+// less, and the selection kernel's few workgroups no longer copy: 8192 tokens, 8 heads, selection 15 -> 10.5 us), but
+// its workgroups there take the places of streaming ones (LDS and registers are the pass's): with 512 heads of
+// 1024 rows that pass took 392 us instead of 230.  With many heads the selection kernel does it: while one
+// workgroup selects, others copy (140 us for both, against 36 + 100 in two launches).  Otherwise - few heads with large
+// budgets, lists from elsewhere - it has its own launch, or shares that of the given-set preparation.
+enum class GatherIn { kPass, kDone, kOwnLaunch };
+GatherIn gather_place(const calidrop_params* p, const cd::GatherArgs& ga, bool lds_selection) {
+  const int64_t pairs = static_cast<int64_t>(p->batch) * p->n_kv_heads;
+  if (pairs * ga.blocks <= 256) return GatherIn::kPass;
+  return lds_selection && pairs >= 128 ? GatherIn::kDone : GatherIn::kOwnLaunch;
+}
+
+cd::GatherArgs gather_args(const calidrop_params* p, const int32_t* indices, const int32_t* cache_offsets, const void* k, const void* v,
+                           void* k_c, void* v_c) {
+  const int row_bytes = p->head_dim * (p->dtype == CALIDROP_BF16 ? 2 : 4);
+  const int64_t vecs = static_cast<int64_t>(p->budget) * (row_bytes / 16);
+  return cd::GatherArgs{indices, cache_offsets, k, v, k_c, v_c, row_bytes, static_cast<int>((vecs + cd::kGatherVecs - 1) / cd::kGatherVecs)};
+}
+
+// Pooling + selection for scores already in sa.vote.  Heads whose pooled scores fit in
 // LDS are pooled inside the single-workgroup selection kernel; longer ones go through the
 // pooled-score buffer and the multi-workgroup chain.  `window` = trailing positions always kept.
 int run_selection(const calidrop_params* p, int window, int pool_k, int max_seq_len, cd::SelectArgs& se,
-                  cd::ScoreArgs& sa, uint32_t* sel_hist, uint32_t* sel_cnt, int NSEG, hipStream_t st) {
+                  cd::ScoreArgs& sa, uint32_t* sel_hist, uint32_t* sel_cnt, int NSEG, GatherIn& place, hipStream_t st) {
   int rc;
   const int bg = p->batch * p->n_kv_heads;
   const int max_prefix = max_seq_len - window;
   se.write_scores = (p->flags & CALIDROP_OPT_WRITE_SCORES) ? 1 : 0;
-  if (max_prefix <= cd::kSelMaxLdsKeys && p->budget <= cd::kSelMaxLdsKeys && pool_k <= cd::kSelMaxPool &&
-      !(p->flags & CALIDROP_OPT_WIDE_SELECTION)) {
+  const bool lds_selection = max_prefix <= cd::kSelMaxLdsKeys && p->budget <= cd::kSelMaxLdsKeys && pool_k <= cd::kSelMaxPool &&
+                             !(p->flags & CALIDROP_OPT_WIDE_SELECTION);
+  place = gather_place(p, se.gather, lds_selection);
+  se.gather_here = place == GatherIn::kDone;
+  if (lds_selection) {
     // dynamic LDS: staged votes (padded), later reused for the retained indices
-    size_t lds = static_cast<size_t>(p->budget) * sizeof(int32_t);
-    if (max_seq_len > p->budget) {
-      const size_t votes = (static_cast<size_t>(max_prefix) + max_prefix / 32 + 1) * sizeof(float);
-      if (votes > lds) lds = votes;
-    }
-    // positions per thread: the smallest of 8 / 16 / 32 that covers the longest prefix
-    const int per = max_prefix <= cd::kSelThreads * 8 ? 8 : max_prefix <= cd::kSelThreads * 16 ? 16 : 32;
-    const void* fn = per == 8    ? reinterpret_cast<const void*>(&cd::select_gather_lds_kernel<cd::kSelThreads, 8>)
-                     : per == 16 ? reinterpret_cast<const void*>(&cd::select_gather_lds_kernel<cd::kSelThreads, 16>)
-                                 : reinterpret_cast<const void*>(&cd::select_gather_lds_kernel<cd::kSelThreads, 32>);
-    if ((rc = ensure_kernel_lds(per == 8 ? kLdsSelect8 : per == 16 ? kLdsSelect16 : kLdsSelect32, fn, kSelMaxLdsBytes, "select_gather"))) return rc;
-    const dim3 grid(bg), block(cd::kSelThreads);
-    if (per == 8) hipLaunchKernelGGL((cd::select_gather_lds_kernel<cd::kSelThreads, 8>), grid, block, lds, st, se);
-    else if (per == 16) hipLaunchKernelGGL((cd::select_gather_lds_kernel<cd::kSelThreads, 16>), grid, block, lds, st, se);
-    else hipLaunchKernelGGL((cd::select_gather_lds_kernel<cd::kSelThreads, 32>), grid, block, lds, st, se);
+    size_t lds = max_seq_len > p->budget ? (static_cast<size_t>(max_prefix) + max_prefix / 32 + 1) * sizeof(float) : 0;
+    if (se.gather_here) lds = std::max(lds, static_cast<size_t>(p->budget) * sizeof(int32_t));
+    // 1024 threads, and positions per thread: the smallest of 8 / 16 / 32 that covers the longest prefix.
+    const dim3 grid(bg);
+    auto launch = [&](auto per) {
+      constexpr int PER = decltype(per)::value;
+      const auto fn = &cd::select_lds_kernel<cd::kSelThreads, PER>;
+      const int slot = kLdsSelect + (PER == 8 ? 0 : PER == 16 ? 1 : 2);
+      if (int e = ensure_kernel_lds(slot, reinterpret_cast<const void*>(fn), kSelMaxLdsBytes, "select")) return e;
+      hipLaunchKernelGGL(fn, grid, dim3(cd::kSelThreads), lds, st, se);
+      return static_cast<int>(CALIDROP_OK);
+    };
+    using std::integral_constant;
+    if (max_prefix <= cd::kSelThreads * 8) rc = launch(integral_constant<int, 8>{});
+    else if (max_prefix <= cd::kSelThreads * 16) rc = launch(integral_constant<int, 16>{});
+    else rc = launch(integral_constant<int, 32>{});
+    if (rc) return rc;
   } else {
     cd::WideArgs wa{};
     wa.s = se; wa.NSEG = NSEG;
@@ -285,11 +315,28 @@ int run_selection(const calidrop_params* p, int window, int pool_k, int max_seq_
       if ((rc = launch_status("wide_count"))) return rc;
     }
     hipLaunchKernelGGL(cd::wide_emit_kernel, grid_w, dim3(cd::kWideThreads), 0, st, wa);
-    if ((rc = launch_status("wide_emit"))) return rc;
-    const int vecs = p->budget * (se.row_bytes / 16);
-    hipLaunchKernelGGL(cd::gather_kv_kernel, dim3(ceil_div(vecs, 256), bg), dim3(256), 0, st, se);
   }
-  return launch_status("select_gather");
+  return launch_status("select");
+}
+
+// The streaming pass over KV_evict, and the gather unless the selection has done it.
+template <typename T, int D>
+int launch_calibration(const calidrop_params* p, cd::AttendArgs& aa, const cd::GatherArgs& ga, GatherIn place, hipStream_t st) {
+  const bool evicts = aa.max_len > p->budget;          // otherwise no sequence can have anything to evict
+  if (place == GatherIn::kOwnLaunch || (place == GatherIn::kPass && !evicts)) {
+    cd::GatherOnlyArgs go{ga, aa.row_off, aa.total_tokens, p->n_kv_heads, p->budget, aa.max_len};
+    hipLaunchKernelGGL(cd::gather_kv_kernel, dim3(ga.blocks, p->batch * p->n_kv_heads), dim3(256), 0, st, go);
+    if (int rc = launch_status("gather_kv")) return rc;
+  }
+  if (!evicts) return CALIDROP_OK;
+  aa.gather = ga;
+  const bool carry = place == GatherIn::kPass;
+  const dim3 grid(aa.NS + (carry ? ga.blocks : 0), p->n_kv_heads, p->batch);
+  if (aa.cal_logit && carry) hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, true, false, true>), grid, dim3(256), 0, st, aa);
+  else if (aa.cal_logit) hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, true>), grid, dim3(256), 0, st, aa);
+  else if (carry) hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, false, false, true>), grid, dim3(256), 0, st, aa);
+  else hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, false>), grid, dim3(256), 0, st, aa);
+  return launch_status("attend_partial(calibration)");
 }
 
 template <typename T, int D>
@@ -341,18 +388,20 @@ int compress_impl(const calidrop_params* p, const void* q_win, const void* k, co
     if ((rc = launch_status("score_votes"))) return rc;
   }
 
-  // Pooling + selection + gather.  Heads whose pooled scores fit in LDS are pooled inside the
+  // Pooling + selection.  Heads whose pooled scores fit in LDS are pooled inside the
   // selection kernel; longer ones go through the pooled-score buffer in the workspace.
+  const cd::GatherArgs ga = gather_args(p, indices, cache_offsets, k, v, k_c, v_c);
+  GatherIn place;
   cd::SelectArgs se{};
-  se.seq_off = seq_offsets; se.cache_off = cache_offsets; se.total_tokens = total_tokens; se.batch = p->batch;
+  se.gather = ga;
+  se.seq_off = seq_offsets; se.total_tokens = total_tokens; se.batch = p->batch;
   se.Hkv = p->n_kv_heads; se.w = p->window; se.B = p->budget; se.max_seq_len = max_seq_len; se.W32 = L.W32;
-  se.NRB = L.NRB; se.pool_k = p->pool_kernel; se.row_bytes = D * static_cast<int>(sizeof(T));
+  se.NRB = L.NRB; se.pool_k = p->pool_kernel;
   se.vote = sa.vote; se.plane = sa.plane; se.score = sa.score; se.indices = indices; se.cache_lens = cache_lens;
   se.calib = p->calib_size; se.cal_indices = cal_indices;
   se.bitmap = reinterpret_cast<uint32_t*>(ws + L.bitmap);
-  se.k = k; se.v = v; se.k_c = k_c; se.v_c = v_c;
   if ((rc = run_selection(p, p->window, p->pool_kernel, max_seq_len, se, sa, reinterpret_cast<uint32_t*>(ws + L.sel_hist),
-                          reinterpret_cast<uint32_t*>(ws + L.sel_cnt), L.NSEG, st)))
+                          reinterpret_cast<uint32_t*>(ws + L.sel_cnt), L.NSEG, place, st)))
     return rc;
 
   cd::AttendArgs aa{};
@@ -364,19 +413,14 @@ int compress_impl(const calidrop_params* p, const void* q_win, const void* k, co
   aa.cal_logit = sa.cal_logit; aa.zstride = L.zstride;
   aa.part_o = reinterpret_cast<float*>(ws + L.part_o);
   aa.part_ml = reinterpret_cast<float2*>(ws + L.part_ml);
-  if (max_seq_len > p->budget) {
-    const dim3 grid_a(L.sp.NS, p->n_kv_heads, p->batch);
-    if (aa.cal_logit) hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, true>), grid_a, dim3(256), 0, st, aa);
-    else hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, false>), grid_a, dim3(256), 0, st, aa);
-    if ((rc = launch_status("attend_partial(calibration)"))) return rc;
-  }
+  if ((rc = launch_calibration<T, D>(p, aa, ga, place, st))) return rc;
   cd::FinalArgs fa{};
   fa.part_o = aa.part_o; fa.part_ml = aa.part_ml; fa.row_off = seq_offsets; fa.row_len = nullptr;
   fa.total_tokens = total_tokens; fa.batch = p->batch; fa.Hq = p->n_q_heads; fa.Hkv = p->n_kv_heads; fa.G = G;
   fa.w = p->window; fa.B = p->budget; fa.max_len = max_seq_len; fa.rows_per_split = L.sp.rows_per_split;
   fa.NS = L.sp.NS; fa.calib_mode = 1; fa.q_is_window = aa.q_is_window; fa.q = aa.q;
   fa.c_q = c_q; fa.c_out = c_out; fa.c_lse = c_lse;
-  hipLaunchKernelGGL((cd::attend_finalize_kernel<T, D>), dim3(p->n_q_heads, p->batch), dim3(D), 0, st, fa);
+  hipLaunchKernelGGL((cd::attend_finalize_kernel<T, D>), dim3(p->n_q_heads, p->batch), dim3(cd::kFinalGroups * D), 0, st, fa);
   return launch_status("attend_finalize(calibration)");
 }
 
@@ -428,7 +472,7 @@ int decode_impl(const calidrop_params* p, const void* q_t, const void* k_c, cons
   fa.NS = L.sp.NS; fa.calib_mode = 0; fa.q_is_window = 0; fa.q = q_t; fa.theta1 = p->theta1; fa.theta2 = p->theta2;
   fa.c_q = const_cast<float*>(c_q); fa.c_out = const_cast<float*>(c_out); fa.c_lse = const_cast<float*>(c_lse);
   fa.out = out; fa.a_lse = a_lse; fa.flags = flags;
-  hipLaunchKernelGGL((cd::attend_finalize_kernel<T, D>), dim3(p->n_q_heads, p->batch), dim3(D), 0, st, fa);
+  hipLaunchKernelGGL((cd::attend_finalize_kernel<T, D>), dim3(p->n_q_heads, p->batch), dim3(cd::kFinalGroups * D), 0, st, fa);
   return launch_status("attend_finalize(decode)");
 }
 
@@ -437,7 +481,7 @@ struct RecalLayout { size_t bitmap, part_o, part_ml, total; int W32; SplitPlan s
 RecalLayout recal_layout(const calidrop_params* p, int32_t max_seq_len) {
   RecalLayout L{};
   L.W32 = ceil_div(max_seq_len, 64) * 2;
-  L.sp = plan_splits(p->batch * p->n_kv_heads, max_seq_len);
+  L.sp = plan_splits(p->batch * p->n_kv_heads, max_seq_len, true);
   const size_t slots = static_cast<size_t>(p->batch) * p->n_q_heads * L.sp.NS;
   size_t off = 0;
   L.bitmap = off;  off += round256(static_cast<size_t>(p->batch) * p->n_kv_heads * L.W32 * sizeof(uint32_t));
@@ -482,9 +526,13 @@ int recal_impl(const calidrop_params* p, const void* q_t, const void* k, const v
   fa.w = 0; fa.B = p->budget; fa.max_len = max_seq_len; fa.rows_per_split = L.sp.rows_per_split;
   fa.NS = L.sp.NS; fa.calib_mode = 2; fa.q_is_window = 0; fa.q = q_t;
   fa.c_q = c_q; fa.c_out = c_out; fa.c_lse = c_lse; fa.out = out; fa.a_lse = const_cast<float*>(a_lse); fa.flags = flags;
-  hipLaunchKernelGGL((cd::attend_finalize_kernel<T, D>), dim3(p->n_q_heads, p->batch), dim3(D), 0, st, fa);
+  hipLaunchKernelGGL((cd::attend_finalize_kernel<T, D>), dim3(p->n_q_heads, p->batch), dim3(cd::kFinalGroups * D), 0, st, fa);
   return launch_status("attend_finalize(recalibrate)");
 }
+
+// Skip bitmap of a sequence in LDS (131072 positions) for the given-set preparation; the gather blocks that share its
+// launch then still fit eight to a compute unit.
+constexpr size_t kGivenLdsBytes = 16 * 1024;
 
 // Alg. 1 steps 4-8 for a retained set that is already known (caller's strategy, or the
 // StreamingLLM list): bitmap + cache_lens, gather, calibration pass over everything else.
@@ -500,17 +548,15 @@ int compress_given_impl(const calidrop_params* p, const void* q_cal, const void*
   ga.seq_off = seq_offsets; ga.total_tokens = total_tokens; ga.batch = p->batch; ga.Hkv = p->n_kv_heads;
   ga.B = p->budget; ga.max_seq_len = max_seq_len; ga.W32 = L.W32; ga.indices = indices; ga.cache_lens = cache_lens;
   ga.bitmap = reinterpret_cast<uint32_t*>(ws + L.bitmap);
-  hipLaunchKernelGGL(cd::given_prepare_kernel, dim3(bg), dim3(256), 0, st, ga);
+  // the gather needs nothing the preparation produces: both in one launch, the bitmaps first
+  const cd::GatherArgs gather = gather_args(p, indices, cache_offsets, k, v, k_c, v_c);
+  const size_t lds = static_cast<size_t>(L.W32) * sizeof(uint32_t);
+  const bool in_lds = lds <= kGivenLdsBytes;
+  ga.gather = gather;
+  const dim3 grid_p(in_lds ? 1 + gather.blocks : 1, bg);
+  if (in_lds) hipLaunchKernelGGL(cd::given_prepare_kernel<true>, grid_p, dim3(256), lds, st, ga);
+  else hipLaunchKernelGGL(cd::given_prepare_kernel<false>, grid_p, dim3(256), 0, st, ga);
   if ((rc = launch_status("given_prepare"))) return rc;
-
-  cd::SelectArgs se{};
-  se.seq_off = seq_offsets; se.cache_off = cache_offsets; se.total_tokens = total_tokens; se.batch = p->batch;
-  se.Hkv = p->n_kv_heads; se.w = 0; se.B = p->budget; se.max_seq_len = max_seq_len; se.W32 = L.W32;
-  se.row_bytes = D * static_cast<int>(sizeof(T)); se.indices = indices; se.cache_lens = cache_lens;
-  se.k = k; se.v = v; se.k_c = k_c; se.v_c = v_c;
-  const int vecs = p->budget * (se.row_bytes / 16);
-  hipLaunchKernelGGL(cd::gather_kv_kernel, dim3(ceil_div(vecs, 256), bg), dim3(256), 0, st, se);
-  if ((rc = launch_status("gather_kv"))) return rc;
 
   cd::AttendArgs aa{};
   aa.q = q_cal; aa.q_is_window = 0; aa.k = k; aa.v = v; aa.row_off = seq_offsets; aa.row_len = nullptr;
@@ -519,18 +565,14 @@ int compress_given_impl(const calidrop_params* p, const void* q_cal, const void*
   aa.rows_per_split = L.sp.rows_per_split; aa.NS = L.sp.NS; aa.sl2 = logit_scale(p) * cd::kLog2e;
   aa.part_o = reinterpret_cast<float*>(ws + L.part_o);
   aa.part_ml = reinterpret_cast<float2*>(ws + L.part_ml);
-  if (max_seq_len > p->budget) {
-    hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, false>), dim3(L.sp.NS, p->n_kv_heads, p->batch), dim3(256), 0,
-                       st, aa);
-    if ((rc = launch_status("attend_partial(given)"))) return rc;
-  }
+  if ((rc = launch_calibration<T, D>(p, aa, gather, in_lds ? GatherIn::kDone : GatherIn::kOwnLaunch, st))) return rc;
   cd::FinalArgs fa{};
   fa.part_o = aa.part_o; fa.part_ml = aa.part_ml; fa.row_off = seq_offsets; fa.row_len = nullptr;
   fa.total_tokens = total_tokens; fa.batch = p->batch; fa.Hq = p->n_q_heads; fa.Hkv = p->n_kv_heads; fa.G = G;
   fa.w = 0; fa.B = p->budget; fa.max_len = max_seq_len; fa.rows_per_split = L.sp.rows_per_split;
   fa.NS = L.sp.NS; fa.calib_mode = 1; fa.q_is_window = 0; fa.q = q_cal;
   fa.c_q = c_q; fa.c_out = c_out; fa.c_lse = c_lse;
-  hipLaunchKernelGGL((cd::attend_finalize_kernel<T, D>), dim3(p->n_q_heads, p->batch), dim3(D), 0, st, fa);
+  hipLaunchKernelGGL((cd::attend_finalize_kernel<T, D>), dim3(p->n_q_heads, p->batch), dim3(cd::kFinalGroups * D), 0, st, fa);
   return launch_status("attend_finalize(given)");
 }
 
@@ -618,7 +660,7 @@ int recal_packed_impl(const calidrop_params* p, const void* q_t, const void* k_e
   fa.w = 0; fa.B = p->budget; fa.max_len = max_evict_len; fa.rows_per_split = L.sp.rows_per_split;
   fa.NS = L.sp.NS; fa.calib_mode = 2; fa.q_is_window = 0; fa.q = q_t;
   fa.c_q = c_q; fa.c_out = c_out; fa.c_lse = c_lse; fa.out = out; fa.a_lse = const_cast<float*>(a_lse); fa.flags = flags;
-  hipLaunchKernelGGL((cd::attend_finalize_kernel<T, D>), dim3(p->n_q_heads, p->batch), dim3(D), 0, st, fa);
+  hipLaunchKernelGGL((cd::attend_finalize_kernel<T, D>), dim3(p->n_q_heads, p->batch), dim3(cd::kFinalGroups * D), 0, st, fa);
   return launch_status("attend_finalize(recalibrate, packed)");
 }
 
@@ -632,7 +674,7 @@ H2oLayout h2o_layout(const calidrop_params* p, int64_t total_tokens, int32_t max
   H2oLayout L{};
   L.lse_stride = ceil_div(max_seq_len, 256) * 256;
   L.W32 = ceil_div(max_seq_len, 64) * 2;
-  L.sp = plan_splits(p->batch * p->n_kv_heads, max_seq_len);
+  L.sp = plan_splits(p->batch * p->n_kv_heads, max_seq_len, true);
   L.NSEG = ceil_div(std::max(max_seq_len - n_local, 1), cd::kWideSeg);
   const size_t toks = static_cast<size_t>(total_tokens) * p->n_kv_heads;
   const size_t slots = static_cast<size_t>(p->batch) * p->n_q_heads * L.sp.NS;
@@ -684,16 +726,18 @@ int h2o_impl(const calidrop_params* p, int n_local, const void* q_full, const vo
   sa.seq_off = seq_offsets; sa.total_tokens = total_tokens; sa.batch = p->batch; sa.Hq = p->n_q_heads;
   sa.Hkv = p->n_kv_heads; sa.G = G; sa.w = n_local; sa.B = p->budget; sa.NRB = G; sa.max_seq_len = max_seq_len;
   sa.pool_k = 1; sa.vote = ha.vote; sa.plane = ha.plane; sa.score = reinterpret_cast<float*>(ws + L.score);
+  const cd::GatherArgs ga = gather_args(p, indices, cache_offsets, k, v, k_c, v_c);
+  GatherIn place;
   cd::SelectArgs se{};
-  se.seq_off = seq_offsets; se.cache_off = cache_offsets; se.total_tokens = total_tokens; se.batch = p->batch;
+  se.gather = ga;
+  se.seq_off = seq_offsets; se.total_tokens = total_tokens; se.batch = p->batch;
   se.Hkv = p->n_kv_heads; se.w = n_local; se.B = p->budget; se.max_seq_len = max_seq_len; se.W32 = L.W32;
-  se.NRB = G; se.pool_k = 1; se.row_bytes = D * static_cast<int>(sizeof(T));
+  se.NRB = G; se.pool_k = 1;
   se.vote = sa.vote; se.plane = sa.plane; se.score = sa.score; se.indices = indices; se.cache_lens = cache_lens;
   se.calib = p->calib_size; se.cal_indices = cal_indices;
   se.bitmap = reinterpret_cast<uint32_t*>(ws + L.bitmap);
-  se.k = k; se.v = v; se.k_c = k_c; se.v_c = v_c;
   if ((rc = run_selection(p, n_local, 1, max_seq_len, se, sa, reinterpret_cast<uint32_t*>(ws + L.sel_hist),
-                          reinterpret_cast<uint32_t*>(ws + L.sel_cnt), L.NSEG, st)))
+                          reinterpret_cast<uint32_t*>(ws + L.sel_cnt), L.NSEG, place, st)))
     return rc;
 
   cd::AttendArgs aa{};
@@ -703,18 +747,14 @@ int h2o_impl(const calidrop_params* p, int n_local, const void* q_full, const vo
   aa.rows_per_split = L.sp.rows_per_split; aa.NS = L.sp.NS; aa.sl2 = sl2;
   aa.part_o = reinterpret_cast<float*>(ws + L.part_o);
   aa.part_ml = reinterpret_cast<float2*>(ws + L.part_ml);
-  if (max_seq_len > p->budget) {
-    hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, false>), dim3(L.sp.NS, p->n_kv_heads, p->batch), dim3(256), 0,
-                       st, aa);
-    if ((rc = launch_status("attend_partial(h2o)"))) return rc;
-  }
+  if ((rc = launch_calibration<T, D>(p, aa, ga, place, st))) return rc;
   cd::FinalArgs fa{};
   fa.part_o = aa.part_o; fa.part_ml = aa.part_ml; fa.row_off = seq_offsets; fa.row_len = nullptr;
   fa.total_tokens = total_tokens; fa.batch = p->batch; fa.Hq = p->n_q_heads; fa.Hkv = p->n_kv_heads; fa.G = G;
   fa.w = n_local; fa.B = p->budget; fa.max_len = max_seq_len; fa.rows_per_split = L.sp.rows_per_split;
   fa.NS = L.sp.NS; fa.calib_mode = 1; fa.q_is_window = 0; fa.q = ha.q_last;
   fa.c_q = c_q; fa.c_out = c_out; fa.c_lse = c_lse;
-  hipLaunchKernelGGL((cd::attend_finalize_kernel<T, D>), dim3(p->n_q_heads, p->batch), dim3(D), 0, st, fa);
+  hipLaunchKernelGGL((cd::attend_finalize_kernel<T, D>), dim3(p->n_q_heads, p->batch), dim3(cd::kFinalGroups * D), 0, st, fa);
   return launch_status("attend_finalize(h2o)");
 }
 

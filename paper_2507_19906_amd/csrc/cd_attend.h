@@ -11,6 +11,7 @@
 #pragma once
 #include "cd_common.h"
 #include "cd_score.h"
+#include "cd_select.h"
 
 namespace cd {
 
@@ -32,6 +33,7 @@ struct AttendArgs {
   const uint8_t* only_flagged; // optional [batch][Hq]: skip KV groups in which no head carries flag 2
   float* part_o;              // [batch][Hq][NS][D]
   float2* part_ml;            // [batch][Hq][NS]  (max in log2 units, sum)
+  GatherArgs gather;          // compress: workgroups NS .. NS + gather.blocks - 1 of the launch gather KV_compress
 };
 
 // Number of rows the streaming pass covers for sequence b, the stride between heads and the
@@ -309,12 +311,22 @@ struct AttendWave {
 
 // kLogits: calibration mode with the logits precomputed by the scoring pass (K is not read).
 // kRowsK: K rows are requested whole and regrouped in LDS (rows that live in host memory).
-template <typename T, int D, bool kLogits, bool kRowsK = false>
+// kGather: the launch carries the workgroups that gather the retained rows as well.
+template <typename T, int D, bool kLogits, bool kRowsK = false, bool kGather = false>
 __global__ __launch_bounds__(256) void attend_partial_kernel(AttendArgs a) {
   // grid: x = split of the rows (rotated per head so that the splits every sequence has do not
-  // all land on the same XCDs of the round-robin deal), y = KV head, z = sequence
+  // all land on the same XCDs of the round-robin deal), behind them in small calls the workgroups that
+  // gather the retained rows, y = KV head, z = sequence
   const int g = blockIdx.y, b = blockIdx.z;
-  const int split = (blockIdx.x + g + a.Hkv * b) % gridDim.x;
+  if constexpr (kGather) {
+    if (static_cast<int>(blockIdx.x) >= a.NS) {
+      int off0;
+      const int n = seq_len_checked(a.row_off, b, a.max_len, a.total_tokens, off0);
+      gather_block(a.gather, blockIdx.x - a.NS, b, g, a.Hkv, a.B, n, off0);
+      return;
+    }
+  }
+  const int split = (blockIdx.x + g + a.Hkv * b) % a.NS;
   int rows, head_stride, off0;
   attend_geometry(a, b, rows, head_stride, off0);
   const int row_begin = split * a.rows_per_split;
@@ -393,7 +405,8 @@ struct FinalArgs {
 };
 
 __device__ __forceinline__ float block_sum(float x, float* red, int nthreads) {
-  // sum over the workgroup (nthreads = 64 or 128), fixed order; result in every thread
+  // sum over the first nthreads (64 or 128) threads of the workgroup, fixed order; result in every one of them.
+  // Called by the whole workgroup.
   x = wave_sum(x);
   const int wv = wave_index();
   __syncthreads();
@@ -404,14 +417,18 @@ __device__ __forceinline__ float block_sum(float x, float* red, int nthreads) {
   return t;
 }
 
-// One workgroup of D threads per (sequence, query head): merge the split partials (Eq. 1-2
-// applied NS-1 times), then either store the calibration state (Alg. 1 steps 6-8) or apply
-// the cosine gate and the calibration merge (Alg. 2 steps 2-15).
+// One workgroup of 4 D threads per (sequence, query head): merge the split partials (Eq. 1-2 applied NS-1 times),
+// then either store the calibration state (Alg. 1 steps 6-8) or apply the cosine gate and the calibration
+// merge (Alg. 2 steps 2-15).  Nothing but latency: the splits are dealt to four groups of D threads, so that up
+// to 128 partials are four short chains of loads instead of one long one, and the four results meet in LDS.
+constexpr int kFinalGroups = 4;
 template <typename T, int D>
-__global__ __launch_bounds__(D) void attend_finalize_kernel(FinalArgs a) {
-  const int h = blockIdx.x, b = blockIdx.y, d = threadIdx.x;
-  const int g = h / a.G;
-  __shared__ float red[4];
+__global__ __launch_bounds__(kFinalGroups * D) void attend_finalize_kernel(FinalArgs a) {
+  const int h = blockIdx.x, b = blockIdx.y, d = threadIdx.x % D;
+  const int grp = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / D);
+  __shared__ float red[kFinalGroups * D / 64];
+  __shared__ float s_o[kFinalGroups][D];
+  __shared__ float2 s_ml[kFinalGroups];
   if (a.calib_mode == 2 && a.flags[b * a.Hq + h] != 2) return;      // only heads flagged for recomputation
   int rows;
   if (!a.row_len) {                   // rows of a prompt (minus the window); else live rows of a packed buffer
@@ -423,7 +440,6 @@ __global__ __launch_bounds__(D) void attend_finalize_kernel(FinalArgs a) {
     int len = a.row_len[b];
     rows = (len < 0 || len > cap || len > a.max_len) ? 0 : len;
   }
-  (void)g;
   const int ns = (rows + a.rows_per_split - 1) / a.rows_per_split;
   const int64_t slot0 = static_cast<int64_t>(b * a.Hq + h) * a.NS;
   const int64_t hd = static_cast<int64_t>(b * a.Hq + h);
@@ -432,22 +448,53 @@ __global__ __launch_bounds__(D) void attend_finalize_kernel(FinalArgs a) {
   const float qd = a.q_is_window ? load_elem<T>(qp, (hd * a.w + (a.w - 1)) * D + d) : load_elem<T>(qp, hd * D + d);
   float cq = 0.f, co = 0.f, c_lse_in = -INFINITY;
   if (a.calib_mode == 0) { cq = a.c_q[hd * D + d]; co = a.c_out[hd * D + d]; c_lse_in = a.c_lse[hd]; }
-  float mm = -INFINITY;
-#pragma unroll 8
-  for (int s = 0; s < ns; ++s) mm = fmaxf(mm, a.part_ml[slot0 + s].x);
-  const float ms = (mm == -INFINITY) ? 0.f : mm;
-  float o = 0.f, ll = 0.f;
-#pragma unroll 8
-  for (int s = 0; s < ns; ++s) {
-    const float2 ml = a.part_ml[slot0 + s];
-    const float sc = fast_exp2(ml.x - ms);
-    o += a.part_o[(slot0 + s) * D + d] * sc;
-    ll += ml.y * sc;
+  float o = 0.f, ll = 0.f, mm = -INFINITY;
+  for (int s0 = grp; s0 < ns; s0 += 8 * kFinalGroups) {             // eight partials in flight at a time
+    float2 ml[8];
+    float po[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int s = s0 + u * kFinalGroups;
+      ml[u] = s < ns ? a.part_ml[slot0 + s] : make_float2(-INFINITY, 0.f);
+      po[u] = s < ns ? a.part_o[(slot0 + s) * D + d] : 0.f;
+    }
+    float mn = mm;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) mn = fmaxf(mn, ml[u].x);
+    const float ms = (mn == -INFINITY) ? 0.f : mn;
+    const float keep = fast_exp2(mm - ms);
+    o *= keep;
+    ll *= keep;
+    mm = mn;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const float sc = fast_exp2(ml[u].x - ms);
+      o += po[u] * sc;
+      ll += ml[u].y * sc;
+    }
+  }
+  s_o[grp][d] = o;
+  if (d == 0) s_ml[grp] = make_float2(mm, ll);
+  __syncthreads();
+  {
+    mm = -INFINITY;
+#pragma unroll
+    for (int gg = 0; gg < kFinalGroups; ++gg) mm = fmaxf(mm, s_ml[gg].x);
+    const float ms = (mm == -INFINITY) ? 0.f : mm;
+    o = 0.f;
+    ll = 0.f;
+#pragma unroll
+    for (int gg = 0; gg < kFinalGroups; ++gg) {
+      const float sc = fast_exp2(s_ml[gg].x - ms);
+      o += s_o[gg][d] * sc;
+      ll += s_ml[gg].y * sc;
+    }
   }
   const bool any = ll > 0.f;
   const float o_n = any ? o / ll : 0.f;
   const float lse = any ? (mm + fast_log2(ll)) * kLn2 : -INFINITY;     // natural-log units
   if (a.calib_mode) {
+    if (grp != 0) return;
     a.c_q[hd * D + d] = qd;
     a.c_out[hd * D + d] = o_n;
     if (a.calib_mode == 2) {
@@ -456,8 +503,7 @@ __global__ __launch_bounds__(D) void attend_finalize_kernel(FinalArgs a) {
       const float aj = any ? 1.f / (1.f + __expf(a_lse - lse)) : 0.f;
       const float o_a = load_elem<T>(static_cast<const T*>(a.out), hd * D + d);
       store_elem<T>(static_cast<T*>(a.out), hd * D + d, (1.f - aj) * o_a + aj * o_n);
-      __syncthreads();                 // every thread has read the flag before it changes
-      if (d == 0) a.flags[hd] = 3;
+      if (d == 0) a.flags[hd] = 3;     // every thread read the flag before the barrier above
     }
     if (d == 0) a.c_lse[hd] = lse;
     return;
@@ -466,6 +512,7 @@ __global__ __launch_bounds__(D) void attend_finalize_kernel(FinalArgs a) {
   const float dot = block_sum(qd * cq, red, D);
   const float nq2 = block_sum(qd * qd, red, D);
   const float nc2 = block_sum(cq * cq, red, D);
+  if (grp != 0) return;
   float rho = 0.f;
   if (nq2 > 0.f && nc2 > 0.f) rho = dot / (sqrtf(nq2) * sqrtf(nc2));
   const float c_lse = c_lse_in;

@@ -11,7 +11,7 @@
 // calibration size m is set, k_sel + m (retained + the m most important evicted tokens, which
 // form the calibration set; everything below is dropped for good).
 //
-// Two variants: select_gather_lds_kernel (prefix up to 32768 positions: one workgroup per head
+// Two variants: select_lds_kernel (prefix up to 32768 positions: one workgroup per head
 // pools the votes itself and keeps the keys in registers) and the wide_* kernels (longer
 // prefixes: many workgroups per head, keys read from the pooled-score buffer that
 // pool_scores_kernel wrote, histograms and counts combined in global memory).
@@ -26,11 +26,65 @@ constexpr int kSelPerThread = 32;              // LDS variant: positions per thr
 constexpr int kSelMaxLdsKeys = kSelThreads * kSelPerThread;   // longest prefix the LDS variant takes
 constexpr int kSelMaxPool = 15;                // widest pooling kernel the LDS variant takes
 
+// K_c[g][r] = K[g][idx[g][r]], V likewise, 16 bytes per thread and copy.
+struct GatherArgs {
+  const int32_t* indices;        // [batch][Hkv][B]
+  const int32_t* cache_off;
+  const void* k; const void* v;
+  void* k_c; void* v_c;
+  int row_bytes;
+  int blocks;                    // workgroups of 256 threads that cover one (sequence, KV head)
+};
+constexpr int kGatherCopies = 1;                       // independent copies of K and of V in flight per thread
+constexpr int kGatherVecs = 256 * kGatherCopies;       // 16-byte pieces per workgroup of 256 threads
+
+// Pieces t0, t0 + NT, ... (kCopies of them, below `total`) of the retained rows of one (sequence, KV head).
+template <int NT, int kCopies>
+__device__ __forceinline__ void gather_pieces(const GatherArgs& a, const int32_t* idx, int t0, int total, int n, bool keeps_all,
+                                              int64_t src_row, int64_t dst_row) {
+  const int vec_per_row = a.row_bytes / 16;
+  u32x4 kk[kCopies], vv[kCopies];
+#pragma unroll
+  for (int u = 0; u < kCopies; ++u) {
+    const int t = t0 + u * NT;
+    if (t < total) {
+      const int r = t / vec_per_row, vcol = t - r * vec_per_row;
+      // a sequence within the budget keeps every row (its list may be written by this very launch); clamped: the
+      // list may be the caller's (a strategy applied outside the library)
+      const int src = keeps_all ? r : min(max(idx[r], 0), n - 1);
+      const int64_t so = (src_row + src) * a.row_bytes + vcol * 16;
+      kk[u] = ld16(static_cast<const char*>(a.k) + so);
+      vv[u] = ld16(static_cast<const char*>(a.v) + so);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < kCopies; ++u) {
+    const int t = t0 + u * NT;
+    if (t < total) {
+      const int r = t / vec_per_row, vcol = t - r * vec_per_row;
+      const int64_t dof = (dst_row + r) * a.row_bytes + vcol * 16;
+      st16(static_cast<char*>(a.k_c) + dof, kk[u]);
+      st16(static_cast<char*>(a.v_c) + dof, vv[u]);
+    }
+  }
+}
+
+// Workgroup `block` of the a.blocks (256 threads each) that gather the rows of one (sequence, KV head).
+__device__ __forceinline__ void gather_block(const GatherArgs& a, int block, int b, int g, int Hkv, int B, int n, int off0) {
+  const int len = min(n, B);
+  const int c0 = a.cache_off[b];
+  const int cap = a.cache_off[b + 1] - c0;
+  if (cap < len) return;                 // capacity contract broken: write nothing
+  gather_pieces<256, kGatherCopies>(a, a.indices + (static_cast<int64_t>(b) * Hkv + g) * B,
+                                    block * kGatherVecs + static_cast<int>(threadIdx.x), len * (a.row_bytes / 16), n, n <= B,
+                                    static_cast<int64_t>(off0) * Hkv + static_cast<int64_t>(g) * n,
+                                    static_cast<int64_t>(c0) * Hkv + static_cast<int64_t>(g) * cap);
+}
+
 struct SelectArgs {
   const int32_t* seq_off;
-  const int32_t* cache_off;
   int64_t total_tokens;
-  int batch, Hkv, w, B, max_seq_len, W32, NRB, pool_k, row_bytes;
+  int batch, Hkv, w, B, max_seq_len, W32, NRB, pool_k;
   int calib;               // calibration size m (0 = every evicted token)
   int write_scores;        // LDS variant: also store the pooled scores (inspection only)
   const float* vote;       // [NRB][plane]   (LDS-key variant pools these itself)
@@ -40,30 +94,52 @@ struct SelectArgs {
   int32_t* cal_indices;    // [batch][Hkv][calib] positions of the calibration set, or NULL
   int32_t* cache_lens;     // [batch]
   uint32_t* bitmap;        // [batch*Hkv][W32]: bit set = position is NOT in the calibration set
-  const void* k; const void* v; void* k_c; void* v_c;
+  GatherArgs gather;
+  int gather_here;         // LDS variant: the workgroup also gathers the rows it has chosen
 };
 
-struct RadixShared {
-  uint32_t hist[256];
-  uint32_t prefix, remaining;
-};
+// The bin of a finished 256-bin histogram in which the count from the top reaches `remaining`;
+// updates prefix / remaining like one radix pass.  Lane l holds bins 4l..4l+3 in `hb`.  Called
+// by all 64 lanes of a wave.
+__device__ __forceinline__ void wide_pick(const u32x4 hb, int shift, uint32_t& prefix, uint32_t& remaining) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t h0 = hb[0], h1 = hb[1], h2 = hb[2], h3 = hb[3];
+  const uint32_t mine = h0 + h1 + h2 + h3;
+  const uint32_t upto = wave_inclusive_scan(mine);
+  const uint32_t above = last_lane(upto) - upto;      // keys in bins owned by higher lanes
+  const uint32_t acc = above + mine;
+  const bool hit = above < remaining && remaining <= acc;
+  uint32_t cum = above;
+  int bin = 0;
+  if (cum + h3 >= remaining) bin = 3;
+  else { cum += h3; if (cum + h2 >= remaining) bin = 2;
+    else { cum += h2; if (cum + h1 >= remaining) bin = 1; else { cum += h1; bin = 0; } } }
+  const uint64_t who = __ballot(hit);
+  if (who == 0) return;                              // inconsistent histogram: leave the digit 0
+  const int src = __ffsll(static_cast<long long>(who)) - 1;
+  const uint32_t digit = __shfl(static_cast<uint32_t>(4 * lane + bin), src);
+  const uint32_t rem = __shfl(remaining - cum, src);
+  prefix |= digit << shift;
+  remaining = rem;
+}
 
 // Radix select of the `rank`-th largest key (rank >= 1, at most the number of keys).
 // `for_each_key(visit)` must call visit(u) once for every key this thread owns.  On return
 // thr = that key's bit pattern and need_eq = how many keys equal to thr lie within the rank.
-// Must be called by every thread of the workgroup.
-template <int NT, typename ForEach>
-__device__ __forceinline__ void radix_select(RadixShared& sh, uint32_t rank, ForEach&& for_each_key, uint32_t& thr,
+// `hist`: one 256-bin histogram per pass, all zero, with a barrier since they were cleared.  Must be called by
+// every thread of the workgroup.  Latency is all there is to it (a head of 8192 scores keeps one compute unit busy for
+// some microseconds): one barrier per pass, every wave finds the digit for itself, the last runs of a wave are
+// added up before they reach the histogram (selection of 32768 scores 42 -> 33 us, three barriers a pass before).
+template <typename ForEach>
+__device__ __forceinline__ void radix_select(uint32_t (*hist)[256], uint32_t rank, ForEach&& for_each_key, uint32_t& thr,
                                              uint32_t& need_eq) {
-  const int tid = threadIdx.x, lane = tid & 63, wv = wave_index();
+  const int lane = threadIdx.x & 63;
   uint32_t prefix = 0;            // bits decided so far (the high bits of the answer)
   uint32_t remaining = rank;      // rank of the answer among the keys matching `prefix`
 #pragma unroll
   for (int pass = 0; pass < 4; ++pass) {
     const int shift = 24 - 8 * pass;
     const uint32_t himask = (pass == 0) ? 0u : (0xFFFFFFFFu << (shift + 8));
-    for (int t = tid; t < 256; t += NT) sh.hist[t] = 0;
-    __syncthreads();
     {
       // run-length compressed updates: scores share their leading digits, so consecutive keys
       // of a thread mostly fall in the same bin and only bin changes touch the histogram
@@ -71,78 +147,25 @@ __device__ __forceinline__ void radix_select(RadixShared& sh, uint32_t rank, For
       for_each_key([&](uint32_t u) {
         if ((u & himask) == prefix) {
           const uint32_t bin = (u >> shift) & 0xFF;
-          if (bin != run_bin && run_len) { atomicAdd(&sh.hist[run_bin], run_len); run_len = 0; }
+          if (bin != run_bin && run_len) { atomicAdd(&hist[pass][run_bin], run_len); run_len = 0; }
           run_bin = bin;
           ++run_len;
         }
       });
-      if (run_len) atomicAdd(&sh.hist[run_bin], run_len);
-    }
-    __syncthreads();
-    if (wv == 0) {
-      // lane t owns bins 4t..4t+3; find the bin where the count from the top reaches `remaining`
-      const uint32_t h0 = sh.hist[4 * lane], h1 = sh.hist[4 * lane + 1], h2 = sh.hist[4 * lane + 2],
-                     h3 = sh.hist[4 * lane + 3];
-      const uint32_t mine = h0 + h1 + h2 + h3;
-      const uint32_t upto = wave_inclusive_scan(mine);
-      const uint32_t above = last_lane(upto) - upto;    // keys in bins owned by higher lanes
-      const uint32_t acc = above + mine;
-      if (above < remaining && remaining <= acc) {      // exactly one lane
-        uint32_t cum = above;
-        int bin;
-        if (cum + h3 >= remaining) bin = 3;
-        else { cum += h3; if (cum + h2 >= remaining) bin = 2;
-          else { cum += h2; if (cum + h1 >= remaining) bin = 1; else { cum += h1; bin = 0; } } }
-        sh.prefix = prefix | (static_cast<uint32_t>(4 * lane + bin) << shift);
-        sh.remaining = remaining - cum;
+      // the last runs of a wave are mostly in one bin (the leading digits): one addition then
+      const uint32_t first = __builtin_amdgcn_readfirstlane(run_bin);
+      if (__all(run_bin == first)) {
+        const uint32_t sum = last_lane(wave_inclusive_scan(run_len));
+        if (lane == 0 && sum) atomicAdd(&hist[pass][first], sum);
+      } else if (run_len) {
+        atomicAdd(&hist[pass][run_bin], run_len);
       }
     }
     __syncthreads();
-    // (no barrier after these reads: sh.prefix is next written two barriers further on, and the
-    // histogram, which the next pass clears right away, was last read before the barrier above)
-    prefix = sh.prefix;
-    remaining = sh.remaining;
+    wide_pick(*reinterpret_cast<const u32x4*>(&hist[pass][4 * lane]), shift, prefix, remaining);
   }
-  __syncthreads();                  // the caller may reuse `sh` at once
   thr = prefix;
   need_eq = remaining;
-}
-
-// K_c[g][r] = K[g][idx[r]], V likewise, for r < len; 16 bytes per thread per copy, 8 independent
-// copies in flight per thread.  `idx` may live in LDS or in global memory.
-template <int NT>
-__device__ __forceinline__ void gather_rows(const SelectArgs& a, const int32_t* idx, int len, int b, int g,
-                                            int64_t head_tok) {
-  const int tid = threadIdx.x;
-  const int c0 = a.cache_off[b];
-  const int cap = a.cache_off[b + 1] - c0;
-  if (cap < len) return;                 // capacity contract broken: write nothing
-  const int vec_per_row = a.row_bytes / 16;
-  const char* ksrc = static_cast<const char*>(a.k) + head_tok * a.row_bytes;
-  const char* vsrc = static_cast<const char*>(a.v) + head_tok * a.row_bytes;
-  const int64_t dst_head = (static_cast<int64_t>(c0) * a.Hkv + static_cast<int64_t>(g) * cap) * a.row_bytes;
-  char* kdst = static_cast<char*>(a.k_c) + dst_head;
-  char* vdst = static_cast<char*>(a.v_c) + dst_head;
-  constexpr int kBatch = 8;
-  const int total = len * vec_per_row;
-  for (int t0 = tid; t0 < total; t0 += kBatch * NT) {
-    u32x4 kk[kBatch], vv[kBatch];
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const int t = t0 + u * NT;
-      if (t < total) {
-        const int64_t so = static_cast<int64_t>(idx[t / vec_per_row]) * a.row_bytes + (t % vec_per_row) * 16;
-        kk[u] = ld16(ksrc + so);
-        vv[u] = ld16(vsrc + so);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const int t = t0 + u * NT;
-      const int64_t dof = static_cast<int64_t>(t / vec_per_row) * a.row_bytes + (t % vec_per_row) * 16;
-      if (t < total) { st16(kdst + dof, kk[u]); st16(vdst + dof, vv[u]); }
-    }
-  }
 }
 
 // Membership of one candidate, given how many greater / equal keys precede it in position order.
@@ -176,31 +199,6 @@ struct WideArgs {
   uint32_t* seg_cnt;     // [batch*Hkv][NSEG][4]: greater1, equal1, greater2, equal2 per segment
   int NSEG, pass;
 };
-
-// The bin of a finished 256-bin histogram in which the count from the top reaches `remaining`;
-// updates prefix / remaining like one radix pass.  Lane l holds bins 4l..4l+3 in `hb`.  Called
-// by all 64 lanes of a wave.
-__device__ __forceinline__ void wide_pick(const u32x4 hb, int shift, uint32_t& prefix, uint32_t& remaining) {
-  const int lane = threadIdx.x & 63;
-  const uint32_t h0 = hb[0], h1 = hb[1], h2 = hb[2], h3 = hb[3];
-  const uint32_t mine = h0 + h1 + h2 + h3;
-  const uint32_t upto = wave_inclusive_scan(mine);
-  const uint32_t above = last_lane(upto) - upto;      // keys in bins owned by higher lanes
-  const uint32_t acc = above + mine;
-  const bool hit = above < remaining && remaining <= acc;
-  uint32_t cum = above;
-  int bin = 0;
-  if (cum + h3 >= remaining) bin = 3;
-  else { cum += h3; if (cum + h2 >= remaining) bin = 2;
-    else { cum += h2; if (cum + h1 >= remaining) bin = 1; else { cum += h1; bin = 0; } } }
-  const uint64_t who = __ballot(hit);
-  if (who == 0) return;                              // inconsistent histogram: leave the digit 0
-  const int src = __ffsll(static_cast<long long>(who)) - 1;
-  const uint32_t digit = __shfl(static_cast<uint32_t>(4 * lane + bin), src);
-  const uint32_t rem = __shfl(remaining - cum, src);
-  prefix |= digit << shift;
-  remaining = rem;
-}
 
 struct WideHead {
   int n, P, k_sel, b, g, bg;
@@ -408,28 +406,19 @@ __global__ __launch_bounds__(kWideThreads) void wide_emit_kernel(WideArgs a) {
   if (j0 < h.P) s.bitmap[static_cast<int64_t>(h.bg) * s.W32 + (j0 >> 5)] = word;
 }
 
-// K_c[g][r] = K[g][idx[g][r]], V likewise (long-prefix path and caller-supplied lists); 16 bytes
-// per thread.
-__global__ __launch_bounds__(256) void gather_kv_kernel(SelectArgs a) {
+// The gather as a launch of its own: where no streaming pass or selection kernel carries it.
+struct GatherOnlyArgs {
+  GatherArgs g;
+  const int32_t* seq_off;
+  int64_t total_tokens;
+  int Hkv, B, max_seq_len;
+};
+__global__ __launch_bounds__(256) void gather_kv_kernel(GatherOnlyArgs a) {
   const int bg = blockIdx.y;
-  const int g = bg % a.Hkv;
-  const int b = bg / a.Hkv;
+  const int g = bg % a.Hkv, b = bg / a.Hkv;
   int off0;
   const int n = seq_len_checked(a.seq_off, b, a.max_seq_len, a.total_tokens, off0);
-  const int len = min(n, a.B);
-  const int c0 = a.cache_off[b];
-  const int cap = a.cache_off[b + 1] - c0;
-  if (cap < len) return;                 // capacity contract broken: write nothing
-  const int vec_per_row = a.row_bytes / 16;
-  const int t = blockIdx.x * 256 + threadIdx.x;
-  const int r = t / vec_per_row, vcol = t - r * vec_per_row;
-  if (r >= len) return;
-  // clamped: the list may be the caller's (a strategy applied outside the library)
-  const int src = min(max(a.indices[static_cast<int64_t>(bg) * a.B + r], 0), n - 1);
-  const int64_t so = ((static_cast<int64_t>(off0) * a.Hkv + static_cast<int64_t>(g) * n + src) * a.row_bytes) + vcol * 16;
-  const int64_t dof = ((static_cast<int64_t>(c0) * a.Hkv + static_cast<int64_t>(g) * cap + r) * a.row_bytes) + vcol * 16;
-  st16(static_cast<char*>(a.k_c) + dof, ld16(static_cast<const char*>(a.k) + so));
-  st16(static_cast<char*>(a.v_c) + dof, ld16(static_cast<const char*>(a.v) + so));
+  gather_block(a.g, blockIdx.x, b, g, a.Hkv, a.B, n, off0);
 }
 
 // LDS variant for prefixes of up to PER * NT positions (NT = 1024 threads in use: smaller
@@ -438,13 +427,12 @@ __global__ __launch_bounds__(256) void gather_kv_kernel(SelectArgs a) {
 // radix passes and the compaction.  PER = 32: their bits are exactly bitmap word t (prefixes up
 // to 32768); PER = 16 / 8: half a word / a byte, so that prefixes up to 16384 / 8192 still keep
 // every thread busy.  The votes are staged once in LDS
-// (padded by one word per 32 so that the stride-32 accesses do not collide), and the same
-// LDS later holds the retained indices for the gather.
+// (padded by one word per 32 so that the stride-32 accesses do not collide).
 template <int NT, int PER>
-__global__ __launch_bounds__(NT) void select_gather_lds_kernel(SelectArgs a) {
+__global__ __launch_bounds__(NT) void select_lds_kernel(SelectArgs a) {
   extern __shared__ uint32_t s_sel[];
   float* s_vote = reinterpret_cast<float*>(s_sel);
-  int32_t* s_idx = reinterpret_cast<int32_t*>(s_sel);      // reused after pooling
+  int32_t* s_idx = reinterpret_cast<int32_t*>(s_sel);      // gather_here: the list, once the votes are done with
   const int bg = blockIdx.x;
   const int g = bg % a.Hkv;
   const int b = bg / a.Hkv;
@@ -453,11 +441,10 @@ __global__ __launch_bounds__(NT) void select_gather_lds_kernel(SelectArgs a) {
   const int n = seq_len_checked(a.seq_off, b, a.max_seq_len, a.total_tokens, off0);
   int32_t* idx = a.indices + static_cast<int64_t>(bg) * a.B;
   int32_t* cal = (a.cal_indices && a.calib > 0) ? a.cal_indices + static_cast<int64_t>(bg) * a.calib : nullptr;
-  const int len = min(n, a.B);
-  if (g == 0 && tid == 0) a.cache_lens[b] = len;
+  if (g == 0 && tid == 0) a.cache_lens[b] = min(n, a.B);
   const int64_t head_tok = static_cast<int64_t>(off0) * a.Hkv + static_cast<int64_t>(g) * n;
 
-  __shared__ RadixShared sh;
+  __shared__ __attribute__((aligned(16))) uint32_t s_hist[2][4][256];
   __shared__ uint32_t wave_tot[2][NT / 64];
   static_assert(PER == 32 || PER == 16 || PER == 8, "a thread owns a whole bitmap word, a half or a byte of one");
   auto pad = [](int j) { return j + (j >> 5); };
@@ -465,12 +452,13 @@ __global__ __launch_bounds__(NT) void select_gather_lds_kernel(SelectArgs a) {
   if (n <= a.B) {                       // nothing to evict: keep every position
     for (int r = tid; r < a.B; r += NT) {
       idx[r] = (r < n) ? r : -1;
-      if (r < n) s_idx[r] = r;
+      if (a.gather_here && r < n) s_idx[r] = r;
     }
     if (cal) for (int r = tid; r < a.calib; r += NT) cal[r] = -1;
   } else {
     const int P = n - a.w;
     const int k_sel = a.B - a.w;
+    for (int t = tid; t < 2 * 4 * 256; t += NT) (&s_hist[0][0][0])[t] = 0;
     // ---- stage the votes (row-block partials added first, fixed order) ---------------------
     {
       // 16 bytes per lane from the 16-byte boundary at or below the head's first vote (every vote
@@ -557,10 +545,10 @@ __global__ __launch_bounds__(NT) void select_gather_lds_kernel(SelectArgs a) {
     };
     Cut c1, c2;                          // c1: retained prefix tokens; c2: retained + calibration set
     c1.all = false;
-    radix_select<NT>(sh, k_sel, each_key, c1.thr, c1.need_eq);
+    radix_select(s_hist[0], k_sel, each_key, c1.thr, c1.need_eq);
     c2.all = a.calib <= 0 || k_sel + a.calib >= P;
     c2.thr = 0; c2.need_eq = 0;
-    if (!c2.all) radix_select<NT>(sh, k_sel + a.calib, each_key, c2.thr, c2.need_eq);
+    if (!c2.all) radix_select(s_hist[1], k_sel + a.calib, each_key, c2.thr, c2.need_eq);
 
     // ---- ordered compaction: exclusive scans of the per-thread (greater, equal) counts of
     //      both cuts, greater in the low half-word and equal in the high half-word -------------
@@ -580,7 +568,7 @@ __global__ __launch_bounds__(NT) void select_gather_lds_kernel(SelectArgs a) {
     const uint32_t cnt2 = __popc(gtm2) + (static_cast<uint32_t>(__popc(eqm2)) << 16);
     const uint32_t inc1 = wave_inclusive_scan(cnt1), inc2 = wave_inclusive_scan(cnt2);
     if (lane == 63) { wave_tot[0][wv] = inc1; wave_tot[1][wv] = inc2; }
-    __syncthreads();                      // also: every thread is done reading the staged votes
+    __syncthreads();
     uint32_t bef1 = inc1 - cnt1, bef2 = inc2 - cnt2;
     for (int ww = 0; ww < wv; ++ww) { bef1 += wave_tot[0][ww]; bef2 += wave_tot[1][ww]; }
     const uint32_t gt1 = bef1 & 0xFFFFu, eq1 = bef1 >> 16, gt2 = bef2 & 0xFFFFu, eq2 = bef2 >> 16;
@@ -606,7 +594,7 @@ __global__ __launch_bounds__(NT) void select_gather_lds_kernel(SelectArgs a) {
       for (uint32_t m = keepm; m; m &= m - 1u, ++pos) {
         const int j = j0 + (__ffs(m) - 1);
         idx[pos] = j;
-        s_idx[pos] = j;
+        if (a.gather_here) s_idx[pos] = j;
       }
     }
     if (cal) {
@@ -626,14 +614,27 @@ __global__ __launch_bounds__(NT) void select_gather_lds_kernel(SelectArgs a) {
       for (int q = 1; q < LPW; ++q) w32 |= (__shfl_down(word, q) & kMask) << (q * PER);
       if ((tid & (LPW - 1)) == 0 && j0 < P) a.bitmap[static_cast<int64_t>(bg) * a.W32 + (j0 >> 5)] = w32;
     }
-    for (int r = tid; r < a.w; r += NT) { idx[k_sel + r] = P + r; s_idx[k_sel + r] = P + r; }
+    for (int r = tid; r < a.w; r += NT) {
+      idx[k_sel + r] = P + r;
+      if (a.gather_here) s_idx[k_sel + r] = P + r;
+    }
     if (cal) {                                                              // pad a short calibration set
       const int n_cal = min(a.calib, P - k_sel);
       for (int r = n_cal + tid; r < a.calib; r += NT) cal[r] = -1;
     }
   }
+  if (!a.gather_here) return;
   __syncthreads();
-  gather_rows<NT>(a, s_idx, len, b, g, head_tok);
+  const int len = min(n, a.B);
+  const int c0 = a.gather.cache_off[b];
+  const int cap = a.gather.cache_off[b + 1] - c0;
+  if (cap < len) return;                 // capacity contract broken: write nothing
+  constexpr int kCopies = 4;
+  const int total = len * (a.gather.row_bytes / 16);
+#pragma unroll 1
+  for (int t0 = tid; t0 < total; t0 += kCopies * NT)
+    gather_pieces<NT, kCopies>(a.gather, s_idx, t0, total, n, n <= a.B, head_tok,
+                               static_cast<int64_t>(c0) * a.Hkv + static_cast<int64_t>(g) * cap);
 }
 
 }  // namespace cd
