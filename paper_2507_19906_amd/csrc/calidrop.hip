@@ -161,8 +161,8 @@ CompressLayout compress_layout(const calidrop_params* p, int64_t total_tokens, i
   L.part_ml = off; off += round256(slots * sizeof(float2));
   // multi-workgroup selection (prefixes beyond the single-workgroup variant): histograms and counts
   L.NSEG = ceil_div(std::max(max_seq_len - p->window, 1), cd::kWideSeg);
-  L.sel_hist = off; off += round256(static_cast<size_t>(p->batch) * p->n_kv_heads * 2 * 4 * 256 * sizeof(uint32_t));
-  L.sel_cnt = off;  off += round256(static_cast<size_t>(p->batch) * p->n_kv_heads * L.NSEG * 4 * sizeof(uint32_t));
+  L.sel_hist = off; off += round256(static_cast<size_t>(p->batch) * p->n_kv_heads * cd::kWideHistWords * sizeof(uint32_t));
+  L.sel_cnt = off;  off += round256(static_cast<size_t>(p->batch) * p->n_kv_heads * L.NSEG * cd::kWideSegWords * sizeof(uint32_t));
   L.total = off;
   return L;
 }
@@ -265,17 +265,23 @@ cd::GatherArgs gather_args(const calidrop_params* p, const int32_t* indices, con
   return cd::GatherArgs{indices, cache_offsets, k, v, k_c, v_c, row_bytes, static_cast<int>((vecs + cd::kGatherVecs - 1) / cd::kGatherVecs)};
 }
 
-// Pooling + selection for scores already in sa.vote.  Heads whose pooled scores fit in
-// LDS are pooled inside the single-workgroup selection kernel; longer ones go through the
-// pooled-score buffer and the multi-workgroup chain.  `window` = trailing positions always kept.
-int run_selection(const calidrop_params* p, int window, int pool_k, int max_seq_len, cd::SelectArgs& se,
-                  cd::ScoreArgs& sa, uint32_t* sel_hist, uint32_t* sel_cnt, int NSEG, GatherIn& place, hipStream_t st) {
+// Heads whose pooled scores fit in LDS are pooled and selected by one workgroup each; longer ones (and wider pooling)
+// go through the multi-workgroup chain.  `window` = trailing positions always kept.
+bool uses_lds_selection(const calidrop_params* p, int window, int pool_k, int max_seq_len) {
+  return max_seq_len - window <= cd::kSelMaxLdsKeys && p->budget <= cd::kSelMaxLdsKeys && pool_k <= cd::kSelMaxPool &&
+         !(p->flags & CALIDROP_OPT_WIDE_SELECTION);
+}
+// Words a kernel ahead of the selection has to clear for it.
+int64_t wide_words(const calidrop_params* p) { return static_cast<int64_t>(p->batch) * p->n_kv_heads * cd::kWideHistWords; }
+
+// Pooling + selection of the votes in se.vote.  For the multi-workgroup chain `sel_hist` has been cleared.
+int run_selection(const calidrop_params* p, int max_seq_len, cd::SelectArgs& se, uint32_t* sel_hist, uint32_t* sel_seg, int NSEG,
+                  GatherIn& place, hipStream_t st) {
   int rc;
   const int bg = p->batch * p->n_kv_heads;
-  const int max_prefix = max_seq_len - window;
+  const int max_prefix = max_seq_len - se.w;
   se.write_scores = (p->flags & CALIDROP_OPT_WRITE_SCORES) ? 1 : 0;
-  const bool lds_selection = max_prefix <= cd::kSelMaxLdsKeys && p->budget <= cd::kSelMaxLdsKeys && pool_k <= cd::kSelMaxPool &&
-                             !(p->flags & CALIDROP_OPT_WIDE_SELECTION);
+  const bool lds_selection = uses_lds_selection(p, se.w, se.pool_k, max_seq_len);
   place = gather_place(p, se.gather, lds_selection);
   se.gather_here = place == GatherIn::kDone;
   if (lds_selection) {
@@ -299,22 +305,17 @@ int run_selection(const calidrop_params* p, int window, int pool_k, int max_seq_
     if (rc) return rc;
   } else {
     cd::WideArgs wa{};
-    wa.s = se; wa.NSEG = NSEG;
-    wa.hist = sel_hist;
-    wa.seg_cnt = sel_cnt;
-    sa.zero_words = wa.hist; sa.zero_per_head = 2 * 4 * 256;
-    hipLaunchKernelGGL(cd::pool_scores_kernel, dim3(ceil_div(max_seq_len, 256), bg), dim3(256), 0, st, sa);
-    if ((rc = launch_status("pool_scores"))) return rc;
-    const dim3 grid_w(NSEG, bg);
+    wa.s = se; wa.NSEG = NSEG; wa.hist = sel_hist; wa.seg = sel_seg;
+    const dim3 grid_w(NSEG, bg), block_w(cd::kWideThreads);
     if (max_seq_len > p->budget) {
-      for (wa.pass = 0; wa.pass < 4; ++wa.pass) {
-        hipLaunchKernelGGL(cd::wide_hist_kernel, grid_w, dim3(cd::kWideThreads), 0, st, wa);
-        if ((rc = launch_status("wide_hist"))) return rc;
-      }
-      hipLaunchKernelGGL(cd::wide_count_kernel, grid_w, dim3(cd::kWideThreads), 0, st, wa);
-      if ((rc = launch_status("wide_count"))) return rc;
+      hipLaunchKernelGGL(cd::wide_pool_kernel, grid_w, block_w, 0, st, wa);
+      if ((rc = launch_status("wide_pool"))) return rc;
+      hipLaunchKernelGGL(cd::wide_hist_kernel, grid_w, block_w, 0, st, wa);
+      if ((rc = launch_status("wide_hist"))) return rc;
+      hipLaunchKernelGGL(cd::wide_last_kernel, grid_w, block_w, 0, st, wa);
+      if ((rc = launch_status("wide_last"))) return rc;
     }
-    hipLaunchKernelGGL(cd::wide_emit_kernel, grid_w, dim3(cd::kWideThreads), 0, st, wa);
+    hipLaunchKernelGGL(cd::wide_emit_kernel, grid_w, block_w, 0, st, wa);
   }
   return launch_status("select");
 }
@@ -353,7 +354,7 @@ int compress_impl(const calidrop_params* p, const void* q_win, const void* k, co
   sa.q_win = q_win; sa.k = k; sa.seq_off = seq_offsets; sa.total_tokens = total_tokens;
   sa.batch = p->batch; sa.Hq = p->n_q_heads; sa.Hkv = p->n_kv_heads; sa.G = G; sa.w = p->window;
   sa.B = p->budget; sa.R = G * p->window; sa.RB = L.RB; sa.row_stride = L.NRB * L.RB; sa.NRB = L.NRB; sa.NCH = L.NCH; sa.max_seq_len = max_seq_len;
-  sa.pool_k = p->pool_kernel; sa.sl2 = sl2; sa.chunk_keys = L.chunk_keys;
+  sa.sl2 = sl2; sa.chunk_keys = L.chunk_keys;
   // K of the whole call well inside the 256 MB last-level cache: pass 1 reads it with cached loads so
   // that pass 2 finds it there; larger calls stream it both times
   sa.keep_k = static_cast<int64_t>(total_tokens) * p->n_kv_heads * D * static_cast<int64_t>(sizeof(T)) <= (160ll << 20);
@@ -361,7 +362,9 @@ int compress_impl(const calidrop_params* p, const void* q_win, const void* k, co
   sa.row_lse = reinterpret_cast<float*>(ws + L.row_lse);
   sa.vote = reinterpret_cast<float*>(ws + L.vote);
   sa.plane = vote_plane(total_tokens, p->n_kv_heads);
-  sa.score = reinterpret_cast<float*>(ws + L.score);
+  if (!uses_lds_selection(p, p->window, p->pool_kernel, max_seq_len)) {
+    sa.zero_words = reinterpret_cast<uint32_t*>(ws + L.sel_hist); sa.zero_count = wide_words(p);
+  }
   // default calibration query = last window query: the vote pass exports its logits
   sa.cal_logit = (q_cal || G > cd::kMaxCalHeads || p->window % 4 != 0)
                      ? nullptr : reinterpret_cast<float*>(ws + L.cal_logit);
@@ -397,10 +400,10 @@ int compress_impl(const calidrop_params* p, const void* q_win, const void* k, co
   se.seq_off = seq_offsets; se.total_tokens = total_tokens; se.batch = p->batch;
   se.Hkv = p->n_kv_heads; se.w = p->window; se.B = p->budget; se.max_seq_len = max_seq_len; se.W32 = L.W32;
   se.NRB = L.NRB; se.pool_k = p->pool_kernel;
-  se.vote = sa.vote; se.plane = sa.plane; se.score = sa.score; se.indices = indices; se.cache_lens = cache_lens;
+  se.vote = sa.vote; se.plane = sa.plane; se.score = reinterpret_cast<float*>(ws + L.score); se.indices = indices; se.cache_lens = cache_lens;
   se.calib = p->calib_size; se.cal_indices = cal_indices;
   se.bitmap = reinterpret_cast<uint32_t*>(ws + L.bitmap);
-  if ((rc = run_selection(p, p->window, p->pool_kernel, max_seq_len, se, sa, reinterpret_cast<uint32_t*>(ws + L.sel_hist),
+  if ((rc = run_selection(p, max_seq_len, se, reinterpret_cast<uint32_t*>(ws + L.sel_hist),
                           reinterpret_cast<uint32_t*>(ws + L.sel_cnt), L.NSEG, place, st)))
     return rc;
 
@@ -687,8 +690,8 @@ H2oLayout h2o_layout(const calidrop_params* p, int64_t total_tokens, int32_t max
   L.q_last = off;  off += round256(static_cast<size_t>(p->batch) * p->n_q_heads * p->head_dim * sizeof(float));
   L.part_o = off;  off += round256(slots * p->head_dim * sizeof(float));
   L.part_ml = off; off += round256(slots * sizeof(float2));
-  L.sel_hist = off; off += round256(static_cast<size_t>(p->batch) * p->n_kv_heads * 2 * 4 * 256 * sizeof(uint32_t));
-  L.sel_cnt = off;  off += round256(static_cast<size_t>(p->batch) * p->n_kv_heads * L.NSEG * 4 * sizeof(uint32_t));
+  L.sel_hist = off; off += round256(static_cast<size_t>(p->batch) * p->n_kv_heads * cd::kWideHistWords * sizeof(uint32_t));
+  L.sel_cnt = off;  off += round256(static_cast<size_t>(p->batch) * p->n_kv_heads * L.NSEG * cd::kWideSegWords * sizeof(uint32_t));
   L.total = off;
   return L;
 }
@@ -712,6 +715,9 @@ int h2o_impl(const calidrop_params* p, int n_local, const void* q_full, const vo
   ha.vote = reinterpret_cast<float*>(ws + L.vote);
   ha.plane = vote_plane(total_tokens, p->n_kv_heads);
   ha.q_last = ws + L.q_last;
+  if (!uses_lds_selection(p, n_local, 1, max_seq_len)) {
+    ha.zero_words = reinterpret_cast<uint32_t*>(ws + L.sel_hist); ha.zero_count = wide_words(p);
+  }
   const int nblk = ceil_div(max_seq_len, cd::h2o_block<T>());     // blocks of stationary rows (or keys)
   // always launched: it also extracts Q_{-1}, which prompts within the budget need as C_q
   hipLaunchKernelGGL((cd::h2o_rowlse_kernel<T, D>), dim3(nblk, p->batch * p->n_q_heads), dim3(256), 0, st, ha);
@@ -722,10 +728,6 @@ int h2o_impl(const calidrop_params* p, int n_local, const void* q_full, const vo
   }
   // selection: the votes are the scores (no pooling); the local window plays the part of the
   // observation window (always kept, not a candidate)
-  cd::ScoreArgs sa{};
-  sa.seq_off = seq_offsets; sa.total_tokens = total_tokens; sa.batch = p->batch; sa.Hq = p->n_q_heads;
-  sa.Hkv = p->n_kv_heads; sa.G = G; sa.w = n_local; sa.B = p->budget; sa.NRB = G; sa.max_seq_len = max_seq_len;
-  sa.pool_k = 1; sa.vote = ha.vote; sa.plane = ha.plane; sa.score = reinterpret_cast<float*>(ws + L.score);
   const cd::GatherArgs ga = gather_args(p, indices, cache_offsets, k, v, k_c, v_c);
   GatherIn place;
   cd::SelectArgs se{};
@@ -733,10 +735,10 @@ int h2o_impl(const calidrop_params* p, int n_local, const void* q_full, const vo
   se.seq_off = seq_offsets; se.total_tokens = total_tokens; se.batch = p->batch;
   se.Hkv = p->n_kv_heads; se.w = n_local; se.B = p->budget; se.max_seq_len = max_seq_len; se.W32 = L.W32;
   se.NRB = G; se.pool_k = 1;
-  se.vote = sa.vote; se.plane = sa.plane; se.score = sa.score; se.indices = indices; se.cache_lens = cache_lens;
+  se.vote = ha.vote; se.plane = ha.plane; se.score = reinterpret_cast<float*>(ws + L.score); se.indices = indices; se.cache_lens = cache_lens;
   se.calib = p->calib_size; se.cal_indices = cal_indices;
   se.bitmap = reinterpret_cast<uint32_t*>(ws + L.bitmap);
-  if ((rc = run_selection(p, n_local, 1, max_seq_len, se, sa, reinterpret_cast<uint32_t*>(ws + L.sel_hist),
+  if ((rc = run_selection(p, max_seq_len, se, reinterpret_cast<uint32_t*>(ws + L.sel_hist),
                           reinterpret_cast<uint32_t*>(ws + L.sel_cnt), L.NSEG, place, st)))
     return rc;
 

@@ -41,6 +41,8 @@ struct H2oArgs {
   float* vote;               // [G][plane]: one plane per query head of the group, each packed like K with one float per row
   int64_t plane;             // floats per plane: total_tokens*Hkv rounded up to a multiple of 64
   void* q_last;              // [batch][Hq][D]: the last prompt query of every head (Q_{-1})
+  uint32_t* zero_words;      // words pass 1 clears for the selection that follows, or NULL
+  int64_t zero_count;
 };
 
 template <typename T, int D>
@@ -48,6 +50,7 @@ __global__ __launch_bounds__(256, 2) void h2o_rowlse_kernel(H2oArgs a) {
   using KS = KeyStream<T, D>;
   constexpr int RT = h2o_tiles<T>(), KT = KS::KT, NK = KS::NK, SK = KS::kStageKeys, EPL = KS::EPL, KD = KS::KD;
   constexpr int WR = 16 * RT, BR = 4 * WR;
+  clear_words(a.zero_words, a.zero_count);
   int vx, vh;                                    // row block and (sequence, query head) of this workgroup
   xcd_head_major(vx, vh);
   const int hq = vh % a.Hq, b = vh / a.Hq, g = hq / a.G;

@@ -4,7 +4,6 @@
 //           keys of one chunk; the chunks are merged into a row log-sum-exp (rowstats_merge).
 //   pass 2 (score_votes):    S recomputed, p = exp2(s - lse_row), column sums over the G*w
 //           rows of the KV head -> vote[j] for prefix columns j < P.
-//   pool_scores: 1-D average pooling of the votes.
 // A workgroup owns a block of query rows (128, or 256 when the KV head has more than 128 - so that
 // such heads stream their keys once per pass, not once per 128 rows) and a chunk of keys; its waves
 // own 32 or 64 rows each and share the key tiles through LDS.  Pass 1 forms S^T = K Q^T (a lane owns
@@ -26,7 +25,7 @@ struct ScoreArgs {
   const void* k;
   const int32_t* seq_off;
   int64_t total_tokens;
-  int batch, Hq, Hkv, G, w, B, R, NRB, NCH, max_seq_len, pool_k;
+  int batch, Hq, Hkv, G, w, B, R, NRB, NCH, max_seq_len;
   int RB;               // window-query rows per row block: 128, or 256 when a KV head has more than 128 (R = G*w)
   int row_stride;       // rows per KV head in rowpart / row_lse: NRB * RB
   int chunk_keys;       // keys per workgroup (multiple of 64); each wave takes chunk_keys/4 contiguous keys
@@ -36,12 +35,19 @@ struct ScoreArgs {
   float* row_lse;       // [batch*Hkv][row_stride] log2-domain row log-sum-exp (+inf for padding rows)
   float* vote;          // [NRB][plane]: one plane of votes per row block, each packed like K with one float per row
   int64_t plane;        // floats per plane: total_tokens*Hkv rounded up to a multiple of 64 (planes stay 256-byte aligned)
-  float* score;         // [total_tokens*Hkv]
   float* cal_logit;     // [batch*Hq][zstride] log2-unit logits of the last window query, or NULL
   int zstride;
-  uint32_t* zero_words; // pool_scores_kernel only: [batch*Hkv][zero_per_head] words to clear, or NULL
-  int zero_per_head;
+  uint32_t* zero_words; // words to clear for the selection that follows (its histograms), or NULL
+  int64_t zero_count;
 };
+
+// Clears `count` words with the threads of the whole grid (a kernel ahead of the selection does this on the side).
+__device__ __forceinline__ void clear_words(uint32_t* words, int64_t count) {
+  if (!words) return;
+  const int64_t nblk = static_cast<int64_t>(gridDim.x) * gridDim.y;
+  const int64_t me = (static_cast<int64_t>(blockIdx.y) * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x;
+  for (int64_t t = me; t < count; t += nblk * blockDim.x) words[t] = 0u;
+}
 
 // Length of sequence b as the kernels use it: 0 when the offsets break the host-side contract
 // (so nothing out of bounds is ever touched).
@@ -312,6 +318,7 @@ __global__ __launch_bounds__(NR * 64, sizeof(T) == 2 ? 4 : 2) void score_rowstat
 // hundreds of partials per row: one thread per row spent as long on them as a scoring pass.)
 template <int GS>
 __global__ __launch_bounds__(256) void rowstats_merge_kernel(ScoreArgs a) {
+  clear_words(a.zero_words, a.zero_count);
   const int64_t gr = static_cast<int64_t>(blockIdx.x) * (256 / GS) + threadIdx.x / GS;
   const int lane = threadIdx.x % GS;
   const int64_t rows_total = static_cast<int64_t>(a.batch) * a.Hkv * a.row_stride;
@@ -340,6 +347,7 @@ __global__ __launch_bounds__(256) void rowstats_merge_kernel(ScoreArgs a) {
 // (positions 0..P+i) - the by-product a prefill attention kernel has for these rows anyway.  One
 // thread per row slot; padding rows get +inf like above.
 __global__ __launch_bounds__(256) void rowlse_import_kernel(ScoreArgs a, const float* win_lse) {
+  clear_words(a.zero_words, a.zero_count);
   const int64_t gr = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
   const int64_t rows_total = static_cast<int64_t>(a.batch) * a.Hkv * a.row_stride;
   if (gr >= rows_total) return;
@@ -509,35 +517,6 @@ __global__ __launch_bounds__(NR * 64, sizeof(T) == 2 ? 4 : 2) void score_votes_k
   }
   stage_barrier();
   flush(s_v[(nstages - 1) & 1], s_z[(nstages - 1) & 1], key_base + (nstages - 1) * SK);
-}
-
-// score[j] = (1/k) * sum_{d=-k/2..k/2} vote[j+d], zero outside [0, P); votes of the row
-// blocks are added first, always in the same order.
-__global__ __launch_bounds__(256) void pool_scores_kernel(ScoreArgs a) {
-  const int bg = blockIdx.y;
-  const int g = bg % a.Hkv;
-  const int b = bg / a.Hkv;
-  int off0;
-  const int n = seq_len_checked(a.seq_off, b, a.max_seq_len, a.total_tokens, off0);
-  if (blockIdx.x == 0 && a.zero_words)          // clears the selection histograms of this head
-    for (int t = threadIdx.x; t < a.zero_per_head; t += 256) a.zero_words[static_cast<int64_t>(bg) * a.zero_per_head + t] = 0u;
-  if (n <= a.B) return;
-  const int P = n - a.w;
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= P) return;
-  const int64_t head_tok = static_cast<int64_t>(off0) * a.Hkv + static_cast<int64_t>(g) * n;
-  const int64_t plane = a.plane;
-  const int half = a.pool_k / 2;
-  float sum = 0.f;
-  for (int d = -half; d <= half; ++d) {
-    int jj = j + d;
-    float val = 0.f;
-    if (jj >= 0 && jj < P) {
-      for (int rb = 0; rb < a.NRB; ++rb) val += a.vote[rb * plane + head_tok + jj];
-    }
-    sum += val;
-  }
-  a.score[head_tok + j] = sum / static_cast<float>(a.pool_k);
 }
 
 }  // namespace cd

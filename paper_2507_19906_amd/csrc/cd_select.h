@@ -13,8 +13,7 @@
 //
 // Two variants: select_lds_kernel (prefix up to 32768 positions: one workgroup per head
 // pools the votes itself and keeps the keys in registers) and the wide_* kernels (longer
-// prefixes: many workgroups per head, keys read from the pooled-score buffer that
-// pool_scores_kernel wrote, histograms and counts combined in global memory).
+// prefixes: many workgroups per head, histograms and counts combined in global memory).
 #pragma once
 #include "cd_common.h"
 #include "cd_score.h"
@@ -172,32 +171,51 @@ __device__ __forceinline__ void radix_select(uint32_t (*hist)[256], uint32_t ran
 struct Cut {
   uint32_t thr, need_eq;
   bool all;              // no cut: every candidate is inside
-  __device__ __forceinline__ bool inside(uint32_t u, uint32_t eq_before) const {
-    return all || u > thr || (u == thr && eq_before < need_eq);
-  }
   // number of inside candidates among the first `pos` positions, from the running counts
   __device__ __forceinline__ uint32_t rank(uint32_t pos, uint32_t gt_before, uint32_t eq_before) const {
     return all ? pos : gt_before + min(eq_before, need_eq);
   }
 };
 
+// Members of a cut among the positions of one thread, as bit masks: everything above the threshold, and of the
+// keys equal to it the first (need_eq - equal ones at earlier positions), i.e. ties go to the lower index.
+__device__ __forceinline__ uint32_t cut_members(const Cut& c, uint32_t gtm, uint32_t eqm, uint32_t eq_before, uint32_t valid) {
+  if (c.all) return valid;
+  const uint32_t allow = c.need_eq > eq_before ? c.need_eq - eq_before : 0u;
+  if (allow < static_cast<uint32_t>(__popc(eqm))) {
+    uint32_t kept = 0;
+    for (uint32_t t = 0; t < allow; ++t) { const uint32_t low = eqm & (0u - eqm); kept |= low; eqm ^= low; }
+    eqm = kept;
+  }
+  return gtm | eqm;
+}
+
 // ---- long prefixes: selection spread over many workgroups ------------------------------------
 // One workgroup per head cannot sweep hundreds of thousands of scores quickly, so the prefix is
 // cut into segments of kWideSeg positions, one workgroup each, and the radix select becomes a
-// chain of launches that meet in global memory: four histogram passes (each adds its segment's
-// digit counts to the head's 256-bin histogram of that pass), a count pass (greater / equal
-// counts per segment once the thresholds are known) and an emit pass (ordered compaction:
-// counts of the earlier segments + a scan inside the segment).  Nothing waits inside a kernel;
-// every workgroup re-derives the decided digits from the finished histograms of earlier passes.
-constexpr int kWideThreads = 256;
-constexpr int kWidePer = 32;                          // positions per thread (= one bitmap word)
+// chain of launches that meet in global memory, with digits of 12, 12 and 8 bits:
+//   wide_pool   average pooling of the votes, scores stored, histogram of the first digit;
+//   wide_hist   histogram of the second digit among the keys that match the first;
+//   wide_last   per segment: how many keys lie above the 24 bits decided, and the 256-bin histogram of
+//               the last digit among those that match them (also added up per head);
+//   wide_emit   the counts of the earlier segments follow from what wide_last stored, so the ordered
+//               compaction needs no pass of its own for them.
+// Nothing waits inside a kernel; every workgroup re-derives the decided digits from the finished
+// histograms.  What bounds it is the number of dependent launches (8 heads of 131072 scores are half a megabyte
+// each): four of 1024 threads, 34 us, where digits of 8 bits, a count pass and a pooling pass apart took seven
+// of 256 threads and 54 us.
+constexpr int kWideThreads = 1024;
+constexpr int kWidePer = 8;                           // positions per thread
 constexpr int kWideSeg = kWideThreads * kWidePer;     // positions per workgroup
+constexpr int kWideBins = 4096;                       // bins of the first two digits
+constexpr int kWideHistWords = 3 * kWideBins + 2 * 256;   // per head: digit 1 (shared by the cuts), digit 2 per cut, digit 3 per cut
+constexpr int kWideSegWords = 2 * 256 + 4;            // per segment: digit 3 per cut, keys above the 24 bits per cut
 
 struct WideArgs {
   SelectArgs s;
-  uint32_t* hist;        // [batch*Hkv][2 cuts][4 passes][256], zero before the first pass
-  uint32_t* seg_cnt;     // [batch*Hkv][NSEG][4]: greater1, equal1, greater2, equal2 per segment
-  int NSEG, pass;
+  uint32_t* hist;        // [batch*Hkv][kWideHistWords], zero before wide_pool
+  uint32_t* seg;         // [batch*Hkv][NSEG][kWideSegWords]
+  int NSEG;
 };
 
 struct WideHead {
@@ -217,27 +235,111 @@ __device__ __forceinline__ WideHead wide_head(const SelectArgs& a, int bg) {
   return h;
 }
 
-// Digits decided by passes 0..upto-1, for both cuts.  The histograms of all those passes are
-// fetched together (one round trip); only the scans depend on each other.
-__device__ __forceinline__ void wide_derive(const WideArgs& a, const WideHead& h, int upto, uint32_t (&prefix)[2],
+struct WideShared {
+  uint32_t tot[2][kWideThreads / 64];
+  uint32_t digit[2][2], rem[2][2];       // [digit][cut]
+};
+
+// One 12-bit digit of both cuts from finished histograms (thread t holds bins 4t..4t+3): the bin in which the
+// count from the top reaches `remaining`.  Called by the whole workgroup; `which` = 0, 1.
+__device__ __forceinline__ void wide_digit(WideShared& sh, int which, int ncut, const u32x4 (&hb)[2], int shift, uint32_t (&prefix)[2],
+                                           uint32_t (&remaining)[2]) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = wave_index();
+  uint32_t mine[2], inc[2];
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    mine[c] = hb[c][0] + hb[c][1] + hb[c][2] + hb[c][3];
+    inc[c] = wave_inclusive_scan(mine[c]);
+    if (lane == 63) sh.tot[c][wv] = inc[c];
+    if (tid == c) { sh.digit[which][c] = 0; sh.rem[which][c] = remaining[c]; }     // inconsistent histogram: the digit stays 0
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    if (c >= ncut) continue;
+    uint32_t above = last_lane(inc[c]) - inc[c];
+    for (int ww = wv + 1; ww < kWideThreads / 64; ++ww) above += sh.tot[c][ww];
+    if (above < remaining[c] && remaining[c] <= above + mine[c]) {                   // exactly one thread
+      uint32_t cum = above;
+      int bin = 3;
+      while (bin > 0 && cum + hb[c][bin] < remaining[c]) { cum += hb[c][bin]; --bin; }
+      sh.digit[which][c] = 4 * tid + bin;
+      sh.rem[which][c] = remaining[c] - cum;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    prefix[c] |= sh.digit[which][c] << shift;
+    remaining[c] = sh.rem[which][c];
+  }
+}
+
+// The first kDigits digits of both cuts.  The histograms are fetched together; only the scans depend on each other.
+template <int kDigits>
+__device__ __forceinline__ void wide_derive(const WideArgs& a, const WideHead& h, WideShared& sh, uint32_t (&prefix)[2],
                                             uint32_t (&remaining)[2]) {
-  const int lane = threadIdx.x & 63;
+  const int tid = threadIdx.x, lane = tid & 63;
   const int ncut = h.all2 ? 1 : 2;
-  u32x4 hb[2][4];
+  const uint32_t* H = a.hist + static_cast<int64_t>(h.bg) * kWideHistWords;
+  u32x4 h1[2], h2[2], h3[2];
+  h1[0] = h1[1] = ld16(H + 4 * tid);
 #pragma unroll
-  for (int c = 0; c < 2; ++c)
-#pragma unroll
-    for (int ps = 0; ps < 4; ++ps)
-      if (c < ncut && ps < upto)
-        hb[c][ps] = ld16(a.hist + ((static_cast<int64_t>(h.bg) * 2 + c) * 4 + ps) * 256 + 4 * lane);
+  for (int c = 0; c < 2; ++c) {
+    h2[c] = h3[c] = zero16();
+    if (kDigits > 1 && c < ncut) h2[c] = ld16(H + (1 + c) * kWideBins + 4 * tid);
+    if (kDigits > 2 && c < ncut) h3[c] = ld16(H + 3 * kWideBins + c * 256 + 4 * lane);
+  }
   prefix[0] = prefix[1] = 0;
   remaining[0] = h.k_sel;
   remaining[1] = h.k_sel + a.s.calib;
+  wide_digit(sh, 0, ncut, h1, 20, prefix, remaining);
+  if constexpr (kDigits > 1) wide_digit(sh, 1, ncut, h2, 8, prefix, remaining);
+  if constexpr (kDigits > 2) {
+    wide_pick(h3[0], 0, prefix[0], remaining[0]);
+    if (ncut > 1) wide_pick(h3[1], 0, prefix[1], remaining[1]);
+  }
+}
+
+// score[j] = (1/k) * sum_{d=-k/2..k/2} vote[j+d], zero outside [0, P), taps left to right; the votes of the row
+// blocks are added first, always in the same order.
+constexpr int kWideHalo = 64;            // widest half pooling width staged in LDS; wider ones read the votes where they are
+__global__ __launch_bounds__(kWideThreads) void wide_pool_kernel(WideArgs a) {
+  const SelectArgs& s = a.s;
+  const WideHead h = wide_head(s, blockIdx.y);
+  const int lo = blockIdx.x * kWideSeg;
+  if (h.n <= s.B || lo >= h.P) return;
+  const int tid = threadIdx.x;
+  __shared__ float s_vote[kWideSeg + 2 * kWideHalo];
+  __shared__ uint32_t s_hist[kWideBins];
+  const float* vote = s.vote + h.head_tok;
+  auto vote_at = [&](int j) {
+    float val = 0.f;
+    if (j >= 0 && j < h.P)
+      for (int rb = 0; rb < s.NRB; ++rb) val += vote[rb * s.plane + j];
+    return val;
+  };
+  const int half = s.pool_k / 2;
+  const bool staged = half <= kWideHalo;
+  if (staged)
+    for (int t = tid; t < kWideSeg + 2 * half; t += kWideThreads) s_vote[t] = vote_at(lo - half + t);
+  for (int t = tid; t < kWideBins; t += kWideThreads) s_hist[t] = 0;
+  __syncthreads();
 #pragma unroll
-  for (int c = 0; c < 2; ++c)
-#pragma unroll
-    for (int ps = 0; ps < 4; ++ps)
-      if (c < ncut && ps < upto) wide_pick(hb[c][ps], 24 - 8 * ps, prefix[c], remaining[c]);
+  for (int q = 0; q < kWidePer; ++q) {
+    const int t = tid + q * kWideThreads, j = lo + t;
+    if (j >= h.P) continue;
+    float sum = 0.f;
+    if (staged) for (int d = 0; d < s.pool_k; ++d) sum += s_vote[t + d];
+    else for (int d = -half; d <= half; ++d) sum += vote_at(j + d);
+    const float sc = sum / static_cast<float>(s.pool_k);
+    s.score[h.head_tok + j] = sc;
+    atomicAdd(&s_hist[__builtin_bit_cast(uint32_t, sc) >> 20], 1u);
+  }
+  __syncthreads();
+  uint32_t* H = a.hist + static_cast<int64_t>(h.bg) * kWideHistWords;
+  for (int t = tid; t < kWideBins; t += kWideThreads)
+    if (const uint32_t v = s_hist[t]) atomicAdd(H + t, v);
 }
 
 __global__ __launch_bounds__(kWideThreads) void wide_hist_kernel(WideArgs a) {
@@ -246,80 +348,59 @@ __global__ __launch_bounds__(kWideThreads) void wide_hist_kernel(WideArgs a) {
   if (h.n <= a.s.B || lo >= h.P) return;
   const int tid = threadIdx.x;
   const uint32_t* gkey = reinterpret_cast<const uint32_t*>(a.s.score) + h.head_tok;
-  uint32_t u[kWidePer];                 // issued first: in flight while the digits are derived
+  uint32_t u[kWidePer];                 // issued first: in flight while the digit is derived
 #pragma unroll
   for (int q = 0; q < kWidePer; ++q) { const int j = lo + tid + q * kWideThreads; u[q] = j < h.P ? gkey[j] : 0u; }
+  __shared__ WideShared sh;
+  __shared__ uint32_t s_hist[2][kWideBins];
+  for (int t = tid; t < 2 * kWideBins; t += kWideThreads) (&s_hist[0][0])[t] = 0;
   uint32_t prefix[2], remaining[2];
-  wide_derive(a, h, a.pass, prefix, remaining);
-  __shared__ uint32_t s_hist[2][256];
-  s_hist[0][tid] = 0; s_hist[1][tid] = 0;
-  __syncthreads();
-  const int shift = 24 - 8 * a.pass;
-  const uint32_t himask = a.pass == 0 ? 0u : (0xFFFFFFFFu << (shift + 8));
-  for (int c = 0; c < (h.all2 ? 1 : 2); ++c) {
-    uint32_t run_bin = 0, run_len = 0;               // run-length compressed updates
+  wide_derive<1>(a, h, sh, prefix, remaining);         // its barriers also publish the cleared histograms
+  const int ncut = h.all2 ? 1 : 2;
+  for (int c = 0; c < ncut; ++c)
 #pragma unroll
-    for (int q = 0; q < kWidePer; ++q) {
-      if (lo + tid + q * kWideThreads < h.P && (u[q] & himask) == prefix[c]) {
-        const uint32_t bin = (u[q] >> shift) & 0xFF;
-        if (bin != run_bin && run_len) { atomicAdd(&s_hist[c][run_bin], run_len); run_len = 0; }
-        run_bin = bin;
-        ++run_len;
-      }
-    }
-    if (run_len) atomicAdd(&s_hist[c][run_bin], run_len);
-  }
+    for (int q = 0; q < kWidePer; ++q)
+      if (lo + tid + q * kWideThreads < h.P && (u[q] >> 20) == (prefix[c] >> 20)) atomicAdd(&s_hist[c][(u[q] >> 8) & 0xFFF], 1u);
   __syncthreads();
-  for (int c = 0; c < (h.all2 ? 1 : 2); ++c) {
-    const uint32_t v = s_hist[c][tid];
-    if (v) atomicAdd(a.hist + ((static_cast<int64_t>(h.bg) * 2 + c) * 4 + a.pass) * 256 + tid, v);
-  }
+  uint32_t* H = a.hist + static_cast<int64_t>(h.bg) * kWideHistWords + kWideBins;
+  for (int t = tid; t < ncut * kWideBins; t += kWideThreads)
+    if (const uint32_t v = (&s_hist[0][0])[t]) atomicAdd(H + t, v);
 }
 
-__device__ __forceinline__ void wide_cuts(const WideArgs& a, const WideHead& h, Cut& c1, Cut& c2) {
-  uint32_t prefix[2], remaining[2];
-  wide_derive(a, h, 4, prefix, remaining);
-  c1.all = false; c1.thr = prefix[0]; c1.need_eq = remaining[0];
-  c2.all = h.all2; c2.thr = h.all2 ? 0u : prefix[1]; c2.need_eq = h.all2 ? 0u : remaining[1];
-}
-
-// Sum over the workgroup of four counters; result in every thread.  `red` holds 4 x 4 words.
-__device__ __forceinline__ void wide_block_sum4(uint32_t (&v)[4], uint32_t (*red)[4]) {
-  const int lane = threadIdx.x & 63, wv = wave_index();
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-#pragma unroll
-    for (int sft = 32; sft >= 1; sft >>= 1) v[q] += __shfl_xor(v[q], sft);
-  __syncthreads();
-  if (lane == 0)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) red[wv][q] = v[q];
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < 4; ++q) v[q] = red[0][q] + red[1][q] + red[2][q] + red[3][q];
-}
-
-__global__ __launch_bounds__(kWideThreads) void wide_count_kernel(WideArgs a) {
+__global__ __launch_bounds__(kWideThreads) void wide_last_kernel(WideArgs a) {
   const WideHead h = wide_head(a.s, blockIdx.y);
   const int lo = blockIdx.x * kWideSeg;
   if (h.n <= a.s.B || lo >= h.P) return;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
   const uint32_t* gkey = reinterpret_cast<const uint32_t*>(a.s.score) + h.head_tok;
   uint32_t u[kWidePer];
 #pragma unroll
   for (int q = 0; q < kWidePer; ++q) { const int j = lo + tid + q * kWideThreads; u[q] = j < h.P ? gkey[j] : 0u; }
-  Cut c1, c2;
-  wide_cuts(a, h, c1, c2);
-  uint32_t cnt[4] = {0, 0, 0, 0};
+  __shared__ WideShared sh;
+  __shared__ uint32_t s_hist[2 * 256 + 2];             // digit 3 per cut, keys above the 24 bits per cut
+  if (tid < 2 * 256 + 2) s_hist[tid] = 0;
+  uint32_t prefix[2], remaining[2];
+  wide_derive<2>(a, h, sh, prefix, remaining);         // its barriers also publish the cleared counters
+  const int ncut = h.all2 ? 1 : 2;
+  for (int c = 0; c < ncut; ++c) {
+    uint32_t gt = 0;
 #pragma unroll
-  for (int q = 0; q < kWidePer; ++q)
-    if (lo + tid + q * kWideThreads < h.P) {
-      cnt[0] += u[q] > c1.thr; cnt[1] += u[q] == c1.thr;
-      cnt[2] += u[q] > c2.thr; cnt[3] += u[q] == c2.thr;
-    }
-  __shared__ uint32_t red[4][4];
-  wide_block_sum4(cnt, red);
-  if (tid < 4) a.seg_cnt[(static_cast<int64_t>(h.bg) * a.NSEG + blockIdx.x) * 4 + tid] = cnt[tid];
+    for (int q = 0; q < kWidePer; ++q)
+      if (lo + tid + q * kWideThreads < h.P) {
+        gt += (u[q] >> 8) > (prefix[c] >> 8) ? 1u : 0u;
+        if ((u[q] >> 8) == (prefix[c] >> 8)) atomicAdd(&s_hist[c * 256 + (u[q] & 0xFF)], 1u);
+      }
+    gt = last_lane(wave_inclusive_scan(gt));
+    if (lane == 0 && gt) atomicAdd(&s_hist[512 + c], gt);
+  }
+  __syncthreads();
+  uint32_t* S = a.seg + (static_cast<int64_t>(h.bg) * a.NSEG + blockIdx.x) * kWideSegWords;
+  uint32_t* H = a.hist + static_cast<int64_t>(h.bg) * kWideHistWords + 3 * kWideBins;
+  if (tid < 2 * 256 + 2) {
+    const uint32_t v = s_hist[tid];
+    S[tid] = v;
+    if (tid < ncut * 256 && v) atomicAdd(H + tid, v);
+  }
 }
 
 __global__ __launch_bounds__(kWideThreads) void wide_emit_kernel(WideArgs a) {
@@ -346,64 +427,80 @@ __global__ __launch_bounds__(kWideThreads) void wide_emit_kernel(WideArgs a) {
     }
   }
   if (lo >= h.P) return;
-  // keys of the segment: coalesced loads, then blocked ownership (thread t: positions lo+32t..)
-  // through LDS, padded by one word per 32 so that the stride-32 reads do not collide
-  __shared__ uint32_t s_key[kWideSeg + kWideSeg / 32];
-  __shared__ uint32_t red[4][4];
-  __shared__ uint32_t wave_tot[2][kWideThreads / 64];
-  auto pad = [](int j) { return j + (j >> 5); };
   const uint32_t* gkey = reinterpret_cast<const uint32_t*>(s.score) + h.head_tok;
-  Cut c1, c2;
-  uint32_t pre[4] = {0, 0, 0, 0};
-  {
-    uint32_t u[kWidePer];
-#pragma unroll
-    for (int q = 0; q < kWidePer; ++q) { const int j = lo + tid + q * kWideThreads; u[q] = j < h.P ? gkey[j] : 0u; }
-    // counts of all earlier segments and the thresholds, while the keys are in flight
-    for (int sg = tid; sg < seg; sg += kWideThreads) {
-      const u32x4 cp = ld16(a.seg_cnt + (static_cast<int64_t>(h.bg) * a.NSEG + sg) * 4);
-#pragma unroll
-      for (int q = 0; q < 4; ++q) pre[q] += cp[q];
-    }
-    wide_cuts(a, h, c1, c2);
-#pragma unroll
-    for (int q = 0; q < kWidePer; ++q) s_key[pad(tid + q * kWideThreads)] = u[q];
-  }
-  wide_block_sum4(pre, red);            // its barriers also publish s_key
+  const int j0 = lo + tid * kWidePer;                  // this thread's positions
   uint32_t key[kWidePer];
-  const int j0 = lo + tid * kWidePer;
 #pragma unroll
-  for (int u = 0; u < kWidePer; ++u) key[u] = s_key[pad(tid * kWidePer + u)];
-  uint32_t cnt1 = 0, cnt2 = 0;          // (greater | equal << 16) of this thread's positions, per cut
+  for (int u = 0; u < kWidePer; ++u) key[u] = j0 + u < h.P ? gkey[j0 + u] : 0u;
+  __shared__ WideShared sh;
+  __shared__ uint32_t s_pre[4];                        // greater1, equal1, greater2, equal2 of the earlier segments
+  __shared__ uint32_t wave_tot[2][kWideThreads / 64];
+  if (tid < 4) s_pre[tid] = 0;
+  uint32_t prefix[2], remaining[2];
+  wide_derive<3>(a, h, sh, prefix, remaining);         // its barriers also publish s_pre
+  Cut c1, c2;
+  c1.all = false; c1.thr = prefix[0]; c1.need_eq = remaining[0];
+  c2.all = h.all2; c2.thr = h.all2 ? 0u : prefix[1]; c2.need_eq = h.all2 ? 0u : remaining[1];
+  {
+    uint32_t pre[4] = {0, 0, 0, 0};
+    const int ncut = h.all2 ? 1 : 2;
+    for (int sg = wv; sg < seg; sg += kWideThreads / 64) {      // a wave per earlier segment, four bins per lane
+      const uint32_t* S = a.seg + (static_cast<int64_t>(h.bg) * a.NSEG + sg) * kWideSegWords;
+      for (int c = 0; c < ncut; ++c) {
+        const u32x4 v = ld16(S + c * 256 + 4 * lane);
+        const uint32_t d3 = prefix[c] & 0xFF;
+        if (lane == 0) pre[2 * c] += S[512 + c];
 #pragma unroll
-  for (int u = 0; u < kWidePer; ++u)
-    if (j0 + u < h.P) {
-      cnt1 += (key[u] > c1.thr ? 1u : 0u) + (key[u] == c1.thr ? 0x10000u : 0u);
-      cnt2 += (key[u] > c2.thr ? 1u : 0u) + (key[u] == c2.thr ? 0x10000u : 0u);
+        for (int q = 0; q < 4; ++q) {
+          const uint32_t bin = 4 * lane + q;
+          if (bin > d3) pre[2 * c] += v[q];
+          if (bin == d3) pre[2 * c + 1] += v[q];
+        }
+      }
     }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t sum = last_lane(wave_inclusive_scan(pre[q]));
+      if (lane == 0 && sum) atomicAdd(&s_pre[q], sum);
+    }
+  }
+  constexpr uint32_t kAll = (1u << kWidePer) - 1u;
+  const uint32_t valid = j0 >= h.P ? 0u : (h.P - j0 >= kWidePer ? kAll : (1u << (h.P - j0)) - 1u);
+  uint32_t gtm1 = 0, eqm1 = 0, gtm2 = 0, eqm2 = 0;
+#pragma unroll
+  for (int u = 0; u < kWidePer; ++u) {
+    gtm1 |= (key[u] > c1.thr ? 1u : 0u) << u;
+    eqm1 |= (key[u] == c1.thr ? 1u : 0u) << u;
+    gtm2 |= (key[u] > c2.thr ? 1u : 0u) << u;
+    eqm2 |= (key[u] == c2.thr ? 1u : 0u) << u;
+  }
+  gtm1 &= valid; eqm1 &= valid; gtm2 &= valid; eqm2 &= valid;
+  const uint32_t cnt1 = __popc(gtm1) + (static_cast<uint32_t>(__popc(eqm1)) << 16);      // at most 8192 in a segment
+  const uint32_t cnt2 = __popc(gtm2) + (static_cast<uint32_t>(__popc(eqm2)) << 16);
   const uint32_t inc1 = wave_inclusive_scan(cnt1), inc2 = wave_inclusive_scan(cnt2);
   if (lane == 63) { wave_tot[0][wv] = inc1; wave_tot[1][wv] = inc2; }
   __syncthreads();
   uint32_t bef1 = inc1 - cnt1, bef2 = inc2 - cnt2;
   for (int ww = 0; ww < wv; ++ww) { bef1 += wave_tot[0][ww]; bef2 += wave_tot[1][ww]; }
-  uint32_t gt1 = pre[0] + (bef1 & 0xFFFFu), eq1 = pre[1] + (bef1 >> 16);
-  uint32_t gt2 = pre[2] + (bef2 & 0xFFFFu), eq2 = pre[3] + (bef2 >> 16);
-  uint32_t word = 0;
-#pragma unroll
-  for (int u = 0; u < kWidePer; ++u) {
-    const int j = j0 + u;
-    const bool in = j < h.P;
-    const bool keep = in && c1.inside(key[u], eq1);
-    const bool calib = in && !keep && c2.inside(key[u], eq2);
-    if (keep) idx[c1.rank(j, gt1, eq1)] = j;
-    if (calib && cal) cal[c2.rank(j, gt2, eq2) - c1.rank(j, gt1, eq1)] = j;
-    if (in) {
-      gt1 += key[u] > c1.thr; eq1 += key[u] == c1.thr;
-      gt2 += key[u] > c2.thr; eq2 += key[u] == c2.thr;
-    }
-    word |= (calib ? 0u : 1u) << u;       // bit = skip in the calibration pass
+  const uint32_t gt1 = s_pre[0] + (bef1 & 0xFFFFu), eq1 = s_pre[1] + (bef1 >> 16);
+  const uint32_t gt2 = s_pre[2] + (bef2 & 0xFFFFu), eq2 = s_pre[3] + (bef2 >> 16);
+  const uint32_t keepm = cut_members(c1, gtm1, eqm1, eq1, valid);
+  const uint32_t calm = cut_members(c2, gtm2, eqm2, eq2, valid) & ~keepm;
+  const uint32_t base1 = c1.rank(j0, gt1, eq1);
+  {
+    uint32_t pos = base1;
+    for (uint32_t m = keepm; m; m &= m - 1u, ++pos) idx[pos] = j0 + (__ffs(m) - 1);
   }
-  if (j0 < h.P) s.bitmap[static_cast<int64_t>(h.bg) * s.W32 + (j0 >> 5)] = word;
+  if (cal) {
+    uint32_t pos = c2.rank(j0, gt2, eq2) - base1;
+    for (uint32_t m = calm; m; m &= m - 1u, ++pos) cal[pos] = j0 + (__ffs(m) - 1);
+  }
+  // four neighbouring lanes hold the bytes of one bitmap word (bit = skip in the calibration pass; positions beyond
+  // the prefix are marked)
+  uint32_t w32 = ~calm & kAll;
+#pragma unroll
+  for (int q = 1; q < 4; ++q) w32 |= (__shfl_down(~calm, q) & kAll) << (q * kWidePer);
+  if ((tid & 3) == 0 && j0 < h.P) s.bitmap[static_cast<int64_t>(h.bg) * s.W32 + (j0 >> 5)] = w32;
 }
 
 // The gather as a launch of its own: where no streaming pass or selection kernel carries it.
@@ -572,20 +669,8 @@ __global__ __launch_bounds__(NT) void select_lds_kernel(SelectArgs a) {
     uint32_t bef1 = inc1 - cnt1, bef2 = inc2 - cnt2;
     for (int ww = 0; ww < wv; ++ww) { bef1 += wave_tot[0][ww]; bef2 += wave_tot[1][ww]; }
     const uint32_t gt1 = bef1 & 0xFFFFu, eq1 = bef1 >> 16, gt2 = bef2 & 0xFFFFu, eq2 = bef2 >> 16;
-    // positions of this thread inside a cut: everything above the threshold, and of the keys equal
-    // to it the first (need_eq - equal ones at earlier positions), i.e. ties go to the lower index
-    auto inside_mask = [&](const Cut& c, uint32_t gtm, uint32_t eqm, uint32_t eq_before) -> uint32_t {
-      if (c.all) return valid;
-      const uint32_t allow = c.need_eq > eq_before ? c.need_eq - eq_before : 0u;
-      if (allow < static_cast<uint32_t>(__popc(eqm))) {
-        uint32_t kept = 0;
-        for (uint32_t t = 0; t < allow; ++t) { const uint32_t low = eqm & (0u - eqm); kept |= low; eqm ^= low; }
-        eqm = kept;
-      }
-      return gtm | eqm;
-    };
-    const uint32_t keepm = inside_mask(c1, gtm1, eqm1, eq1);
-    const uint32_t calm = inside_mask(c2, gtm2, eqm2, eq2) & ~keepm;
+    const uint32_t keepm = cut_members(c1, gtm1, eqm1, eq1, valid);
+    const uint32_t calm = cut_members(c2, gtm2, eqm2, eq2, valid) & ~keepm;
     // the cut's members are emitted in position order: a thread's first one lands at the number of
     // members at earlier positions
     const uint32_t base1 = c1.rank(j0, gt1, eq1);

@@ -458,6 +458,28 @@ def test_multi_workgroup_selection_on_short_prompts(wl, wide_selection):
     run_case(wl)
 
 
+@pytest.mark.parametrize("pool,m", [(1, 0), (7, 500), (15, 40000)])
+def test_multi_workgroup_selection_at_segment_edges(pool, m):
+    # prefixes that end one short of, at and one past a segment of 8192 scores (and at the second one): the lists of
+    # the two selection variants are the same integers
+    w = 16
+    wl = small("bf16", 4, 2, 64, [8191 + w, 8192 + w, 8193 + w, 16384 + w, 16385 + w, 60], w, 700, pool, T=0, name="segment_edges")
+    x = to_dev(synth.make_inputs(wl, 29))
+    one = H.gpu_compress(wl, x, calib_size=m, flags=0)
+    many = H.gpu_compress(wl, x, calib_size=m, flags=cd.OPT_WIDE_SELECTION)
+    assert torch.equal(one.indices, many.indices)
+    assert torch.equal(one.k_c, many.k_c) and torch.equal(one.v_c, many.v_c) and torch.equal(one.cache_lens, many.cache_lens)
+    assert torch.equal(one.c_out, many.c_out) and torch.equal(one.c_lse, many.c_lse)
+    if m:
+        assert torch.equal(one.cal_indices, many.cal_indices)
+
+
+@pytest.mark.parametrize("pool", [127, 129, 131])
+def test_pooling_widths_around_what_is_staged(pool):
+    # half widths of 63, 64 (the widest kept in LDS) and 65, over a segment boundary
+    run_case(small("fp32", 2, 2, 64, [8192 + 16 + 300, 400], 16, 200, pool, T=0, name=f"pool_{pool}"))
+
+
 def test_exact_ties_with_multi_workgroup_selection(wide_selection):
     test_exact_ties_lower_index_wins(16 * 40 + 16, 1, 40, 50)
     test_exact_ties_lower_index_wins(20016, 1, 3000, 2500)
