@@ -501,26 +501,35 @@ int recal_impl(const calidrop_params* p, const void* q_t, const void* k, const v
                const RecalLayout& L, hipStream_t st) {
   const int G = p->n_q_heads / p->n_kv_heads;
   int rc;
-  cd::BitmapArgs ba{};
-  ba.seq_off = seq_offsets; ba.indices = indices; ba.cal_indices = cal_indices;
-  ba.bitmap = reinterpret_cast<uint32_t*>(ws + L.bitmap); ba.calib = p->calib_size;
-  ba.total_tokens = total_tokens; ba.batch = p->batch; ba.Hkv = p->n_kv_heads; ba.B = p->budget;
-  ba.max_seq_len = max_seq_len; ba.W32 = L.W32;
-  ba.only_flagged = flags; ba.Hq = p->n_q_heads; ba.G = G;
-  launch_bitmap(ba, p->batch * p->n_kv_heads, st);
-  if ((rc = launch_status("bitmap_from_indices"))) return rc;
+  // the skip bits: made by each workgroup of the pass from the position list while that list is short beside the rows it
+  // streams, otherwise by a launch ahead
+  const bool from_cal = p->calib_size > 0;
+  const int list_len = from_cal ? p->calib_size : p->budget;
+  const bool in_pass = L.sp.rows_per_split <= cd::kListMaxRows && list_len <= 2 * L.sp.rows_per_split;
+  if (!in_pass) {
+    cd::BitmapArgs ba{};
+    ba.seq_off = seq_offsets; ba.indices = indices; ba.cal_indices = cal_indices;
+    ba.bitmap = reinterpret_cast<uint32_t*>(ws + L.bitmap); ba.calib = p->calib_size;
+    ba.total_tokens = total_tokens; ba.batch = p->batch; ba.Hkv = p->n_kv_heads; ba.B = p->budget;
+    ba.max_seq_len = max_seq_len; ba.W32 = L.W32;
+    ba.only_flagged = flags; ba.Hq = p->n_q_heads; ba.G = G;
+    launch_bitmap(ba, p->batch * p->n_kv_heads, st);
+    if ((rc = launch_status("bitmap_from_indices"))) return rc;
+  }
 
   cd::AttendArgs aa{};
   aa.q = q_t; aa.q_is_window = 0; aa.k = k; aa.v = v; aa.row_off = seq_offsets; aa.row_len = nullptr;
-  aa.bitmap = ba.bitmap; aa.total_tokens = total_tokens; aa.batch = p->batch; aa.Hq = p->n_q_heads;
+  aa.bitmap = reinterpret_cast<uint32_t*>(ws + L.bitmap); aa.total_tokens = total_tokens; aa.batch = p->batch; aa.Hq = p->n_q_heads;
   // w = 0: the pass covers every position; the bitmap masks the retained ones, window included
   aa.Hkv = p->n_kv_heads; aa.G = G; aa.w = 0; aa.B = p->budget; aa.max_len = max_seq_len; aa.W32 = L.W32;
   aa.rows_per_split = L.sp.rows_per_split; aa.NS = L.sp.NS; aa.sl2 = logit_scale(p) * cd::kLog2e;
   aa.cal_logit = nullptr; aa.zstride = 0; aa.only_flagged = flags;
   aa.part_o = reinterpret_cast<float*>(ws + L.part_o);
   aa.part_ml = reinterpret_cast<float2*>(ws + L.part_ml);
-  hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, false>), dim3(L.sp.NS, p->n_kv_heads, p->batch), dim3(256), 0,
-                     st, aa);
+  aa.list = from_cal ? cal_indices : indices; aa.list_len = list_len; aa.list_is_calib = from_cal;
+  const dim3 grid(L.sp.NS, p->n_kv_heads, p->batch);
+  if (in_pass) hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, false, false, false, true>), grid, dim3(256), 0, st, aa);
+  else hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, false>), grid, dim3(256), 0, st, aa);
   if ((rc = launch_status("attend_partial(recalibrate)"))) return rc;
 
   cd::FinalArgs fa{};

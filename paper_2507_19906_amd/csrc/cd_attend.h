@@ -24,6 +24,8 @@ struct AttendArgs {
   const int32_t* row_off;     // [batch+1] token offsets of the K/V buffers
   const int32_t* row_len;     // decode: live rows per sequence; NULL in calibration mode
   const uint32_t* bitmap;     // calibration mode: [batch*Hkv][W32] not-evicted bits; else NULL
+  const int32_t* list;        // kList: [batch*Hkv][list_len] positions the bits are made from (see skip_bits)
+  int list_len, list_is_calib;
   int64_t total_tokens;       // calibration mode: contract check of row_off
   int batch, Hq, Hkv, G, w, B, max_len, W32, rows_per_split, NS;
   int q_is_window;            // 1: q points at q_win and the last window row is the query
@@ -39,7 +41,7 @@ struct AttendArgs {
 // Number of rows the streaming pass covers for sequence b, the stride between heads and the
 // token offset, for both modes.  rows = 0 means nothing to do.
 __device__ __forceinline__ void attend_geometry(const AttendArgs& a, int b, int& rows, int& head_stride, int& off0) {
-  if (a.bitmap) {                                   // calibration: prefix rows of the prompt
+  if (!a.row_len) {                                 // calibration: prefix rows of the prompt
     int n = seq_len_checked(a.row_off, b, a.max_len, a.total_tokens, off0);
     head_stride = n;
     rows = (n > a.B) ? n - a.w : 0;
@@ -190,7 +192,7 @@ struct AttendWave {
 
   // Process the 32-row tiles row_first, row_first + row_step, ... below row_end.  `rows` is
   // the number of valid rows of the head (loads are clamped to it); `bm` (optional) marks rows
-  // to skip, one bit per row, word index = row / 32.
+  // to skip, one bit per row: the word of the first tile, those of the next ones bm_step words further each.
   // Logits of rows row0 + 16 g2 + 4 c + r (r = 0..3) of head i, precomputed by the scoring pass.
   __device__ __forceinline__ static void load_z(const float* zhead, int row0, int c, bool valid, f32x4 (&z)[2]) {
 #pragma unroll
@@ -210,7 +212,7 @@ struct AttendWave {
   __device__ __forceinline__ void run(const T* kbase, const T* vbase, const uint32_t* bm, int rows, int row_first,
                                       int row_end, int row_step, float sl2, int i, int c,
                                       const float* zhead = nullptr, bool zvalid = false, bool k_requested = false,
-                                      F while_waiting = F(), char* k_stage = nullptr) {
+                                      F while_waiting = F(), char* k_stage = nullptr, int bm_step = 0) {
     u32x4 kf[2][NK];
     f32x4 zf[2];
     auto fetch_k = [&](int row0) {
@@ -253,7 +255,8 @@ struct AttendWave {
           if (next0 < row_end) fetch_k(next0);
         }
       }
-      const uint32_t skip = bm ? bm[row0 >> 5] : 0u;
+      const uint32_t skip = bm ? *bm : 0u;
+      bm += bm ? bm_step : 0;
       float p[2][4];
       softmax_tile<kLogits>(acc_s, row0, row_end, skip, sl2, c, p);
       // ---- O^T += V^T P^T -----------------------------------------------------------------
@@ -312,7 +315,11 @@ struct AttendWave {
 // kLogits: calibration mode with the logits precomputed by the scoring pass (K is not read).
 // kRowsK: K rows are requested whole and regrouped in LDS (rows that live in host memory).
 // kGather: the launch carries the workgroups that gather the retained rows as well.
-template <typename T, int D, bool kLogits, bool kRowsK = false, bool kGather = false>
+// kList: every workgroup makes the skip bits of its own rows from the position list while its first K rows are on their
+// way, instead of a launch ahead that makes the whole bitmap (recomputation of 8 layers of 32768 tokens: that launch
+// took 4.7 us; a call 110.4 -> 108.5 us, the list is 2 KiB beside a workgroup's 512 KiB of rows).
+constexpr int kListMaxRows = 8192;      // longest split whose bits (one per row) a workgroup keeps
+template <typename T, int D, bool kLogits, bool kRowsK = false, bool kGather = false, bool kList = false>
 __global__ __launch_bounds__(256) void attend_partial_kernel(AttendArgs a) {
   // grid: x = split of the rows (rotated per head so that the splits every sequence has do not
   // all land on the same XCDs of the round-robin deal), behind them in small calls the workgroups that
@@ -329,24 +336,36 @@ __global__ __launch_bounds__(256) void attend_partial_kernel(AttendArgs a) {
   const int split = (blockIdx.x + g + a.Hkv * b) % a.NS;
   int rows, head_stride, off0;
   attend_geometry(a, b, rows, head_stride, off0);
-  const int row_begin = split * a.rows_per_split;
-  if (row_begin >= rows) return;
+  // With K and V both streamed the splits of a head take its 128-row blocks in turn, so that at any time they read one
+  // moving window of the rows together.  As contiguous ranges - a power of two of bytes, all at the same distance from
+  // their start - they fell on the same memory channels, and the time depended on where the tensors lay (given set, 8
+  // layers of 32768 rows: 170 us a call with one set of tensors, 190 with three used in turn; now 175 and 180).  A
+  // cache of 4100 rows in 17 splits: 11.1 -> 10.6 us a call.  The pass that streams V alone keeps contiguous ranges
+  // (32 layers: 342 us, in turn 350).
+  const int splits = (rows + a.rows_per_split - 1) / a.rows_per_split;
+  if (split >= splits) return;
+  const int row_first = kLogits ? split * a.rows_per_split + wave_index() * kTileRows : (split * kAttWaves + wave_index()) * kTileRows;
+  const int row_step = kLogits ? kAttWaves * kTileRows : splits * kAttWaves * kTileRows;
+  const int row_end = kLogits ? min(rows, (split + 1) * a.rows_per_split) : rows;
   if (a.only_flagged) {
     bool any = false;
     for (int hh = 0; hh < a.G; ++hh) any |= a.only_flagged[b * a.Hq + g * a.G + hh] == 2;
     if (!any) return;
   }
-  const int row_end = min(rows, row_begin + a.rows_per_split);
   const int lane = threadIdx.x & 63, wv = wave_index();
   const int i = lane & 15, c = lane >> 4;
   const int64_t head_tok = static_cast<int64_t>(off0) * a.Hkv + static_cast<int64_t>(g) * head_stride;
   const T* kbase = static_cast<const T*>(a.k) + head_tok * D;
   const T* vbase = static_cast<const T*>(a.v) + head_tok * D;
   const uint32_t* bm = a.bitmap ? a.bitmap + static_cast<int64_t>(b * a.Hkv + g) * a.W32 : nullptr;
+  __shared__ uint32_t s_bits[kList ? kListMaxRows / 32 : 1];
 
   __shared__ __attribute__((aligned(16))) float s_o[kAttWaves][16 * D];
   __shared__ float2 s_ml[kAttWaves][16];
   AttendWave<T, D> w;
+  using NoWork = typename AttendWave<T, D>::NoWork;
+  const uint32_t* bm_first = bm ? bm + (row_first >> 5) : nullptr;
+  const int bm_step = row_step >> 5;
   {
     const int h = g * a.G + i;
     const T* qp = static_cast<const T*>(a.q);
@@ -357,16 +376,34 @@ __global__ __launch_bounds__(256) void attend_partial_kernel(AttendArgs a) {
   if constexpr (kLogits) {
     // padding rows of the last tile hold whatever the workspace held: they are masked before use
     const float* zhead = a.cal_logit + static_cast<int64_t>(b * a.Hq + g * a.G + i) * a.zstride;
-    w.template run<true, true>(kbase, vbase, bm, rows, row_begin + wv * kTileRows, row_end, kAttWaves * kTileRows,
-                               a.sl2, i, c, zhead, i < a.G);
+    w.template run<true, true>(kbase, vbase, bm_first, rows, row_first, row_end, row_step,
+                               a.sl2, i, c, zhead, i < a.G, false, NoWork(), nullptr, bm_step);
   } else if constexpr (kRowsK) {
     // 16 rows of K fit the area the wave publishes its outputs to afterwards
     static_assert(16 * D * sizeof(T) <= sizeof(s_o[0]), "K staging area");
-    w.template run<true, false, typename AttendWave<T, D>::NoWork, true>(
-        kbase, vbase, bm, rows, row_begin + wv * kTileRows, row_end, kAttWaves * kTileRows, a.sl2, i, c, nullptr, false,
-        false, typename AttendWave<T, D>::NoWork(), reinterpret_cast<char*>(s_o[wv]));
+    w.template run<true, false, NoWork, true>(
+        kbase, vbase, bm_first, rows, row_first, row_end, row_step, a.sl2, i, c, nullptr, false,
+        false, NoWork(), reinterpret_cast<char*>(s_o[wv]), bm_step);
+  } else if constexpr (kList) {
+    w.request_first_k(kbase, min(row_first, rows - 1), rows, i, c);
+    // bit = skip: the listed positions, or with the calibration set listed every other one
+    const int words = a.rows_per_split / 32;
+    for (int t = threadIdx.x; t < words; t += 256) s_bits[t] = a.list_is_calib ? 0xFFFFFFFFu : 0u;
+    __syncthreads();
+    const int32_t* list = a.list + static_cast<int64_t>(b * a.Hkv + g) * a.list_len;
+    for (int t = threadIdx.x; t < a.list_len; t += 256) {
+      const int pos = list[t];
+      const int block = pos / (kAttWaves * kTileRows);            // word = position of the tile among this workgroup's
+      if (pos >= 0 && pos < rows && block % splits == split) {
+        const int word = block / splits * kAttWaves + (pos / kTileRows) % kAttWaves;
+        if (a.list_is_calib) atomicAnd(&s_bits[word], ~(1u << (pos % kTileRows)));
+        else atomicOr(&s_bits[word], 1u << (pos % kTileRows));
+      }
+    }
+    __syncthreads();
+    w.run(kbase, vbase, s_bits + wv, rows, row_first, row_end, row_step, a.sl2, i, c, nullptr, false, true, NoWork(), nullptr, kAttWaves);
   } else {
-    w.run(kbase, vbase, bm, rows, row_begin + wv * kTileRows, row_end, kAttWaves * kTileRows, a.sl2, i, c);
+    w.run(kbase, vbase, bm_first, rows, row_first, row_end, row_step, a.sl2, i, c, nullptr, false, false, NoWork(), nullptr, bm_step);
   }
 
   // ---- merge the 4 waves through LDS and write this split's partial ------------------------

@@ -278,6 +278,27 @@ def test_full_decode_loop_with_recomputation(wl):
     assert rep["recal_heads"] > 0 and flags[1] > 0        # both branches were exercised
 
 
+@pytest.mark.parametrize("dtype,budget,m", [("bf16", 40, 0), ("fp32", 40, 50), ("bf16", 700, 0), ("bf16", 40, 900)])
+def test_recomputation_at_the_edges_of_its_row_blocks(dtype, budget, m):
+    # prompts that end one short of, at and one past one and several blocks of 128 rows; position lists short
+    # enough to be read by the streaming pass itself (up to twice the rows of a split) and longer ones
+    wl = small(dtype, 4, 2, 64, [127, 128, 129, 255, 257, 1151, 1153, 2049, 30], 16, budget, 5, T=3, name="row_blocks")
+    wl.theta1 = wl.theta2 = 2.0                      # every head is recomputed at every step
+    x = to_dev(synth.make_inputs(wl, 83))
+    bufs = H.gpu_compress(wl, x, calib_size=m)
+    rep = {}
+    for t in range(wl.decode_steps):
+        q_t = x["q_dec"][t]
+        bufs.decode(q_t)
+        torch.cuda.synchronize()
+        before = H.snapshot_state(bufs)
+        bufs.recalibrate(q_t, x["k"], x["v"], x["seq_offsets"])
+        torch.cuda.synchronize()
+        for b in range(wl.batch):
+            H.check_recalibrate(wl, x, bufs, q_t, b, before, report=rep)
+    assert rep["recal_heads"] == wl.batch * wl.n_q_heads * wl.decode_steps
+
+
 def test_recomputation_yields_exact_full_attention():
     # after recomputation with the current query, the calibrated output is the attention over
     # the whole prompt (Eq. 1 with the true query on both parts)
