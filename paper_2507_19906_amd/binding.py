@@ -136,16 +136,30 @@ def _check(status: int) -> None:
         raise CalidropError(status, calidrop_last_error())
 
 
+# A small decode call is over sooner on the GPU than its arguments are marshalled (8.4 us a call with the Stream object of
+# torch.cuda.current_stream() and an isinstance check per pointer), so these three stay on the short way.
 def _ptr(t) -> Optional[int]:
     if t is None:
         return None
-    if isinstance(t, int):
-        return t
-    return t.data_ptr()
+    try:
+        return t.data_ptr()
+    except AttributeError:
+        if isinstance(t, int):
+            return t
+        raise
+
+
+def _nbytes(t) -> int:
+    return 0 if t is None else t.nbytes
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)     # no public name for it
 
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream(torch.cuda.current_device()) or None      # no Stream object around it
         stream = torch.cuda.current_stream()
     if isinstance(stream, int):
         return stream or None
@@ -176,30 +190,27 @@ def calidrop_compress_workspace_region(p: Params, total_tokens: int, max_seq_len
 def calidrop_compress(p: Params, q_win, k, v, seq_offsets, total_tokens: int, max_seq_len: int,
                       q_cal, k_c, v_c, cache_offsets, cache_lens, indices, cal_indices, c_q, c_out, c_lse,
                       workspace, stream=None) -> None:
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
     _check(lib().calidrop_compress(
         ctypes.byref(p), _ptr(q_win), _ptr(k), _ptr(v), _ptr(seq_offsets), total_tokens, max_seq_len,
         _ptr(q_cal), _ptr(k_c), _ptr(v_c), _ptr(cache_offsets), _ptr(cache_lens), _ptr(indices),
-        _ptr(cal_indices), _ptr(c_q), _ptr(c_out), _ptr(c_lse), _ptr(workspace), ws_bytes, _stream(stream)))
+        _ptr(cal_indices), _ptr(c_q), _ptr(c_out), _ptr(c_lse), _ptr(workspace), _nbytes(workspace), _stream(stream)))
 
 
 def calidrop_compress_with_lse(p: Params, q_win, k, v, seq_offsets, total_tokens: int, max_seq_len: int,
                                win_lse, q_cal, k_c, v_c, cache_offsets, cache_lens, indices, cal_indices, c_q,
                                c_out, c_lse, workspace, stream=None) -> None:
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
     _check(lib().calidrop_compress_with_lse(
         ctypes.byref(p), _ptr(q_win), _ptr(k), _ptr(v), _ptr(seq_offsets), total_tokens, max_seq_len,
         _ptr(win_lse), _ptr(q_cal), _ptr(k_c), _ptr(v_c), _ptr(cache_offsets), _ptr(cache_lens), _ptr(indices),
-        _ptr(cal_indices), _ptr(c_q), _ptr(c_out), _ptr(c_lse), _ptr(workspace), ws_bytes, _stream(stream)))
+        _ptr(cal_indices), _ptr(c_q), _ptr(c_out), _ptr(c_lse), _ptr(workspace), _nbytes(workspace), _stream(stream)))
 
 
 def calidrop_decode(p: Params, q_t, k_c, v_c, cache_offsets, cache_lens, max_cache_len: int, c_q,
                     c_out, c_lse, out, a_lse, flags, workspace, stream=None) -> None:
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
     _check(lib().calidrop_decode(
         ctypes.byref(p), _ptr(q_t), _ptr(k_c), _ptr(v_c), _ptr(cache_offsets), _ptr(cache_lens),
         max_cache_len, _ptr(c_q), _ptr(c_out), _ptr(c_lse), _ptr(out), _ptr(a_lse), _ptr(flags),
-        _ptr(workspace), ws_bytes, _stream(stream)))
+        _ptr(workspace), _nbytes(workspace), _stream(stream)))
 
 
 STATIC_SCRATCH_BYTES = 8 << 20      # CALIDROP_STATIC_SCRATCH_BYTES
@@ -227,11 +238,10 @@ def calidrop_recalibrate_workspace_bytes(p: Params, max_seq_len: int) -> int:
 
 def calidrop_recalibrate(p: Params, q_t, k, v, seq_offsets, total_tokens: int, max_seq_len: int, indices,
                          cal_indices, flags, a_lse, out, c_q, c_out, c_lse, workspace, stream=None) -> None:
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
     _check(lib().calidrop_recalibrate(
         ctypes.byref(p), _ptr(q_t), _ptr(k), _ptr(v), _ptr(seq_offsets), total_tokens, max_seq_len,
         _ptr(indices), _ptr(cal_indices), _ptr(flags), _ptr(a_lse), _ptr(out), _ptr(c_q), _ptr(c_out),
-        _ptr(c_lse), _ptr(workspace), ws_bytes, _stream(stream)))
+        _ptr(c_lse), _ptr(workspace), _nbytes(workspace), _stream(stream)))
 
 
 def calidrop_compress_given_workspace_bytes(p: Params, max_seq_len: int) -> int:
@@ -250,11 +260,10 @@ def calidrop_streaming_indices(p: Params, n_sink: int, seq_offsets, total_tokens
 def calidrop_compress_given(p: Params, q_cal, k, v, seq_offsets, total_tokens: int, max_seq_len: int,
                             indices, k_c, v_c, cache_offsets, cache_lens, c_q, c_out, c_lse, workspace,
                             stream=None) -> None:
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
     _check(lib().calidrop_compress_given(
         ctypes.byref(p), _ptr(q_cal), _ptr(k), _ptr(v), _ptr(seq_offsets), total_tokens, max_seq_len,
         _ptr(indices), _ptr(k_c), _ptr(v_c), _ptr(cache_offsets), _ptr(cache_lens), _ptr(c_q), _ptr(c_out),
-        _ptr(c_lse), _ptr(workspace), ws_bytes, _stream(stream)))
+        _ptr(c_lse), _ptr(workspace), _nbytes(workspace), _stream(stream)))
 
 
 def calidrop_compress_h2o_workspace_bytes(p: Params, n_local: int, total_tokens: int, max_seq_len: int) -> int:
@@ -275,11 +284,10 @@ def calidrop_compress_h2o_workspace_region(p: Params, n_local: int, total_tokens
 def calidrop_compress_h2o(p: Params, n_local: int, q_full, k, v, seq_offsets, total_tokens: int, max_seq_len: int,
                           k_c, v_c, cache_offsets, cache_lens, indices, cal_indices, c_q, c_out, c_lse, workspace,
                           stream=None) -> None:
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
     _check(lib().calidrop_compress_h2o(
         ctypes.byref(p), n_local, _ptr(q_full), _ptr(k), _ptr(v), _ptr(seq_offsets), total_tokens, max_seq_len,
         _ptr(k_c), _ptr(v_c), _ptr(cache_offsets), _ptr(cache_lens), _ptr(indices), _ptr(cal_indices), _ptr(c_q),
-        _ptr(c_out), _ptr(c_lse), _ptr(workspace), ws_bytes, _stream(stream)))
+        _ptr(c_out), _ptr(c_lse), _ptr(workspace), _nbytes(workspace), _stream(stream)))
 
 
 def calidrop_packed_rows(p: Params, seq_len: int) -> int:
@@ -299,11 +307,10 @@ def calidrop_pack_evicted_workspace_bytes(p: Params, max_seq_len: int) -> int:
 def calidrop_pack_evicted(p: Params, k, v, seq_offsets, total_tokens: int, max_seq_len: int, indices,
                           cal_indices, k_e, v_e, evict_offsets, evict_lens, evict_indices, workspace,
                           stream=None) -> None:
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
     _check(lib().calidrop_pack_evicted(
         ctypes.byref(p), _ptr(k), _ptr(v), _ptr(seq_offsets), total_tokens, max_seq_len, _ptr(indices),
         _ptr(cal_indices), _ptr(k_e), _ptr(v_e), _ptr(evict_offsets), _ptr(evict_lens), _ptr(evict_indices),
-        _ptr(workspace), ws_bytes, _stream(stream)))
+        _ptr(workspace), _nbytes(workspace), _stream(stream)))
 
 
 def calidrop_recalibrate_packed_workspace_bytes(p: Params, max_evict_len: int) -> int:
@@ -315,11 +322,10 @@ def calidrop_recalibrate_packed_workspace_bytes(p: Params, max_evict_len: int) -
 
 def calidrop_recalibrate_packed(p: Params, q_t, k_e, v_e, evict_offsets, evict_lens, max_evict_len: int,
                                 flags, a_lse, out, c_q, c_out, c_lse, workspace, stream=None) -> None:
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
     _check(lib().calidrop_recalibrate_packed(
         ctypes.byref(p), _ptr(q_t), _ptr(k_e), _ptr(v_e), _ptr(evict_offsets), _ptr(evict_lens),
         max_evict_len, _ptr(flags), _ptr(a_lse), _ptr(out), _ptr(c_q), _ptr(c_out), _ptr(c_lse),
-        _ptr(workspace), ws_bytes, _stream(stream)))
+        _ptr(workspace), _nbytes(workspace), _stream(stream)))
 
 
 class EvictedStore:
