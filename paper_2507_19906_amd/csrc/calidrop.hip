@@ -332,7 +332,8 @@ int launch_calibration(const calidrop_params* p, cd::AttendArgs& aa, const cd::G
   if (!evicts) return CALIDROP_OK;
   aa.gather = ga;
   const bool carry = place == GatherIn::kPass;
-  const dim3 grid(aa.NS + (carry ? ga.blocks : 0), p->n_kv_heads, p->batch);
+  // the gathering workgroups fill whole planes of NS x Hkv behind the last sequence's
+  const dim3 grid(aa.NS, p->n_kv_heads, p->batch + (carry ? ceil_div(p->batch * ga.blocks, aa.NS) : 0));
   if (aa.cal_logit && carry) hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, true, false, true>), grid, dim3(256), 0, st, aa);
   else if (aa.cal_logit) hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, true>), grid, dim3(256), 0, st, aa);
   else if (carry) hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, false, false, true>), grid, dim3(256), 0, st, aa);

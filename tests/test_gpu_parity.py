@@ -506,6 +506,13 @@ def test_exact_ties_with_multi_workgroup_selection(wide_selection):
     test_exact_ties_lower_index_wins(20016, 1, 3000, 2500)
 
 
+@pytest.mark.parametrize("dtype,budget", [("fp32", 64), ("fp32", 700), ("fp32", 2688), ("fp32", 2690), ("bf16", 1500)])
+def test_gather_workgroups_behind_the_streaming_ones(dtype, budget):
+    # 1024 pieces of 16 bytes per gathering workgroup: less than one plane of the streaming pass's grid, several planes
+    # with a partial last one, 252 workgroups (the pass still carries them) and 258 (a launch of their own)
+    run_case(small(dtype, 4, 2, 64, [2900, budget - 1, 2850], 16, budget, 5, T=1, name=f"gather_{budget}"))
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 def test_window_scoring_with_logits_far_above_the_reference(dtype):
     # pass 1 sums against the first logit of each key chunk and redoes a stage against its true
