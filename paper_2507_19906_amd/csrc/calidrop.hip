@@ -708,6 +708,11 @@ H2oLayout h2o_layout(const calidrop_params* p, int64_t total_tokens, int32_t max
 
 // Alg. 1 steps 3-8 with H2O as f: accumulated attention of every prompt query (two dense passes),
 // top-(B - n_local) among the positions outside the local window, gather, calibration state.
+// Blocks of 256 stationary rows from which a call of H2O uses them (bf16): five and a half rounds of two workgroups on
+// each of the 256 compute units.  Below that 128-row blocks, twice as many workgroups, win or are within 3 %: one prompt,
+// 32 heads, 2573 tokens 130 us against 174, 8192 tokens 605 / 640, 12000 tokens (1504 blocks) 1209 / 1272, 16384 2235 /
+// 2170, 20000 (2528 blocks) 3270 / 3330; above it 24000 (3008) 4596 / 4368, 28000 6226 / 6250, 32768 8.2 / 7.9 ms.
+constexpr int64_t kH2oWideBlocks = 2816;
 template <typename T, int D>
 int h2o_impl(const calidrop_params* p, int n_local, const void* q_full, const void* k, const void* v,
              const int32_t* seq_offsets, int64_t total_tokens, int32_t max_seq_len, void* k_c, void* v_c,
@@ -728,14 +733,20 @@ int h2o_impl(const calidrop_params* p, int n_local, const void* q_full, const vo
   if (!uses_lds_selection(p, n_local, 1, max_seq_len)) {
     ha.zero_words = reinterpret_cast<uint32_t*>(ws + L.sel_hist); ha.zero_count = wide_words(p);
   }
-  const int nblk = ceil_div(max_seq_len, cd::h2o_block<T>());     // blocks of stationary rows (or keys)
-  // always launched: it also extracts Q_{-1}, which prompts within the budget need as C_q
-  hipLaunchKernelGGL((cd::h2o_rowlse_kernel<T, D>), dim3(nblk, p->batch * p->n_q_heads), dim3(256), 0, st, ha);
-  if ((rc = launch_status("h2o_rowlse"))) return rc;
-  if (max_seq_len > p->budget) {
-    hipLaunchKernelGGL((cd::h2o_votes_kernel<T, D>), dim3((nblk + 1) / 2, bg, G), dim3(256), 0, st, ha);
-    if ((rc = launch_status("h2o_votes"))) return rc;
-  }
+  auto passes = [&](auto tiles) {
+    constexpr int RT = decltype(tiles)::value;
+    const int nblk = ceil_div(max_seq_len, cd::h2o_block(RT));     // blocks of stationary rows (or keys)
+    // always launched: it also extracts Q_{-1}, which prompts within the budget need as C_q
+    hipLaunchKernelGGL((cd::h2o_rowlse_kernel<T, D, RT>), dim3(nblk, p->batch * p->n_q_heads), dim3(256), 0, st, ha);
+    if (int e = launch_status("h2o_rowlse")) return e;
+    if (max_seq_len <= p->budget) return static_cast<int>(CALIDROP_OK);
+    hipLaunchKernelGGL((cd::h2o_votes_kernel<T, D, RT>), dim3((nblk + 1) / 2, bg, G), dim3(256), 0, st, ha);
+    return launch_status("h2o_votes");
+  };
+  const int64_t blocks = static_cast<int64_t>(ceil_div(max_seq_len, cd::h2o_block(4))) * p->batch * p->n_q_heads;
+  if constexpr (sizeof(T) == 2) rc = blocks >= kH2oWideBlocks ? passes(std::integral_constant<int, 4>{}) : passes(std::integral_constant<int, 2>{});
+  else rc = passes(std::integral_constant<int, 2>{});
+  if (rc) return rc;
   // selection: the votes are the scores (no pooling); the local window plays the part of the
   // observation window (always kept, not a candidate)
   const cd::GatherArgs ga = gather_args(p, indices, cache_offsets, k, v, k_c, v_c);

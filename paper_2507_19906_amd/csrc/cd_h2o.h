@@ -24,10 +24,9 @@ namespace cd {
 // both passes 8.7 -> 7.9 ms; 32 rows per wave 8.2 ms, 128 rows 8.0 ms, 32 x 32 x 16 matrix instructions 8.4 ms
 // (same cycles, lower clock).  A dense bf16 product of 8192 x 8192 reaches 1.33 PFLOP/s on the same card, at which
 // the 8.8 TFLOP of the two passes would take 6.6 ms without a single exponential.
-// fp32 keeps 32 rows: 64 would need all 256 registers.
-// 16-row tiles of stationary rows per wave, and stationary rows (or keys) per workgroup of 4 waves.
-template <typename T> constexpr int h2o_tiles() { return sizeof(T) == 2 ? 4 : 2; }
-template <typename T> constexpr int h2o_block() { return 4 * 16 * h2o_tiles<T>(); }
+// fp32 keeps 32 rows: 64 would need all 256 registers; so do bf16 calls of few workgroups (the launch decides).
+// RT = 16-row tiles of stationary rows per wave; stationary rows (or keys) per workgroup of 4 waves:
+constexpr int h2o_block(int tiles) { return 4 * 16 * tiles; }
 
 struct H2oArgs {
   const void* q_full;        // packed like K with Hq heads: sequence b at token seq_off[b], inside [Hq][n_b][D]
@@ -45,10 +44,10 @@ struct H2oArgs {
   int64_t zero_count;
 };
 
-template <typename T, int D>
+template <typename T, int D, int RT>
 __global__ __launch_bounds__(256, 2) void h2o_rowlse_kernel(H2oArgs a) {
   using KS = KeyStream<T, D>;
-  constexpr int RT = h2o_tiles<T>(), KT = KS::KT, NK = KS::NK, SK = KS::kStageKeys, EPL = KS::EPL, KD = KS::KD;
+  constexpr int KT = KS::KT, NK = KS::NK, SK = KS::kStageKeys, EPL = KS::EPL, KD = KS::KD;
   constexpr int WR = 16 * RT, BR = 4 * WR;
   clear_words(a.zero_words, a.zero_count);
   int vx, vh;                                    // row block and (sequence, query head) of this workgroup
@@ -197,10 +196,10 @@ __global__ __launch_bounds__(256, 2) void h2o_rowlse_kernel(H2oArgs a) {
   }
 }
 
-template <typename T, int D>
+template <typename T, int D, int RT>
 __global__ __launch_bounds__(256, 2) void h2o_votes_kernel(H2oArgs a) {
   using KS = KeyStream<T, D>;
-  constexpr int RT = h2o_tiles<T>(), KT = KS::KT, NK = KS::NK, SK = KS::kStageKeys, EPL = KS::EPL, KD = KS::KD;
+  constexpr int KT = KS::KT, NK = KS::NK, SK = KS::kStageKeys, EPL = KS::EPL, KD = KS::KD;
   constexpr int WR = 16 * RT, BR = 4 * WR;
   // grid: x = pair of key blocks (block x and its mirror nblk-1-x: early keys are seen by many
   // rows, late keys by few, so every workgroup gets the same amount of work), y = (sequence, KV

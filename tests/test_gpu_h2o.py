@@ -84,8 +84,11 @@ def check_h2o(wl, x, q_full, bufs, n_local, rep, calib=0):
     (small("bf16", 32, 8, 128, [2050], 32, 512, 1, T=2, name="h2o_llama_shape"), 0),
     (small("bf16", 14, 2, 128, [900, 130], 16, 128, 1, T=2, name="h2o_g7"), 0),
     (small("fp32", 6, 2, 64, [611], 16, 90, 1, T=2, name="h2o_g3_fp32"), 17),
-    # blocks of 256 (fp32: 128) stationary rows: one short, exact, one past, and the mirror pairing at an odd block count
-    (small("bf16", 4, 2, 128, [255, 256, 257, 512, 769], 16, 60, 1, T=1, name="h2o_block_edges"), 0),
+    # blocks of 128 and, in calls of at least 2816 of the larger, 256 stationary rows (fp32: 128): one short, exact, one past,
+    # and the mirror pairing at an odd block count
+    (small("bf16", 4, 2, 128, [127, 128, 129, 255, 256, 257, 512, 769], 16, 60, 1, T=1, name="h2o_block_edges"), 0),
+    (small("bf16", 32, 8, 128, [255, 256, 257, 512, 769] + [50] * 19, 16, 60, 1, T=1, name="h2o_block_edges_wide"), 0),
+    (small("bf16", 32, 8, 64, [255, 256, 257, 512, 1025] + [50] * 15, 16, 60, 1, T=1, name="h2o_block_edges_wide_d64"), 0),
     (small("fp32", 4, 2, 64, [127, 128, 129, 385], 16, 60, 1, T=1, name="h2o_block_edges_fp32"), 0),
 ], ids=lambda v: v.name if hasattr(v, "name") else str(v))
 def test_h2o_strategy(wl, n_local):
