@@ -144,6 +144,9 @@ CompressLayout compress_layout(const calidrop_params* p, int64_t total_tokens, i
     L.chunk_keys = static_cast<int>(each <= 32 ? each : 16) * cd::kChunkUnit;
   }
   L.NCH = ceil_div(max_seq_len, L.chunk_keys);
+  // the chunks of the longest prompt alike: 62 prompts of 1050-1174 keys, 40 heads, 1024 + 150 keys 259 us per call,
+  // 640 + 534 keys 204 us; 60 prompts of 2100 keys 236 -> 209 us
+  L.chunk_keys = ceil_div(ceil_div(max_seq_len, L.NCH), cd::kChunkUnit) * cd::kChunkUnit;
   L.W32 = ceil_div(max_seq_len, 64) * 2;
   L.sp = plan_splits(p->batch * p->n_kv_heads, max_seq_len, true);
   const size_t rows = static_cast<size_t>(p->batch) * p->n_kv_heads * L.NRB * L.RB;

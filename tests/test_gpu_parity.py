@@ -514,6 +514,14 @@ def test_gather_workgroups_behind_the_streaming_ones(dtype, budget):
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_scoring_chunks_of_equal_length(dtype):
+    # many short prompts of two query-row blocks: one round of 512 workgroups would be 1408 keys each, which are evened
+    # out over the longest prompt (1500 keys: two of 768), with prompts that end one short of, at and one past them
+    lens = [1500, 767, 768, 769, 1499] + [1090] * 35
+    run_case(small(dtype, 40, 8, 64, lens, 64, 64, 7, T=0, name=f"even_chunks_{dtype}"))
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 def test_window_scoring_with_logits_far_above_the_reference(dtype):
     # pass 1 sums against the first logit of each key chunk and redoes a stage against its true
     # maximum only when a sum outgrows 2^64: tiny first keys and a few huge later keys force that
