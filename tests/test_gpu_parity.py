@@ -518,7 +518,7 @@ def test_scoring_chunks_of_equal_length(dtype):
     # many short prompts of two query-row blocks: one round of 512 workgroups would be 1408 keys each, which are evened
     # out over the longest prompt (1500 keys: two of 768), with prompts that end one short of, at and one past them
     lens = [1500, 767, 768, 769, 1499] + [1090] * 35
-    run_case(small(dtype, 40, 8, 64, lens, 64, 64, 7, T=0, name=f"even_chunks_{dtype}"))
+    run_case(small(dtype, 40, 8, 64, lens, 64, 80, 7, T=0, name=f"even_chunks_{dtype}"))
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
