@@ -16,7 +16,7 @@ LIB_PATH = os.path.join(_PKG_DIR, "libcalidrop.so")
 OK, EINVAL, ESHAPE, EALIGN, EWORKSPACE, EUNSUPPORTED, EHIP = 0, -1, -2, -3, -4, -5, -6
 BF16, FP32 = 0, 1
 FLAG_NONE, FLAG_CALIBRATED, FLAG_RECOMPUTE, FLAG_RECOMPUTED = 0, 1, 2, 3
-REGION_ROW_LSE, REGION_SCORE, REGION_VOTE_PLANES = 0, 1, 2
+REGION_ROW_LSE, REGION_SCORE, REGION_VOTE_PLANES, REGION_ROW_PARTS = 0, 1, 2, 3
 OPT_WRITE_SCORES, OPT_WIDE_SELECTION = 1, 2
 
 

@@ -9,6 +9,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <limits>
 
 #include "cd_attend.h"
 #include "cd_common.h"
@@ -123,6 +124,39 @@ SplitPlan plan_splits(int heads_kv_total, int max_rows, bool prompt = false) {
   return SplitPlan{rps, ceil_div(max_rows, rps)};
 }
 
+// Keys per scoring workgroup, in units of 64.  The 256 compute units share the workgroups of a launch, so a plan costs the
+// workgroups of the fullest unit times the key units of one, plus half a unit for its start (query fragments, first
+// stage); with fewer than `least` workgroups its waves leave the matrix pipe or the memory waiting, so fewer save nothing.
+// The chunk of least cost is taken, all chunks of the longest prompt alike, at most 12 units (256-row blocks start
+// slower: 32).  Prompts of different lengths: the host knows their sum and the longest only.  What the short last
+// chunks take is estimated (half a workgroup per prompt at 128 rows, nothing at 256, where they fill gaps), and since
+// the last round is not full everywhere, the rounded count weighs one part and the plain one, half a round later,
+// three; at 128 rows chunks stay at 8 units.
+// Measured over 485 calls (400 to 131072 tokens, 1 to 64 prompts, both types, D 64 and 128, 16 to 256 window rows per KV
+// head), each at 21 chunk lengths: the chunk taken is on average 1.5 % slower than the best of them.  Examples, us a call
+// at 256-512 keys and many rounds / at one workgroup for each of 512 places / now: fp32, 256 rows, 6 prompts of
+// 9000-17000 tokens 798 / 958 / 730; one of 16384 230 / 209 / 192; bf16, 131072 tokens, 256 rows 281 / 239 / 239.
+int plan_chunk(const calidrop_params* p, int64_t total_tokens, int32_t max_seq_len, int RB, int NRB) {
+  const bool even = total_tokens == static_cast<int64_t>(p->batch) * max_seq_len;
+  const bool narrow = RB == cd::kRowBlock;
+  const int64_t rows = static_cast<int64_t>(p->n_kv_heads) * NRB;          // grid rows of one prompt
+  const int64_t least = narrow ? 2 : 1;
+  int best = cd::kChunkUnit;
+  int64_t best_cost = std::numeric_limits<int64_t>::max();
+  for (int most = narrow ? (even ? 12 : 8) : 32; most >= 1; --most) {
+    const int nch = ceil_div(max_seq_len, most * cd::kChunkUnit);
+    const int units = ceil_div(ceil_div(max_seq_len, nch), cd::kChunkUnit);      // the chunks of the longest prompt alike
+    const int64_t keys = static_cast<int64_t>(units) * cd::kChunkUnit;
+    const bool last = narrow || (p->dtype == CALIDROP_FP32 && total_tokens < 4 * keys * p->batch);
+    const int64_t groups = even ? rows * p->batch * ((max_seq_len + keys - 1) / keys) : total_tokens * rows / keys + (last ? rows * p->batch / 2 : 0);
+    const int64_t full = (groups + 255) / 256;
+    const int64_t load = std::max(even ? 1024 * full : 256 * full + 3 * (groups + 128), 1024 * least);
+    const int64_t cost = load * (2 * units + 1);
+    if (cost < best_cost) { best_cost = cost; best = static_cast<int>(keys); }
+  }
+  return best;
+}
+
 struct CompressLayout {
   size_t rowpart, row_lse, vote, score, bitmap, cal_logit, part_o, part_ml, sel_hist, sel_cnt, total;
   int RB, NRB, NCH, W32, chunk_keys, zstride, NSEG;
@@ -134,19 +168,8 @@ CompressLayout compress_layout(const calidrop_params* p, int64_t total_tokens, i
   const int G = p->n_q_heads / p->n_kv_heads;
   L.RB = G * p->window > cd::kRowBlock ? 2 * cd::kRowBlock : cd::kRowBlock;     // 256-row blocks: such heads stream K once
   L.NRB = ceil_div(G * p->window, L.RB);
-  {  // Keys per scoring workgroup: one workgroup in each of 512 places (two per compute unit) while that keeps it
-     // at 32 stages of 64 keys or less, otherwise 16 stages and as many rounds as it takes.  Measured: 131072 keys,
-     // 256 rows, both passes 155 us at 2048 keys (one round) against 172 us at 512; 8192 keys 17 us at 128 keys,
-     // 19 us at 64 and 256; 512 keys in fp32 (two KV heads) 31 us per call at 64 keys against 49 us at 256; a
-     // ragged batch of 64 prompts 899 us per call at 1024, 921 us at 2048; 32 layers of 32768 1179 against 1196 us.
-    const int64_t stages = (total_tokens + cd::kChunkUnit - 1) / cd::kChunkUnit * p->n_kv_heads * L.NRB;
-    const int64_t each = (stages + 511) / 512;
-    L.chunk_keys = static_cast<int>(each <= 32 ? each : 16) * cd::kChunkUnit;
-  }
+  L.chunk_keys = plan_chunk(p, total_tokens, max_seq_len, L.RB, L.NRB);
   L.NCH = ceil_div(max_seq_len, L.chunk_keys);
-  // the chunks of the longest prompt alike: 62 prompts of 1050-1174 keys, 40 heads, 1024 + 150 keys 259 us per call,
-  // 640 + 534 keys 204 us; 60 prompts of 2100 keys 236 -> 209 us
-  L.chunk_keys = ceil_div(ceil_div(max_seq_len, L.NCH), cd::kChunkUnit) * cd::kChunkUnit;
   L.W32 = ceil_div(max_seq_len, 64) * 2;
   L.sp = plan_splits(p->batch * p->n_kv_heads, max_seq_len, true);
   const size_t rows = static_cast<size_t>(p->batch) * p->n_kv_heads * L.NRB * L.RB;
@@ -821,6 +844,9 @@ int calidrop_compress_workspace_region(const calidrop_params* p_in, int64_t tota
   } else if (region == CALIDROP_REGION_SCORE) {
     *offset = L.score;
     *bytes = static_cast<size_t>(total_tokens) * p->n_kv_heads * sizeof(float);
+  } else if (region == CALIDROP_REGION_ROW_PARTS) {
+    *offset = L.rowpart;
+    *bytes = static_cast<size_t>(p->batch) * p->n_kv_heads * L.NRB * L.RB * L.NCH * sizeof(float2);
   } else {
     return fail(CALIDROP_EINVAL, "unknown workspace region %d", region);
   }

@@ -28,7 +28,7 @@ struct ScoreArgs {
   int batch, Hq, Hkv, G, w, B, R, NRB, NCH, max_seq_len;
   int RB;               // window-query rows per row block: 128, or 256 when a KV head has more than 128 (R = G*w)
   int row_stride;       // rows per KV head in rowpart / row_lse: NRB * RB
-  int chunk_keys;       // keys per workgroup (multiple of 64); each wave takes chunk_keys/4 contiguous keys
+  int chunk_keys;       // keys per workgroup (multiple of 64); every wave reads all of them for query rows of its own
   float sl2;            // scale * log2(e)
   int keep_k;           // pass 1 leaves K in the last-level cache for pass 2 (K of the whole call fits it)
   float2* rowpart;      // [batch*Hkv][row_stride][NCH] (max, sum) per chunk

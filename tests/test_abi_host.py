@@ -45,6 +45,35 @@ def test_workspace_sizes():
     assert nbytes == 2 * 8 * 128 * 4
 
 
+@pytest.mark.parametrize("lens,heads,w,dtype", [
+    ([131072], 8, 64, "bf16"), ([131200], 8, 64, "bf16"), ([140000], 8, 64, "bf16"), ([8192], 8, 32, "bf16"), ([500], 2, 16, "fp32"),
+    ([32768] * 32, 8, 32, "bf16"), ([13804] * 13, 2, 32, "fp32"), ([3000] * 20, 8, 64, "fp32"), ([2816, 2816, 2816], 1, 8, "fp32"),
+    ([16384, 9000, 13300, 12100, 9900, 16000], 8, 64, "fp32"), ([1200 - 10 * b for b in range(60)], 8, 64, "fp32"),
+    ([16384 - 190 * b for b in range(64)], 8, 32, "bf16"), ([4194, 2641, 3000, 3300, 3600, 4000], 8, 64, "fp32")])
+def test_scoring_chunks_fill_the_compute_units_with_what_is_launched(lens, heads, w, dtype):
+    # the cost of a plan, from the workgroups the lengths really launch: those of the fullest of 256 compute units times
+    # the 64-key units of one and what it takes to start; no chunk length that is allowed may be clearly better
+    p = cd.make_params(dtype=cd.BF16 if dtype == "bf16" else cd.FP32, batch=len(lens), n_q_heads=4 * heads, n_kv_heads=heads,
+                       head_dim=128, window=w, budget=w + 8, pool_kernel=7)
+    block = 256 if 4 * w > 128 else 128
+    rows = len(lens) * heads * block
+    _, nbytes = cd.calidrop_compress_workspace_region(p, sum(lens), max(lens), cd.REGION_ROW_PARTS)
+    nch = nbytes // (rows * 8)
+    assert nbytes == rows * 8 * nch
+    ceil = lambda a, b: -(-a // b)
+    even = len(set(lens)) == 1
+
+    def cost(units):
+        groups = sum(ceil(n, 64 * units) for n in lens) * heads
+        load = ceil(groups, 256) if even else 0.25 * ceil(groups, 256) + 0.75 * (groups / 256 + 0.5)
+        return max(load, 1 if block == 256 else 2) * (units + 0.5)
+
+    most = 32 if block == 256 else 12 if even else 8
+    taken = ceil(ceil(max(lens), nch), 64)
+    assert taken <= most
+    assert cost(taken) <= (1.0 if even else 1.15) * min(cost(u) for u in range(1, min(most, ceil(max(lens), 64)) + 1))
+
+
 @pytest.mark.parametrize("kw,status", [
     (dict(head_dim=96), cd.EUNSUPPORTED),
     (dict(n_q_heads=30), cd.ESHAPE),
