@@ -196,8 +196,12 @@ __global__ __launch_bounds__(256, 2) void h2o_rowlse_kernel(H2oArgs a) {
   }
 }
 
+// fp32 has to fit three workgroups on a compute unit (168 registers a lane; with 184 two fit, and 2 prompts of 2584
+// tokens, 32 heads, D = 128, took 599 us instead of 515): the addresses of the row stream are therefore worked out anew
+// for every stage - hidden from the compiler, which would keep them in registers or, short of those, in memory - a
+// dozen instructions beside 256 matrix products (now 510 us).
 template <typename T, int D, int RT>
-__global__ __launch_bounds__(256, 2) void h2o_votes_kernel(H2oArgs a) {
+__global__ __launch_bounds__(256, sizeof(T) == 4 ? 3 : 2) void h2o_votes_kernel(H2oArgs a) {
   using KS = KeyStream<T, D>;
   constexpr int KT = KS::KT, NK = KS::NK, SK = KS::kStageKeys, EPL = KS::EPL, KD = KS::KD;
   constexpr int WR = 16 * RT, BR = 4 * WR;
@@ -224,8 +228,6 @@ __global__ __launch_bounds__(256, 2) void h2o_votes_kernel(H2oArgs a) {
 
   __shared__ __attribute__((aligned(16))) char s_q[2][KS::kStageBytes];
   __shared__ __attribute__((aligned(16))) float s_z[2][64];      // row log-sum-exp of the staged rows
-  KeyStreamDirect<T, D> ks;
-  ks.init();
   typename KS::Frags fr;
   fr.init(i, c);
 
@@ -254,8 +256,12 @@ __global__ __launch_bounds__(256, 2) void h2o_votes_kernel(H2oArgs a) {
     const int nstages = (n - j0 + SK - 1) / SK;
     auto issue = [&](int st, char* rows, float* z) __attribute__((always_inline)) {   // rows and their log-sum-exp, straight into LDS
       const int q0 = j0 + st * SK;
+      uint32_t tid = threadIdx.x;
+      if constexpr (sizeof(T) == 4) asm("" : "+v"(tid));
+      KeyStreamDirect<T, D> ks;
+      ks.init(tid);
       ks.issue(qbase, q0, n, rows);
-      if (threadIdx.x < SK) load_to_lds4(lse_row + q0 + threadIdx.x, z);
+      if (tid < SK) load_to_lds4(lse_row + q0 + tid, z);
     };
     __syncthreads();                               // the previous job is done with the buffers
     issue(0, s_q[0], s_z[0]);

@@ -107,9 +107,9 @@ struct KeyStreamDirect {
   static constexpr int kKeys = NT / CH;
   uint32_t key0, ch0;    // of slot threadIdx.x: its stage-local key, its global chunk index
 
-  __device__ __forceinline__ void init() {
-    key0 = threadIdx.x / CH;
-    ch0 = (threadIdx.x % CH) ^ KS::swz(key0);
+  __device__ __forceinline__ void init(uint32_t tid = threadIdx.x) {
+    key0 = tid / CH;
+    ch0 = (tid % CH) ^ KS::swz(key0);
   }
   // kStream: the rows are read once and not again soon - non-temporal loads
   template <bool kStream = false>

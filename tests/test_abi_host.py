@@ -3,6 +3,7 @@ header declares, and rejects bad arguments before touching HIP."""
 import ctypes
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -43,6 +44,30 @@ def test_workspace_sizes():
     assert nbytes == 2 * 8192 * 8 * 4 and off % 256 == 0 and off + nbytes <= n1
     off, nbytes = cd.calidrop_compress_workspace_region(p, 2 * 8192, 8192, cd.REGION_ROW_LSE)
     assert nbytes == 2 * 8 * 128 * 4
+
+
+def kernel_registers(lib, tmp_path):
+    """{mangled kernel name: (vector registers, spilled ones)} from the metadata of a library's gfx950 code object."""
+    tool = "/opt/rocm/llvm/bin/"
+    fat, code = str(tmp_path / "fat"), str(tmp_path / "code")
+    subprocess.run([tool + "llvm-objcopy", "--dump-section", ".hip_fatbin=" + fat, lib, os.devnull], check=True)
+    subprocess.run([tool + "clang-offload-bundler", "--unbundle", "--type=o", "--input=" + fat, "--output=" + code,
+                    "--targets=hipv4-amdgcn-amd-amdhsa--gfx950"], check=True)
+    notes = subprocess.run([tool + "llvm-readelf", "--notes", code], check=True, capture_output=True, text=True).stdout
+    out = {}
+    for block in re.split(r"\n\s+- \.agpr_count", notes)[1:]:
+        field = lambda k: re.search(r"\." + k + r":\s+(\S+)", block).group(1)
+        out[field("name")] = (int(field("vgpr_count")), int(field("vgpr_spill_count")))
+    return out
+
+
+@pytest.mark.skipif(not os.path.exists("/opt/rocm/llvm/bin/clang-offload-bundler"), reason="needs the ROCm object tools")
+def test_kernels_keep_their_registers(tmp_path):
+    # 512 registers a lane and SIMD: what a kernel may use so that the workgroups it counts on fit a compute unit
+    regs = kernel_registers(cd.LIB_PATH, tmp_path)
+    assert len(regs) > 40 and all(spilled == 0 for _, spilled in regs.values()), {k: v for k, v in regs.items() if v[1]}
+    (votes,) = [v for k, v in regs.items() if "h2o_votes_kernelIfLi128ELi2" in k]
+    assert votes[0] <= 512 // 3 // 8 * 8
 
 
 @pytest.mark.parametrize("lens,heads,w,dtype", [
