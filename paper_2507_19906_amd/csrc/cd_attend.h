@@ -342,17 +342,12 @@ __global__ __launch_bounds__(256) void attend_partial_kernel(AttendArgs a) {
   const int split = (blockIdx.x + g + a.Hkv * b) % a.NS;
   int rows, head_stride, off0;
   attend_geometry(a, b, rows, head_stride, off0);
-  // With K and V both streamed the splits of a head take its 128-row blocks in turn, so that at any time they read one
-  // moving window of the rows together.  As contiguous ranges - a power of two of bytes, all at the same distance from
-  // their start - they fell on the same memory channels, and the time depended on where the tensors lay (given set, 8
-  // layers of 32768 rows: 170 us a call with one set of tensors, 190 with three used in turn; now 175 and 180).  A
-  // cache of 4100 rows in 17 splits: 11.1 -> 10.6 us a call.  The pass that streams V alone keeps contiguous ranges
-  // (32 layers: 342 us, in turn 350).
-  const int splits = (rows + a.rows_per_split - 1) / a.rows_per_split;
-  if (split >= splits) return;
-  const int row_first = kLogits ? split * a.rows_per_split + wave_index() * kTileRows : (split * kAttWaves + wave_index()) * kTileRows;
-  const int row_step = kLogits ? kAttWaves * kTileRows : splits * kAttWaves * kTileRows;
-  const int row_end = kLogits ? min(rows, (split + 1) * a.rows_per_split) : rows;
+  // Contiguous rows.  With the 128-row blocks of a head dealt to its splits in turn, a pass over K and V took 0.887 to 1.127
+  // of the time, on average half a percent more (214 shapes, four places in memory for the tensors of each), without a
+  // size or stride that says which.
+  const int row_begin = split * a.rows_per_split;
+  if (row_begin >= rows) return;
+  const int row_end = min(rows, row_begin + a.rows_per_split);
   if (a.only_flagged) {
     bool any = false;
     for (int hh = 0; hh < a.G; ++hh) any |= a.only_flagged[b * a.Hq + g * a.G + hh] == 2;
@@ -370,8 +365,9 @@ __global__ __launch_bounds__(256) void attend_partial_kernel(AttendArgs a) {
   __shared__ float2 s_ml[kAttWaves][16];
   AttendWave<T, D> w;
   using NoWork = typename AttendWave<T, D>::NoWork;
+  const int row_first = row_begin + wv * kTileRows;
+  constexpr int kRowStep = kAttWaves * kTileRows;
   const uint32_t* bm_first = bm ? bm + (row_first >> 5) : nullptr;
-  const int bm_step = row_step >> 5;
   {
     const int h = g * a.G + i;
     const T* qp = static_cast<const T*>(a.q);
@@ -382,14 +378,14 @@ __global__ __launch_bounds__(256) void attend_partial_kernel(AttendArgs a) {
   if constexpr (kLogits) {
     // padding rows of the last tile hold whatever the workspace held: they are masked before use
     const float* zhead = a.cal_logit + static_cast<int64_t>(b * a.Hq + g * a.G + i) * a.zstride;
-    w.template run<true, true>(kbase, vbase, bm_first, rows, row_first, row_end, row_step,
-                               a.sl2, i, c, zhead, i < a.G, false, NoWork(), nullptr, bm_step);
+    w.template run<true, true>(kbase, vbase, bm_first, rows, row_first, row_end, kRowStep,
+                               a.sl2, i, c, zhead, i < a.G, false, NoWork(), nullptr, kAttWaves);
   } else if constexpr (kRowsK) {
     // 16 rows of K fit the area the wave publishes its outputs to afterwards
     static_assert(16 * D * sizeof(T) <= sizeof(s_o[0]), "K staging area");
     w.template run<true, false, NoWork, true>(
-        kbase, vbase, bm_first, rows, row_first, row_end, row_step, a.sl2, i, c, nullptr, false,
-        false, NoWork(), reinterpret_cast<char*>(s_o[wv]), bm_step);
+        kbase, vbase, bm_first, rows, row_first, row_end, kRowStep, a.sl2, i, c, nullptr, false,
+        false, NoWork(), reinterpret_cast<char*>(s_o[wv]), kAttWaves);
   } else if constexpr (kList) {
     w.request_first_k(kbase, min(row_first, rows - 1), rows, i, c);
     // bit = skip: the listed positions, or with the calibration set listed every other one
@@ -399,17 +395,16 @@ __global__ __launch_bounds__(256) void attend_partial_kernel(AttendArgs a) {
     const int32_t* list = a.list + static_cast<int64_t>(b * a.Hkv + g) * a.list_len;
     for (int t = threadIdx.x; t < a.list_len; t += 256) {
       const int pos = list[t];
-      const int block = pos / (kAttWaves * kTileRows);            // word = position of the tile among this workgroup's
-      if (pos >= 0 && pos < rows && block % splits == split) {
-        const int word = block / splits * kAttWaves + (pos / kTileRows) % kAttWaves;
-        if (a.list_is_calib) atomicAnd(&s_bits[word], ~(1u << (pos % kTileRows)));
-        else atomicOr(&s_bits[word], 1u << (pos % kTileRows));
+      if (pos >= row_begin && pos < row_end) {
+        const int bit = pos - row_begin;
+        if (a.list_is_calib) atomicAnd(&s_bits[bit / kTileRows], ~(1u << (bit % kTileRows)));
+        else atomicOr(&s_bits[bit / kTileRows], 1u << (bit % kTileRows));
       }
     }
     __syncthreads();
-    w.run(kbase, vbase, s_bits + wv, rows, row_first, row_end, row_step, a.sl2, i, c, nullptr, false, true, NoWork(), nullptr, kAttWaves);
+    w.run(kbase, vbase, s_bits + wv, rows, row_first, row_end, kRowStep, a.sl2, i, c, nullptr, false, true, NoWork(), nullptr, kAttWaves);
   } else {
-    w.run(kbase, vbase, bm_first, rows, row_first, row_end, row_step, a.sl2, i, c, nullptr, false, false, NoWork(), nullptr, bm_step);
+    w.run(kbase, vbase, bm_first, rows, row_first, row_end, kRowStep, a.sl2, i, c, nullptr, false, false, NoWork(), nullptr, kAttWaves);
   }
 
   // ---- merge the 4 waves through LDS and write this split's partial ------------------------

@@ -299,6 +299,27 @@ def test_recomputation_at_the_edges_of_its_row_blocks(dtype, budget, m):
     assert rep["recal_heads"] == wl.batch * wl.n_q_heads * wl.decode_steps
 
 
+@pytest.mark.parametrize("dtype,m", [("bf16", 0), ("fp32", 0), ("bf16", 900), ("fp32", 1280), ("bf16", 1281)])
+def test_recomputation_with_several_row_blocks_per_split(dtype, m):
+    # splits of 640 rows, five blocks each: lengths that end one short of, at and one past a split and a block; lists of
+    # up to twice a split, read by the streaming pass itself, and one entry more; short prompts in the same batch
+    wl = small(dtype, 4, 2, 64, [20001, 19840, 19841, 19839, 640, 641, 130, 30], 16, 40, 5, T=2, name="split_blocks")
+    wl.theta1 = wl.theta2 = 2.0                      # every head is recomputed at every step
+    x = to_dev(synth.make_inputs(wl, 84))
+    bufs = H.gpu_compress(wl, x, calib_size=m)
+    rep = {}
+    for t in range(wl.decode_steps):
+        q_t = x["q_dec"][t]
+        bufs.decode(q_t)
+        torch.cuda.synchronize()
+        before = H.snapshot_state(bufs)
+        bufs.recalibrate(q_t, x["k"], x["v"], x["seq_offsets"])
+        torch.cuda.synchronize()
+        for b in range(wl.batch):
+            H.check_recalibrate(wl, x, bufs, q_t, b, before, report=rep)
+    assert rep["recal_heads"] == wl.batch * wl.n_q_heads * wl.decode_steps
+
+
 def test_recomputation_yields_exact_full_attention():
     # after recomputation with the current query, the calibrated output is the attention over
     # the whole prompt (Eq. 1 with the true query on both parts)
