@@ -404,7 +404,11 @@ __global__ __launch_bounds__(256) void attend_partial_kernel(AttendArgs a) {
     __syncthreads();
     w.run(kbase, vbase, s_bits + wv, rows, row_first, row_end, kRowStep, a.sl2, i, c, nullptr, false, true, NoWork(), nullptr, kAttWaves);
   } else {
-    w.run(kbase, vbase, bm_first, rows, row_first, row_end, kRowStep, a.sl2, i, c, nullptr, false, false, NoWork(), nullptr, kAttWaves);
+    // requested here and not in run(): there the compiler moves the loads ahead of the loop and drops their
+    // non-temporal hint, the first tile of every wave (a quarter of K at 512 rows per split) then goes through the
+    // caches and evicts what the gather left there (32 prompts of 7000, fp32: 436 us a call, with the hint 387)
+    w.request_first_k(kbase, min(row_first, rows - 1), rows, i, c);
+    w.run(kbase, vbase, bm_first, rows, row_first, row_end, kRowStep, a.sl2, i, c, nullptr, false, true, NoWork(), nullptr, kAttWaves);
   }
 
   // ---- merge the 4 waves through LDS and write this split's partial ------------------------

@@ -46,14 +46,23 @@ def test_workspace_sizes():
     assert nbytes == 2 * 8 * 128 * 4
 
 
-def kernel_registers(lib, tmp_path):
-    """{mangled kernel name: (vector registers, spilled ones)} from the metadata of a library's gfx950 code object."""
-    tool = "/opt/rocm/llvm/bin/"
+TOOLS = "/opt/rocm/llvm/bin/"
+needs_object_tools = pytest.mark.skipif(not os.path.exists(TOOLS + "clang-offload-bundler"), reason="needs the ROCm object tools")
+
+
+def code_object(lib, tmp_path):
+    """The gfx950 code object inside a library built here, as a file."""
     fat, code = str(tmp_path / "fat"), str(tmp_path / "code")
-    subprocess.run([tool + "llvm-objcopy", "--dump-section", ".hip_fatbin=" + fat, lib, os.devnull], check=True)
-    subprocess.run([tool + "clang-offload-bundler", "--unbundle", "--type=o", "--input=" + fat, "--output=" + code,
+    subprocess.run([TOOLS + "llvm-objcopy", "--dump-section", ".hip_fatbin=" + fat, lib, os.devnull], check=True)
+    subprocess.run([TOOLS + "clang-offload-bundler", "--unbundle", "--type=o", "--input=" + fat, "--output=" + code,
                     "--targets=hipv4-amdgcn-amd-amdhsa--gfx950"], check=True)
-    notes = subprocess.run([tool + "llvm-readelf", "--notes", code], check=True, capture_output=True, text=True).stdout
+    return code
+
+
+def kernel_registers(lib, tmp_path):
+    """{mangled kernel name: (vector registers, spilled ones)} from the code object's metadata."""
+    notes = subprocess.run([TOOLS + "llvm-readelf", "--notes", code_object(lib, tmp_path)], check=True, capture_output=True,
+                           text=True).stdout
     out = {}
     for block in re.split(r"\n\s+- \.agpr_count", notes)[1:]:
         field = lambda k: re.search(r"\." + k + r":\s+(\S+)", block).group(1)
@@ -61,13 +70,29 @@ def kernel_registers(lib, tmp_path):
     return out
 
 
-@pytest.mark.skipif(not os.path.exists("/opt/rocm/llvm/bin/clang-offload-bundler"), reason="needs the ROCm object tools")
+@needs_object_tools
 def test_kernels_keep_their_registers(tmp_path):
     # 512 registers a lane and SIMD: what a kernel may use so that the workgroups it counts on fit a compute unit
     regs = kernel_registers(cd.LIB_PATH, tmp_path)
     assert len(regs) > 40 and all(spilled == 0 for _, spilled in regs.values()), {k: v for k, v in regs.items() if v[1]}
     (votes,) = [v for k, v in regs.items() if "h2o_votes_kernelIfLi128ELi2" in k]
     assert votes[0] <= 512 // 3 // 8 * 8
+
+
+@needs_object_tools
+def test_streamed_rows_bypass_the_caches(tmp_path):
+    # every 16-byte load of K and V in the streaming passes carries the non-temporal hint; without it are the pieces of the
+    # query and, in the launches that carry the gather, one K and one V piece of a retained row
+    asm = subprocess.run([TOOLS + "llvm-objdump", "-d", "--no-show-raw-insn", code_object(cd.LIB_PATH, tmp_path)], check=True,
+                         capture_output=True, text=True).stdout
+    seen = 0
+    for head, body in re.findall(r"^[0-9a-f]+ <(_ZN2cd21attend_partial_kernelI[^>]*)>:\n(.*?)(?=^\S|\Z)", asm, re.M | re.S):
+        elem, d, logits, gather = re.search(r"kernelI(f|NS_6bf16_tE)Li(\d+)ELb(\d)ELb\dELb(\d)E", head).groups()
+        loads = [l for l in body.splitlines() if "global_load_dwordx4" in l]
+        pieces = int(d) * (4 if elem == "f" else 2) // 64
+        assert sum(" nt" not in l for l in loads) == (0 if logits == "1" else pieces) + 2 * int(gather), head
+        seen += 1
+    assert seen == 24
 
 
 @pytest.mark.parametrize("lens,heads,w,dtype", [
