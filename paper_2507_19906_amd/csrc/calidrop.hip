@@ -106,10 +106,13 @@ constexpr int kFusedMaxRowsFewPairs = 2048;
 
 // How the rows of a streaming-attention pass are split over workgroups.
 struct SplitPlan { int rows_per_split, NS; };
-// `prompt`: a pass over prompt rows.  Where that leaves only a few hundred workgroups with a few tiles per wave
-// each, they are halved down to one tile per wave: 8 KV heads of 8192 rows 7.9 -> 6.3 us at 128 rows instead of 256.
-// Longer splits stay at 32 (131072 rows: 44 us at 4096 rows, 45 us at 1024).
-SplitPlan plan_splits(int heads_kv_total, int max_rows, bool prompt = false) {
+// `few`: a pass over prompt rows whose splits, where there are no more than `few` of them with a few tiles per wave each,
+// are halved down to one tile per wave.  In 288 calls (2 to 64 (sequence, KV head) pairs, 2048 to 16384 rows) that is up to
+// 28 % faster while it ends below two workgroups per compute unit - where V is streamed alone, and in fp32, whose products
+// keep a wave busy longer (8 heads of 8192 rows, V alone 7.9 -> 6.3 us) - and up to 21 % slower where it goes on to more
+// (16 heads of 8192 rows, K and V in bf16: 17.9 us a call at 256 rows, 20.3 at 128), in bf16 with K and V streamed from
+// one per unit on.  Longer splits stay at 32 (131072 rows: 44 us at 4096 rows, 45 us at 1024).
+SplitPlan plan_splits(int heads_kv_total, int max_rows, int few = 0) {
   const int kTargetGroups = 4096;                      // ~16 workgroups per compute unit
   const int kMaxSplits = 32;
   const int kMinRows = cd::kTileRows * cd::kAttWaves;  // one tile per wave
@@ -119,10 +122,13 @@ SplitPlan plan_splits(int heads_kv_total, int max_rows, bool prompt = false) {
   if (want > kMaxSplits) want = kMaxSplits;
   int rps = ceil_div(ceil_div(max_rows, want), kMinRows) * kMinRows;
   if (rps < kMinRows) rps = kMinRows;
-  if (prompt && rps <= 4 * kMinRows)
-    while (rps > kMinRows && static_cast<int64_t>(heads_kv_total) * ceil_div(max_rows, rps) <= 512) rps = ceil_div(rps / 2, kMinRows) * kMinRows;
+  if (rps <= 4 * kMinRows)
+    while (rps > kMinRows && static_cast<int64_t>(heads_kv_total) * ceil_div(max_rows, rps) <= few) rps = ceil_div(rps / 2, kMinRows) * kMinRows;
   return SplitPlan{rps, ceil_div(max_rows, rps)};
 }
+
+constexpr int kFewV = 256;                             // V alone streamed (the logits come from the scoring pass)
+int few_kv(const calidrop_params* p) { return p->dtype == CALIDROP_FP32 ? 256 : 128; }      // K and V streamed
 
 // Keys per scoring workgroup, in units of 64.  The 256 compute units share the workgroups of a launch, so a plan costs the
 // workgroups of the fullest unit times the key units of one, plus half a unit for its start (query fragments, first
@@ -171,7 +177,7 @@ CompressLayout compress_layout(const calidrop_params* p, int64_t total_tokens, i
   L.chunk_keys = plan_chunk(p, total_tokens, max_seq_len, L.RB, L.NRB);
   L.NCH = ceil_div(max_seq_len, L.chunk_keys);
   L.W32 = ceil_div(max_seq_len, 64) * 2;
-  L.sp = plan_splits(p->batch * p->n_kv_heads, max_seq_len, true);
+  L.sp = plan_splits(p->batch * p->n_kv_heads, max_seq_len, kFewV);
   const size_t rows = static_cast<size_t>(p->batch) * p->n_kv_heads * L.NRB * L.RB;
   const size_t toks = static_cast<size_t>(total_tokens) * p->n_kv_heads;
   size_t off = 0;
@@ -511,7 +517,7 @@ struct RecalLayout { size_t bitmap, part_o, part_ml, total; int W32; SplitPlan s
 RecalLayout recal_layout(const calidrop_params* p, int32_t max_seq_len) {
   RecalLayout L{};
   L.W32 = ceil_div(max_seq_len, 64) * 2;
-  L.sp = plan_splits(p->batch * p->n_kv_heads, max_seq_len, true);
+  L.sp = plan_splits(p->batch * p->n_kv_heads, max_seq_len, few_kv(p));
   const size_t slots = static_cast<size_t>(p->batch) * p->n_q_heads * L.sp.NS;
   size_t off = 0;
   L.bitmap = off;  off += round256(static_cast<size_t>(p->batch) * p->n_kv_heads * L.W32 * sizeof(uint32_t));
@@ -713,7 +719,7 @@ H2oLayout h2o_layout(const calidrop_params* p, int64_t total_tokens, int32_t max
   H2oLayout L{};
   L.lse_stride = ceil_div(max_seq_len, 256) * 256;
   L.W32 = ceil_div(max_seq_len, 64) * 2;
-  L.sp = plan_splits(p->batch * p->n_kv_heads, max_seq_len, true);
+  L.sp = plan_splits(p->batch * p->n_kv_heads, max_seq_len, few_kv(p));
   L.NSEG = ceil_div(std::max(max_seq_len - n_local, 1), cd::kWideSeg);
   const size_t toks = static_cast<size_t>(total_tokens) * p->n_kv_heads;
   const size_t slots = static_cast<size_t>(p->batch) * p->n_q_heads * L.sp.NS;
