@@ -459,18 +459,17 @@ __device__ __forceinline__ float block_sum(float x, float* red, int nthreads) {
   return t;
 }
 
-// One workgroup of 4 D threads per (sequence, query head): merge the split partials (Eq. 1-2 applied NS-1 times),
-// then either store the calibration state (Alg. 1 steps 6-8) or apply the cosine gate and the calibration
-// merge (Alg. 2 steps 2-15).  Nothing but latency: the splits are dealt to four groups of D threads, so that up
-// to 128 partials are four short chains of loads instead of one long one, and the four results meet in LDS.
-constexpr int kFinalGroups = 4;
-template <typename T, int D>
-__global__ __launch_bounds__(kFinalGroups * D) void attend_finalize_kernel(FinalArgs a) {
+// One workgroup per (sequence, query head): merge the split partials (Eq. 1-2 applied NS-1 times), then either store the
+// calibration state (Alg. 1 steps 6-8) or apply the cosine gate and the calibration merge (Alg. 2 steps 2-15).
+// Nothing but latency: the splits are dealt to kGroups groups of D threads, so that up to 128 partials are short
+// chains of loads instead of one long one, and the results of the groups meet in LDS.
+template <typename T, int D, int kGroups>
+__global__ __launch_bounds__(kGroups * D) void attend_finalize_kernel(FinalArgs a) {
   const int h = blockIdx.x, b = blockIdx.y, d = threadIdx.x % D;
   const int grp = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / D);
-  __shared__ float red[kFinalGroups * D / 64];
-  __shared__ float s_o[kFinalGroups][D];
-  __shared__ float2 s_ml[kFinalGroups];
+  __shared__ float red[kGroups * D / 64];
+  __shared__ float s_o[kGroups][D];
+  __shared__ float2 s_ml[kGroups];
   if (a.calib_mode == 2 && a.flags[b * a.Hq + h] != 2) return;      // only heads flagged for recomputation
   int rows;
   if (!a.row_len) {                   // rows of a prompt (minus the window); else live rows of a packed buffer
@@ -491,12 +490,12 @@ __global__ __launch_bounds__(kFinalGroups * D) void attend_finalize_kernel(Final
   float cq = 0.f, co = 0.f, c_lse_in = -INFINITY;
   if (a.calib_mode == 0) { cq = a.c_q[hd * D + d]; co = a.c_out[hd * D + d]; c_lse_in = a.c_lse[hd]; }
   float o = 0.f, ll = 0.f, mm = -INFINITY;
-  for (int s0 = grp; s0 < ns; s0 += 8 * kFinalGroups) {             // eight partials in flight at a time
+  for (int s0 = grp; s0 < ns; s0 += 8 * kGroups) {             // eight partials in flight at a time
     float2 ml[8];
     float po[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int s = s0 + u * kFinalGroups;
+      const int s = s0 + u * kGroups;
       ml[u] = s < ns ? a.part_ml[slot0 + s] : make_float2(-INFINITY, 0.f);
       po[u] = s < ns ? a.part_o[(slot0 + s) * D + d] : 0.f;
     }
@@ -515,18 +514,20 @@ __global__ __launch_bounds__(kFinalGroups * D) void attend_finalize_kernel(Final
       ll += ml[u].y * sc;
     }
   }
-  s_o[grp][d] = o;
-  if (d == 0) s_ml[grp] = make_float2(mm, ll);
-  __syncthreads();
-  {
+  if constexpr (kGroups > 1) {
+    s_o[grp][d] = o;
+    if (d == 0) s_ml[grp] = make_float2(mm, ll);
+  }
+  __syncthreads();                     // also: every thread has read its head's flag
+  if constexpr (kGroups > 1) {
     mm = -INFINITY;
 #pragma unroll
-    for (int gg = 0; gg < kFinalGroups; ++gg) mm = fmaxf(mm, s_ml[gg].x);
+    for (int gg = 0; gg < kGroups; ++gg) mm = fmaxf(mm, s_ml[gg].x);
     const float ms = (mm == -INFINITY) ? 0.f : mm;
     o = 0.f;
     ll = 0.f;
 #pragma unroll
-    for (int gg = 0; gg < kFinalGroups; ++gg) {
+    for (int gg = 0; gg < kGroups; ++gg) {
       const float sc = fast_exp2(s_ml[gg].x - ms);
       o += s_o[gg][d] * sc;
       ll += s_ml[gg].y * sc;

@@ -534,6 +534,30 @@ def test_gather_workgroups_behind_the_streaming_ones(dtype, budget):
     run_case(small(dtype, 4, 2, 64, [2900, budget - 1, 2850], 16, budget, 5, T=1, name=f"gather_{budget}"))
 
 
+@pytest.mark.parametrize("batch", [96, 97])
+def test_split_partials_merged_by_four_groups_or_one(batch):
+    # 768 heads are the last that four groups of threads each merge, 776 the first with one group; 11 splits, so that
+    # the groups get unequal shares, prompts with fewer splits and with none (within the budget)
+    wl = small("fp32", 8, 2, 64, [1400, 60, 129 + 16, 700] + [300 + 7 * b for b in range(batch - 5)] + [1399], 16, 80, 5, T=2,
+               name=f"merge_{batch}")
+    wl.theta1 = wl.theta2 = 2.0                      # every head is recomputed at every step
+    x = to_dev(synth.make_inputs(wl, 85))
+    bufs = H.gpu_compress(wl, x)
+    rep = {}
+    some = (0, 1, 2, 3, batch // 2, batch - 1)
+    for b in some:
+        H.check_compress(wl, x, bufs, b, report=rep)
+    for t in range(wl.decode_steps):
+        q_t = x["q_dec"][t]
+        bufs.decode(q_t)
+        torch.cuda.synchronize()
+        before = H.snapshot_state(bufs)
+        bufs.recalibrate(q_t, x["k"], x["v"], x["seq_offsets"])
+        torch.cuda.synchronize()
+        for b in some:
+            H.check_recalibrate(wl, x, bufs, q_t, b, before, report=rep)
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 def test_scoring_chunks_of_equal_length(dtype):
     # many short prompts of two query-row blocks: one round of 512 workgroups would be 1408 keys each, which are evened
