@@ -77,6 +77,8 @@ def test_kernels_keep_their_registers(tmp_path):
     assert len(regs) > 40 and all(spilled == 0 for _, spilled in regs.values()), {k: v for k, v in regs.items() if v[1]}
     (votes,) = [v for k, v in regs.items() if "h2o_votes_kernelIfLi128ELi2" in k]
     assert votes[0] <= 512 // 3 // 8 * 8
+    (select,) = [v for k, v in regs.items() if "select_lds_kernelILi1024ELi8" in k]
+    assert select[0] <= 512 // 8                     # two workgroups of 1024 threads
 
 
 @needs_object_tools
