@@ -102,7 +102,8 @@ typedef struct {
 enum { CALIDROP_OPT_WRITE_SCORES = 1u, CALIDROP_OPT_WIDE_SELECTION = 2u };
 
 /* Bytes of device workspace calidrop_compress needs for these shapes (0 on invalid params).
- * total_tokens = sum of prompt lengths, max_seq_len = longest prompt.                       */
+ * total_tokens = sum of prompt lengths, max_seq_len = longest prompt.  CALIDROP_OPT_WIDE_SELECTION in
+ * p->flags asks for more (the histograms of that selection), so ask with the flags of the call. */
 size_t calidrop_compress_workspace_bytes(const calidrop_params* p, int64_t total_tokens,
                                          int32_t max_seq_len);
 

@@ -135,12 +135,12 @@ int few_kv(const calidrop_params* p) { return p->dtype == CALIDROP_FP32 ? 256 : 
 // stage); with fewer than `least` workgroups its waves leave the matrix pipe or the memory waiting, so fewer save nothing.
 // The chunk of least cost is taken, all chunks of the longest prompt alike, at most 12 units (256-row blocks start
 // slower: 32).  Prompts of different lengths: the host knows their sum and the longest only.  What the short last
-// chunks take is estimated (half a workgroup per prompt at 128 rows, nothing at 256, where they fill gaps), and since
-// the last round is not full everywhere, the rounded count weighs one part and the plain one, half a round later,
-// three; at 128 rows chunks stay at 8 units.
-// Measured over 485 calls (400 to 131072 tokens, 1 to 64 prompts, both types, D 64 and 128, 16 to 256 window rows per KV
-// head), each at 21 chunk lengths: the chunk taken is on average 1.5 % slower than the best of them.  Examples, us a call
-// at 256-512 keys and many rounds / at one workgroup for each of 512 places / now: fp32, 256 rows, 6 prompts of
+// chunks take is estimated (half a workgroup per prompt at 128 rows and, in fp32, while a prompt has fewer than four chunks;
+// else nothing: with 256 rows they mostly fill gaps), and since the last round is not full everywhere, the rounded count
+// weighs one part and the plain one, half a round later, three; at 128 rows chunks stay at 8 units.
+// Measured over 635 calls (350 to 131072 tokens, 1 to 64 prompts, both types, D 64 and 128, 16 to 256 window rows per KV
+// head), each at 21 chunk lengths: the chunk taken is on average 1 % (prompts of one length) to 3.5 % (256 rows, several
+// lengths) slower than the best of them.  Examples, us a call at 256-512 keys and many rounds / at one workgroup for each of 512 places / now: fp32, 256 rows, 6 prompts of
 // 9000-17000 tokens 798 / 958 / 730; one of 16384 230 / 209 / 192; bf16, 131072 tokens, 256 rows 281 / 239 / 239.
 int plan_chunk(const calidrop_params* p, int64_t total_tokens, int32_t max_seq_len, int RB, int NRB) {
   const bool even = total_tokens == static_cast<int64_t>(p->batch) * max_seq_len;
@@ -161,6 +161,22 @@ int plan_chunk(const calidrop_params* p, int64_t total_tokens, int32_t max_seq_l
     if (cost < best_cost) { best_cost = cost; best = static_cast<int>(keys); }
   }
   return best;
+}
+
+// Heads whose pooled scores fit in LDS are pooled and selected by one workgroup each; longer ones (and wider pooling)
+// go through the multi-workgroup chain.  `window` = trailing positions always kept.
+bool uses_lds_selection(const calidrop_params* p, int window, int pool_k, int max_seq_len) {
+  return max_seq_len - window <= cd::kSelMaxLdsKeys && p->budget <= cd::kSelMaxLdsKeys && pool_k <= cd::kSelMaxPool &&
+         !(p->flags & CALIDROP_OPT_WIDE_SELECTION);
+}
+// Words a kernel ahead of the selection has to clear for it.
+int64_t wide_words(const calidrop_params* p) { return static_cast<int64_t>(p->batch) * p->n_kv_heads * cd::kWideHistWords; }
+// What the multi-workgroup selection keeps in the workspace: nothing where it is not used.
+struct WideRegions { size_t hist = 0, seg = 0; };      // bytes
+WideRegions wide_regions(const calidrop_params* p, int window, int pool_k, int max_seq_len, int nseg) {
+  if (uses_lds_selection(p, window, pool_k, max_seq_len)) return {};
+  const size_t heads = static_cast<size_t>(p->batch) * p->n_kv_heads;
+  return {round256(heads * cd::kWideHistWords * sizeof(uint32_t)), round256(heads * nseg * cd::kWideSegWords * sizeof(uint32_t))};
 }
 
 struct CompressLayout {
@@ -193,8 +209,9 @@ CompressLayout compress_layout(const calidrop_params* p, int64_t total_tokens, i
   L.part_ml = off; off += round256(slots * sizeof(float2));
   // multi-workgroup selection (prefixes beyond the single-workgroup variant): histograms and counts
   L.NSEG = ceil_div(std::max(max_seq_len - p->window, 1), cd::kWideSeg);
-  L.sel_hist = off; off += round256(static_cast<size_t>(p->batch) * p->n_kv_heads * cd::kWideHistWords * sizeof(uint32_t));
-  L.sel_cnt = off;  off += round256(static_cast<size_t>(p->batch) * p->n_kv_heads * L.NSEG * cd::kWideSegWords * sizeof(uint32_t));
+  const WideRegions wide = wide_regions(p, p->window, p->pool_kernel, max_seq_len, L.NSEG);
+  L.sel_hist = off; off += wide.hist;
+  L.sel_cnt = off;  off += wide.seg;
   L.total = off;
   return L;
 }
@@ -296,15 +313,6 @@ cd::GatherArgs gather_args(const calidrop_params* p, const int32_t* indices, con
   const int64_t vecs = static_cast<int64_t>(p->budget) * (row_bytes / 16);
   return cd::GatherArgs{indices, cache_offsets, k, v, k_c, v_c, row_bytes, static_cast<int>((vecs + cd::kGatherVecs - 1) / cd::kGatherVecs)};
 }
-
-// Heads whose pooled scores fit in LDS are pooled and selected by one workgroup each; longer ones (and wider pooling)
-// go through the multi-workgroup chain.  `window` = trailing positions always kept.
-bool uses_lds_selection(const calidrop_params* p, int window, int pool_k, int max_seq_len) {
-  return max_seq_len - window <= cd::kSelMaxLdsKeys && p->budget <= cd::kSelMaxLdsKeys && pool_k <= cd::kSelMaxPool &&
-         !(p->flags & CALIDROP_OPT_WIDE_SELECTION);
-}
-// Words a kernel ahead of the selection has to clear for it.
-int64_t wide_words(const calidrop_params* p) { return static_cast<int64_t>(p->batch) * p->n_kv_heads * cd::kWideHistWords; }
 
 // Pooling + selection of the votes in se.vote.  For the multi-workgroup chain `sel_hist` has been cleared.
 int run_selection(const calidrop_params* p, int max_seq_len, cd::SelectArgs& se, uint32_t* sel_hist, uint32_t* sel_seg, int NSEG,
@@ -739,8 +747,9 @@ H2oLayout h2o_layout(const calidrop_params* p, int64_t total_tokens, int32_t max
   L.q_last = off;  off += round256(static_cast<size_t>(p->batch) * p->n_q_heads * p->head_dim * sizeof(float));
   L.part_o = off;  off += round256(slots * p->head_dim * sizeof(float));
   L.part_ml = off; off += round256(slots * sizeof(float2));
-  L.sel_hist = off; off += round256(static_cast<size_t>(p->batch) * p->n_kv_heads * cd::kWideHistWords * sizeof(uint32_t));
-  L.sel_cnt = off;  off += round256(static_cast<size_t>(p->batch) * p->n_kv_heads * L.NSEG * cd::kWideSegWords * sizeof(uint32_t));
+  const WideRegions wide = wide_regions(p, n_local, 1, max_seq_len, L.NSEG);
+  L.sel_hist = off; off += wide.hist;
+  L.sel_cnt = off;  off += wide.seg;
   L.total = off;
   return L;
 }

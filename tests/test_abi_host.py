@@ -46,6 +46,23 @@ def test_workspace_sizes():
     assert nbytes == 2 * 8 * 128 * 4
 
 
+@pytest.mark.parametrize("lens,budget", [([1024] * 512, 512), ([600] * 4096, 512), ([8192], 512), ([32768 + 32], 2000)])
+def test_short_prompts_carry_no_histograms(lens, budget):
+    # the multi-workgroup selection's histograms (50 KiB per KV head, 2 KiB per 8192 positions of one) belong to the calls
+    # that run it: prompts beyond 32768 candidates, wide pooling, or on demand
+    kw = dict(batch=len(lens), budget=budget)
+    args = (sum(lens), max(lens))
+    heads = len(lens) * 8
+    extra = heads * 4 * ((3 * 4096 + 512) + -(-(max(lens) - 32) // 8192) * 516)
+    size = cd.calidrop_compress_workspace_bytes(good(**kw), *args)
+    for wide in (dict(flags=cd.OPT_WIDE_SELECTION), dict(pool_kernel=17)):
+        assert 0 <= cd.calidrop_compress_workspace_bytes(good(**kw, **wide), *args) - size - extra <= 512
+    if max(lens) == 32768 + 32:                      # one candidate more than one workgroup selects from
+        assert cd.calidrop_compress_workspace_bytes(good(**kw), args[0] + 1, args[1] + 1) >= size + extra
+    h2o = cd.calidrop_compress_h2o_workspace_bytes
+    assert 0 <= h2o(good(**kw, flags=cd.OPT_WIDE_SELECTION), 32, *args) - h2o(good(**kw), 32, *args) - extra <= 512
+
+
 TOOLS = "/opt/rocm/llvm/bin/"
 needs_object_tools = pytest.mark.skipif(not os.path.exists(TOOLS + "clang-offload-bundler"), reason="needs the ROCm object tools")
 
