@@ -103,7 +103,10 @@ enum { CALIDROP_OPT_WRITE_SCORES = 1u, CALIDROP_OPT_WIDE_SELECTION = 2u };
 
 /* Bytes of device workspace calidrop_compress needs for these shapes (0 on invalid params).
  * total_tokens = sum of prompt lengths, max_seq_len = longest prompt.  CALIDROP_OPT_WIDE_SELECTION in
- * p->flags asks for more (the histograms of that selection), so ask with the flags of the call. */
+ * p->flags asks for more (the histograms of that selection), so ask with the flags of the call.
+ * This size and those for recomputation, a given set and H2O do not fall as total_tokens or
+ * max_seq_len grow (the other parameters being the same): a workspace for the longest prompts
+ * serves the shorter ones.                                                                   */
 size_t calidrop_compress_workspace_bytes(const calidrop_params* p, int64_t total_tokens,
                                          int32_t max_seq_len);
 
@@ -120,7 +123,8 @@ size_t calidrop_decode_workspace_bytes(const calidrop_params* p, int32_t max_cac
  *   SCORE     float, packed like K with D = 1: pooled score of prefix position j of KV head g
  *             of sequence b at [seq_offsets[b]*Hkv + g*n_b + j], j < n_b - w.
  *   ROW_PARTS (compress only) float [batch][Hkv][S][chunks][2]: the (maximum, sum) of every row over each key
- *             chunk; shows into how many chunks the call cuts its longest prompt.
+ *             chunk.  Overwritten by later steps of the call; its size shows into how many chunks the call cuts its
+ *             longest prompt.
  * Returns CALIDROP_OK and fills offset/bytes, or CALIDROP_EINVAL.                            */
 typedef enum { CALIDROP_REGION_ROW_LSE = 0, CALIDROP_REGION_SCORE = 1, CALIDROP_REGION_VOTE_PLANES = 2, CALIDROP_REGION_ROW_PARTS = 3 } calidrop_region;
 int calidrop_compress_workspace_region(const calidrop_params* p, int64_t total_tokens,

@@ -127,6 +127,14 @@ SplitPlan plan_splits(int heads_kv_total, int max_rows, int few = 0) {
   return SplitPlan{rps, ceil_div(max_rows, rps)};
 }
 
+// The most splits any prompt of up to max_rows plans: a number that does not fall as prompts grow, unlike a plan's own, so that a
+// workspace sized for a long prompt serves the shorter ones.  (A plan starts from at most `want` splits and halves only
+// prompts of up to 32 * 512 rows, to at most twice the splits that `few` allows.)
+int most_splits(int heads_kv_total, int max_rows, int few) {
+  const int want = std::min(std::max(ceil_div(4096, heads_kv_total), 1), 32);
+  return std::min(ceil_div(std::max(max_rows, 1), cd::kTileRows * cd::kAttWaves), std::max(want, std::min(2 * (few / heads_kv_total), 128)));
+}
+
 constexpr int kFewV = 256;                             // V alone streamed (the logits come from the scoring pass)
 int few_kv(const calidrop_params* p) { return p->dtype == CALIDROP_FP32 ? 256 : 128; }      // K and V streamed
 
@@ -142,15 +150,17 @@ int few_kv(const calidrop_params* p) { return p->dtype == CALIDROP_FP32 ? 256 : 
 // head), each at 21 chunk lengths: the chunk taken is on average 1 % (prompts of one length) to 3.5 % (256 rows, several
 // lengths) slower than the best of them.  Examples, us a call at 256-512 keys and many rounds / at one workgroup for each of 512 places / now: fp32, 256 rows, 6 prompts of
 // 9000-17000 tokens 798 / 958 / 730; one of 16384 230 / 209 / 192; bf16, 131072 tokens, 256 rows 281 / 239 / 239.
-int plan_chunk(const calidrop_params* p, int64_t total_tokens, int32_t max_seq_len, int RB, int NRB) {
+// `most_chunks`: what the workspace has room for.
+int plan_chunk(const calidrop_params* p, int64_t total_tokens, int32_t max_seq_len, int RB, int NRB, int64_t most_chunks) {
   const bool even = total_tokens == static_cast<int64_t>(p->batch) * max_seq_len;
   const bool narrow = RB == cd::kRowBlock;
   const int64_t rows = static_cast<int64_t>(p->n_kv_heads) * NRB;          // grid rows of one prompt
   const int64_t least = narrow ? 2 : 1;
-  int best = cd::kChunkUnit;
+  int best = 0;
   int64_t best_cost = std::numeric_limits<int64_t>::max();
   for (int most = narrow ? (even ? 12 : 8) : 32; most >= 1; --most) {
     const int nch = ceil_div(max_seq_len, most * cd::kChunkUnit);
+    if (best && nch > most_chunks) break;
     const int units = ceil_div(ceil_div(max_seq_len, nch), cd::kChunkUnit);      // the chunks of the longest prompt alike
     const int64_t keys = static_cast<int64_t>(units) * cd::kChunkUnit;
     const bool last = narrow || (p->dtype == CALIDROP_FP32 && total_tokens < 4 * keys * p->batch);
@@ -190,29 +200,35 @@ CompressLayout compress_layout(const calidrop_params* p, int64_t total_tokens, i
   const int G = p->n_q_heads / p->n_kv_heads;
   L.RB = G * p->window > cd::kRowBlock ? 2 * cd::kRowBlock : cd::kRowBlock;     // 256-row blocks: such heads stream K once
   L.NRB = ceil_div(G * p->window, L.RB);
-  L.chunk_keys = plan_chunk(p, total_tokens, max_seq_len, L.RB, L.NRB);
-  L.NCH = ceil_div(max_seq_len, L.chunk_keys);
   L.W32 = ceil_div(max_seq_len, 64) * 2;
-  L.sp = plan_splits(p->batch * p->n_kv_heads, max_seq_len, kFewV);
-  const size_t rows = static_cast<size_t>(p->batch) * p->n_kv_heads * L.NRB * L.RB;
+  L.zstride = ceil_div(max_seq_len, 32) * 32;
+  L.NSEG = ceil_div(std::max(max_seq_len - p->window, 1), cd::kWideSeg);
+  const int heads = p->batch * p->n_kv_heads;
+  L.sp = plan_splits(heads, max_seq_len, kFewV);
+  const size_t rows = static_cast<size_t>(heads) * L.NRB * L.RB;
   const size_t toks = static_cast<size_t>(total_tokens) * p->n_kv_heads;
   size_t off = 0;
-  L.rowpart = off; off += round256(rows * L.NCH * sizeof(float2));
   L.row_lse = off; off += round256(rows * sizeof(float));
-  L.vote = off;    off += round256(static_cast<size_t>(vote_plane(total_tokens, p->n_kv_heads)) * L.NRB * sizeof(float));
-  L.score = off;   off += round256(toks * sizeof(float));
-  L.bitmap = off;  off += round256(static_cast<size_t>(p->batch) * p->n_kv_heads * L.W32 * sizeof(uint32_t));
-  L.zstride = ceil_div(max_seq_len, 32) * 32;
-  L.cal_logit = off; off += round256(static_cast<size_t>(p->batch) * p->n_q_heads * L.zstride * sizeof(float));
-  const size_t slots = static_cast<size_t>(p->batch) * p->n_q_heads * L.sp.NS;
-  L.part_o = off;  off += round256(slots * p->head_dim * sizeof(float));
-  L.part_ml = off; off += round256(slots * sizeof(float2));
   // multi-workgroup selection (prefixes beyond the single-workgroup variant): histograms and counts
-  L.NSEG = ceil_div(std::max(max_seq_len - p->window, 1), cd::kWideSeg);
   const WideRegions wide = wide_regions(p, p->window, p->pool_kernel, max_seq_len, L.NSEG);
   L.sel_hist = off; off += wide.hist;
   L.sel_cnt = off;  off += wide.seg;
-  L.total = off;
+  // The partials of pass 1 are merged into row_lse before anything is written to the regions from the votes on: they lie
+  // under them.  No plan takes more room than those regions, or than chunks of 8 units need where that is more, so that the
+  // size of the workspace does not fall as prompts grow.
+  L.rowpart = off;
+  L.vote = off;    off += round256(static_cast<size_t>(vote_plane(total_tokens, p->n_kv_heads)) * L.NRB * sizeof(float));
+  L.score = off;   off += round256(toks * sizeof(float));
+  L.bitmap = off;  off += round256(static_cast<size_t>(heads) * L.W32 * sizeof(uint32_t));
+  L.cal_logit = off; off += round256(static_cast<size_t>(p->batch) * p->n_q_heads * L.zstride * sizeof(float));
+  const size_t slots = static_cast<size_t>(p->batch) * p->n_q_heads * most_splits(heads, max_seq_len, kFewV);
+  L.part_o = off;  off += round256(slots * p->head_dim * sizeof(float));
+  L.part_ml = off; off += round256(slots * sizeof(float2));
+  const size_t chunk_bytes = rows * sizeof(float2);
+  const size_t room = std::max(off - L.rowpart, round256(chunk_bytes * ceil_div(max_seq_len, 8 * cd::kChunkUnit)));
+  L.chunk_keys = plan_chunk(p, total_tokens, max_seq_len, L.RB, L.NRB, static_cast<int64_t>(room / chunk_bytes));
+  L.NCH = ceil_div(max_seq_len, L.chunk_keys);
+  L.total = L.rowpart + room;
   return L;
 }
 
@@ -536,7 +552,7 @@ RecalLayout recal_layout(const calidrop_params* p, int32_t max_seq_len) {
   RecalLayout L{};
   L.W32 = ceil_div(max_seq_len, 64) * 2;
   L.sp = plan_splits(p->batch * p->n_kv_heads, max_seq_len, few_kv(p));
-  const size_t slots = static_cast<size_t>(p->batch) * p->n_q_heads * L.sp.NS;
+  const size_t slots = static_cast<size_t>(p->batch) * p->n_q_heads * most_splits(p->batch * p->n_kv_heads, max_seq_len, few_kv(p));
   size_t off = 0;
   L.bitmap = off;  off += round256(static_cast<size_t>(p->batch) * p->n_kv_heads * L.W32 * sizeof(uint32_t));
   L.part_o = off;  off += round256(slots * p->head_dim * sizeof(float));
@@ -737,7 +753,7 @@ H2oLayout h2o_layout(const calidrop_params* p, int64_t total_tokens, int32_t max
   L.sp = plan_splits(p->batch * p->n_kv_heads, max_seq_len, few_kv(p));
   L.NSEG = ceil_div(std::max(max_seq_len - n_local, 1), cd::kWideSeg);
   const size_t toks = static_cast<size_t>(total_tokens) * p->n_kv_heads;
-  const size_t slots = static_cast<size_t>(p->batch) * p->n_q_heads * L.sp.NS;
+  const size_t slots = static_cast<size_t>(p->batch) * p->n_q_heads * most_splits(p->batch * p->n_kv_heads, max_seq_len, few_kv(p));
   size_t off = 0;
   L.row_lse = off; off += round256(static_cast<size_t>(p->batch) * p->n_q_heads * L.lse_stride * sizeof(float));
   L.vote = off;    // one plane per head of a group

@@ -2,6 +2,7 @@
 header declares, and rejects bad arguments before touching HIP."""
 import ctypes
 import os
+import random
 import re
 import subprocess
 
@@ -44,6 +45,33 @@ def test_workspace_sizes():
     assert nbytes == 2 * 8192 * 8 * 4 and off % 256 == 0 and off + nbytes <= n1
     off, nbytes = cd.calidrop_compress_workspace_region(p, 2 * 8192, 8192, cd.REGION_ROW_LSE)
     assert nbytes == 2 * 8 * 128 * 4
+
+
+@pytest.mark.parametrize("kw", [
+    dict(batch=1), dict(batch=1, dtype=cd.FP32), dict(batch=1, n_q_heads=8, n_kv_heads=8, window=16), dict(batch=2, head_dim=64),
+    dict(batch=1, n_q_heads=2, n_kv_heads=1), dict(batch=3, n_q_heads=40), dict(batch=7, window=64, dtype=cd.FP32), dict(batch=64),
+    dict(batch=1, n_q_heads=16, n_kv_heads=1, window=100), dict(batch=1, n_q_heads=3, n_kv_heads=3, window=300),
+    dict(batch=1, flags=cd.OPT_WIDE_SELECTION), dict(batch=20, pool_kernel=17, n_kv_heads=32)])
+def test_a_workspace_for_long_prompts_serves_shorter_ones(kw):
+    p = good(**kw)
+    nb = p.batch
+    recal = [cd.calidrop_recalibrate_workspace_bytes(p, n) for n in range(1, 42000, 37)]
+    assert recal == sorted(recal) and min(recal) > 0
+    given = [cd.calidrop_compress_given_workspace_bytes(p, n) for n in range(16300, 16500)]
+    assert given == sorted(given)
+    # every prompt the longest; one long and the others short; lengths in between
+    for total in (lambda n: nb * n, lambda n: n + nb - 1, lambda n: n + (nb - 1) * n // 2):
+        for lens in (range(1, 42000, 41), range(16200, 16700, 3), range(130900, 131400, 7)):
+            for size in ([cd.calidrop_compress_workspace_bytes(p, total(n), n) for n in lens],
+                         [cd.calidrop_compress_h2o_workspace_bytes(p, 0, total(n), n) for n in lens]):
+                assert size == sorted(size) and size[0] > 0
+    rng = random.Random(3)
+    for _ in range(3000):
+        big = rng.randint(2, 200000)
+        small = rng.randint(1, big)
+        tot_big = rng.randint(big, nb * big)
+        tot_small = rng.randint(small, min(nb * small, tot_big))
+        assert cd.calidrop_compress_workspace_bytes(p, tot_small, small) <= cd.calidrop_compress_workspace_bytes(p, tot_big, big)
 
 
 @pytest.mark.parametrize("lens,budget", [([1024] * 512, 512), ([600] * 4096, 512), ([8192], 512), ([32768 + 32], 2000)])
