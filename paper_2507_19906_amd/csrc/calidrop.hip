@@ -310,17 +310,20 @@ int static_scratch_ptr(char** out) {
   return CALIDROP_OK;
 }
 
-// Where the gather of the retained rows runs.  In a small call it shares the launch of the streaming pass (a launch
-// less, and the selection kernel's few workgroups no longer copy: 8192 tokens, 8 heads, selection 15 -> 10.5 us), but
-// its workgroups there take the places of streaming ones (LDS and registers are the pass's): with 512 heads of
-// 1024 rows that pass took 392 us instead of 230.  With many heads the selection kernel does it: while one
-// workgroup selects, others copy (140 us for both, against 36 + 100 in two launches).  Otherwise - few heads with large
-// budgets, lists from elsewhere - it has its own launch, or shares that of the given-set preparation.
+// Where the gather of the retained rows runs.  As further workgroups of the streaming pass it costs no launch and the
+// selection kernel's few workgroups do not copy, but there its workgroups take the places of streaming ones (LDS and
+// registers are the pass's).  In 228 calls (2 to 96 (sequence, KV head) pairs, budgets 64 to 2048, 2100 to 100000 rows)
+// that was 2-3 us faster than a launch of its own while the splits of the pass are short, whatever the budget (8 heads of
+// 8192 rows, budget 500 / 1024 / 2048: 40.1 -> 37.9, 41.3 -> 38.9, 43.1 -> 40.7 us a call), the same at splits of 1024 rows
+// and 1-5 % slower with longer ones (100000 rows, budget 512: 170 -> 173 us, 2048: 170 -> 179 us).  Measured up to some
+// 8000 gathering workgroups; 512 heads of 1024 rows, 32768 of them, held the pass up for 160 us.
+// With many heads the selection kernel does it: while one workgroup selects, others copy (140 us for both, against
+// 36 + 100 in two launches).
 enum class GatherIn { kPass, kDone, kOwnLaunch };
-GatherIn gather_place(const calidrop_params* p, const cd::GatherArgs& ga, bool lds_selection) {
+GatherIn gather_place(const calidrop_params* p, const cd::GatherArgs& ga, int rows_per_split, bool lds_selection) {
   const int64_t pairs = static_cast<int64_t>(p->batch) * p->n_kv_heads;
-  if (pairs * ga.blocks <= 256) return GatherIn::kPass;
-  return lds_selection && pairs >= 128 ? GatherIn::kDone : GatherIn::kOwnLaunch;
+  if (lds_selection && pairs >= 128 && pairs * ga.blocks > 256) return GatherIn::kDone;
+  return rows_per_split < 1024 && pairs * ga.blocks <= 4096 ? GatherIn::kPass : GatherIn::kOwnLaunch;
 }
 
 cd::GatherArgs gather_args(const calidrop_params* p, const int32_t* indices, const int32_t* cache_offsets, const void* k, const void* v,
@@ -332,13 +335,13 @@ cd::GatherArgs gather_args(const calidrop_params* p, const int32_t* indices, con
 
 // Pooling + selection of the votes in se.vote.  For the multi-workgroup chain `sel_hist` has been cleared.
 int run_selection(const calidrop_params* p, int max_seq_len, cd::SelectArgs& se, uint32_t* sel_hist, uint32_t* sel_seg, int NSEG,
-                  GatherIn& place, hipStream_t st) {
+                  int rows_per_split, GatherIn& place, hipStream_t st) {
   int rc;
   const int bg = p->batch * p->n_kv_heads;
   const int max_prefix = max_seq_len - se.w;
   se.write_scores = (p->flags & CALIDROP_OPT_WRITE_SCORES) ? 1 : 0;
   const bool lds_selection = uses_lds_selection(p, se.w, se.pool_k, max_seq_len);
-  place = gather_place(p, se.gather, lds_selection);
+  place = gather_place(p, se.gather, rows_per_split, lds_selection);
   se.gather_here = place == GatherIn::kDone;
   if (lds_selection) {
     // dynamic LDS: staged votes (padded), later reused for the retained indices
@@ -473,7 +476,7 @@ int compress_impl(const calidrop_params* p, const void* q_win, const void* k, co
   se.calib = p->calib_size; se.cal_indices = cal_indices;
   se.bitmap = reinterpret_cast<uint32_t*>(ws + L.bitmap);
   if ((rc = run_selection(p, max_seq_len, se, reinterpret_cast<uint32_t*>(ws + L.sel_hist),
-                          reinterpret_cast<uint32_t*>(ws + L.sel_cnt), L.NSEG, place, st)))
+                          reinterpret_cast<uint32_t*>(ws + L.sel_cnt), L.NSEG, L.sp.rows_per_split, place, st)))
     return rc;
 
   cd::AttendArgs aa{};
@@ -824,7 +827,7 @@ int h2o_impl(const calidrop_params* p, int n_local, const void* q_full, const vo
   se.calib = p->calib_size; se.cal_indices = cal_indices;
   se.bitmap = reinterpret_cast<uint32_t*>(ws + L.bitmap);
   if ((rc = run_selection(p, max_seq_len, se, reinterpret_cast<uint32_t*>(ws + L.sel_hist),
-                          reinterpret_cast<uint32_t*>(ws + L.sel_cnt), L.NSEG, place, st)))
+                          reinterpret_cast<uint32_t*>(ws + L.sel_cnt), L.NSEG, L.sp.rows_per_split, place, st)))
     return rc;
 
   cd::AttendArgs aa{};

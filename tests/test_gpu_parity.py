@@ -527,11 +527,21 @@ def test_exact_ties_with_multi_workgroup_selection(wide_selection):
     test_exact_ties_lower_index_wins(20016, 1, 3000, 2500)
 
 
-@pytest.mark.parametrize("dtype,budget", [("fp32", 64), ("fp32", 700), ("fp32", 2688), ("fp32", 2690), ("bf16", 1500)])
+@pytest.mark.parametrize("dtype,budget", [("fp32", 64), ("fp32", 700), ("fp32", 2688), ("fp32", 2690), ("bf16", 1500),
+                                          ("fp32", 10912), ("fp32", 10913)])
 def test_gather_workgroups_behind_the_streaming_ones(dtype, budget):
-    # 1024 pieces of 16 bytes per gathering workgroup: less than one plane of the streaming pass's grid, several planes
-    # with a partial last one, 252 workgroups (the pass still carries them) and 258 (a launch of their own)
-    run_case(small(dtype, 4, 2, 64, [2900, budget - 1, 2850], 16, budget, 5, T=1, name=f"gather_{budget}"))
+    # 256 pieces of 16 bytes per gathering workgroup, 16 rows in fp32 and 32 in bf16 here.  Budget 64: 12 of them per KV head,
+    # less than one plane of the streaming pass's 23 splits; 700, 2688, 2690 and 1500: 132, 504, 507 and 141, several planes
+    # with a partial last one; 10912: 4092 for the six (sequence, KV head) pairs, the pass still carries them; 10913: 4098,
+    # a launch of their own
+    lens = [2900, budget - 1, 2850] if budget < 2800 else [11500, budget - 1, 10990]
+    run_case(small(dtype, 4, 2, 64, lens, 16, budget, 5, T=1, name=f"gather_{budget}"))
+
+
+@pytest.mark.parametrize("n", [28672, 28673])
+def test_gather_beside_short_and_long_splits(n):
+    # splits of 896 rows: the streaming pass carries the gather; of 1024: it has a launch of its own
+    run_case(small("bf16", 8, 2, 128, [n], 16, 200, 5, T=1, name=f"gather_n{n}"))
 
 
 @pytest.mark.parametrize("batch", [96, 97])
