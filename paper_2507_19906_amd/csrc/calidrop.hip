@@ -140,33 +140,39 @@ int few_kv(const calidrop_params* p) { return p->dtype == CALIDROP_FP32 ? 256 : 
 
 // Keys per scoring workgroup, in units of 64.  The 256 compute units share the workgroups of a launch, so a plan costs the
 // workgroups of the fullest unit times the key units of one, plus half a unit for its start (query fragments, first
-// stage); with fewer than `least` workgroups its waves leave the matrix pipe or the memory waiting, so fewer save nothing.
-// The chunk of least cost is taken, all chunks of the longest prompt alike, at most 12 units (256-row blocks start
+// stage).  A unit holds `fit` 128-row workgroups at a time; fewer than three of them (bf16, D = 128: two) save nothing, the
+// matrix pipe or the memory waits, and one left over when the others are through takes the time of two (fp32, 4
+// prompts of 20000 tokens, 8 KV heads, 64 window rows: four of 640 keys 455 us a call, five of 512 keys 406).
+// The chunk of least cost is taken, all chunks of the longest prompt alike, at most 16 units (256-row blocks start
 // slower: 32).  Prompts of different lengths: the host knows their sum and the longest only.  What the short last
 // chunks take is estimated (half a workgroup per prompt at 128 rows and, in fp32, while a prompt has fewer than four chunks;
 // else nothing: with 256 rows they mostly fill gaps), and since the last round is not full everywhere, the rounded count
 // weighs one part and the plain one, half a round later, three; at 128 rows chunks stay at 8 units.
 // Measured over 635 calls (350 to 131072 tokens, 1 to 64 prompts, both types, D 64 and 128, 16 to 256 window rows per KV
 // head), each at 21 chunk lengths: the chunk taken is on average 1 % (prompts of one length) to 3.5 % (256 rows, several
-// lengths) slower than the best of them.  Examples, us a call at 256-512 keys and many rounds / at one workgroup for each of 512 places / now: fp32, 256 rows, 6 prompts of
-// 9000-17000 tokens 798 / 958 / 730; one of 16384 230 / 209 / 192; bf16, 131072 tokens, 256 rows 281 / 239 / 239.
+// lengths) slower than the best of them.  Examples, us a call at 256-512 keys and many rounds / at one workgroup for each
+// of 512 places / now: fp32, 256 rows, 6 prompts of 9000-17000 tokens 798 / 958 / 730; one of 16384 230 / 209 / 192; bf16,
+// 131072 tokens, 256 rows 281 / 239 / 239.
 // `most_chunks`: what the workspace has room for.
 int plan_chunk(const calidrop_params* p, int64_t total_tokens, int32_t max_seq_len, int RB, int NRB, int64_t most_chunks) {
   const bool even = total_tokens == static_cast<int64_t>(p->batch) * max_seq_len;
   const bool narrow = RB == cd::kRowBlock;
   const int64_t rows = static_cast<int64_t>(p->n_kv_heads) * NRB;          // grid rows of one prompt
-  const int64_t least = narrow ? 2 : 1;
+  const bool bf16 = p->dtype == CALIDROP_BF16;
+  const int fit = bf16 ? 4 : p->head_dim == 128 ? 3 : 5, least = !narrow ? 1 : even && !(bf16 && p->head_dim == 128) ? 3 : 2;
   int best = 0;
   int64_t best_cost = std::numeric_limits<int64_t>::max();
-  for (int most = narrow ? (even ? 12 : 8) : 32; most >= 1; --most) {
+  for (int most = narrow ? (even ? 16 : 8) : 32; most >= 1; --most) {
     const int nch = ceil_div(max_seq_len, most * cd::kChunkUnit);
     if (best && nch > most_chunks) break;
     const int units = ceil_div(ceil_div(max_seq_len, nch), cd::kChunkUnit);      // the chunks of the longest prompt alike
     const int64_t keys = static_cast<int64_t>(units) * cd::kChunkUnit;
-    const bool last = narrow || (p->dtype == CALIDROP_FP32 && total_tokens < 4 * keys * p->batch);
+    const bool last = narrow || (!bf16 && total_tokens < 4 * keys * p->batch);
     const int64_t groups = even ? rows * p->batch * ((max_seq_len + keys - 1) / keys) : total_tokens * rows / keys + (last ? rows * p->batch / 2 : 0);
     const int64_t full = (groups + 255) / 256;
-    const int64_t load = std::max(even ? 1024 * full : 256 * full + 3 * (groups + 128), 1024 * least);
+    int64_t load = even ? 1024 * full : 256 * full + 3 * (groups + 128);         // 1024 = one workgroup on every unit
+    if (narrow && even && full % fit == 1) load += 1024;
+    load = std::max<int64_t>(load, 1024 * least);
     const int64_t cost = load * (2 * units + 1);
     if (cost < best_cost) { best_cost = cost; best = static_cast<int>(keys); }
   }

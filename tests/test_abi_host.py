@@ -144,7 +144,7 @@ def test_streamed_rows_bypass_the_caches(tmp_path):
 
 @pytest.mark.parametrize("lens,heads,w,dtype", [
     ([131072], 8, 64, "bf16"), ([131200], 8, 64, "bf16"), ([140000], 8, 64, "bf16"), ([8192], 8, 32, "bf16"), ([500], 2, 16, "fp32"),
-    ([32768] * 32, 8, 32, "bf16"), ([13804] * 13, 2, 32, "fp32"), ([3000] * 20, 8, 64, "fp32"), ([2816, 2816, 2816], 1, 8, "fp32"),
+    ([32768] * 32, 8, 32, "bf16"), ([13804] * 13, 2, 32, "fp32"), ([3000] * 20, 8, 64, "fp32"), ([2816, 2816, 2816], 1, 8, "fp32"), ([20000] * 4, 8, 32, "fp32"),
     ([16384, 9000, 13300, 12100, 9900, 16000], 8, 64, "fp32"), ([1200 - 10 * b for b in range(60)], 8, 64, "fp32"),
     ([16384 - 190 * b for b in range(64)], 8, 32, "bf16"), ([4194, 2641, 3000, 3300, 3600, 4000], 8, 64, "fp32")])
 def test_scoring_chunks_fill_the_compute_units_with_what_is_launched(lens, heads, w, dtype):
@@ -162,10 +162,14 @@ def test_scoring_chunks_fill_the_compute_units_with_what_is_launched(lens, heads
 
     def cost(units):
         groups = sum(ceil(n, 64 * units) for n in lens) * heads
-        load = ceil(groups, 256) if even else 0.25 * ceil(groups, 256) + 0.75 * (groups / 256 + 0.5)
-        return max(load, 1 if block == 256 else 2) * (units + 0.5)
+        full = ceil(groups, 256)
+        if not even:
+            load = max(0.25 * full + 0.75 * (groups / 256 + 0.5), 1 if block == 256 else 2)
+        else:                                        # 128 rows: a unit holds 4 (fp32: 3), one left over takes the time of two
+            load = full if block == 256 else max(full + (full % (4 if dtype == "bf16" else 3) == 1), 2 if dtype == "bf16" else 3)
+        return load * (units + 0.5)
 
-    most = 32 if block == 256 else 12 if even else 8
+    most = 32 if block == 256 else 16 if even else 8
     taken = ceil(ceil(max(lens), nch), 64)
     assert taken <= most
     assert cost(taken) <= (1.0 if even else 1.15) * min(cost(u) for u in range(1, min(most, ceil(max(lens), 64)) + 1))
