@@ -24,7 +24,7 @@ struct AttendArgs {
   const int32_t* row_off;     // [batch+1] token offsets of the K/V buffers
   const int32_t* row_len;     // decode: live rows per sequence; NULL in calibration mode
   const uint32_t* bitmap;     // calibration mode: [batch*Hkv][W32] not-evicted bits; else NULL
-  const int32_t* list;        // kList: [batch*Hkv][list_len] positions the bits are made from (see skip_bits)
+  const int32_t* list;        // kList: [batch*Hkv][list_len] positions a workgroup makes the bits of its own rows from
   int list_len, list_is_calib;
   int64_t total_tokens;       // calibration mode: contract check of row_off
   int batch, Hq, Hkv, G, w, B, max_len, W32, rows_per_split, NS;
@@ -35,7 +35,7 @@ struct AttendArgs {
   const uint8_t* only_flagged; // optional [batch][Hq]: skip KV groups in which no head carries flag 2
   float* part_o;              // [batch][Hq][NS][D]
   float2* part_ml;            // [batch][Hq][NS]  (max in log2 units, sum)
-  GatherArgs gather;          // compress: workgroups NS .. NS + gather.blocks - 1 of the launch gather KV_compress
+  GatherArgs gather;          // kGather: what the workgroups of the planes z >= batch gather (KV_compress)
 };
 
 // Number of rows the streaming pass covers for sequence b, the stride between heads and the

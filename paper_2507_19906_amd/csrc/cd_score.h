@@ -6,7 +6,7 @@
 //           rows of the KV head -> vote[j] for prefix columns j < P.
 // A workgroup owns a block of query rows (128, or 256 when the KV head has more than 128 - so that
 // such heads stream their keys once per pass, not once per 128 rows) and a chunk of keys; its waves
-// own 32 or 64 rows each and share the key tiles through LDS.  Pass 1 forms S^T = K Q^T (a lane owns
+// own 32 rows each and share the key tiles through LDS.  Pass 1 forms S^T = K Q^T (a lane owns
 // one query row per tile: running row statistics stay in registers); pass 2 forms S = Q K^T (a
 // lane owns one key: the column sum over rows is an in-lane sum plus a 4-lane tree).
 #pragma once
