@@ -457,15 +457,15 @@ int compress_impl(const calidrop_params* p, const void* q_win, const void* k, co
                          win_lse);
       if ((rc = launch_status("rowlse_import"))) return rc;
     } else {
-      if (L.RB == 256) hipLaunchKernelGGL((cd::score_rowstats_kernel<T, D, 2, 8>), grid_s, dim3(512), 0, st, sa);
-      else hipLaunchKernelGGL((cd::score_rowstats_kernel<T, D, 2, 4>), grid_s, dim3(256), 0, st, sa);
+      if (L.RB == 256) hipLaunchKernelGGL((cd::score_rowstats_kernel<T, D, 8>), grid_s, dim3(512), 0, st, sa);
+      else hipLaunchKernelGGL((cd::score_rowstats_kernel<T, D, 4>), grid_s, dim3(256), 0, st, sa);
       if ((rc = launch_status("score_rowstats"))) return rc;
       if (L.NCH > 64) hipLaunchKernelGGL(cd::rowstats_merge_kernel<64>, dim3(static_cast<unsigned>((rows + 3) / 4)), dim3(256), 0, st, sa);
       else hipLaunchKernelGGL(cd::rowstats_merge_kernel<16>, dim3(static_cast<unsigned>((rows + 15) / 16)), dim3(256), 0, st, sa);
       if ((rc = launch_status("rowstats_merge"))) return rc;
     }
-    if (L.RB == 256) hipLaunchKernelGGL((cd::score_votes_kernel<T, D, 2, 8>), grid_s, dim3(512), 0, st, sa);
-    else hipLaunchKernelGGL((cd::score_votes_kernel<T, D, 2, 4>), grid_s, dim3(256), 0, st, sa);
+    if (L.RB == 256) hipLaunchKernelGGL((cd::score_votes_kernel<T, D, 8>), grid_s, dim3(512), 0, st, sa);
+    else hipLaunchKernelGGL((cd::score_votes_kernel<T, D, 4>), grid_s, dim3(256), 0, st, sa);
     if ((rc = launch_status("score_votes"))) return rc;
   }
 

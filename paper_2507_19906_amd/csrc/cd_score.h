@@ -17,6 +17,7 @@
 namespace cd {
 
 constexpr int kRowBlock = 128;     // query rows per workgroup, doubled for KV heads with more than 128 window rows
+constexpr int kRowTiles = 2;       // 16-row tiles of query rows per wave
 constexpr int kMaxCalHeads = 8;    // largest GQA group whose calibration logits the vote pass exports
 constexpr int kChunkUnit = 64;      // keys per workgroup in the scoring passes: a multiple of this
 
@@ -155,14 +156,14 @@ __device__ __forceinline__ void operands_ready() { __builtin_amdgcn_s_waitcnt(0x
 // Bound by HBM at 128 rows (32 layers x 32768 keys: 340 us = 6.3 TB/s, what a plain read of the same size
 // reaches), by the chip's power at 256 (131072 keys: 86 -> 75 us with the stage loads overlapped, 8 waves of
 // 32 rows and 2048 keys per workgroup; 4 waves of 64 rows: 82 us).
-// A workgroup of NR waves keeps 16 RT NR window-query rows stationary, 16 RT per wave (128 rows, or 256 so
+// A workgroup of NR waves keeps 32 NR window-query rows stationary, 32 per wave (128 rows, or 256 so
 // that a KV head with up to 256 window rows - G*w - streams its keys once).
-template <typename T, int D, int RT, int NR>
+template <typename T, int D, int NR>
 __global__ __launch_bounds__(NR * 64, sizeof(T) == 2 ? 4 : 2) void score_rowstats_kernel(ScoreArgs a) {
   constexpr int NT = NR * 64;
   using KS = KeyStream<T, D, NT>;
   constexpr int KT = KS::KT, NK = KS::NK, SK = KS::kStageKeys, EPL = KS::EPL, KD = KS::KD;
-  constexpr int WR = 16 * RT, RB = NR * WR;
+  constexpr int RT = kRowTiles, WR = 16 * RT, RB = NR * WR;
   // every chunk of a (sequence, KV head, row block) behind the same L2, so that its query rows are fetched
   // from memory once and not once per XCD; when the rows do not divide over the XCDs, the chunk index is
   // rotated instead so that the chunks every sequence has do not all land on the same XCDs
@@ -362,15 +363,15 @@ __global__ __launch_bounds__(256) void rowlse_import_kernel(ScoreArgs a, const f
   a.row_lse[gr] = val;
 }
 
-// NR waves of 16 RT rows each (RT = 2: 4 waves for a block of 128 rows, 8 for 256).  With the stage loads
+// NR waves of 32 rows each (4 waves for a block of 128 rows, 8 for 256).  With the stage loads
 // overlapped and the stage free of branches: 448 -> 426 us for 32 layers x 32768 keys (HBM, 160 MiB of votes
 // and logits written into the read stream), 105 -> 80 us for 131072 keys at 256 rows.  64 rows per wave
-// (RT = 4, half the LDS reads) leaves too few waves: 440 us and 90 us or more.
-template <typename T, int D, int RT, int NR>
+// (half the LDS reads) leaves too few waves: 440 us and 90 us or more.
+template <typename T, int D, int NR>
 __global__ __launch_bounds__(NR * 64, sizeof(T) == 2 ? 4 : 2) void score_votes_kernel(ScoreArgs a) {
   constexpr int NT = NR * 64;
   using KS = KeyStream<T, D, NT>;
-  constexpr int KT = KS::KT, NK = KS::NK, SK = KS::kStageKeys, RB = 16 * RT * NR, EPL = KS::EPL, KD = KS::KD;
+  constexpr int KT = KS::KT, NK = KS::NK, SK = KS::kStageKeys, RT = kRowTiles, RB = 16 * RT * NR, EPL = KS::EPL, KD = KS::KD;
   // grid: x = key chunk, y = (sequence, KV head, row block).  Workgroups are dealt to the 8 XCDs
   // round-robin in launch order: the launch index is re-read so that every chunk of a y sits behind the
   // same L2 (the stationary query rows are then fetched from memory once, not once per XCD); when y
