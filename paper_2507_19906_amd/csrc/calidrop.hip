@@ -397,6 +397,18 @@ int launch_finalize(const calidrop_params* p, const cd::FinalArgs& fa, hipStream
   return launch_status(what);
 }
 
+// A pass over K and V of `rows` cached or prompt rows.  The first tile of a wave - all of K while a split is one tile per wave -
+// goes through the caches while the K and V of the call are at most three times the last-level cache, and around it beyond:
+// decode calls and given sets that are repeated find it there (120 calls, us with / without: 44 caches of 3026 rows, 68 MB,
+// 16.4 / 18.2; one cache of 4100 rows 9.7 / 9.9; 216 prompts of 462, 51 MB, 20.1 / 21.1; 104 prompts of 3660, 195 MB,
+// 36.2 / 39.7); from 0.6 to 1.2 GB both are alike, above that it is up to 12 % slower (1.5 GB: 303 / 269).
+template <typename T, int D, bool kGather = false>
+void launch_kv_pass(const cd::AttendArgs& aa, dim3 grid, int64_t rows, hipStream_t st) {
+  const bool keep = 2 * rows * aa.Hkv * D * static_cast<int64_t>(sizeof(T)) <= (768ll << 20);
+  if (keep) hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, false, false, kGather, false, true>), grid, dim3(256), 0, st, aa);
+  else hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, false, false, kGather>), grid, dim3(256), 0, st, aa);
+}
+
 // The streaming pass over KV_evict, and the gather unless the selection has done it.
 template <typename T, int D>
 int launch_calibration(const calidrop_params* p, cd::AttendArgs& aa, const cd::GatherArgs& ga, GatherIn place, hipStream_t st) {
@@ -413,8 +425,8 @@ int launch_calibration(const calidrop_params* p, cd::AttendArgs& aa, const cd::G
   const dim3 grid(aa.NS, p->n_kv_heads, p->batch + (carry ? ceil_div(p->batch * ga.blocks, aa.NS) : 0));
   if (aa.cal_logit && carry) hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, true, false, true>), grid, dim3(256), 0, st, aa);
   else if (aa.cal_logit) hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, true>), grid, dim3(256), 0, st, aa);
-  else if (carry) hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, false, false, true>), grid, dim3(256), 0, st, aa);
-  else hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, false>), grid, dim3(256), 0, st, aa);
+  else if (carry) launch_kv_pass<T, D, true>(aa, grid, aa.total_tokens, st);
+  else launch_kv_pass<T, D>(aa, grid, aa.total_tokens, st);
   return launch_status("attend_partial(calibration)");
 }
 
@@ -542,8 +554,7 @@ int decode_impl(const calidrop_params* p, const void* q_t, const void* k_c, cons
   aa.cal_logit = nullptr; aa.zstride = 0;
   aa.part_o = reinterpret_cast<float*>(ws + L.part_o);
   aa.part_ml = reinterpret_cast<float2*>(ws + L.part_ml);
-  hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, false>), dim3(L.sp.NS, p->n_kv_heads, p->batch), dim3(256), 0,
-                     st, aa);
+  launch_kv_pass<T, D>(aa, dim3(L.sp.NS, p->n_kv_heads, p->batch), static_cast<int64_t>(p->batch) * max_cache_len, st);
   if ((rc = launch_status("attend_partial(decode)"))) return rc;
   cd::FinalArgs fa{};
   fa.part_o = aa.part_o; fa.part_ml = aa.part_ml; fa.row_off = cache_offsets; fa.row_len = cache_lens;
@@ -605,7 +616,7 @@ int recal_impl(const calidrop_params* p, const void* q_t, const void* k, const v
   aa.list = from_cal ? cal_indices : indices; aa.list_len = list_len; aa.list_is_calib = from_cal;
   const dim3 grid(L.sp.NS, p->n_kv_heads, p->batch);
   if (in_pass) hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, false, false, false, true>), grid, dim3(256), 0, st, aa);
-  else hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, false>), grid, dim3(256), 0, st, aa);
+  else launch_kv_pass<T, D>(aa, grid, total_tokens, st);
   if ((rc = launch_status("attend_partial(recalibrate)"))) return rc;
 
   cd::FinalArgs fa{};
@@ -738,7 +749,7 @@ int recal_packed_impl(const calidrop_params* p, const void* q_t, const void* k_e
   // 64-byte pieces of the operand layout a quarter slower
   const dim3 grid(L.sp.NS, p->n_kv_heads, p->batch);
   if (is_host_memory(k_e)) hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, false, true>), grid, dim3(256), 0, st, aa);
-  else hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, false>), grid, dim3(256), 0, st, aa);
+  else launch_kv_pass<T, D>(aa, grid, static_cast<int64_t>(p->batch) * max_evict_len, st);
   if ((rc = launch_status("attend_partial(recalibrate, packed)"))) return rc;
   cd::FinalArgs fa{};
   fa.part_o = aa.part_o; fa.part_ml = aa.part_ml; fa.row_off = evict_offsets; fa.row_len = evict_lens;

@@ -78,17 +78,20 @@ struct AttendWave {
   // The K rows of the wave's first tile, requested before the number of live rows is known (it may
   // still be on its way from memory): `clamp` is a row count that is certainly addressable.
   u32x4 kpre[2][NK];
+  // kKeep: through the caches, so that the next call over the same rows finds them.
+  template <bool kKeep = false>
   __device__ __forceinline__ void request_first_k(const T* kbase, int row0, int clamp, int i, int c) {
-    load_k(kbase, row0, clamp, i, c, kpre);
+    load_k<kKeep>(kbase, row0, clamp, i, c, kpre);
   }
 
+  template <bool kKeep = false>
   __device__ __forceinline__ void load_k(const T* kbase, int row0, int rows, int i, int c, u32x4 (&kf)[2][NK]) const {
 #pragma unroll
     for (int g2 = 0; g2 < 2; ++g2) {
       const int krow = min(row0 + 16 * g2 + i, rows - 1);
       const T* kp = kbase + static_cast<int64_t>(krow) * D + c * EPL;
 #pragma unroll
-      for (int kk = 0; kk < NK; ++kk) kf[g2][kk] = ld16_stream(kp + kk * KD);
+      for (int kk = 0; kk < NK; ++kk) kf[g2][kk] = kKeep ? ld16(kp + kk * KD) : ld16_stream(kp + kk * KD);
     }
   }
 
@@ -318,8 +321,9 @@ struct AttendWave {
 // kList: every workgroup makes the skip bits of its own rows from the position list while its first K rows are on their
 // way, instead of a launch ahead that makes the whole bitmap (recomputation of 8 layers of 32768 tokens: that launch
 // took 4.7 us; a call 110.4 -> 108.5 us, the list is 2 KiB beside a workgroup's 512 KiB of rows).
+// kKeep: the first tile of every wave is read through the caches in passes small enough to find it there again.
 constexpr int kListMaxRows = 8192;      // longest split whose bits (one per row) a workgroup keeps
-template <typename T, int D, bool kLogits, bool kRowsK = false, bool kGather = false, bool kList = false>
+template <typename T, int D, bool kLogits, bool kRowsK = false, bool kGather = false, bool kList = false, bool kKeep = false>
 __global__ __launch_bounds__(256) void attend_partial_kernel(AttendArgs a) {
   // grid: x = split of the rows (rotated per head so that the splits every sequence has do not
   // all land on the same XCDs of the round-robin deal), y = KV head, z = sequence.  The planes z >= batch are, in small
@@ -406,8 +410,8 @@ __global__ __launch_bounds__(256) void attend_partial_kernel(AttendArgs a) {
   } else {
     // requested here and not in run(): there the compiler moves the loads ahead of the loop and drops their
     // non-temporal hint, the first tile of every wave (a quarter of K at 512 rows per split) then goes through the
-    // caches and evicts what the gather left there (32 prompts of 7000, fp32: 436 us a call, with the hint 387)
-    w.request_first_k(kbase, min(row_first, rows - 1), rows, i, c);
+    // caches, and large passes evict what they will need (32 prompts of 7000, fp32: 436 us a call, with the hint 387)
+    w.template request_first_k<kKeep>(kbase, min(row_first, rows - 1), rows, i, c);
     w.run(kbase, vbase, bm_first, rows, row_first, row_end, kRowStep, a.sl2, i, c, nullptr, false, true, NoWork(), nullptr, kAttWaves);
   }
 

@@ -129,17 +129,18 @@ def test_kernels_keep_their_registers(tmp_path):
 @needs_object_tools
 def test_streamed_rows_bypass_the_caches(tmp_path):
     # every 16-byte load of K and V in the streaming passes carries the non-temporal hint; without it are the pieces of the
-    # query and, in the launches that carry the gather, one K and one V piece of a retained row
+    # query, in the launches that carry the gather one K and one V piece of a retained row, and in the variant for small
+    # passes the two 16-row halves of a wave's first K tile
     asm = subprocess.run([TOOLS + "llvm-objdump", "-d", "--no-show-raw-insn", code_object(cd.LIB_PATH, tmp_path)], check=True,
                          capture_output=True, text=True).stdout
     seen = 0
     for head, body in re.findall(r"^[0-9a-f]+ <(_ZN2cd21attend_partial_kernelI[^>]*)>:\n(.*?)(?=^\S|\Z)", asm, re.M | re.S):
-        elem, d, logits, gather = re.search(r"kernelI(f|NS_6bf16_tE)Li(\d+)ELb(\d)ELb\dELb(\d)E", head).groups()
+        elem, d, logits, gather, keep = re.search(r"kernelI(f|NS_6bf16_tE)Li(\d+)ELb(\d)ELb\dELb(\d)ELb\dELb(\d)E", head).groups()
         loads = [l for l in body.splitlines() if "global_load_dwordx4" in l]
         pieces = int(d) * (4 if elem == "f" else 2) // 64
-        assert sum(" nt" not in l for l in loads) == (0 if logits == "1" else pieces) + 2 * int(gather), head
+        assert sum(" nt" not in l for l in loads) == (0 if logits == "1" else pieces) + 2 * int(gather) + 2 * pieces * int(keep), head
         seen += 1
-    assert seen == 24
+    assert seen == 32
 
 
 @pytest.mark.parametrize("lens,heads,w,dtype", [

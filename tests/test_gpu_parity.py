@@ -568,6 +568,37 @@ def test_split_partials_merged_by_four_groups_or_one(batch):
             H.check_recalibrate(wl, x, bufs, q_t, b, before, report=rep)
 
 
+@pytest.mark.parametrize("dtype,cap", [("fp32", 196608), ("bf16", 393216)])
+def test_split_decode_of_small_and_large_caches(dtype, cap):
+    # K and V of two such caches are 768 MiB, the most whose first rows are read through the caches; with a third
+    # sequence they are read around them.  The splits are the same, so the first two sequences repeat bit for bit
+    D, Hkv, Hq = 128, 2, 8
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device=DEV).manual_seed(91)
+    lens = [cap, 7001, 33]
+    kv = torch.randn((2, Hkv, cap, D), generator=gen, device=DEV, dtype=dt)
+    q = torch.randn((3, Hq, D), generator=gen, device=DEV, dtype=dt)
+    outs = []
+    for nb in (2, 3):
+        p = cd.make_params(dtype=cd.BF16 if dtype == "bf16" else cd.FP32, batch=nb, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D,
+                           window=16, budget=64, pool_kernel=5)
+        bufs = cd.CompressBuffers(p, [64] * nb, DEV, capacities=[cap] * nb)
+        for cache, x in ((bufs.k_c, kv[0]), (bufs.v_c, kv[1])):
+            cache.view(nb, Hkv, cap, D).copy_(x)
+        bufs.cache_lens.copy_(torch.tensor(lens[:nb], dtype=torch.int32))
+        bufs.decode(q[:nb].contiguous())
+        torch.cuda.synchronize()
+        outs.append((bufs.out.clone(), bufs.a_lse.clone()))
+    assert torch.equal(outs[0][0], outs[1][0][:2]) and torch.equal(outs[0][1], outs[1][1][:2])
+    for b, n in enumerate(lens):
+        for h in range(Hq):
+            k, v = (x[h // (Hq // Hkv), :n].double() for x in kv)
+            z = k @ q[b, h].double() * D ** -0.5
+            o = torch.softmax(z, 0) @ v
+            assert (outs[1][0][b, h].double() - o).abs().max() < (2e-2 if dtype == "bf16" else 1e-4)
+            assert (outs[1][1][b, h].double() - torch.logsumexp(z, 0)).abs() < (2e-3 if dtype == "bf16" else 1e-4)
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 def test_scoring_chunks_of_equal_length(dtype):
     # many short prompts of two query-row blocks: one round of 512 workgroups would be 1408 keys each, which are evened
