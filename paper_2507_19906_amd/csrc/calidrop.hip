@@ -275,15 +275,16 @@ void launch_bitmap(const cd::BitmapArgs& ba, int pairs, hipStream_t st) {
   else hipLaunchKernelGGL(cd::bitmap_from_indices_kernel, dim3(pairs), dim3(256), 0, st, ba);
 }
 
-// The single-workgroup selection kernels stage up to kSelMaxLdsKeys votes (padded) in dynamic LDS, more
+// The single-workgroup selection kernels stage up to kSelMaxLdsKeys votes in dynamic LDS, more
 // than the 48 KiB a kernel may use without asking.  The limit is raised to the largest size any call
-// can need, once per (kernel variant, device) at that variant's first use on the device - a host-side
+// can need of a variant, once per (kernel variant, device) at that variant's first use on the device - a host-side
 // setting that enqueues nothing - and never again, so that calls on the enqueue path (also under
 // stream capture) only launch.
-constexpr size_t kSelMaxLdsBytes = (static_cast<size_t>(cd::kSelMaxLdsKeys) + cd::kSelMaxLdsKeys / 32 + 1) * sizeof(float);
+constexpr size_t kSelMaxListBytes = 64 * 1024;            // the retained list, where the selection gathers too
+constexpr size_t select_max_lds(int per) { return std::max(cd::select_row_bytes(cd::kSelThreads * per, per), kSelMaxListBytes); }
 constexpr int kMaxDevices = 64;
 constexpr int kLdsSlots = 8;                              // kernels that ask for more than 48 KiB of dynamic LDS
-enum { kLdsSelect = 0 };                                  // three variants of the selection kernel
+enum { kLdsSelect = 0 };                                  // four variants of the selection kernel
 std::atomic<uint8_t> g_lds_ready[kLdsSlots][kMaxDevices]; // zero-initialised: nothing raised yet
 
 // `bytes` is the largest size any call can ask of this kernel, so one setting per (slot, device) is enough.
@@ -328,7 +329,8 @@ int static_scratch_ptr(char** out) {
 enum class GatherIn { kPass, kDone, kOwnLaunch };
 GatherIn gather_place(const calidrop_params* p, const cd::GatherArgs& ga, int rows_per_split, bool lds_selection) {
   const int64_t pairs = static_cast<int64_t>(p->batch) * p->n_kv_heads;
-  if (lds_selection && pairs >= 128 && pairs * ga.blocks > 256) return GatherIn::kDone;
+  const bool fits = p->budget * sizeof(int32_t) <= kSelMaxListBytes;           // the list in LDS
+  if (lds_selection && fits && pairs >= 128 && pairs * ga.blocks > 256) return GatherIn::kDone;
   return rows_per_split < 1024 && pairs * ga.blocks <= 4096 ? GatherIn::kPass : GatherIn::kOwnLaunch;
 }
 
@@ -350,21 +352,22 @@ int run_selection(const calidrop_params* p, int max_seq_len, cd::SelectArgs& se,
   place = gather_place(p, se.gather, rows_per_split, lds_selection);
   se.gather_here = place == GatherIn::kDone;
   if (lds_selection) {
-    // dynamic LDS: staged votes (padded), later reused for the retained indices
-    size_t lds = max_seq_len > p->budget ? (static_cast<size_t>(max_prefix) + max_prefix / 32 + 1) * sizeof(float) : 0;
-    if (se.gather_here) lds = std::max(lds, static_cast<size_t>(p->budget) * sizeof(int32_t));
-    // 1024 threads, and positions per thread: the smallest of 8 / 16 / 32 that covers the longest prefix.
+    // 1024 threads, and positions per thread: the smallest of 2 / 8 / 16 / 32 that covers the longest prefix.
     const dim3 grid(bg);
     auto launch = [&](auto per) {
       constexpr int PER = decltype(per)::value;
       const auto fn = &cd::select_lds_kernel<cd::kSelThreads, PER>;
-      const int slot = kLdsSelect + (PER == 8 ? 0 : PER == 16 ? 1 : 2);
-      if (int e = ensure_kernel_lds(slot, reinterpret_cast<const void*>(fn), kSelMaxLdsBytes, "select")) return e;
+      const int slot = kLdsSelect + (PER == 2 ? 3 : PER == 8 ? 0 : PER == 16 ? 1 : 2);
+      // dynamic LDS: staged votes, later reused for the retained indices
+      size_t lds = max_seq_len > p->budget ? cd::select_row_bytes(max_prefix, PER) : 0;
+      if (se.gather_here) lds = std::max(lds, static_cast<size_t>(p->budget) * sizeof(int32_t));
+      if (int e = ensure_kernel_lds(slot, reinterpret_cast<const void*>(fn), select_max_lds(PER), "select")) return e;
       hipLaunchKernelGGL(fn, grid, dim3(cd::kSelThreads), lds, st, se);
       return static_cast<int>(CALIDROP_OK);
     };
     using std::integral_constant;
-    if (max_prefix <= cd::kSelThreads * 8) rc = launch(integral_constant<int, 8>{});
+    if (max_prefix <= cd::kSelThreads * 2) rc = launch(integral_constant<int, 2>{});
+    else if (max_prefix <= cd::kSelThreads * 8) rc = launch(integral_constant<int, 8>{});
     else if (max_prefix <= cd::kSelThreads * 16) rc = launch(integral_constant<int, 16>{});
     else rc = launch(integral_constant<int, 32>{});
     if (rc) return rc;

@@ -21,7 +21,7 @@
 namespace cd {
 
 constexpr int kSelThreads = 1024;
-constexpr int kSelPerThread = 32;              // LDS variant: positions per thread (= one bitmap word)
+constexpr int kSelPerThread = 32;              // LDS variant: most positions per thread (= one bitmap word)
 constexpr int kSelMaxLdsKeys = kSelThreads * kSelPerThread;   // longest prefix the LDS variant takes
 constexpr int kSelMaxPool = 15;                // widest pooling kernel the LDS variant takes
 
@@ -122,50 +122,185 @@ __device__ __forceinline__ void wide_pick(const u32x4 hb, int shift, uint32_t& p
   remaining = rem;
 }
 
-// Radix select of the `rank`-th largest key (rank >= 1, at most the number of keys).
-// `for_each_key(visit)` must call visit(u) once for every key this thread owns.  On return
-// thr = that key's bit pattern and need_eq = how many keys equal to thr lie within the rank.
-// `hist`: one 256-bin histogram per pass, all zero, with a barrier since they were cleared.  Must be called by
-// every thread of the workgroup.  Latency is all there is to it (a head of 8192 scores keeps one compute unit busy for
-// some microseconds): one barrier per pass, every wave finds the digit for itself, the last runs of a wave are
-// added up before they reach the histogram (selection of 32768 scores 42 -> 33 us, three barriers a pass before).
-template <typename ForEach>
-__device__ __forceinline__ void radix_select(uint32_t (*hist)[256], uint32_t rank, ForEach&& for_each_key, uint32_t& thr,
-                                             uint32_t& need_eq) {
-  const int lane = threadIdx.x & 63;
-  uint32_t prefix = 0;            // bits decided so far (the high bits of the answer)
-  uint32_t remaining = rank;      // rank of the answer among the keys matching `prefix`
+constexpr int kSelThreadWaves = kSelThreads / 64;
+constexpr uint32_t kNoKey = 0x80000000u;               // scores have no sign: a key with this bit is no score
+// First digit of the single-workgroup selection: its bits.  Scores crowd in few of its bins (a pooled vote rarely is more than
+// an octave from the next), and lanes that add to one word of LDS do so one after the other: the more keys there are, the
+// finer the digit (32768 keys within 6 % of each other: 4096 bins 26.8 us, 16384 bins 20.7 us).
+__host__ __device__ constexpr int select_bits(int per) { return per == 2 ? 12 : per == 8 ? 13 : 14; }
+// Words of its histogram; the first one behind the bins takes the keys that are no score.
+__host__ __device__ constexpr int select_first_words(int per) { return (1 << select_bits(per)) + 16; }
+// Keys of the bin the first digit ends in that are ranked against each other, instead of two more histograms (bits - 31 to 9,
+// and the last 9) over all keys.
+constexpr int kSelFewKeys = 256;
+constexpr int kSelLastBits = 9;
+__host__ __device__ constexpr int select_later_words(int per) { return (1 << (31 - select_bits(per) - kSelLastBits)) + (1 << kSelLastBits); }
+static_assert(kSelThreads == 4 * kSelFewKeys && kSelFewKeys % 64 == 0, "four threads a key, sixteen keys a step");
+static_assert(2 * kSelFewKeys <= select_later_words(32), "the few keys and their ranks take the place of the later histograms");
+__host__ __device__ constexpr int select_hist_words(int per) { return select_first_words(per) + select_later_words(per); }
+// Short prefixes: histograms beside the votes, cleared while those are on their way; longer ones: in their place once they
+// are pooled, so that two workgroups for 16384 positions fit a compute unit.
+__host__ __device__ constexpr bool select_own_hist(int per) { return per <= 8; }
+struct SelectShared {
+  uint32_t wave_tot[2][kSelThreadWaves];
+  uint32_t digit, rem, in_bin, few;
+};
+
+template <int NT>
+__device__ __forceinline__ void clear_hist(uint32_t* hist, int words, int tid) {
 #pragma unroll
-  for (int pass = 0; pass < 4; ++pass) {
-    const int shift = 24 - 8 * pass;
-    const uint32_t himask = (pass == 0) ? 0u : (0xFFFFFFFFu << (shift + 8));
-    {
-      // run-length compressed updates: scores share their leading digits, so consecutive keys
-      // of a thread mostly fall in the same bin and only bin changes touch the histogram
-      uint32_t run_bin = 0, run_len = 0;
-      for_each_key([&](uint32_t u) {
-        if ((u & himask) == prefix) {
-          const uint32_t bin = (u >> shift) & 0xFF;
-          if (bin != run_bin && run_len) { atomicAdd(&hist[pass][run_bin], run_len); run_len = 0; }
-          run_bin = bin;
-          ++run_len;
-        }
-      });
-      // the last runs of a wave are mostly in one bin (the leading digits): one addition then
-      const uint32_t first = __builtin_amdgcn_readfirstlane(run_bin);
-      if (__all(run_bin == first)) {
-        const uint32_t sum = last_lane(wave_inclusive_scan(run_len));
-        if (lane == 0 && sum) atomicAdd(&hist[pass][first], sum);
-      } else if (run_len) {
-        atomicAdd(&hist[pass][run_bin], run_len);
+  for (int t = tid; t < words / 4; t += NT) *reinterpret_cast<u32x4*>(hist + 4 * t) = zero16();
+}
+
+// Sum of tot[0 .. wave - 1] of the workgroup's waves, in every lane (one LDS read and a scan; a loop over the waves waits
+// for LDS once per wave).
+template <int NT>
+__device__ __forceinline__ uint32_t before_wave(const uint32_t* tot, int wave) {
+  static_assert(NT / 64 <= 16, "the totals of one row of lanes");
+  const int lane = threadIdx.x & 63;
+  const uint32_t v = lane < wave ? tot[lane & 15] : 0u;
+  return last_lane(wave_inclusive_scan(v));
+}
+
+// Where chunk q (16 bytes) of the staged row lies: rows of 16 chunks, rotated by exclusive or, so that both consecutive
+// chunks (staging) and chunks PER / 4 apart (windows) of sixteen neighbouring lanes are in different banks.
+__device__ __forceinline__ int select_chunk(int q) { return q ^ ((q >> 4) & 15); }
+// Slot s of the staged row holds vote s - shift - kSelFront, shift = the head's first vote modulo 4: 16-byte pieces of memory
+// are chunks of the row.
+constexpr int kSelFront = 8;                           // zeros ahead: two chunks, at least half the widest pooling
+static_assert(kSelFront % 4 == 0 && kSelFront >= kSelMaxPool / 2, "the first window starts in the row");
+// Chunks a thread's window takes, wherever in a chunk it starts.
+__host__ __device__ constexpr int select_window_chunks(int per) { return (per + kSelMaxPool - 1 + 3 + 3) / 4; }
+// Bytes of the staged row of a prefix of up to P positions (what the windows read, whole rows of chunks) and of the histograms
+// where they take its place.
+__host__ __device__ constexpr size_t select_row_bytes(int P, int per) {
+  const size_t row = static_cast<size_t>((P - 1 + kSelFront + 3) / 4 + select_window_chunks(per) + 15) / 16 * 16 * 16;
+  const size_t hist = select_own_hist(per) ? 0 : select_hist_words(per) * sizeof(uint32_t);
+  return row > hist ? row : hist;
+}
+
+// The bin of a finished histogram in which the count from the top reaches `remaining`; `remaining` becomes the rank inside it,
+// `in_bin` its count.  Thread t looks at bins BPT t .. BPT t + BPT - 1.
+template <int NT, int BPT>
+__device__ __forceinline__ uint32_t pick_digit(SelectShared& sh, const uint32_t* hist, int bins, uint32_t& remaining, uint32_t& in_bin) {
+  constexpr int kChunks = BPT / 4;                             // of 16 bytes
+  const int tid = threadIdx.x, lane = tid & 63, wv = wave_index();
+  uint32_t mine = 0;
+  if (BPT * tid < bins) {
+#pragma unroll
+    for (int q = 0; q < kChunks; ++q) {                         // sixteen lanes start with different chunks: all banks at once
+      const u32x4 c = ld16(hist + BPT * tid + 4 * ((q + tid / (16 / kChunks)) % kChunks));
+      mine += (c[0] + c[1]) + (c[2] + c[3]);
+    }
+  }
+  const uint32_t inc = wave_inclusive_scan(mine);
+  if (lane == 63) sh.wave_tot[0][wv] = inc;
+  if (tid == 0) { sh.digit = 0; sh.rem = remaining; sh.in_bin = ~0u; sh.few = 0; }      // never left so by a consistent histogram
+  __syncthreads();
+  const uint32_t t = lane < NT / 64 ? sh.wave_tot[0][lane & 15] : 0u;
+  const uint32_t upto = wave_inclusive_scan(t);
+  const uint32_t above = last_lane(upto) - __builtin_amdgcn_readlane(upto, wv) + last_lane(inc) - inc;
+  if (above < remaining && remaining <= above + mine) {         // exactly one thread
+    u32x4 c[kChunks];
+#pragma unroll
+    for (int q = 0; q < kChunks; ++q) c[q] = ld16(hist + BPT * tid + 4 * q);
+    uint32_t cum = above, cnt = 0;
+    int bin = BPT;
+#pragma unroll
+    for (int x = BPT - 1; x >= 0; --x)
+      if (cum + cnt < remaining) { cum += cnt; cnt = c[x / 4][x % 4]; bin = x; }
+    sh.digit = BPT * tid + bin;
+    sh.rem = remaining - cum;
+    sh.in_bin = cnt;
+  }
+  __syncthreads();
+  remaining = sh.rem;
+  in_bin = sh.in_bin;
+  return sh.digit;
+}
+
+// Radix select of the `rank`-th largest key (rank >= 1, at most the number of keys).
+// `for_each_key(visit)` must call visit(u) once for every key this thread owns; keys with kNoKey are none.  On return
+// thr = that key's bit pattern and need_eq = how many keys equal to thr lie within the rank.
+// `hist`: zero, with a barrier since it was cleared.  Must be called by every thread of the workgroup.
+// kSecond: another rank of the same keys; the histogram of the first digit is still there.
+template <int NT, int PER, bool kSecond, typename ForEach>
+__device__ __forceinline__ void radix_select(uint32_t* hist, SelectShared& sh, uint32_t rank, ForEach&& for_each_key, uint32_t& thr,
+                                             uint32_t& need_eq) {
+  constexpr int kBits = select_bits(PER), kLow = 31 - kBits, kLater = select_later_words(PER);      // kLow: bits below the first digit
+  const int tid = threadIdx.x;
+  uint32_t remaining = rank;      // rank of the answer among the keys matching the bits decided so far
+  uint32_t in_bin;
+  if constexpr (!kSecond)
+    for_each_key([&](uint32_t u) __attribute__((always_inline)) { atomicAdd(&hist[u >> kLow], 1u); });
+  __syncthreads();                // second: everyone has read what the first left in `sh`
+  uint32_t prefix = pick_digit<NT, (1 << kBits) / NT>(sh, hist, 1 << kBits, remaining, in_bin) << kLow;
+  uint32_t* h = hist + select_first_words(PER);
+  auto clear_again = [&]() {
+    if constexpr (kSecond) {
+      for (int t = tid; t < kLater; t += NT) h[t] = 0u;
+      __syncthreads();
+    }
+  };
+  if (in_bin <= kSelFewKeys) {
+    // the keys of the bin in any order, then for each how many are greater, and how many greater or equal (high half): thread t
+    // counts for key t modulo 256 over every fourth group of four keys
+    uint32_t* list = h;
+    uint32_t* ranks = h + kSelFewKeys;
+    clear_again();
+    for_each_key([&](uint32_t u) __attribute__((always_inline)) {
+      if ((u ^ prefix) < (1u << kLow)) list[atomicAdd(&sh.few, 1u)] = (u ^ prefix) + 1u;       // 0: none
+    });
+    __syncthreads();
+    const uint32_t me = tid % kSelFewKeys;
+    uint32_t own = 0;
+    if (wave_index() % (kSelFewKeys / 64) * 64u < in_bin) {
+      own = list[me];
+      uint32_t higher = 0, reach = 0;
+      for (uint32_t j = 0; j < in_bin; j += 64) {                // four groups in flight; zeros behind the last key
+        u32x4 o[4];
+#pragma unroll
+        for (int x = 0; x < 4; ++x) o[x] = ld16(list + j + 16 * x + 4 * (tid / kSelFewKeys));
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) { higher += o[x][q] > own ? 1u : 0u; reach += o[x][q] >= own ? 1u : 0u; }
       }
+      if (me < in_bin) atomicAdd(&ranks[me], higher | (reach << 16));
     }
     __syncthreads();
-    wide_pick(*reinterpret_cast<const u32x4*>(&hist[pass][4 * lane]), shift, prefix, remaining);
+    if (tid < kSelFewKeys && me < in_bin) {
+      const uint32_t r = ranks[me], higher = r & 0xFFFFu, reach = r >> 16;
+      if (higher < remaining && remaining <= reach) { sh.digit = own - 1u; sh.rem = remaining - higher; }      // equal keys write the same
+    }
+    __syncthreads();
+    thr = prefix | sh.digit;
+    need_eq = sh.rem;
+    return;
+  }
+  clear_again();
+#pragma unroll 1                  // one copy of the code: fetching it costs more than the loop
+  for (int pass = 0; pass < 2; ++pass) {
+    const int bins = pass ? 1 << kSelLastBits : 1 << (kLow - kSelLastBits), shift = pass ? 0 : kSelLastBits, decided = pass ? kSelLastBits : kLow;
+    for_each_key([&](uint32_t u) __attribute__((always_inline)) {
+      if (((u ^ prefix) >> decided) == 0) atomicAdd(&h[(u >> shift) & (bins - 1)], 1u);
+    });
+    __syncthreads();
+    prefix |= pick_digit<NT, 4>(sh, h, bins, remaining, in_bin) << shift;
+    h += bins;
   }
   thr = prefix;
   need_eq = remaining;
 }
+
+// s / k for an odd k up to kSelMaxPool, rounded as the division rounds it: two corrections of s times the rounded reciprocal
+// (checked over every 24-bit significand for every such k).  Sums outside 2^-100 .. 2^100 other than 0 - their
+// remainders may leave the range - and what is no number are for the division itself.
+__device__ __forceinline__ float divide_small(float s, float k, float rk) {
+  const float q = s * rk;
+  return fmaf(fmaf(-k, q, s), rk, q);
+}
+constexpr uint32_t kDivideLow = 27u << 23, kDivideHigh = 227u << 23;      // bit patterns of 2^-100 and 2^100
 
 // Membership of one candidate, given how many greater / equal keys precede it in position order.
 struct Cut {
@@ -521,14 +656,18 @@ __global__ __launch_bounds__(256) void gather_kv_kernel(GatherOnlyArgs a) {
 // LDS variant for prefixes of up to PER * NT positions (NT = 1024 threads in use: smaller
 // workgroups were measured slower, their staging and gather phases have too few threads).
 // Thread t owns positions PER*t..PER*t+PER-1: their pooled scores live in its registers for the
-// radix passes and the compaction.  PER = 32: their bits are exactly bitmap word t (prefixes up
-// to 32768); PER = 16 / 8: half a word / a byte, so that prefixes up to 16384 / 8192 still keep
-// every thread busy.  The votes are staged once in LDS
-// (padded by one word per 32 so that the stride-32 accesses do not collide).
+// radix passes and the compaction.  PER = 32 covers prefixes up to 32768; 16, 8 and 2 are there so that
+// shorter ones (16384, 8192, 2048) still keep every thread busy.
+// What bounds it is instruction issue on the one compute unit a head has: each of the 16 waves spends its instructions per key
+// in every pass over the keys, some 500 cycles per instruction and pass at 32768 keys.  Hence one wide first digit counted with
+// plain LDS atomics and the few keys of its bin ranked directly (four 8-bit digits with run-length compressed counts before),
+// windows read 16 bytes at a time from a zero-padded row, a three-instruction division, waves without positions that skip
+// all of it, and a second cut only where there is one.  Eight heads, four digits / now, us: 8192 scores 10.0 / 7.5, 16000
+// 13.8 / 11.4, 32768 21.5 / 15.8; two heads of 512 8.6 / 5.1; the same with all scores within 6 % of each other 10.1 / 9.2, 14.3 /
+// 14.0, 22.2 / 20.7, 8.6 / 5.7; 512 heads of 14000 with the gather of 1024 rows 110 / 98 (two workgroups on a compute unit).
 template <int NT, int PER>
 __global__ __launch_bounds__(NT) void select_lds_kernel(SelectArgs a) {
-  extern __shared__ uint32_t s_sel[];
-  float* s_vote = reinterpret_cast<float*>(s_sel);
+  extern __shared__ __attribute__((aligned(16))) uint32_t s_sel[];
   int32_t* s_idx = reinterpret_cast<int32_t*>(s_sel);      // gather_here: the list, once the votes are done with
   const int bg = blockIdx.x;
   const int g = bg % a.Hkv;
@@ -541,10 +680,10 @@ __global__ __launch_bounds__(NT) void select_lds_kernel(SelectArgs a) {
   if (g == 0 && tid == 0) a.cache_lens[b] = min(n, a.B);
   const int64_t head_tok = static_cast<int64_t>(off0) * a.Hkv + static_cast<int64_t>(g) * n;
 
-  __shared__ __attribute__((aligned(16))) uint32_t s_hist[2][4][256];
-  __shared__ uint32_t wave_tot[2][NT / 64];
-  static_assert(PER == 32 || PER == 16 || PER == 8, "a thread owns a whole bitmap word, a half or a byte of one");
-  auto pad = [](int j) { return j + (j >> 5); };
+  constexpr bool kOwnHist = select_own_hist(PER);
+  __shared__ __attribute__((aligned(16))) uint32_t s_own[kOwnHist ? select_hist_words(PER) : 4];
+  __shared__ SelectShared sh;
+  uint32_t* hist = kOwnHist ? s_own : s_sel;
 
   if (n <= a.B) {                       // nothing to evict: keep every position
     for (int r = tid; r < a.B; r += NT) {
@@ -555,58 +694,64 @@ __global__ __launch_bounds__(NT) void select_lds_kernel(SelectArgs a) {
   } else {
     const int P = n - a.w;
     const int k_sel = a.B - a.w;
-    for (int t = tid; t < 2 * 4 * 256; t += NT) (&s_hist[0][0][0])[t] = 0;
-    // ---- stage the votes (row-block partials added first, fixed order) ---------------------
+    const int half = a.pool_k / 2;
+    // ---- stage the votes (row-block partials added first, fixed order) into the zero-padded row.  16 bytes per lane from the
+    // 16-byte boundary at or below the head's first vote (every vote plane starts 256-byte aligned - the plane stride is a
+    // multiple of 64 floats - and a head starts anywhere inside).  All loads of a thread are in flight together.
+    const int shift = static_cast<int>(head_tok & 3);
+    const float* vsrc = a.vote + (head_tok - shift);
+    const int nvec = (P + shift + half + 3) / 4;           // behind the prefix: zeros for the last windows
+    constexpr int kVec = PER >= 4 ? PER / 4 + 1 : 1;       // (P + 3 + 7 + 3) / 4 <= NT * kVec
+    static_assert(static_cast<int64_t>(NT) * kVec * 4 >= static_cast<int64_t>(NT) * PER + 13, "a thread stages kVec chunks");
     {
-      // 16 bytes per lane from the 16-byte boundary at or below the head's first vote (every vote
-      // plane starts 256-byte aligned - the plane stride is a multiple of 64 floats - and a head
-      // starts anywhere inside): vector v covers positions
-      // 4v - shift .. 4v - shift + 3.  All loads of a thread are in flight together.
-      const int64_t plane = a.plane;
-      const int shift = static_cast<int>(head_tok & 3);
-      const float* vsrc = a.vote + (head_tok - shift);
-      f32x4 tmp[PER / 4];
+      f32x4 tmp[kVec];
 #pragma unroll
-      for (int u = 0; u < PER / 4; ++u) {
-        const int v4 = tid + u * NT;
-        f32x4 val = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (4 * v4 - shift < P) {
-          val = *reinterpret_cast<const f32x4*>(vsrc + 4 * v4);
-          for (int rb = 1; rb < a.NRB; ++rb) val += *reinterpret_cast<const f32x4*>(vsrc + rb * plane + 4 * v4);
-        }
-        tmp[u] = val;
-      }
+      for (int u = 0; u < kVec; ++u) tmp[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int rb = 0; rb < a.NRB; ++rb) {
+        const float* src = vsrc + rb * a.plane;
 #pragma unroll
-      for (int u = 0; u < PER / 4; ++u) {
-        const int jb = 4 * (tid + u * NT) - shift;
-#pragma unroll
-        for (int x = 0; x < 4; ++x) {
-          const int j = jb + x;
-          if (j >= 0 && j < P) s_vote[pad(j)] = tmp[u][x];
+        for (int u = 0; u < kVec; ++u) {
+          const int v4 = tid + u * NT;
+          if (4 * v4 - shift < P) tmp[u] += *reinterpret_cast<const f32x4*>(src + 4 * v4);
         }
       }
-      // the vectors end `shift` positions short of PER * NT: the last few of a full-length prefix
-      const int jt = PER * NT - shift + tid;
-      if (tid < shift && jt < P) {
-        float val = a.vote[head_tok + jt];
-        for (int rb = 1; rb < a.NRB; ++rb) val += a.vote[rb * plane + head_tok + jt];
-        s_vote[pad(jt)] = val;
+      if constexpr (kOwnHist) clear_hist<NT>(hist, select_hist_words(PER), tid);
+      if (tid < kSelFront / 4) *reinterpret_cast<u32x4*>(s_sel + 4 * select_chunk(tid)) = zero16();
+#pragma unroll
+      for (int u = 0; u < kVec; ++u) {
+        const int v4 = tid + u * NT, first = 4 * v4 - shift;
+        if (first < 0 || first + 4 > P) {                  // both ends: neighbouring heads' votes, words that are none
+#pragma unroll
+          for (int x = 0; x < 4; ++x) tmp[u][x] = (first + x >= 0 && first + x < P) ? tmp[u][x] : 0.f;
+        }
+        if (v4 < nvec) *reinterpret_cast<f32x4*>(s_sel + 4 * select_chunk(v4 + kSelFront / 4)) = tmp[u];
       }
     }
     __syncthreads();
     // ---- pooling: score[j] = (1/k) sum_{d=-k/2..k/2} vote[j+d], zeros outside [0, P), summed
-    //      left to right at every position ------------------------------------------------------
+    //      left to right at every position.  Positions beyond the prefix get a key that matches no digit. ---------------
     uint32_t key[PER];
     const int j0 = tid * PER;
-    {
-      // the thread's window of votes: w[x] = vote[j0 - half + x], zeros outside [0, P)
-      const int half = a.pool_k / 2;
-      const float kf = static_cast<float>(a.pool_k);
-      float w[PER + kSelMaxPool - 1];
+    const bool busy = wv * (64 * PER) < P;         // same in every lane: this wave has positions
 #pragma unroll
-      for (int x = 0; x < PER + kSelMaxPool - 1; ++x) {
-        const int jj = j0 - half + x;
-        w[x] = (x < PER + a.pool_k - 1 && jj >= 0 && jj < P) ? s_vote[pad(jj)] : 0.f;
+    for (int u = 0; u < PER; ++u) key[u] = kNoKey;
+    if (busy) {
+      constexpr int kWin = select_window_chunks(PER);
+      float w[4 * kWin];
+      // the window of position j starts in slot j + shift + kSelFront - half; a lane without positions takes the last one's
+      const int slot0 = min(j0, (P - 1) / PER * PER) + shift + kSelFront - half;
+#pragma unroll
+      for (int x = 0; x < kWin; ++x)
+        *reinterpret_cast<f32x4*>(&w[4 * x]) = *reinterpret_cast<const f32x4*>(s_sel + 4 * select_chunk(slot0 / 4 + x));
+      // where in its chunk a window starts is the same in all lanes, with two positions a thread for all odd and all even ones
+      const int o = slot0 & 3;
+      if (PER == 2 ? (o & 1) != 0 : (__builtin_amdgcn_readfirstlane(o) & 1) != 0) {
+#pragma unroll
+        for (int x = 0; x + 1 < 4 * kWin; ++x) w[x] = w[x + 1];
+      }
+      if (PER == 2 ? (o & 2) != 0 : (__builtin_amdgcn_readfirstlane(o) & 2) != 0) {
+#pragma unroll
+        for (int x = 0; x + 2 < 4 * kWin; ++x) w[x] = w[x + 2];
       }
       float sum[PER];
 #pragma unroll
@@ -618,56 +763,75 @@ __global__ __launch_bounds__(NT) void select_lds_kernel(SelectArgs a) {
           for (int u = 0; u < PER; ++u) sum[u] += w[u + dd];
         }
       }
+      const float kf = static_cast<float>(a.pool_k), rk = 1.f / kf;
+      uint32_t top = 0, low = ~0u;                   // bit patterns; less one, so that 0 is no low one
 #pragma unroll
-      for (int u = 0; u < PER; ++u) key[u] = __builtin_bit_cast(uint32_t, sum[u] / kf);
-      if (a.write_scores) {
-        // pooled scores go out through LDS so that the global stores are coalesced
-        __syncthreads();
+      for (int u = 0; u < PER; ++u) {
+        top = max(top, __builtin_bit_cast(uint32_t, sum[u]));
+        low = min(low, __builtin_bit_cast(uint32_t, sum[u]) - 1u);
+      }
+      const bool whole = (wv + 1) * (64 * PER) <= P;      // same in every lane
+      if (whole && __all(top < kDivideHigh && low >= kDivideLow)) {
+#pragma unroll
+        for (int u = 0; u < PER; ++u) key[u] = __builtin_bit_cast(uint32_t, divide_small(sum[u], kf, rk));
+      } else {
 #pragma unroll
         for (int u = 0; u < PER; ++u)
-          if (j0 + u < P) s_sel[pad(j0 + u)] = key[u];
-        __syncthreads();
-        float* dst = a.score + head_tok;
+          if (j0 + u < P) key[u] = __builtin_bit_cast(uint32_t, sum[u] / kf) & ~kNoKey;
+      }
+      if (a.write_scores) {
+        uint32_t* dst = reinterpret_cast<uint32_t*>(a.score) + head_tok;
 #pragma unroll
-        for (int u = 0; u < PER; ++u) {
-          const int j = tid + u * NT;
-          if (j < P) dst[j] = __builtin_bit_cast(float, s_sel[pad(j)]);
-        }
+        for (int u = 0; u < PER; ++u)
+          if (j0 + u < P) dst[j0 + u] = key[u];
       }
     }
-    auto each_key = [&](auto&& visit) {
+    if constexpr (!kOwnHist) {
+      __syncthreads();
+      clear_hist<NT>(hist, select_hist_words(PER), tid);
+      __syncthreads();
+    }
+    auto each_key = [&](auto&& visit) __attribute__((always_inline)) {
+      if (!busy) return;
 #pragma unroll
-      for (int u = 0; u < PER; ++u)
-        if (j0 + u < P) visit(key[u]);
+      for (int u = 0; u < PER; ++u) visit(key[u]);
     };
     Cut c1, c2;                          // c1: retained prefix tokens; c2: retained + calibration set
     c1.all = false;
-    radix_select(s_hist[0], k_sel, each_key, c1.thr, c1.need_eq);
+    radix_select<NT, PER, false>(hist, sh, k_sel, each_key, c1.thr, c1.need_eq);
     c2.all = a.calib <= 0 || k_sel + a.calib >= P;
     c2.thr = 0; c2.need_eq = 0;
-    if (!c2.all) radix_select(s_hist[1], k_sel + a.calib, each_key, c2.thr, c2.need_eq);
+    if (!c2.all) radix_select<NT, PER, true>(hist, sh, k_sel + a.calib, each_key, c2.thr, c2.need_eq);
 
     // ---- ordered compaction: exclusive scans of the per-thread (greater, equal) counts of
     //      both cuts, greater in the low half-word and equal in the high half-word -------------
     // per-thread bit masks over its PER positions: key above the threshold / equal to it
     constexpr uint32_t kAll = PER == 32 ? 0xFFFFFFFFu : (1u << (PER & 31)) - 1u;
     const uint32_t valid = j0 >= P ? 0u : (P - j0 >= PER ? kAll : (1u << ((P - j0) & 31)) - 1u);
-    uint32_t gtm1 = 0, eqm1 = 0, gtm2 = 0, eqm2 = 0;
+    auto masks = [&](uint32_t thr, uint32_t& gtm, uint32_t& eqm) __attribute__((always_inline)) {
+      gtm = eqm = 0;
+      if (!busy) return;
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      gtm1 |= (key[u] > c1.thr ? 1u : 0u) << u;
-      eqm1 |= (key[u] == c1.thr ? 1u : 0u) << u;
-      gtm2 |= (key[u] > c2.thr ? 1u : 0u) << u;
-      eqm2 |= (key[u] == c2.thr ? 1u : 0u) << u;
-    }
-    gtm1 &= valid; eqm1 &= valid; gtm2 &= valid; eqm2 &= valid;
+      for (int u = PER - 1; u >= 0; --u) {           // the sign of a difference is shifted in from below
+        gtm = __builtin_amdgcn_alignbit(gtm, thr - key[u], 31);
+        eqm = __builtin_amdgcn_alignbit(eqm, key[u] - thr, 31);
+      }
+      gtm &= valid;
+      eqm = ~(gtm | eqm) & valid;                    // eqm held the smaller ones
+    };
+    uint32_t gtm1, eqm1, gtm2 = 0, eqm2 = 0;
+    masks(c1.thr, gtm1, eqm1);
     const uint32_t cnt1 = __popc(gtm1) + (static_cast<uint32_t>(__popc(eqm1)) << 16);
-    const uint32_t cnt2 = __popc(gtm2) + (static_cast<uint32_t>(__popc(eqm2)) << 16);
-    const uint32_t inc1 = wave_inclusive_scan(cnt1), inc2 = wave_inclusive_scan(cnt2);
-    if (lane == 63) { wave_tot[0][wv] = inc1; wave_tot[1][wv] = inc2; }
+    const uint32_t inc1 = wave_inclusive_scan(cnt1);
+    uint32_t cnt2 = 0, inc2 = 0;
+    if (!c2.all) {
+      masks(c2.thr, gtm2, eqm2);
+      cnt2 = __popc(gtm2) + (static_cast<uint32_t>(__popc(eqm2)) << 16);
+      inc2 = wave_inclusive_scan(cnt2);
+    }
+    if (lane == 63) { sh.wave_tot[0][wv] = inc1; sh.wave_tot[1][wv] = inc2; }
     __syncthreads();
-    uint32_t bef1 = inc1 - cnt1, bef2 = inc2 - cnt2;
-    for (int ww = 0; ww < wv; ++ww) { bef1 += wave_tot[0][ww]; bef2 += wave_tot[1][ww]; }
+    const uint32_t bef1 = inc1 - cnt1 + before_wave<NT>(sh.wave_tot[0], wv), bef2 = inc2 - cnt2 + before_wave<NT>(sh.wave_tot[1], wv);
     const uint32_t gt1 = bef1 & 0xFFFFu, eq1 = bef1 >> 16, gt2 = bef2 & 0xFFFFu, eq2 = bef2 >> 16;
     const uint32_t keepm = cut_members(c1, gtm1, eqm1, eq1, valid);
     const uint32_t calm = cut_members(c2, gtm2, eqm2, eq2, valid) & ~keepm;
@@ -686,18 +850,25 @@ __global__ __launch_bounds__(NT) void select_lds_kernel(SelectArgs a) {
       uint32_t pos = c2.rank(j0, gt2, eq2) - base1;
       for (uint32_t m = calm; m; m &= m - 1u, ++pos) cal[pos] = j0 + (__ffs(m) - 1);
     }
-    const uint32_t word = ~calm;            // bit = skip in the calibration pass
-    if constexpr (PER == 32) {
-      if (j0 < P) a.bitmap[static_cast<int64_t>(bg) * a.W32 + tid] = word;
-    } else {
-      // 32 / PER neighbouring lanes hold the pieces of one word (positions beyond the prefix were
-      // marked "skip" above, so the pieces of idle threads are all ones)
-      constexpr int LPW = 32 / PER;
-      constexpr uint32_t kMask = (1u << PER) - 1u;
-      uint32_t w32 = word & kMask;
-#pragma unroll
-      for (int q = 1; q < LPW; ++q) w32 |= (__shfl_down(word, q) & kMask) << (q * PER);
-      if ((tid & (LPW - 1)) == 0 && j0 < P) a.bitmap[static_cast<int64_t>(bg) * a.W32 + (j0 >> 5)] = w32;
+    // the bitmap (bit = skip in the calibration pass; positions beyond the prefix are marked), whole words of it: every
+    // thread stores the word, half or byte it owns, with 2 positions a thread every fourth one the byte of four
+    if (wv * (64 * PER) < ((P + 31) & ~31)) {
+      uint32_t word = ~calm;
+      void* bits = a.bitmap + static_cast<int64_t>(bg) * a.W32;
+      const bool mine = j0 < ((P + 31) & ~31);
+      if constexpr (PER == 32) {
+        if (mine) static_cast<uint32_t*>(bits)[tid] = word;
+      } else if constexpr (PER == 16) {
+        if (mine) static_cast<uint16_t*>(bits)[tid] = static_cast<uint16_t>(word);
+      } else if constexpr (PER == 8) {
+        if (mine) static_cast<uint8_t*>(bits)[tid] = static_cast<uint8_t>(word);
+      } else {
+        static_assert(PER == 2, "a thread owns a bitmap word, a half, a byte or two bits");
+        word &= 3u;
+        word |= __shfl_down(word, 1) << 2;
+        word |= __shfl_down(word, 2) << 4;
+        if (mine && (tid & 3) == 0) static_cast<uint8_t*>(bits)[tid / 4] = static_cast<uint8_t>(word);
+      }
     }
     for (int r = tid; r < a.w; r += NT) {
       idx[k_sel + r] = P + r;

@@ -516,6 +516,35 @@ def test_multi_workgroup_selection_at_segment_edges(pool, m):
         assert torch.equal(one.cal_indices, many.cal_indices)
 
 
+@pytest.mark.parametrize("kind", ["normal", "flat", "tiny", "zero", "inf"])
+@pytest.mark.parametrize("per,prefixes", [(2, [2048, 2047, 101]), (8, [8192, 2049, 8189]), (16, [16384, 8193]), (32, [32768, 16385, 40])])
+def test_single_workgroup_selection_at_its_edges(per, prefixes, kind):
+    # the longest prefix of each positions-per-thread variant, the first beyond the one before, neighbours whose votes start at
+    # every offset into 16 bytes: scores, lists and skip bits are those of the multi-workgroup chain, bit for bit.  Scores
+    # that crowd in one bin of the first digit (flat), below the range of the short division (tiny), all equal (zero), infinite.
+    w, Hkv = 15, 3
+    for pool, m in ((7, 0), (15, 300), (1, 33)):
+        wl = small("bf16", 6, Hkv, 64, [n + w for n in prefixes], w, 90, pool, T=0, name="selection_edges")
+        x = to_dev(synth.make_inputs(wl, 31 + per))
+        if kind == "flat":
+            x["k"] = x["k"] * 2.0 ** -9
+        lse = dict(tiny=85.0, zero=300.0, inf=-300.0).get(kind)
+        win_lse = None if lse is None else torch.full((wl.batch, 6, w), lse, device=DEV)
+        one = H.gpu_compress(wl, x, calib_size=m, win_lse=win_lse, flags=cd.OPT_WRITE_SCORES)
+        many = H.gpu_compress(wl, x, calib_size=m, win_lse=win_lse, flags=cd.OPT_WIDE_SELECTION)
+        assert torch.equal(one.indices, many.indices), (kind, pool)
+        assert torch.equal(one.c_out, many.c_out) and torch.equal(one.c_lse, many.c_lse)
+        if m:
+            assert torch.equal(one.cal_indices, many.cal_indices)
+        s1, s2 = (b.region(cd.REGION_SCORE).view(torch.int32) for b in (one, many))
+        off = 0
+        for n in wl.seq_lens:
+            for g in range(Hkv):
+                if n > wl.budget:
+                    assert torch.equal(s1[off:off + n - w], s2[off:off + n - w]), (kind, pool, n, g)
+                off += n
+
+
 @pytest.mark.parametrize("pool", [127, 129, 131])
 def test_pooling_widths_around_what_is_staged(pool):
     # half widths of 63, 64 (the widest kept in LDS) and 65, over a segment boundary
