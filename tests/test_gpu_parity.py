@@ -573,6 +573,27 @@ def test_gather_beside_short_and_long_splits(n):
     run_case(small("bf16", 8, 2, 128, [n], 16, 200, 5, T=1, name=f"gather_n{n}"))
 
 
+@pytest.mark.parametrize("dtype,Hq,Hkv,D,batch,budget", [
+    ("bf16", 16, 4, 128, 2, 516),       # the last number of rows one workgroup takes and the first that are split: 8 pairs,
+    ("bf16", 16, 4, 128, 2, 517),       # where the two launches cost the host 8.8 us
+    ("fp32", 8, 2, 64, 20, 317), ("fp32", 8, 2, 64, 20, 318),
+    ("bf16", 4, 4, 64, 66, 750),        # more pairs than compute units: 264
+    ("fp32", 8, 4, 128, 70, 190),       # 280 pairs, split, 4 waves otherwise
+    ("bf16", 8, 8, 64, 24, 1200)])      # 192 pairs, 8 waves
+def test_decode_forms_at_their_borders(dtype, Hq, Hkv, D, batch, budget):
+    lens = [budget + 40, budget - 5, 60] + [budget + 1 + b for b in range(batch - 3)]
+    lens = lens[:batch]
+    wl = small(dtype, Hq, Hkv, D, lens, 16, budget, 5, T=2, name=f"forms_{batch}x{budget}")
+    x = to_dev(synth.make_inputs(wl, 57))
+    bufs = H.gpu_compress(wl, x)
+    rep = {}
+    for t in range(wl.decode_steps):
+        bufs.decode(x["q_dec"][t])
+        torch.cuda.synchronize()
+        for b in {0, 1, 2 % batch, batch - 1}:
+            H.check_decode_step(wl, bufs, x["q_dec"][t], b, report=rep)
+
+
 @pytest.mark.parametrize("batch", [96, 97])
 def test_split_partials_merged_by_four_groups_or_one(batch):
     # 768 heads are the last that four groups of threads each merge, 776 the first with one group; 11 splits, so that
