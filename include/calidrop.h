@@ -122,9 +122,9 @@ size_t calidrop_decode_workspace_bytes(const calidrop_params* p, int32_t max_cac
  *             (G*w rounded up to a multiple of 128, or of 256 when G*w > 128).
  *   SCORE     float, packed like K with D = 1: pooled score of prefix position j of KV head g
  *             of sequence b at [seq_offsets[b]*Hkv + g*n_b + j], j < n_b - w.
- *   ROW_PARTS (compress only) float [batch][Hkv][S][chunks][2]: the (maximum, sum) of every row over each key
- *             chunk.  Overwritten by later steps of the call; its size shows into how many chunks the call cuts its
- *             longest prompt.
+ *   ROW_PARTS (compress only) float [batch][Hkv][chunks][S][2]: the (maximum, sum) of every row over each key
+ *             chunk.  May be overwritten by later steps of the call; its size shows into how many chunks the call cuts
+ *             its longest prompt.
  * Returns CALIDROP_OK and fills offset/bytes, or CALIDROP_EINVAL.                            */
 typedef enum { CALIDROP_REGION_ROW_LSE = 0, CALIDROP_REGION_SCORE = 1, CALIDROP_REGION_VOTE_PLANES = 2, CALIDROP_REGION_ROW_PARTS = 3 } calidrop_region;
 int calidrop_compress_workspace_region(const calidrop_params* p, int64_t total_tokens,

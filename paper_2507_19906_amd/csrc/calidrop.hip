@@ -210,9 +210,17 @@ WideRegions wide_regions(const calidrop_params* p, int window, int pool_k, int m
   return {round256(heads * cd::kWideHistWords * sizeof(uint32_t)), round256(heads * nseg * cd::kWideSegWords * sizeof(uint32_t))};
 }
 
+// Most chunk partials per row that the workgroups of pass 2 merge for themselves, and most bytes of partials that all of them
+// read for it: every workgroup reads the partials of all its rows, from its L2, before its first stage is done.  236 calls (1 to
+// 12 prompts of 600 to 90000 tokens, both types, 16 to 64 window rows): without the launch that merges them 0.8 to 2.4 us
+// less up to 24 MiB, from there on 0.5 less to 9 us more (131072 tokens, 256 rows, 64 MiB: 244 -> 246).
+constexpr int kMergeInVotes = 64;
+constexpr int64_t kMergeInVotesBytes = 24 << 20;
+
 struct CompressLayout {
   size_t rowpart, row_lse, vote, score, bitmap, cal_logit, part_o, part_ml, sel_hist, sel_cnt, total;
   int RB, NRB, NCH, W32, chunk_keys, zstride, NSEG;
+  bool merge_in_votes;
   SplitPlan sp;
 };
 
@@ -234,10 +242,12 @@ CompressLayout compress_layout(const calidrop_params* p, int64_t total_tokens, i
   const WideRegions wide = wide_regions(p, p->window, p->pool_kernel, max_seq_len, L.NSEG);
   L.sel_hist = off; off += wide.hist;
   L.sel_cnt = off;  off += wide.seg;
-  // The partials of pass 1 are merged into row_lse before anything is written to the regions from the votes on: they lie
-  // under them.  No plan takes more room than those regions, or than chunks of 8 units need where that is more, so that the
-  // size of the workspace does not fall as prompts grow.
-  L.rowpart = off;
+  // Few partials per row are merged by the workgroups of pass 2, next to their writing votes: a region of their own.  Many are
+  // merged into row_lse before anything is written to the regions from the votes on: they lie under them.  No plan takes
+  // more room than those regions, or than chunks of 8 units need where that is more, so that the size of the workspace does not
+  // fall as prompts grow.
+  const size_t chunk_bytes = rows * sizeof(float2);
+  L.rowpart = off; off += round256(chunk_bytes * std::min(kMergeInVotes, ceil_div(max_seq_len, cd::kChunkUnit)));
   L.vote = off;    off += round256(static_cast<size_t>(vote_plane(total_tokens, p->n_kv_heads)) * L.NRB * sizeof(float));
   L.score = off;   off += round256(toks * sizeof(float));
   L.bitmap = off;  off += round256(static_cast<size_t>(heads) * L.W32 * sizeof(uint32_t));
@@ -245,11 +255,12 @@ CompressLayout compress_layout(const calidrop_params* p, int64_t total_tokens, i
   const size_t slots = static_cast<size_t>(p->batch) * p->n_q_heads * most_splits(heads, max_seq_len, kFewV);
   L.part_o = off;  off += round256(slots * p->head_dim * sizeof(float));
   L.part_ml = off; off += round256(slots * sizeof(float2));
-  const size_t chunk_bytes = rows * sizeof(float2);
-  const size_t room = std::max(off - L.rowpart, round256(chunk_bytes * ceil_div(max_seq_len, 8 * cd::kChunkUnit)));
+  const size_t room = std::max(off - L.vote, round256(chunk_bytes * ceil_div(max_seq_len, 8 * cd::kChunkUnit)));
   L.chunk_keys = plan_chunk(p, total_tokens, max_seq_len, L.RB, L.NRB, static_cast<int64_t>(room / chunk_bytes));
   L.NCH = ceil_div(max_seq_len, L.chunk_keys);
-  L.total = L.rowpart + room;
+  L.merge_in_votes = L.NCH <= kMergeInVotes && static_cast<int64_t>(chunk_bytes) * L.NCH * L.NCH <= kMergeInVotesBytes;
+  if (L.NCH > kMergeInVotes) L.rowpart = L.vote;
+  L.total = L.vote + room;
   return L;
 }
 
@@ -482,17 +493,16 @@ int compress_impl(const calidrop_params* p, const void* q_win, const void* k, co
   if (max_seq_len > p->budget) {       // otherwise no sequence can need eviction
     dim3 grid_s(L.NCH, bg * L.NRB);
     const int64_t rows = static_cast<int64_t>(bg) * L.NRB * L.RB;
-    if (win_lse) {      // pass 1 is the caller's: only a unit conversion into the row table
-      hipLaunchKernelGGL(cd::rowlse_import_kernel, dim3(static_cast<unsigned>((rows + 255) / 256)), dim3(256), 0, st, sa,
-                         win_lse);
-      if ((rc = launch_status("rowlse_import"))) return rc;
-    } else {
+    sa.win_lse = win_lse;                // pass 1 is the caller's
+    if (!win_lse) {
       if (L.RB == 256) hipLaunchKernelGGL((cd::score_rowstats_kernel<T, D, 8>), grid_s, dim3(512), 0, st, sa);
       else hipLaunchKernelGGL((cd::score_rowstats_kernel<T, D, 4>), grid_s, dim3(256), 0, st, sa);
       if ((rc = launch_status("score_rowstats"))) return rc;
-      if (L.NCH > 64) hipLaunchKernelGGL(cd::rowstats_merge_kernel<64>, dim3(static_cast<unsigned>((rows + 3) / 4)), dim3(256), 0, st, sa);
-      else hipLaunchKernelGGL(cd::rowstats_merge_kernel<16>, dim3(static_cast<unsigned>((rows + 15) / 16)), dim3(256), 0, st, sa);
-      if ((rc = launch_status("rowstats_merge"))) return rc;
+      sa.rows_merged = !L.merge_in_votes;
+      if (sa.rows_merged) {
+        hipLaunchKernelGGL(cd::rowstats_merge_kernel, dim3(static_cast<unsigned>(rows / cd::kMergeRows)), dim3(256), 0, st, sa);
+        if ((rc = launch_status("rowstats_merge"))) return rc;
+      }
     }
     if (L.RB == 256) hipLaunchKernelGGL((cd::score_votes_kernel<T, D, 8>), grid_s, dim3(512), 0, st, sa);
     else hipLaunchKernelGGL((cd::score_votes_kernel<T, D, 4>), grid_s, dim3(256), 0, st, sa);

@@ -1,7 +1,8 @@
 // Observation-window scoring of the eviction strategy f (Alg. 1 step 3, SnapKV-style,
 // Sec. 4.1.3): S = Q_win K^T on the matrix cores in two passes over K.
 //   pass 1 (score_rowstats): per window-query row, max and sum of exp2 of its logits over the
-//           keys of one chunk; the chunks are merged into a row log-sum-exp (rowstats_merge).
+//           keys of one chunk; the chunks are merged into a row log-sum-exp, in small calls by the
+//           workgroups of pass 2, else by rowstats_merge.
 //   pass 2 (score_votes):    S recomputed, p = exp2(s - lse_row), column sums over the G*w
 //           rows of the KV head -> vote[j] for prefix columns j < P.
 // A workgroup owns a block of query rows (128, or 256 when the KV head has more than 128 - so that
@@ -32,8 +33,10 @@ struct ScoreArgs {
   int chunk_keys;       // keys per workgroup (multiple of 64); every wave reads all of them for query rows of its own
   float sl2;            // scale * log2(e)
   int keep_k;           // pass 1 leaves K in the last-level cache for pass 2 (K of the whole call fits it)
-  float2* rowpart;      // [batch*Hkv][row_stride][NCH] (max, sum) per chunk
+  float2* rowpart;      // [batch*Hkv][NCH][row_stride] (max, sum) per chunk
   float* row_lse;       // [batch*Hkv][row_stride] log2-domain row log-sum-exp (+inf for padding rows)
+  int rows_merged;      // pass 2 finds row_lse complete; otherwise its workgroups merge the partials (or take win_lse) themselves
+  const float* win_lse; // [batch][Hq][w] natural-log row log-sum-exp from the caller instead of pass 1, or NULL
   float* vote;          // [NRB][plane]: one plane of votes per row block, each packed like K with one float per row
   int64_t plane;        // floats per plane: total_tokens*Hkv rounded up to a multiple of 64 (planes stay 256-byte aligned)
   float* cal_logit;     // [batch*Hq][zstride] log2-unit logits of the last window query, or NULL
@@ -309,58 +312,49 @@ __global__ __launch_bounds__(NR * 64, sizeof(T) == 2 ? 4 : 2) void score_rowstat
     merge_ml(m[rt], l[rt], __shfl_xor(m[rt], 16), __shfl_xor(l[rt], 16));
     merge_ml(m[rt], l[rt], __shfl_xor(m[rt], 32), __shfl_xor(l[rt], 32));
     if (c == 0)
-      a.rowpart[(static_cast<int64_t>(bg) * a.row_stride + rb * RB + wv * WR + rt * 16 + i) * a.NCH + chunk] = make_float2(m[rt], l[rt]);
+      a.rowpart[(static_cast<int64_t>(bg) * a.NCH + chunk) * a.row_stride + rb * RB + wv * WR + rt * 16 + i] = make_float2(m[rt], l[rt]);
   }
 }
 
-// A group of GS lanes (16, or a whole wave of 64 when a row has more than 64 partials) per query row:
-// lane j of the group merges the chunk partials j, j + GS, ... in that order, then the GS lane results
-// are merged by a fixed tree, into the log2-domain row log-sum-exp.  (A prompt of 131072 tokens has
-// hundreds of partials per row: one thread per row spent as long on them as a scoring pass.)
-template <int GS>
-__global__ __launch_bounds__(256) void rowstats_merge_kernel(ScoreArgs a) {
-  clear_words(a.zero_words, a.zero_count);
-  const int64_t gr = static_cast<int64_t>(blockIdx.x) * (256 / GS) + threadIdx.x / GS;
-  const int lane = threadIdx.x % GS;
-  const int64_t rows_total = static_cast<int64_t>(a.batch) * a.Hkv * a.row_stride;
-  if (gr >= rows_total) return;
-  const int b = static_cast<int>(gr / a.row_stride) / a.Hkv;
-  int off0;
-  const int n = seq_len_checked(a.seq_off, b, a.max_seq_len, a.total_tokens, off0);
-  if (n <= a.B) return;
-  const int rho = static_cast<int>(gr % a.row_stride);    // row inside the KV head
-  const int nch = (n + a.chunk_keys - 1) / a.chunk_keys;
-  const float2* part = a.rowpart + gr * a.NCH;
-  float m = -INFINITY, l = 0.f;
-  if (rho < a.R) {                                        // padding rows have no partials worth reading
-    for (int ch = lane; ch < nch; ch += GS) {
-      const float2 v = part[ch];
-      merge_ml(m, l, v.x, v.y);
-    }
-  }
+// Chunk partials first, first + step, ... of one row, merged in that order, kFlight of them on their way at a time.
+template <int kFlight>
+__device__ __forceinline__ void merge_chunks(const float2* part, int64_t stride, int first, int step, int nch, float& m, float& l) {
+  for (int c0 = first; c0 < nch; c0 += kFlight * step) {
+    float2 v[kFlight];
 #pragma unroll
-  for (int sft = 1; sft < GS; sft <<= 1) merge_ml(m, l, __shfl_xor(m, sft), __shfl_xor(l, sft));
-  if (lane == 0) a.row_lse[gr] = (l > 0.f && rho < a.R) ? m + fast_log2(l) : INFINITY;          // padding rows: +inf
+    for (int u = 0; u < kFlight; ++u) v[u] = c0 + u * step < nch ? part[(c0 + u * step) * stride] : make_float2(-INFINITY, 0.f);
+    float mn = m;
+#pragma unroll
+    for (int u = 0; u < kFlight; ++u) mn = fmaxf(mn, v[u].x);
+    const float ms = (mn == -INFINITY) ? 0.f : mn;
+    l *= fast_exp2(m - ms);
+#pragma unroll
+    for (int u = 0; u < kFlight; ++u) l += v[u].y * fast_exp2(v[u].x - ms);
+    m = mn;
+  }
 }
 
-// The row log-sum-exp taken from the caller instead of pass 1: win_lse [batch][Hq][w] holds, in
-// natural-log units, log sum_j exp(scale q_i.K_j) of window query i over the keys it may attend to
-// (positions 0..P+i) - the by-product a prefill attention kernel has for these rows anyway.  One
-// thread per row slot; padding rows get +inf like above.
-__global__ __launch_bounds__(256) void rowlse_import_kernel(ScoreArgs a, const float* win_lse) {
-  clear_words(a.zero_words, a.zero_count);
-  const int64_t gr = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  const int64_t rows_total = static_cast<int64_t>(a.batch) * a.Hkv * a.row_stride;
-  if (gr >= rows_total) return;
+// The merge as a launch of its own, where a row has so many partials that every workgroup of pass 2 doing it for its
+// rows would read more than its keys: 32 rows per workgroup, every eighth partial per thread, the eight results in order.
+constexpr int kMergeRows = 32;
+__global__ __launch_bounds__(256) void rowstats_merge_kernel(ScoreArgs a) {
+  __shared__ float2 s_ml[8][kMergeRows];
+  const int row = threadIdx.x % kMergeRows, grp = threadIdx.x / kMergeRows;
+  const int64_t gr = static_cast<int64_t>(blockIdx.x) * kMergeRows + row;      // row_stride is a multiple of kMergeRows
   const int bg = static_cast<int>(gr / a.row_stride);
-  const int g = bg % a.Hkv, b = bg / a.Hkv;
   const int rho = static_cast<int>(gr % a.row_stride);    // row inside the KV head
-  float val = INFINITY;
-  if (rho < a.R) {
-    const int hh = rho / a.w, wi = rho - hh * a.w;
-    val = win_lse[(static_cast<int64_t>(b) * a.Hq + g * a.G + hh) * a.w + wi] * kLog2e;
-  }
-  a.row_lse[gr] = val;
+  int off0;
+  const int n = seq_len_checked(a.seq_off, bg / a.Hkv, a.max_seq_len, a.total_tokens, off0);
+  if (n <= a.B) return;                                   // the same in all threads
+  const int nch = (n + a.chunk_keys - 1) / a.chunk_keys;
+  float m = -INFINITY, l = 0.f;
+  if (rho < a.R) merge_chunks<8>(a.rowpart + static_cast<int64_t>(bg) * a.NCH * a.row_stride + rho, a.row_stride, grp, 8, nch, m, l);
+  s_ml[grp][row] = make_float2(m, l);
+  __syncthreads();
+  if (grp != 0) return;
+#pragma unroll
+  for (int q = 1; q < 8; ++q) merge_ml(m, l, s_ml[q][row].x, s_ml[q][row].y);
+  a.row_lse[gr] = (l > 0.f && rho < a.R) ? m + fast_log2(l) : INFINITY;          // padding rows: +inf
 }
 
 // NR waves of 32 rows each (4 waves for a block of 128 rows, 8 for 256).  With the stage loads
@@ -377,6 +371,7 @@ __global__ __launch_bounds__(NR * 64, sizeof(T) == 2 ? 4 : 2) void score_votes_k
   // same L2 (the stationary query rows are then fetched from memory once, not once per XCD); when y
   // does not divide over the XCDs the chunk index is rotated by y instead, so that with sequences of
   // different lengths the chunks every sequence has do not all land on the same XCDs.
+  clear_words(a.zero_words, a.zero_count);
   int chunk, y;
   if (!xcd_rows_interleaved(chunk, y)) chunk = (chunk + y) % static_cast<int>(gridDim.x);
   const int rb = y % a.NRB;
@@ -419,11 +414,34 @@ __global__ __launch_bounds__(NR * 64, sizeof(T) == 2 ? 4 : 2) void score_votes_k
   }
   // S tiles are rows x keys here: lane (i, c) holds key i and rows 16 rt + 4 c + r of the wave
   float lse[RT][4];
+  if (a.rows_merged) {
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt)
+    for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-      lse[rt][r] = a.row_lse[static_cast<int64_t>(bg) * a.row_stride + row0 + rt * 16 + 4 * c + r];   // padding rows: +inf
+      for (int r = 0; r < 4; ++r)
+        lse[rt][r] = a.row_lse[static_cast<int64_t>(bg) * a.row_stride + row0 + rt * 16 + 4 * c + r];   // padding rows: +inf
+  } else {
+    // lanes j and j + 32 of the wave: row j of its 32, every other chunk each
+    const int rho = row0 + (lane & 31);
+    float val = INFINITY;
+    if (a.win_lse) {
+      if (rho < a.R) {
+        const int hh = rho / a.w, wi = rho - hh * a.w;
+        val = a.win_lse[static_cast<int64_t>(b * a.Hq + g * a.G + hh) * a.w + wi] * kLog2e;
+      }
+    } else {
+      float m = -INFINITY, l = 0.f;
+      const int nch = (n + a.chunk_keys - 1) / a.chunk_keys;
+      if (rho < a.R) merge_chunks<16>(a.rowpart + static_cast<int64_t>(bg) * a.NCH * a.row_stride + rho, a.row_stride, lane >> 5, 2, nch, m, l);
+      merge_ml(m, l, __shfl_xor(m, 32), __shfl_xor(l, 32));
+      if (l > 0.f && rho < a.R) val = m + fast_log2(l);
+    }
+    if (chunk == 0 && lane < 32) a.row_lse[static_cast<int64_t>(bg) * a.row_stride + rho] = val;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) lse[rt][r] = __shfl(val, 16 * rt + 4 * c + r);
+  }
 
   // Rows that are the last window query of a head (the default calibration query, Alg. 1
   // step 5) also export their logits, so that the calibration pass need not read K again.

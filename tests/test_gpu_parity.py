@@ -573,6 +573,37 @@ def test_gather_beside_short_and_long_splits(n):
     run_case(small("bf16", 8, 2, 128, [n], 16, 200, 5, T=1, name=f"gather_n{n}"))
 
 
+@pytest.mark.parametrize("dtype,D,w,lens", [
+    ("bf16", 64, 16, [64 * 17]),                            # 64 rows, the rest of the block padding; 17 partials: 9 and 8
+    ("fp32", 128, 33, [4097, 100, 63, 200]),                # 132 rows: a 256-row block; prompts with fewer partials and one
+    ("bf16", 128, 32, [64 * 64]),                           # 64 partials, as many as pass 2 merges
+    ("bf16", 64, 32, [64 * 64 * 3 + 1, 5000]),              # more: a launch of their own
+    ("fp32", 64, 70, [2500])])                              # 280 rows: two row blocks
+def test_chunk_partials_merged_in_pass_2_or_ahead(dtype, D, w, lens):
+    wl = small(dtype, 8, 2, D, lens, w, w + 24, 5, T=0, name="merge_rows")
+    x = to_dev(synth.make_inputs(wl, 63))
+    bufs = H.gpu_compress(wl, x)
+    for b in range(wl.batch):
+        H.check_compress(wl, x, bufs, b)
+    table = bufs.region(cd.REGION_ROW_LSE)
+    rows = 4 * w
+    stride = table.numel() // (2 * wl.batch)
+    table = table.view(wl.batch, 2, stride)
+    q, k, off = x["q_win"].double().cpu(), x["k"].double().cpu().view(-1, D), 0
+    for b, n in enumerate(wl.seq_lens):
+        for g in range(2):
+            if n > wl.budget:
+                z = q[b, 4 * g:4 * g + 4].reshape(rows, D) @ k[off:off + n].t() / D ** 0.5
+                see = n - w + torch.arange(w).repeat(4)
+                z = z.masked_fill(torch.arange(n)[None] > see[:, None], float("-inf"))
+                want = torch.logsumexp(z, 1) * 1.4426950408889634
+                # values up to some 100, where a float32 step is 7.6e-6: roundings of the logit, of the logarithm of the sum
+                # and of adding both, and of merging partials
+                assert (table[b, g, :rows].double().cpu() - want).abs().max() < 5e-5
+                assert torch.isinf(table[b, g, rows:]).all()
+            off += n
+
+
 @pytest.mark.parametrize("dtype,Hq,Hkv,D,batch,budget", [
     ("bf16", 16, 4, 128, 2, 516),       # the last number of rows one workgroup takes and the first that are split: 8 pairs,
     ("bf16", 16, 4, 128, 2, 517),       # where the two launches cost the host 8.8 us
