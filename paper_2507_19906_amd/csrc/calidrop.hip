@@ -343,21 +343,22 @@ int static_scratch_ptr(char** out) {
   return CALIDROP_OK;
 }
 
-// Where the gather of the retained rows runs.  As further workgroups of the streaming pass it costs no launch and the
-// selection kernel's few workgroups do not copy, but there its workgroups take the places of streaming ones (LDS and
-// registers are the pass's).  In 228 calls (2 to 96 (sequence, KV head) pairs, budgets 64 to 2048, 2100 to 100000 rows)
-// that was 2-3 us faster than a launch of its own while the splits of the pass are short, whatever the budget (8 heads of
-// 8192 rows, budget 500 / 1024 / 2048: 40.1 -> 37.9, 41.3 -> 38.9, 43.1 -> 40.7 us a call), the same at splits of 1024 rows
-// and 1-5 % slower with longer ones (100000 rows, budget 512: 170 -> 173 us, 2048: 170 -> 179 us).  Measured up to some
-// 8000 gathering workgroups; 512 heads of 1024 rows, 32768 of them, held the pass up for 160 us.
+// Where the gather of the retained rows runs.  It costs no launch as further workgroups of the streaming pass, where they
+// take the places of streaming ones (LDS and registers are the pass's), or of the launch that merges the pass's partials,
+// where they wait for the pass.  134 calls (2 to 80 (sequence, KV head) pairs, budgets 128 to 2500, 512 to 60000 rows), in the
+// merge / in the pass, us a call: the pass is 1-2 % faster while its splits are short (2 heads of 3000 rows, fp32 30.0 / 29.4, 8
+// heads 28.6 / 28.1), the merge 1-3 % from some 600 rows on (8 heads of 20000 rows 56.7 / 58.5); against a launch of its own the
+// merge saves 3-4 us (131072 rows, budget 4096: 12.1 us in two launches, 8.4 in one).  The pass was measured up to some 8000
+// gathering workgroups; 512 heads of 1024 rows, 32768 of them, held it up for 160 us.  With more heads than the merge takes
+// four groups of threads for, its workgroups are small and the gather is a launch of its own.
 // With many heads the selection kernel does it: while one workgroup selects, others copy (140 us for both, against
 // 36 + 100 in two launches).
-enum class GatherIn { kPass, kDone, kOwnLaunch };
+enum class GatherIn { kPass, kDone, kAfter };
 GatherIn gather_place(const calidrop_params* p, const cd::GatherArgs& ga, int rows_per_split, bool lds_selection) {
   const int64_t pairs = static_cast<int64_t>(p->batch) * p->n_kv_heads;
   const bool fits = p->budget * sizeof(int32_t) <= kSelMaxListBytes;           // the list in LDS
   if (lds_selection && fits && pairs >= 128 && pairs * ga.blocks > 256) return GatherIn::kDone;
-  return rows_per_split < 1024 && pairs * ga.blocks <= 4096 ? GatherIn::kPass : GatherIn::kOwnLaunch;
+  return rows_per_split < 512 && pairs * ga.blocks <= 4096 ? GatherIn::kPass : GatherIn::kAfter;
 }
 
 cd::GatherArgs gather_args(const calidrop_params* p, const int32_t* indices, const int32_t* cache_offsets, const void* k, const void* v,
@@ -417,12 +418,21 @@ int run_selection(const calidrop_params* p, int max_seq_len, cd::SelectArgs& se,
 // The merge of the split partials.  Four groups of threads per head shorten the chain of loads while the heads leave the chip
 // room (32 heads, 64 splits 6.7 -> 4.0 us; 96 heads 4.6 -> 3.7 us; 256 to 640 heads the same); with a thousand heads and more
 // their workgroups no longer fit it at once (1024 heads 5.5 -> 6.5 us, 1920 heads 5.0 -> 7.3 us): one group then.
+constexpr int64_t kFourGroupHeads = 768;
+// `gather`: the rows this launch gathers as well, or NULL (more than kFourGroupHeads heads: always NULL).
 template <typename T, int D>
-int launch_finalize(const calidrop_params* p, const cd::FinalArgs& fa, hipStream_t st, const char* what) {
-  const dim3 grid(p->n_q_heads, p->batch);
-  const bool four = static_cast<int64_t>(p->batch) * p->n_q_heads <= 768;
-  if (four) hipLaunchKernelGGL((cd::attend_finalize_kernel<T, D, 4>), grid, dim3(4 * D), 0, st, fa);
-  else hipLaunchKernelGGL((cd::attend_finalize_kernel<T, D, 1>), grid, dim3(D), 0, st, fa);
+int launch_finalize(const calidrop_params* p, cd::FinalArgs& fa, hipStream_t st, const char* what, const cd::GatherArgs* gather = nullptr) {
+  dim3 grid(p->n_q_heads, p->batch);
+  const bool four = static_cast<int64_t>(p->batch) * p->n_q_heads <= kFourGroupHeads;
+  if (gather) {
+    fa.gather = *gather;
+    grid.x += p->n_kv_heads * ceil_div(gather->blocks * cd::kGatherVecs, 4 * D);
+    hipLaunchKernelGGL((cd::attend_finalize_kernel<T, D, 4, true>), grid, dim3(4 * D), 0, st, fa);
+  } else if (four) {
+    hipLaunchKernelGGL((cd::attend_finalize_kernel<T, D, 4>), grid, dim3(4 * D), 0, st, fa);
+  } else {
+    hipLaunchKernelGGL((cd::attend_finalize_kernel<T, D, 1>), grid, dim3(D), 0, st, fa);
+  }
   return launch_status(what);
 }
 
@@ -438,14 +448,21 @@ void launch_kv_pass(const cd::AttendArgs& aa, dim3 grid, int64_t rows, hipStream
   else hipLaunchKernelGGL((cd::attend_partial_kernel<T, D, false, false, kGather>), grid, dim3(256), 0, st, aa);
 }
 
-// The streaming pass over KV_evict, and the gather unless the selection has done it.
+// The streaming pass over KV_evict, and the gather unless the selection has done it.  `left` is set where the gather is left
+// to the launch that merges the partials.
 template <typename T, int D>
-int launch_calibration(const calidrop_params* p, cd::AttendArgs& aa, const cd::GatherArgs& ga, GatherIn place, hipStream_t st) {
+int launch_calibration(const calidrop_params* p, cd::AttendArgs& aa, const cd::GatherArgs& ga, GatherIn place, hipStream_t st,
+                       const cd::GatherArgs** left) {
   const bool evicts = aa.max_len > p->budget;          // otherwise no sequence can have anything to evict
-  if (place == GatherIn::kOwnLaunch || (place == GatherIn::kPass && !evicts)) {
-    cd::GatherOnlyArgs go{ga, aa.row_off, aa.total_tokens, p->n_kv_heads, p->budget, aa.max_len};
-    hipLaunchKernelGGL(cd::gather_kv_kernel, dim3(ga.blocks, p->batch * p->n_kv_heads), dim3(256), 0, st, go);
-    if (int rc = launch_status("gather_kv")) return rc;
+  *left = nullptr;
+  if (place == GatherIn::kAfter || (place == GatherIn::kPass && !evicts)) {
+    if (static_cast<int64_t>(p->batch) * p->n_q_heads <= kFourGroupHeads) {
+      *left = &ga;
+    } else {
+      cd::GatherOnlyArgs go{ga, aa.row_off, aa.total_tokens, p->n_kv_heads, p->budget, aa.max_len};
+      hipLaunchKernelGGL(cd::gather_kv_kernel, dim3(ga.blocks, p->batch * p->n_kv_heads), dim3(256), 0, st, go);
+      if (int rc = launch_status("gather_kv")) return rc;
+    }
   }
   if (!evicts) return CALIDROP_OK;
   aa.gather = ga;
@@ -534,14 +551,15 @@ int compress_impl(const calidrop_params* p, const void* q_win, const void* k, co
   aa.cal_logit = sa.cal_logit; aa.zstride = L.zstride;
   aa.part_o = reinterpret_cast<float*>(ws + L.part_o);
   aa.part_ml = reinterpret_cast<float2*>(ws + L.part_ml);
-  if ((rc = launch_calibration<T, D>(p, aa, ga, place, st))) return rc;
+  const cd::GatherArgs* left;
+  if ((rc = launch_calibration<T, D>(p, aa, ga, place, st, &left))) return rc;
   cd::FinalArgs fa{};
   fa.part_o = aa.part_o; fa.part_ml = aa.part_ml; fa.row_off = seq_offsets; fa.row_len = nullptr;
   fa.total_tokens = total_tokens; fa.batch = p->batch; fa.Hq = p->n_q_heads; fa.Hkv = p->n_kv_heads; fa.G = G;
   fa.w = p->window; fa.B = p->budget; fa.max_len = max_seq_len; fa.rows_per_split = L.sp.rows_per_split;
   fa.NS = L.sp.NS; fa.calib_mode = 1; fa.q_is_window = aa.q_is_window; fa.q = aa.q;
   fa.c_q = c_q; fa.c_out = c_out; fa.c_lse = c_lse;
-  return launch_finalize<T, D>(p, fa, st, "attend_finalize(calibration)");
+  return launch_finalize<T, D>(p, fa, st, "attend_finalize(calibration)", left);
 }
 
 template <typename T, int D>
@@ -691,14 +709,15 @@ int compress_given_impl(const calidrop_params* p, const void* q_cal, const void*
   aa.rows_per_split = L.sp.rows_per_split; aa.NS = L.sp.NS; aa.sl2 = logit_scale(p) * cd::kLog2e;
   aa.part_o = reinterpret_cast<float*>(ws + L.part_o);
   aa.part_ml = reinterpret_cast<float2*>(ws + L.part_ml);
-  if ((rc = launch_calibration<T, D>(p, aa, gather, in_lds ? GatherIn::kDone : GatherIn::kOwnLaunch, st))) return rc;
+  const cd::GatherArgs* left;
+  if ((rc = launch_calibration<T, D>(p, aa, gather, in_lds ? GatherIn::kDone : GatherIn::kAfter, st, &left))) return rc;
   cd::FinalArgs fa{};
   fa.part_o = aa.part_o; fa.part_ml = aa.part_ml; fa.row_off = seq_offsets; fa.row_len = nullptr;
   fa.total_tokens = total_tokens; fa.batch = p->batch; fa.Hq = p->n_q_heads; fa.Hkv = p->n_kv_heads; fa.G = G;
   fa.w = 0; fa.B = p->budget; fa.max_len = max_seq_len; fa.rows_per_split = L.sp.rows_per_split;
   fa.NS = L.sp.NS; fa.calib_mode = 1; fa.q_is_window = 0; fa.q = q_cal;
   fa.c_q = c_q; fa.c_out = c_out; fa.c_lse = c_lse;
-  return launch_finalize<T, D>(p, fa, st, "attend_finalize(given)");
+  return launch_finalize<T, D>(p, fa, st, "attend_finalize(given)", left);
 }
 
 int packed_rows_host(const calidrop_params* p, int n) {
@@ -882,14 +901,15 @@ int h2o_impl(const calidrop_params* p, int n_local, const void* q_full, const vo
   aa.rows_per_split = L.sp.rows_per_split; aa.NS = L.sp.NS; aa.sl2 = sl2;
   aa.part_o = reinterpret_cast<float*>(ws + L.part_o);
   aa.part_ml = reinterpret_cast<float2*>(ws + L.part_ml);
-  if ((rc = launch_calibration<T, D>(p, aa, ga, place, st))) return rc;
+  const cd::GatherArgs* left;
+  if ((rc = launch_calibration<T, D>(p, aa, ga, place, st, &left))) return rc;
   cd::FinalArgs fa{};
   fa.part_o = aa.part_o; fa.part_ml = aa.part_ml; fa.row_off = seq_offsets; fa.row_len = nullptr;
   fa.total_tokens = total_tokens; fa.batch = p->batch; fa.Hq = p->n_q_heads; fa.Hkv = p->n_kv_heads; fa.G = G;
   fa.w = n_local; fa.B = p->budget; fa.max_len = max_seq_len; fa.rows_per_split = L.sp.rows_per_split;
   fa.NS = L.sp.NS; fa.calib_mode = 1; fa.q_is_window = 0; fa.q = ha.q_last;
   fa.c_q = c_q; fa.c_out = c_out; fa.c_lse = c_lse;
-  return launch_finalize<T, D>(p, fa, st, "attend_finalize(h2o)");
+  return launch_finalize<T, D>(p, fa, st, "attend_finalize(h2o)", left);
 }
 
 }  // namespace

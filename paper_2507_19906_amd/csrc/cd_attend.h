@@ -448,6 +448,7 @@ struct FinalArgs {
   float* c_q; float* c_out; float* c_lse;
   // decode outputs (recalibration mode, calib_mode = 2: out, a_lse and flags are inputs too)
   void* out; float* a_lse; uint8_t* flags;
+  GatherArgs gather;             // kGather: what the workgroups x >= Hq of a sequence gather (KV_compress)
 };
 
 __device__ __forceinline__ float block_sum(float x, float* red, int nthreads) {
@@ -467,8 +468,20 @@ __device__ __forceinline__ float block_sum(float x, float* red, int nthreads) {
 // calibration state (Alg. 1 steps 6-8) or apply the cosine gate and the calibration merge (Alg. 2 steps 2-15).
 // Nothing but latency: the splits are dealt to kGroups groups of D threads, so that up to 128 partials are short
 // chains of loads instead of one long one, and the results of the groups meet in LDS.
-template <typename T, int D, int kGroups>
+// kGather: the launch carries the workgroups that gather the retained rows as well, behind the merging ones.
+template <typename T, int D, int kGroups, bool kGather = false>
 __global__ __launch_bounds__(kGroups * D) void attend_finalize_kernel(FinalArgs a) {
+  if constexpr (kGather) {
+    const int item = static_cast<int>(blockIdx.x) - a.Hq;
+    if (item >= 0) {
+      constexpr int NT = kGroups * D;
+      const int blocks = (a.gather.blocks * kGatherVecs + NT - 1) / NT, g = item / blocks;
+      int off0;
+      const int n = seq_len_checked(a.row_off, blockIdx.y, a.max_len, a.total_tokens, off0);
+      gather_block<NT>(a.gather, item - g * blocks, blockIdx.y, g, a.Hkv, a.B, n, off0);
+      return;
+    }
+  }
   const int h = blockIdx.x, b = blockIdx.y, d = threadIdx.x % D;
   const int grp = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / D);
   __shared__ float red[kGroups * D / 64];

@@ -36,6 +36,7 @@ struct GatherArgs {
 };
 constexpr int kGatherCopies = 1;                       // independent copies of K and of V in flight per thread
 constexpr int kGatherVecs = 256 * kGatherCopies;       // 16-byte pieces per workgroup of 256 threads
+static_assert(kGatherCopies == 1, "a workgroup of NT threads takes NT pieces");
 
 // Pieces t0, t0 + NT, ... (kCopies of them, below `total`) of the retained rows of one (sequence, KV head).
 template <int NT, int kCopies>
@@ -68,14 +69,15 @@ __device__ __forceinline__ void gather_pieces(const GatherArgs& a, const int32_t
   }
 }
 
-// Workgroup `block` of the a.blocks (256 threads each) that gather the rows of one (sequence, KV head).
+// Workgroup `block` of those (NT threads each; a.blocks of them with 256) that gather the rows of one (sequence, KV head).
+template <int NT = 256>
 __device__ __forceinline__ void gather_block(const GatherArgs& a, int block, int b, int g, int Hkv, int B, int n, int off0) {
   const int len = min(n, B);
   const int c0 = a.cache_off[b];
   const int cap = a.cache_off[b + 1] - c0;
   if (cap < len) return;                 // capacity contract broken: write nothing
-  gather_pieces<256, kGatherCopies>(a, a.indices + (static_cast<int64_t>(b) * Hkv + g) * B,
-                                    block * kGatherVecs + static_cast<int>(threadIdx.x), len * (a.row_bytes / 16), n, n <= B,
+  gather_pieces<NT, kGatherCopies>(a, a.indices + (static_cast<int64_t>(b) * Hkv + g) * B,
+                                    block * NT + static_cast<int>(threadIdx.x), len * (a.row_bytes / 16), n, n <= B,
                                     static_cast<int64_t>(off0) * Hkv + static_cast<int64_t>(g) * n,
                                     static_cast<int64_t>(c0) * Hkv + static_cast<int64_t>(g) * cap);
 }
@@ -96,6 +98,24 @@ struct SelectArgs {
   GatherArgs gather;
   int gather_here;         // LDS variant: the workgroup also gathers the rows it has chosen
 };
+
+// Sum of tot[0 .. wave - 1] of the workgroup's waves, in every lane (one LDS read and a scan; a loop over the waves waits
+// for LDS once per wave).
+template <int NT>
+__device__ __forceinline__ uint32_t before_wave(const uint32_t* tot, int wave) {
+  static_assert(NT / 64 <= 16, "the totals of one row of lanes");
+  const int lane = threadIdx.x & 63;
+  const uint32_t v = lane < wave ? tot[lane & 15] : 0u;
+  return last_lane(wave_inclusive_scan(v));
+}
+// The same of tot[wave + 1 ..].
+template <int NT>
+__device__ __forceinline__ uint32_t after_wave(const uint32_t* tot, int wave) {
+  static_assert(NT / 64 <= 16, "the totals of one row of lanes");
+  const int lane = threadIdx.x & 63;
+  const uint32_t v = lane > wave && lane < NT / 64 ? tot[lane & 15] : 0u;
+  return last_lane(wave_inclusive_scan(v));
+}
 
 // The bin of a finished 256-bin histogram in which the count from the top reaches `remaining`;
 // updates prefix / remaining like one radix pass.  Lane l holds bins 4l..4l+3 in `hb`.  Called
@@ -152,16 +172,6 @@ __device__ __forceinline__ void clear_hist(uint32_t* hist, int words, int tid) {
   for (int t = tid; t < words / 4; t += NT) *reinterpret_cast<u32x4*>(hist + 4 * t) = zero16();
 }
 
-// Sum of tot[0 .. wave - 1] of the workgroup's waves, in every lane (one LDS read and a scan; a loop over the waves waits
-// for LDS once per wave).
-template <int NT>
-__device__ __forceinline__ uint32_t before_wave(const uint32_t* tot, int wave) {
-  static_assert(NT / 64 <= 16, "the totals of one row of lanes");
-  const int lane = threadIdx.x & 63;
-  const uint32_t v = lane < wave ? tot[lane & 15] : 0u;
-  return last_lane(wave_inclusive_scan(v));
-}
-
 // Where chunk q (16 bytes) of the staged row lies: rows of 16 chunks, rotated by exclusive or, so that both consecutive
 // chunks (staging) and chunks PER / 4 apart (windows) of sixteen neighbouring lanes are in different banks.
 __device__ __forceinline__ int select_chunk(int q) { return q ^ ((q >> 4) & 15); }
@@ -197,9 +207,7 @@ __device__ __forceinline__ uint32_t pick_digit(SelectShared& sh, const uint32_t*
   if (lane == 63) sh.wave_tot[0][wv] = inc;
   if (tid == 0) { sh.digit = 0; sh.rem = remaining; sh.in_bin = ~0u; sh.few = 0; }      // never left so by a consistent histogram
   __syncthreads();
-  const uint32_t t = lane < NT / 64 ? sh.wave_tot[0][lane & 15] : 0u;
-  const uint32_t upto = wave_inclusive_scan(t);
-  const uint32_t above = last_lane(upto) - __builtin_amdgcn_readlane(upto, wv) + last_lane(inc) - inc;
+  const uint32_t above = last_lane(inc) - inc + after_wave<NT>(sh.wave_tot[0], wv);
   if (above < remaining && remaining <= above + mine) {         // exactly one thread
     u32x4 c[kChunks];
 #pragma unroll
@@ -337,8 +345,9 @@ __device__ __forceinline__ uint32_t cut_members(const Cut& c, uint32_t gtm, uint
 //               compaction needs no pass of its own for them.
 // Nothing waits inside a kernel; every workgroup re-derives the decided digits from the finished
 // histograms.  What bounds it is the number of dependent launches (8 heads of 131072 scores are half a megabyte
-// each): four of 1024 threads, 34 us, where digits of 8 bits, a count pass and a pooling pass apart took seven
-// of 256 threads and 54 us.
+// each) and, inside them, of dependent trips to memory and LDS: four of 1024 threads, 25 us (10.6 + 4.4 + 5.6 + 10.6 = 31 us
+// while the pooling fetched its votes word by word and its taps one after the other, and the totals of the waves were
+// added up in loops; digits of 8 bits, a count pass and a pooling pass apart took seven launches of 256 threads and 54 us).
 constexpr int kWideThreads = 1024;
 constexpr int kWidePer = 8;                           // positions per thread
 constexpr int kWideSeg = kWideThreads * kWidePer;     // positions per workgroup
@@ -392,8 +401,7 @@ __device__ __forceinline__ void wide_digit(WideShared& sh, int which, int ncut, 
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
     if (c >= ncut) continue;
-    uint32_t above = last_lane(inc[c]) - inc[c];
-    for (int ww = wv + 1; ww < kWideThreads / 64; ++ww) above += sh.tot[c][ww];
+    const uint32_t above = last_lane(inc[c]) - inc[c] + after_wave<kWideThreads>(sh.tot[c], wv);
     if (above < remaining[c] && remaining[c] <= above + mine[c]) {                   // exactly one thread
       uint32_t cum = above;
       int bin = 3;
@@ -445,29 +453,61 @@ __global__ __launch_bounds__(kWideThreads) void wide_pool_kernel(WideArgs a) {
   const int lo = blockIdx.x * kWideSeg;
   if (h.n <= s.B || lo >= h.P) return;
   const int tid = threadIdx.x;
-  __shared__ float s_vote[kWideSeg + 2 * kWideHalo];
+  __shared__ __attribute__((aligned(16))) float s_vote[kWideSeg + 2 * kWideHalo + 8];
   __shared__ uint32_t s_hist[kWideBins];
   const float* vote = s.vote + h.head_tok;
-  auto vote_at = [&](int j) {
-    float val = 0.f;
-    if (j >= 0 && j < h.P)
-      for (int rb = 0; rb < s.NRB; ++rb) val += vote[rb * s.plane + j];
-    return val;
-  };
   const int half = s.pool_k / 2;
   const bool staged = half <= kWideHalo;
-  if (staged)
-    for (int t = tid; t < kWideSeg + 2 * half; t += kWideThreads) s_vote[t] = vote_at(lo - half + t);
+  float sum[kWidePer];
+#pragma unroll
+  for (int q = 0; q < kWidePer; ++q) sum[q] = 0.f;
   for (int t = tid; t < kWideBins; t += kWideThreads) s_hist[t] = 0;
-  __syncthreads();
+  if (staged) {
+    // 16 bytes per lane from the 16-byte boundary at or below the first vote of the first window (planes start 256-byte
+    // aligned), all of a thread's on their way together; vectors that hold no vote of the head are not loaded
+    const int64_t first = h.head_tok + lo - half;
+    const int shift = static_cast<int>(first & 3);
+    const float* src = s.vote + (first - shift);
+    constexpr int kVec = (kWideSeg + 2 * kWideHalo + 6 + 4 * kWideThreads - 1) / (4 * kWideThreads);
+    f32x4 tmp[kVec];
+#pragma unroll
+    for (int u = 0; u < kVec; ++u) tmp[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int count = (kWideSeg + 2 * half + shift + 3) / 4;
+    for (int rb = 0; rb < s.NRB; ++rb)
+#pragma unroll
+      for (int u = 0; u < kVec; ++u) {
+        const int v4 = tid + u * kWideThreads, j = lo - half - shift + 4 * v4;
+        if (v4 < count && j + 3 >= 0 && j < h.P) tmp[u] += *reinterpret_cast<const f32x4*>(src + rb * s.plane + 4 * v4);
+      }
+#pragma unroll
+    for (int u = 0; u < kVec; ++u) {
+      const int v4 = tid + u * kWideThreads, j = lo - half - shift + 4 * v4;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) tmp[u][x] = (j + x >= 0 && j + x < h.P) ? tmp[u][x] : 0.f;
+      if (v4 < count) *reinterpret_cast<f32x4*>(s_vote + 4 * v4) = tmp[u];
+    }
+    __syncthreads();
+    for (int d = 0; d < s.pool_k; ++d)                 // taps left to right, eight positions side by side
+#pragma unroll
+      for (int q = 0; q < kWidePer; ++q) sum[q] += s_vote[shift + tid + q * kWideThreads + d];
+  } else {
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kWidePer; ++q) {
+      const int j = lo + tid + q * kWideThreads;
+      if (j >= h.P) continue;
+      for (int i = max(j - half, 0); i <= min(j + half, h.P - 1); ++i) {
+        float val = 0.f;
+        for (int rb = 0; rb < s.NRB; ++rb) val += vote[rb * s.plane + i];
+        sum[q] += val;
+      }
+    }
+  }
 #pragma unroll
   for (int q = 0; q < kWidePer; ++q) {
-    const int t = tid + q * kWideThreads, j = lo + t;
+    const int j = lo + tid + q * kWideThreads;
     if (j >= h.P) continue;
-    float sum = 0.f;
-    if (staged) for (int d = 0; d < s.pool_k; ++d) sum += s_vote[t + d];
-    else for (int d = -half; d <= half; ++d) sum += vote_at(j + d);
-    const float sc = sum / static_cast<float>(s.pool_k);
+    const float sc = sum[q] / static_cast<float>(s.pool_k);
     s.score[h.head_tok + j] = sc;
     atomicAdd(&s_hist[__builtin_bit_cast(uint32_t, sc) >> 20], 1u);
   }
@@ -567,6 +607,19 @@ __global__ __launch_bounds__(kWideThreads) void wide_emit_kernel(WideArgs a) {
   uint32_t key[kWidePer];
 #pragma unroll
   for (int u = 0; u < kWidePer; ++u) key[u] = j0 + u < h.P ? gkey[j0 + u] : 0u;
+  // a wave per earlier segment, four bins of its last digit per lane; the first one's on their way while the digits are derived
+  const int ncut = h.all2 ? 1 : 2;
+  u32x4 bins[2];
+  uint32_t upper[2];
+  auto fetch = [&](int sg) __attribute__((always_inline)) {
+    const uint32_t* S = a.seg + (static_cast<int64_t>(h.bg) * a.NSEG + sg) * kWideSegWords;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      bins[c] = c < ncut ? ld16(S + c * 256 + 4 * lane) : zero16();
+      upper[c] = c < ncut ? S[512 + c] : 0u;
+    }
+  };
+  if (wv < seg) fetch(wv);
   __shared__ WideShared sh;
   __shared__ uint32_t s_pre[4];                        // greater1, equal1, greater2, equal2 of the earlier segments
   __shared__ uint32_t wave_tot[2][kWideThreads / 64];
@@ -578,18 +631,17 @@ __global__ __launch_bounds__(kWideThreads) void wide_emit_kernel(WideArgs a) {
   c2.all = h.all2; c2.thr = h.all2 ? 0u : prefix[1]; c2.need_eq = h.all2 ? 0u : remaining[1];
   {
     uint32_t pre[4] = {0, 0, 0, 0};
-    const int ncut = h.all2 ? 1 : 2;
-    for (int sg = wv; sg < seg; sg += kWideThreads / 64) {      // a wave per earlier segment, four bins per lane
-      const uint32_t* S = a.seg + (static_cast<int64_t>(h.bg) * a.NSEG + sg) * kWideSegWords;
-      for (int c = 0; c < ncut; ++c) {
-        const u32x4 v = ld16(S + c * 256 + 4 * lane);
+    for (int sg = wv; sg < seg; sg += kWideThreads / 64) {
+      if (sg != wv) fetch(sg);
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
         const uint32_t d3 = prefix[c] & 0xFF;
-        if (lane == 0) pre[2 * c] += S[512 + c];
+        if (lane == 0) pre[2 * c] += upper[c];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const uint32_t bin = 4 * lane + q;
-          if (bin > d3) pre[2 * c] += v[q];
-          if (bin == d3) pre[2 * c + 1] += v[q];
+          if (bin > d3) pre[2 * c] += bins[c][q];
+          if (bin == d3) pre[2 * c + 1] += bins[c][q];
         }
       }
     }
@@ -615,8 +667,7 @@ __global__ __launch_bounds__(kWideThreads) void wide_emit_kernel(WideArgs a) {
   const uint32_t inc1 = wave_inclusive_scan(cnt1), inc2 = wave_inclusive_scan(cnt2);
   if (lane == 63) { wave_tot[0][wv] = inc1; wave_tot[1][wv] = inc2; }
   __syncthreads();
-  uint32_t bef1 = inc1 - cnt1, bef2 = inc2 - cnt2;
-  for (int ww = 0; ww < wv; ++ww) { bef1 += wave_tot[0][ww]; bef2 += wave_tot[1][ww]; }
+  const uint32_t bef1 = inc1 - cnt1 + before_wave<kWideThreads>(wave_tot[0], wv), bef2 = inc2 - cnt2 + before_wave<kWideThreads>(wave_tot[1], wv);
   const uint32_t gt1 = s_pre[0] + (bef1 & 0xFFFFu), eq1 = s_pre[1] + (bef1 >> 16);
   const uint32_t gt2 = s_pre[2] + (bef2 & 0xFFFFu), eq2 = s_pre[3] + (bef2 >> 16);
   const uint32_t keepm = cut_members(c1, gtm1, eqm1, eq1, valid);

@@ -625,6 +625,15 @@ def test_decode_forms_at_their_borders(dtype, Hq, Hkv, D, batch, budget):
             H.check_decode_step(wl, bufs, x["q_dec"][t], b, report=rep)
 
 
+@pytest.mark.parametrize("dtype,D,lens,budget", [
+    ("bf16", 128, [12288, 60], 300),       # splits of 384 rows: the gather rides in the streaming pass
+    ("bf16", 128, [12289, 299], 300),      # of 512: in the launch that merges; a prompt within the budget beside it
+    ("fp32", 64, [200, 150], 260)])        # nothing to evict, no pass: in the merging launch as well
+def test_gather_in_the_pass_and_in_the_merge(dtype, D, lens, budget):
+    # 16 (sequence, KV head) pairs; 512 and 256 threads a workgroup, so that 16-byte pieces end inside one
+    run_case(small(dtype, 16, 8, D, lens, 16, budget, 5, T=1, name=f"gather_after_{lens[0]}"))
+
+
 @pytest.mark.parametrize("batch", [96, 97])
 def test_split_partials_merged_by_four_groups_or_one(batch):
     # 768 heads are the last that four groups of threads each merge, 776 the first with one group; 11 splits, so that
