@@ -99,20 +99,19 @@ float logit_scale(const calidrop_params* p) {
 }
 
 // Decode runs as one workgroup per (sequence, KV head) - one launch, no workspace - or with the rows of a pair split over
-// workgroups and a second launch that merges them.  One workgroup moves some 40 GB/s (fp32, whose products keep its
-// waves busy: 25), so what it costs is its rows, nearly twice that where the fullest of the 256 compute units has two of
+// workgroups and a second launch that merges them.  One workgroup moves some 40 GB/s, so what it costs is its rows, nearly twice that where the fullest of the 256 compute units has two of
 // them, and a share of the memory traffic of all; the split form costs its two launches and the traffic, and no less than
 // 8.8 us from the host (9.4 below: at 512 rows, two tiles for each of 8 waves, the estimate for one workgroup is high).
 // us per call, one workgroup / split: 8 pairs of 512 rows, bf16, D = 128 7.7 / 7.5 (from the host 8.2 / 8.8), of 1022 12.5 /
 // 7.5, of 2044 27.3 / 8.0; 64 pairs of 1026 18.1 / 12.7; 184 pairs of 1026 20.5 / 22.9; 296 pairs of 809 30.2 / 26.3; fp32, 8
-// pairs of 1028 43.9 / 13.3.  The constants are fitted to 638 calls (2 to 512 pairs, 90 to 4500 rows, both types and head
-// dimensions): the form taken is 0.3 % slower than the better one on average, 13 % at most.  Rows are the longest cache's.
+// pairs of 1002 29.6 / 10.2.  The constants are fitted to 730 calls (2 to 512 pairs, 90 to 4500 rows, both types and head
+// dimensions): the form taken is 0.3 % slower than the better one on average, 14 % at most.  Rows are the longest cache's.
 struct DecodeCost { float fused, row, pair_row, split, split_pair_row; };      // us; per row, per (pair, row)
 bool decode_splits(const calidrop_params* p, int max_cache_len) {
   const int64_t pairs = static_cast<int64_t>(p->batch) * p->n_kv_heads;
   if (pairs > 512) return false;
   constexpr DecodeCost kCost[2][2] = {{{3.83f, .00615f, 1.58e-5f, 6.9f, 4.24e-5f}, {3.09f, .01196f, 3.09e-5f, 7.16f, 8.54e-5f}},
-                                      {{3.43f, .01730f, 3.56e-5f, 7.6f, 8.21e-5f}, {4.60f, .03820f, 6.40e-5f, 10.4f, 1.97e-4f}}};
+                                      {{3.99f, .01229f, 3.12e-5f, 7.1f, 8.20e-5f}, {5.14f, .02457f, 6.77e-5f, 9.1f, 1.78e-4f}}};
   const DecodeCost& c = kCost[p->dtype == CALIDROP_FP32][p->head_dim == 128];
   const float rows = static_cast<float>(max_cache_len), all = rows * static_cast<float>(pairs);
   const float fused = c.fused + c.row * rows * (pairs > 256 ? 1.82f : 1.f) + c.pair_row * all;
@@ -577,19 +576,24 @@ int decode_impl(const calidrop_params* p, const void* q_t, const void* k_c, cons
     fa.c_q = c_q; fa.c_out = c_out; fa.c_lse = c_lse; fa.out = out; fa.a_lse = a_lse; fa.flags = flags;
     const int tiles = ceil_div(max_cache_len, cd::kTileRows);
     const size_t lds_per_wave = static_cast<size_t>(G) * (D + 2) * sizeof(float);
-    // 8 waves per workgroup, so that its compute unit has more rows in flight, but 4 for caches of at most 4 tiles and where the
-    // pairs fill the chip and that gains nothing: in bf16 with D = 128 (12.8 us with 4 waves, 13.0 with 8 at 512 rows; 40.5 / 42.0
-    // at 2048, where three such workgroups share a compute unit and one's merge overlaps the others' streaming), and in
-    // fp32 with D = 128 from two workgroups on a unit on (384 pairs of 506 rows 51.6 / 54.5).  Else 256 pairs of 500 rows: fp32,
-    // D = 64 18.1 / 15.4, D = 128 32.9 / 29.6, bf16, D = 64 9.5 / 8.5.
+    // 8 waves per workgroup, so that its compute unit has more rows in flight, but 4 for caches of at most 4 tiles, in fp32 (two
+    // pieces of every row in flight per lane: 8 pairs of 1002 rows, D = 128 29.6 us with 4 waves, 33.4 with 8, 512 pairs of 308
+    // 31.0 / 35.3, D = 64 15.6 / 16.6, 16.8 / 18.7) and in bf16 with D = 128 where the pairs fill the chip (12.8 / 13.0 at 512
+    // rows; 40.5 / 42.0 at 2048, where three such workgroups share a compute unit and one's merge overlaps the others'
+    // streaming; with D = 64, 256 pairs of 500 rows, 9.5 / 8.5).
     const int pairs = p->batch * p->n_kv_heads;
-    int nw = tiles <= 4 || (pairs >= 192 && D == 128 && (sizeof(T) == 2 || pairs > 256)) ? 4 : 8;
+    int nw = tiles <= 4 || sizeof(T) == 4 || (pairs >= 192 && D == 128) ? 4 : 8;
     while (nw > 4 && nw * lds_per_wave > 48 * 1024) nw /= 2;     // what a launch may use without raising the limit
     fa.xcd_blocks = (tiles >= 32 && p->batch % 8 == 0) ? 1 : 0;
     const dim3 grid(p->n_kv_heads, p->batch);
     const size_t lds = nw * lds_per_wave;
-    if (nw == 8) hipLaunchKernelGGL((cd::decode_fused_kernel<T, D, 8>), grid, dim3(512), lds, st, fa);
-    else hipLaunchKernelGGL((cd::decode_fused_kernel<T, D, 4>), grid, dim3(256), lds, st, fa);
+    if constexpr (sizeof(T) == 2) {
+      if (nw == 8) {
+        hipLaunchKernelGGL((cd::decode_fused_kernel<T, D, 8>), grid, dim3(512), lds, st, fa);
+        return launch_status("decode_fused");
+      }
+    }
+    hipLaunchKernelGGL((cd::decode_fused_kernel<T, D, 4>), grid, dim3(256), lds, st, fa);
     return launch_status("decode_fused");
   }
   cd::AttendArgs aa{};

@@ -130,13 +130,20 @@ struct AttendWave {
     }
   }
 
-  // bf16 V rows of a tile: lane (i, c) loads, for e = 4 g2 + r, the 16-byte piece i of row
-  // row0 + 16 g2 + 4 c + r (each instruction reads four whole rows, fully coalesced)
-  __device__ __forceinline__ void load_v(const T* vbase, int row0, int rows, int i, int c, u32x4 (&vf)[8]) const {
+  // V rows of a tile: lane (i, c) loads, for e = 4 g2 + r, the 16-byte piece i of row row0 + 16 g2 + 4 c + r, in fp32
+  // the pieces i and (D = 128) i + 16 (each instruction reads four whole rows or halves of rows, fully coalesced)
+  static constexpr int NVP = kBf16 ? 1 : D / 64;    // pieces of a row per lane
+  __device__ __forceinline__ void load_v(const T* vbase, int row0, int rows, int i, int c, u32x4 (&vf)[8 * NVP]) const {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const int vrow = min(row0 + 16 * (e >> 2) + 4 * c + (e & 3), rows - 1);
-      vf[e] = (i < D / 8) ? ld16_stream(vbase + static_cast<int64_t>(vrow) * D + i * 8) : zero16();
+      const T* vp = vbase + static_cast<int64_t>(vrow) * D + i * EPL;
+      if constexpr (kBf16) {
+        vf[e] = (i < D / 8) ? ld16_stream(vp) : zero16();
+      } else {
+#pragma unroll
+        for (int dh = 0; dh < NVP; ++dh) vf[e * NVP + dh] = ld16_stream(vp + dh * 64);
+      }
     }
   }
 
@@ -173,8 +180,17 @@ struct AttendWave {
     }
   }
 
-  // O^T += V^T P^T for a tile whose bf16 V rows sit in vf (as loaded by load_v)
-  __device__ __forceinline__ void pv_bf16(const u32x4 (&vf)[8], const float (&p)[2][4]) {
+  // O^T += V^T P^T for a tile whose V rows sit in vf (as loaded by load_v)
+  __device__ __forceinline__ void pv_f32(const u32x4 (&vf)[8 * NVP], const float (&p)[2][4]) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int dh = 0; dh < NVP; ++dh)
+#pragma unroll
+        for (int xx = 0; xx < 4; ++xx)
+          acc_o[dh * 4 + xx] = __builtin_amdgcn_mfma_f32_16x16x4f32(as_f32(vf[e * NVP + dh][xx]), p[e >> 2][e & 3], acc_o[dh * 4 + xx], 0, 0, 0);
+  }
+  __device__ __forceinline__ void pv_bf16(const u32x4 (&vf)[8 * NVP], const float (&p)[2][4]) {
     u32x4 pf;
     pf[0] = pack_bf16x2(p[0][0], p[0][1]);
     pf[1] = pack_bf16x2(p[0][2], p[0][3]);
@@ -236,9 +252,12 @@ struct AttendWave {
       }
     }
     for (int row0 = row_first; row0 < row_end; row0 += row_step) {
-      // V of this tile first, then K of the next tile: both in flight during the QK product
-      u32x4 vf[8];
-      if constexpr (kBf16) load_v(vbase, row0, rows, i, c, vf);
+      // V of this tile first, then K of the next tile: both in flight during the QK product.  (In fp32 V used to be fetched row by
+      // row inside the PV product, its latency in every tile: given set of 2 prompts of 60000 tokens, 8 KV heads, D = 128 192 ->
+      // 160 us, D = 64 94 -> 83; one cache of 100 rows 9.8 -> 6.9.  The registers of a second tile of both, in the decode kernel
+      // where a workgroup has a compute unit to itself, gain nothing: bf16, 8 heads of 512 rows 7.9 -> 8.3 us.)
+      u32x4 vf[8 * NVP];
+      load_v(vbase, row0, rows, i, c, vf);
       if (row0 == row_first) while_waiting();
       f32x4 acc_s[2];
       const int next0 = row0 + row_step;
@@ -263,23 +282,8 @@ struct AttendWave {
       float p[2][4];
       softmax_tile<kLogits>(acc_s, row0, row_end, skip, sl2, c, p);
       // ---- O^T += V^T P^T -----------------------------------------------------------------
-      if constexpr (kBf16) {
-        pv_bf16(vf, p);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const int vrow = min(row0 + 16 * (e >> 2) + 4 * c + (e & 3), rows - 1);
-          const float pe = p[e >> 2][e & 3];
-#pragma unroll
-          for (int dh = 0; dh < D / 64; ++dh) {
-            u32x4 v4 = ld16_stream(vbase + static_cast<int64_t>(vrow) * D + (i + 16 * dh) * 4);
-#pragma unroll
-            for (int xx = 0; xx < 4; ++xx)
-              acc_o[dh * 4 + xx] =
-                  __builtin_amdgcn_mfma_f32_16x16x4f32(as_f32(v4[xx]), pe, acc_o[dh * 4 + xx], 0, 0, 0);
-          }
-        }
-      }
+      if constexpr (kBf16) pv_bf16(vf, p);
+      else pv_f32(vf, p);
       if constexpr (!kPrefetch && !kLogits) {
         if (next0 < row_end) fetch_k(next0);
       }
