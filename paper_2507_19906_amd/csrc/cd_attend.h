@@ -203,7 +203,10 @@ struct AttendWave {
 #pragma unroll
       for (int ww = 0; ww < 4; ++ww) {
         const uint32_t lo = vf[2 * ww][xx >> 1], hi = vf[2 * ww + 1][xx >> 1];
-        af[ww] = (xx & 1) ? ((lo >> 16) | (hi & 0xFFFF0000u)) : ((lo & 0xFFFFu) | (hi << 16));
+        // the upper or the lower halves, in one byte permutation (and p packed in one conversion): a tenth of a tile's
+        // instructions, which is what few workgroups wait for (8 heads of 512 rows, D = 128 7.62 -> 7.49 us, D = 64 6.16 -> 6.03;
+        // where memory is the limit nothing; a softmax without masks in full tiles 1 % more here, 0.4 % less there)
+        af[ww] = __builtin_amdgcn_perm(hi, lo, (xx & 1) ? 0x07060302u : 0x05040100u);
       }
       mma_step<bf16_t>(acc_o[xx], af, pf);
     }
