@@ -371,7 +371,9 @@ size_t calidrop_compress_h2o_workspace_bytes(const calidrop_params* p, int32_t n
  *           CALIDROP_OPT_WRITE_SCORES in the call's params unless the prompt is longer than 32768);
  *   VOTE_PLANES float [G][total_tokens*Hkv] (H2O only): plane hh holds, packed like SCORE and for
  *           every position j < n_b, the probability mass position j received from the queries
- *           of query head hh of its group; the score is the sum of the G planes.                  */
+ *           of query head hh of its group; the score is the sum of the G planes.  In small calls the
+ *           rows of a head are shared by 2 or 4 workgroups, with a plane each ([G][2 or 4][...]; the
+ *           size of the region shows which): the score is the sum of them all.                    */
 int calidrop_compress_h2o_workspace_region(const calidrop_params* p, int32_t n_local,
                                            int64_t total_tokens, int32_t max_seq_len,
                                            int32_t region, size_t* offset, size_t* bytes);

@@ -811,9 +811,26 @@ int recal_packed_impl(const calidrop_params* p, const void* q_t, const void* k_e
   return launch_finalize<T, D>(p, fa, st, "attend_finalize(recalibrate, packed)");
 }
 
+// Shares into which the streams of a call of few workgroups are cut (blocks: 128-row blocks of all heads of the longest
+// prompt).  us for one layer in 1 -> 2 -> 4 shares: bf16, D = 128, 8 heads x 1793 rows (120 blocks) 74 -> 54 -> 45, 8 x 5000
+// (320) 169 -> 115 -> 100, 8 x 10000 (632) 364 -> 286 -> 261; 32 heads x 700 (192) 43 -> 40 -> 40, 32 x 2600 (672) 126 -> 103
+// -> 107, 32 x 10000 (2528) 964 -> 900 -> 888; 64 x 700 (384) 45 -> 45 -> 48, 64 x 1793 (960) 108 -> 104 -> 110, 64 x 5000
+// (2560) 525 -> 494 -> 494, 64 x 10000 (5056) 1774 -> 1728 -> 1732.  fp32, 8 x 1100, D = 128 (72) 196 -> 117 -> 78, 32 x 1100,
+// D = 64 (288) 136 -> 115 -> 98, 64 x 3000 (1536) 777 -> 731 -> 701.  So four shares of fp32 streams (long ones, for the
+// matrix cores run at an eighth) and of few heads, two otherwise; beyond 2560 blocks 2 to 3 % are left and the planes grow.
+constexpr int64_t kH2oSplitBlocks = 2560;
+constexpr int kH2oMaxSplits = 4;
+int64_t h2o_blocks(const calidrop_params* p, int32_t max_seq_len) {
+  return static_cast<int64_t>(ceil_div(max_seq_len, cd::h2o_block(2))) * p->batch * p->n_q_heads;
+}
+int h2o_splits(const calidrop_params* p, int32_t max_seq_len) {
+  if (h2o_blocks(p, max_seq_len) > kH2oSplitBlocks) return 1;
+  return p->dtype == CALIDROP_FP32 || p->batch * p->n_q_heads < 32 ? kH2oMaxSplits : 2;
+}
+
 struct H2oLayout {
-  size_t row_lse, vote, score, bitmap, q_last, part_o, part_ml, sel_hist, sel_cnt, total;
-  int lse_stride, W32, NSEG;
+  size_t row_part, row_lse, vote, score, bitmap, q_last, part_o, part_ml, sel_hist, sel_cnt, total;
+  int lse_stride, W32, NSEG, splits;
   SplitPlan sp;
 };
 
@@ -827,8 +844,18 @@ H2oLayout h2o_layout(const calidrop_params* p, int64_t total_tokens, int32_t max
   const size_t slots = static_cast<size_t>(p->batch) * p->n_q_heads * most_splits(p->batch * p->n_kv_heads, max_seq_len, few_kv(p));
   size_t off = 0;
   L.row_lse = off; off += round256(static_cast<size_t>(p->batch) * p->n_q_heads * L.lse_stride * sizeof(float));
-  L.vote = off;    // one plane per head of a group
-  off += round256(static_cast<size_t>(vote_plane(total_tokens, p->n_kv_heads)) * (p->n_q_heads / p->n_kv_heads) * sizeof(float));
+  L.splits = h2o_splits(p, max_seq_len);
+  L.vote = off;    // one plane per head of a group and share
+  {
+    // What splits needs, for this and any shorter prompts, so that sizes do not fall as prompts grow: a call with more than one
+    // share has at most kH2oSplitBlocks blocks, so no more than `few` tokens.
+    const int64_t few = std::min<int64_t>(total_tokens, kH2oSplitBlocks * cd::h2o_block(2) / p->n_q_heads + 1);
+    const int64_t plane = std::max(vote_plane(total_tokens, p->n_kv_heads), kH2oMaxSplits * vote_plane(few, p->n_kv_heads));
+    off += round256(static_cast<size_t>(plane) * (p->n_q_heads / p->n_kv_heads) * sizeof(float));
+    const int64_t heads = static_cast<int64_t>(p->batch) * p->n_q_heads;
+    const int64_t rows = std::min(heads * L.lse_stride, kH2oSplitBlocks * cd::h2o_block(2) + heads * 256);
+    L.row_part = off; off += round256(static_cast<size_t>(rows) * kH2oMaxSplits * sizeof(float2));
+  }
   L.score = off;   off += round256(toks * sizeof(float));
   L.bitmap = off;  off += round256(static_cast<size_t>(p->batch) * p->n_kv_heads * L.W32 * sizeof(uint32_t));
   L.q_last = off;  off += round256(static_cast<size_t>(p->batch) * p->n_q_heads * p->head_dim * sizeof(float));
@@ -862,25 +889,35 @@ int h2o_impl(const calidrop_params* p, int n_local, const void* q_full, const vo
   ha.Hq = p->n_q_heads; ha.Hkv = p->n_kv_heads; ha.G = G; ha.B = p->budget; ha.max_seq_len = max_seq_len;
   ha.lse_stride = L.lse_stride; ha.sl2 = sl2;
   ha.row_lse = reinterpret_cast<float*>(ws + L.row_lse);
+  ha.splits = L.splits; ha.row_part = reinterpret_cast<float2*>(ws + L.row_part);
   ha.vote = reinterpret_cast<float*>(ws + L.vote);
   ha.plane = vote_plane(total_tokens, p->n_kv_heads);
   ha.q_last = ws + L.q_last;
   if (!uses_lds_selection(p, n_local, 1, max_seq_len)) {
     ha.zero_words = reinterpret_cast<uint32_t*>(ws + L.sel_hist); ha.zero_count = wide_words(p);
   }
-  auto passes = [&](auto tiles) {
+  auto passes = [&](auto tiles, auto split) {
     constexpr int RT = decltype(tiles)::value;
+    constexpr bool kSplit = decltype(split)::value;
     const int nblk = ceil_div(max_seq_len, cd::h2o_block(RT));     // blocks of stationary rows (or keys)
     // always launched: it also extracts Q_{-1}, which prompts within the budget need as C_q
-    hipLaunchKernelGGL((cd::h2o_rowlse_kernel<T, D, RT>), dim3(nblk, p->batch * p->n_q_heads), dim3(256), 0, st, ha);
+    hipLaunchKernelGGL((cd::h2o_rowlse_kernel<T, D, RT, kSplit>), dim3(nblk * L.splits, p->batch * p->n_q_heads), dim3(256), 0, st, ha);
     if (int e = launch_status("h2o_rowlse")) return e;
     if (max_seq_len <= p->budget) return static_cast<int>(CALIDROP_OK);
-    hipLaunchKernelGGL((cd::h2o_votes_kernel<T, D, RT>), dim3((nblk + 1) / 2, bg, G), dim3(256), 0, st, ha);
+    if constexpr (kSplit) {
+      hipLaunchKernelGGL(cd::h2o_rowmerge_kernel, dim3(ceil_div(L.lse_stride, 256), p->batch * p->n_q_heads), dim3(256), 0, st, ha, cd::h2o_block(RT));
+      if (int e = launch_status("h2o_rowmerge")) return e;
+    }
+    const dim3 pairs((nblk + 1) / 2, bg, G * L.splits);
+    if constexpr (kSplit) hipLaunchKernelGGL((cd::h2o_shared_votes_kernel<T, D, RT>), pairs, dim3(256), 0, st, ha);
+    else hipLaunchKernelGGL((cd::h2o_votes_kernel<T, D, RT>), pairs, dim3(256), 0, st, ha);
     return launch_status("h2o_votes");
   };
+  using std::integral_constant;
   const int64_t blocks = static_cast<int64_t>(ceil_div(max_seq_len, cd::h2o_block(4))) * p->batch * p->n_q_heads;
-  if constexpr (sizeof(T) == 2) rc = blocks >= kH2oWideBlocks ? passes(std::integral_constant<int, 4>{}) : passes(std::integral_constant<int, 2>{});
-  else rc = passes(std::integral_constant<int, 2>{});
+  if (L.splits > 1) rc = passes(integral_constant<int, 2>{}, std::true_type{});
+  else if constexpr (sizeof(T) == 2) rc = blocks >= kH2oWideBlocks ? passes(integral_constant<int, 4>{}, std::false_type{}) : passes(integral_constant<int, 2>{}, std::false_type{});
+  else rc = passes(integral_constant<int, 2>{}, std::false_type{});
   if (rc) return rc;
   // selection: the votes are the scores (no pooling); the local window plays the part of the
   // observation window (always kept, not a candidate)
@@ -890,7 +927,7 @@ int h2o_impl(const calidrop_params* p, int n_local, const void* q_full, const vo
   se.gather = ga;
   se.seq_off = seq_offsets; se.total_tokens = total_tokens; se.batch = p->batch;
   se.Hkv = p->n_kv_heads; se.w = n_local; se.B = p->budget; se.max_seq_len = max_seq_len; se.W32 = L.W32;
-  se.NRB = G; se.pool_k = 1;
+  se.NRB = G * L.splits; se.pool_k = 1;
   se.vote = ha.vote; se.plane = ha.plane; se.score = reinterpret_cast<float*>(ws + L.score); se.indices = indices; se.cache_lens = cache_lens;
   se.calib = p->calib_size; se.cal_indices = cal_indices;
   se.bitmap = reinterpret_cast<uint32_t*>(ws + L.bitmap);
@@ -1324,7 +1361,7 @@ int calidrop_compress_h2o_workspace_region(const calidrop_params* p_in, int32_t 
     *bytes = static_cast<size_t>(total_tokens) * p->n_kv_heads * sizeof(float);
   } else if (region == CALIDROP_REGION_VOTE_PLANES) {
     *offset = L.vote;
-    *bytes = static_cast<size_t>(vote_plane(total_tokens, p->n_kv_heads)) * (p->n_q_heads / p->n_kv_heads) * sizeof(float);
+    *bytes = static_cast<size_t>(vote_plane(total_tokens, p->n_kv_heads)) * (p->n_q_heads / p->n_kv_heads) * L.splits * sizeof(float);
   } else {
     return fail(CALIDROP_EINVAL, "unknown workspace region %d", region);
   }

@@ -37,14 +37,28 @@ struct H2oArgs {
   int lse_stride;            // floats per (sequence, query head) in row_lse; a multiple of the row block
   float sl2;                 // scale * log2(e)
   float* row_lse;            // [batch*Hq][lse_stride], log2 units; rows >= n_b hold +inf
-  float* vote;               // [G][plane]: one plane per query head of the group, each packed like K with one float per row
+  int splits;                // workgroups that share the stream of a block of stationary rows (or pair of key blocks)
+  float2* row_part;          // splits > 1: [batch*Hq][splits][lse_stride] (max, sum) per split, merged into row_lse
+  float* vote;               // [G][splits][plane]: a plane per query head of the group and split, each packed like K with one float per row
   int64_t plane;             // floats per plane: total_tokens*Hkv rounded up to a multiple of 64
   void* q_last;              // [batch][Hq][D]: the last prompt query of every head (Q_{-1})
   uint32_t* zero_words;      // words pass 1 clears for the selection that follows, or NULL
   int64_t zero_count;
 };
 
-template <typename T, int D, int RT>
+// Row statistics of two sets of keys, a sum that is not a number kept also where no maximum is left: a row that sees such a
+// logit has log-sum-exp +inf whichever share it lies in.
+__device__ __forceinline__ void merge_rows(float& m, float& l, float m2, float l2) {
+  const float sum = l + l2;
+  merge_ml(m, l, m2, l2);
+  if (sum != sum) l = sum;
+}
+
+// Calls of few workgroups leave the chip waiting for the longest stream (the last rows see every key), so those split the
+// streams: each of `splits` workgroups takes a share of the stages; row partials are merged by a launch of their own, vote
+// shares have planes of their own, which the selection adds in a fixed order like those of the heads.  kSplit stands apart
+// so that large calls keep their registers (this pass in fp32, D = 128: 160, three workgroups on a compute unit; 184, two).
+template <typename T, int D, int RT, bool kSplit>
 __global__ __launch_bounds__(256, 2) void h2o_rowlse_kernel(H2oArgs a) {
   using KS = KeyStream<T, D>;
   constexpr int KT = KS::KT, NK = KS::NK, SK = KS::kStageKeys, EPL = KS::EPL, KD = KS::KD;
@@ -62,7 +76,8 @@ __global__ __launch_bounds__(256, 2) void h2o_rowlse_kernel(H2oArgs a) {
                   load_elem<T>(qbase, static_cast<int64_t>(n - 1) * D + threadIdx.x));
   if (n <= a.B) return;
   const int nrb = (n + BR - 1) / BR;
-  const int rbp = nrb - 1 - vx;                  // late rows (most keys) are launched first
+  const int nsplit = kSplit ? a.splits : 1, split = kSplit ? vx % nsplit : 0;
+  const int rbp = nrb - 1 - vx / nsplit;         // late rows (most keys) are launched first
   if (rbp < 0) return;
   const int i0 = rbp * BR;
   const int lane = threadIdx.x & 63, wv = wave_index();
@@ -89,10 +104,10 @@ __global__ __launch_bounds__(256, 2) void h2o_rowlse_kernel(H2oArgs a) {
   fr.init(i, c);
 
   const int key_end = min(n, i0 + BR);           // no row of the block sees a key beyond its last row
-  const int nstages = (key_end + SK - 1) / SK;
+  const int all = (key_end + SK - 1) / SK, st0 = split * all / nsplit, nstages = (split + 1) * all / nsplit;
   KeyStreamDirect<T, D> ks;
   ks.init();
-  ks.issue(kbase, 0, n, s_k[0]);
+  if (st0 < nstages) ks.issue(kbase, st0 * SK, n, s_k[st0 & 1]);
 
   // S^T tile kt of a stage: keys 16 kt .. 16 kt + 15 against this wave's rows
   auto mma_tile = [&](const char* lds, int kt, f32x4 (&acc)[RT]) __attribute__((always_inline)) {
@@ -110,7 +125,8 @@ __global__ __launch_bounds__(256, 2) void h2o_rowlse_kernel(H2oArgs a) {
   // products and exponentials of neighbouring key tiles have no branch between them and are scheduled
   // into each other.  The sum is taken against a reference m that need not be the row maximum:
   // m + log2(sum of exp2(s - m)) is the same number for any m that keeps the terms in range.  The
-  // reference is the logit of key 0 (every row sees it).
+  // reference is the logit of the first key of the workgroup's stream (every row sees it: a stage that some row
+  // does not see completely is never followed by one that all see).
   auto stage_full = [&](const char* lds, auto first) __attribute__((always_inline)) {
 #pragma unroll
     for (int kt = 0; kt < KT; ++kt) {
@@ -119,7 +135,7 @@ __global__ __launch_bounds__(256, 2) void h2o_rowlse_kernel(H2oArgs a) {
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
         if constexpr (decltype(first)::value) {
-          if (kt == 0) m[rt] = __shfl(t[rt][0] * a.sl2, i);                 // lane (i, c = 0), result 0: key 0
+          if (kt == 0) m[rt] = __shfl(t[rt][0] * a.sl2, i);                 // lane (i, c = 0), result 0: first key
         }
         const float nm = -m[rt];
         l[rt] += (fast_exp2(fmaf(t[rt][0], a.sl2, nm)) + fast_exp2(fmaf(t[rt][1], a.sl2, nm))) +
@@ -156,7 +172,7 @@ __global__ __launch_bounds__(256, 2) void h2o_rowlse_kernel(H2oArgs a) {
       float l_old[RT];
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) l_old[rt] = l[rt];
-      if (key0 == 0) stage_full(lds, std::true_type{});
+      if (key0 == st0 * SK) stage_full(lds, std::true_type{});
       else stage_full(lds, std::false_type{});
       // a sum that outgrew 2^64: the stage is redone against its running maximum
       bool big = false;
@@ -179,7 +195,7 @@ __global__ __launch_bounds__(256, 2) void h2o_rowlse_kernel(H2oArgs a) {
     compute(cur, st * SK);
   };
   operands_ready();
-  for (int st = 0; st < nstages; ++st) {
+  for (int st = st0; st < nstages; ++st) {
     stage_barrier();
     step(st, s_k[st & 1], s_k[(st + 1) & 1]);
   }
@@ -187,31 +203,51 @@ __global__ __launch_bounds__(256, 2) void h2o_rowlse_kernel(H2oArgs a) {
   // merge the lanes that hold the same row (different keys); padding rows get +inf so that
   // pass 2 turns them into probability 0
   float* out = a.row_lse + static_cast<int64_t>(b * a.Hq + hq) * a.lse_stride;
+  float2* part = kSplit ? a.row_part + (static_cast<int64_t>(b * a.Hq + hq) * nsplit + split) * a.lse_stride : nullptr;
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
-    merge_ml(m[rt], l[rt], __shfl_xor(m[rt], 16), __shfl_xor(l[rt], 16));
-    merge_ml(m[rt], l[rt], __shfl_xor(m[rt], 32), __shfl_xor(l[rt], 32));
+    merge_rows(m[rt], l[rt], __shfl_xor(m[rt], 16), __shfl_xor(l[rt], 16));
+    merge_rows(m[rt], l[rt], __shfl_xor(m[rt], 32), __shfl_xor(l[rt], 32));
     const int row = wrow0 + rt * 16 + i;
-    if (c == 0 && row < a.lse_stride) out[row] = (row < n && l[rt] > 0.f) ? m[rt] + fast_log2(l[rt]) : INFINITY;
+    if (c == 0 && row < a.lse_stride) {
+      if constexpr (kSplit) part[row] = make_float2(m[rt], l[rt]);
+      else out[row] = (row < n && l[rt] > 0.f) ? m[rt] + fast_log2(l[rt]) : INFINITY;
+    }
   }
+}
+
+// The row partials of a call whose streams are split, one thread per row up to the end of its last block.
+__global__ __launch_bounds__(256) void h2o_rowmerge_kernel(H2oArgs a, int block_rows) {
+  const int row = blockIdx.x * 256 + threadIdx.x, head = blockIdx.y, b = head / a.Hq;
+  int off0;
+  const int n = seq_len_checked(a.seq_off, b, a.max_seq_len, a.total_tokens, off0);
+  if (n <= a.B || row >= min((n + block_rows - 1) / block_rows * block_rows, a.lse_stride)) return;
+  const float2* part = a.row_part + static_cast<int64_t>(head) * a.splits * a.lse_stride + row;
+  float m = -INFINITY, l = 0.f;
+  for (int s = 0; s < a.splits; ++s) {
+    const float2 v = part[static_cast<int64_t>(s) * a.lse_stride];
+    merge_rows(m, l, v.x, v.y);
+  }
+  a.row_lse[static_cast<int64_t>(head) * a.lse_stride + row] = (row < n && l > 0.f) ? m + fast_log2(l) : INFINITY;
 }
 
 // fp32 has to fit three workgroups on a compute unit (168 registers a lane; with 184 two fit, and 2 prompts of 2584
 // tokens, 32 heads, D = 128, took 599 us instead of 515): the addresses of the row stream are therefore worked out anew
 // for every stage - hidden from the compiler, which would keep them in registers or, short of those, in memory - a
 // dozen instructions beside 256 matrix products (now 510 us).
-template <typename T, int D, int RT>
-__global__ __launch_bounds__(256, sizeof(T) == 4 ? 3 : 2) void h2o_votes_kernel(H2oArgs a) {
+template <typename T, int D, int RT, bool kSplit>
+__device__ __forceinline__ void h2o_votes(const H2oArgs& a) {
   using KS = KeyStream<T, D>;
   constexpr int KT = KS::KT, NK = KS::NK, SK = KS::kStageKeys, EPL = KS::EPL, KD = KS::KD;
   constexpr int WR = 16 * RT, BR = 4 * WR;
   // grid: x = pair of key blocks (block x and its mirror nblk-1-x: early keys are seen by many
   // rows, late keys by few, so every workgroup gets the same amount of work), y = (sequence, KV
-  // head), z = query head of the group; each query head writes its own plane of votes, which
+  // head), z = query head of the group and share of its rows; each writes its own plane of votes, which
   // the selection adds up in a fixed order.
-  int vx, vh;                                    // block pair and ((sequence, KV head), head in group) of this workgroup
+  int vx, vh;                                    // block pair and ((sequence, KV head), (head in group, share)) of this workgroup
   xcd_head_major(vx, vh);
-  const int bg = vh / static_cast<int>(gridDim.z), hh = vh % static_cast<int>(gridDim.z);   // a group's heads side by side
+  const int bg = vh / static_cast<int>(gridDim.z), pl = vh % static_cast<int>(gridDim.z);   // a group's heads side by side
+  const int nsplit = kSplit ? a.splits : 1, hh = pl / nsplit, split = pl - hh * nsplit;
   const int g = bg % a.Hkv, b = bg / a.Hkv;
   int off0;
   const int n = seq_len_checked(a.seq_off, b, a.max_seq_len, a.total_tokens, off0);
@@ -224,7 +260,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 3 : 2) void h2o_votes_kernel(
   const int hq = g * a.G + hh;
   const T* qbase = static_cast<const T*>(a.q_full) + (static_cast<int64_t>(off0) * a.Hq + static_cast<int64_t>(hq) * n) * D;
   const float* lse_row = a.row_lse + static_cast<int64_t>(b * a.Hq + hq) * a.lse_stride;
-  float* vote = a.vote + static_cast<int64_t>(hh) * a.plane + head_tok;
+  float* vote = a.vote + static_cast<int64_t>(pl) * a.plane + head_tok;
 
   __shared__ __attribute__((aligned(16))) char s_q[2][KS::kStageBytes];
   __shared__ __attribute__((aligned(16))) float s_z[2][64];      // row log-sum-exp of the staged rows
@@ -253,7 +289,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 3 : 2) void h2o_votes_kernel(
     for (int rt = 0; rt < RT; ++rt) v[rt] = 0.f;
 
     // streamed rows: j0 .. n-1 of this query head, SK per stage, with their log-sum-exp
-    const int nstages = (n - j0 + SK - 1) / SK;
+    const int all = (n - j0 + SK - 1) / SK, st0 = split * all / nsplit, nstages = (split + 1) * all / nsplit;
     auto issue = [&](int st, char* rows, float* z) __attribute__((always_inline)) {   // rows and their log-sum-exp, straight into LDS
       const int q0 = j0 + st * SK;
       uint32_t tid = threadIdx.x;
@@ -264,7 +300,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 3 : 2) void h2o_votes_kernel(
       if (tid < SK) load_to_lds4(lse_row + q0 + tid, z);
     };
     __syncthreads();                               // the previous job is done with the buffers
-    issue(0, s_q[0], s_z[0]);
+    if (st0 < nstages) issue(st0, s_q[st0 & 1], s_z[st0 & 1]);
 
     // one stage; with kFull every row sees every key of the wave and the stage is one straight run of
     // code, in which the exponentials of a row tile are scheduled into the products of the next
@@ -308,7 +344,7 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 3 : 2) void h2o_votes_kernel(
       compute(cur, z, st);
     };
     operands_ready();
-    for (int st = 0; st < nstages; ++st) {
+    for (int st = st0; st < nstages; ++st) {
       const int cb = st & 1, ob = cb ^ 1;
       stage_barrier();
       step(st, s_q[cb], s_q[ob], s_z[cb], s_z[ob]);
@@ -322,5 +358,10 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 ? 3 : 2) void h2o_votes_kernel(
     }
   }
 }
+
+template <typename T, int D, int RT>
+__global__ __launch_bounds__(256, sizeof(T) == 4 ? 3 : 2) void h2o_votes_kernel(H2oArgs a) { h2o_votes<T, D, RT, false>(a); }
+template <typename T, int D, int RT>
+__global__ __launch_bounds__(256, sizeof(T) == 4 ? 3 : 2) void h2o_shared_votes_kernel(H2oArgs a) { h2o_votes<T, D, RT, true>(a); }
 
 }  // namespace cd

@@ -115,6 +115,35 @@ def test_h2o_strategy(wl, n_local):
     print(wl.name, rep, flush=True)
 
 
+@pytest.mark.parametrize("wl,shares", [
+    # streams whole, in two and in four shares, at the edges of the 128-row blocks and of the stages (64 rows, 128 at D = 64; fp32
+    # half); the shares of the first blocks are partly empty.  2560 blocks of the longest prompt are the most that are shared.
+    (small("bf16", 32, 8, 128, [257, 127, 128, 129, 256] + [50] * 22, 16, 60, 1, T=0, name="bf16_whole"), 1),
+    (small("bf16", 32, 8, 128, [257, 127, 128, 129, 256] + [50] * 21, 16, 60, 1, T=0, name="bf16_two"), 2),
+    (small("bf16", 31, 31, 64, [65], 16, 60, 1, T=0, name="bf16_d64_four_one_block"), 4),
+    (small("bf16", 32, 8, 64, [641], 16, 60, 1, T=0, name="bf16_d64_two"), 2),
+    (small("fp32", 32, 8, 64, [257, 63, 64, 65, 128] + [50] * 22, 16, 60, 1, T=0, name="fp32_whole"), 1),
+    (small("fp32", 32, 8, 128, [257, 63, 64, 65, 128], 16, 60, 1, T=0, name="fp32_four"), 4),
+], ids=lambda v: v.name if hasattr(v, "name") else str(v))
+def test_h2o_streams_whole_and_in_shares(wl, shares):
+    x = to_dev(synth.make_inputs(wl, 64))
+    q_full = synth.full_queries(wl, x, 64, DEV)
+    bufs = cd.CompressBuffers(H.params_for(wl), wl.seq_lens, DEV)
+    bufs.compress_h2o(q_full, x["k"], x["v"], x["seq_offsets"])
+    torch.cuda.synchronize()
+    floats = -(-sum(wl.seq_lens) * wl.n_kv_heads // 64) * 64          # a plane is padded to 64 floats
+    assert bufs.h2o_region(cd.REGION_VOTE_PLANES).numel() == floats * wl.group * shares
+    check_h2o(wl, x, q_full, bufs, 0, {})
+    # a key that is not a number gives every row that sees it +inf, whichever share it lies in and also as that share's only key
+    n, at = wl.seq_lens[0], wl.seq_lens[0] - 1
+    for key in (at, at // 64 * 64):
+        k = x["k"].clone()
+        synth.seq_view(k, wl, 0)[:, key] = float("nan")
+        bufs.compress_h2o(q_full, k, x["v"], x["seq_offsets"])
+        lse = bufs.h2o_region(cd.REGION_ROW_LSE).view(wl.batch, wl.n_q_heads, -1)[0].cpu()
+        assert torch.isposinf(lse[:, key:n]).all() and torch.isfinite(lse[:, :key]).all()
+
+
 def test_h2o_is_deterministic():
     wl = small("bf16", 8, 2, 128, [1500], 16, 128, 1, T=1, name="h2o_det")
     x = to_dev(synth.make_inputs(wl, 62))
