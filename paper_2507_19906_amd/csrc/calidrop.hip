@@ -101,7 +101,7 @@ float logit_scale(const calidrop_params* p) {
 // Decode runs as one workgroup per (sequence, KV head) - one launch, no workspace - or with the rows of a pair split over
 // workgroups and a second launch that merges them.  One workgroup moves some 40 GB/s, so what it costs is its rows, nearly twice that where the fullest of the 256 compute units has two of
 // them, and a share of the memory traffic of all; the split form costs its two launches and the traffic, and no less than
-// 8.8 us from the host (9.4 below: at 512 rows, two tiles for each of 8 waves, the estimate for one workgroup is high).
+// 8 to 9.3 us from the host, process by process (9.4 below: at 512 rows, two tiles for each of 8 waves, the estimate for one workgroup is high).
 // us per call, one workgroup / split: 8 pairs of 512 rows, bf16, D = 128 7.7 / 7.5 (from the host 8.2 / 8.8), of 1022 12.5 /
 // 7.5, of 2044 27.3 / 8.0; 64 pairs of 1026 18.1 / 12.7; 184 pairs of 1026 20.5 / 22.9; 296 pairs of 809 30.2 / 26.3; fp32, 8
 // pairs of 1002 29.6 / 10.2.  The constants are fitted to 730 calls (2 to 512 pairs, 90 to 4500 rows, both types and head

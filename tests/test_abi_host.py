@@ -7,6 +7,7 @@ import re
 import subprocess
 
 import pytest
+import torch
 
 from paper_2507_19906_amd import binding as cd
 
@@ -434,3 +435,20 @@ def test_public_headers_are_plain_c99(tmp_path):
     res = subprocess.run([gcc, "-std=c99", "-Wall", "-Wextra", "-Werror", "-pedantic", "-I", os.path.join(ROOT, "include"),
                           "-fsyntax-only", str(src)], capture_output=True, text=True)
     assert res.returncode == 0, res.stderr
+
+
+@pytest.mark.parametrize("absent", [(), ("cache_offsets",), ("a_lse", "flags"), ("cache_offsets", "a_lse", "flags", "workspace")])
+@pytest.mark.parametrize("as_ints", [False, True])
+def test_decode_marshals_tensors_addresses_and_nothing_alike(absent, as_ints, monkeypatch):
+    names = ["q_t", "k_c", "v_c", "cache_offsets", "cache_lens", "c_q", "c_out", "c_lse", "out", "a_lse", "flags", "workspace"]
+    given = {k: None if k in absent else torch.zeros(8) for k in names}
+    want = {k: None if t is None else t.data_ptr() for k, t in given.items()}
+    size = 0 if given["workspace"] is None else 32
+    seen = []
+    fake = type("Lib", (), {"calidrop_decode": staticmethod(lambda *a: seen.append(a) or cd.OK)})
+    monkeypatch.setattr(cd, "_lib", fake)
+    args = {k: want[k] if as_ints and k != "workspace" else given[k] for k in names}
+    cd.calidrop_decode(cd.Params(), max_cache_len=77, stream=5, **args)
+    (got,) = seen
+    w = [want[k] for k in names]
+    assert list(got[1:]) == w[:5] + [77] + w[5:] + [size, 5]
