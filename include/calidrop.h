@@ -226,6 +226,10 @@ int calidrop_compress_with_lse(const calidrop_params* p, const void* q_win, cons
  * NULL); flags optional out [batch][Hq] uint8 (may be NULL); workspace >=
  * calidrop_decode_workspace_bytes(p, max_cache_len) bytes, 256-byte aligned.
  * A sequence with cache_lens[b] = 0 yields out = 0 and a_lse = -inf.
+ * The step has two forms: one workgroup per (sequence, KV head), or the rows of each spread over several and
+ * merged (partials in the workspace).  Which one is shorter depends on the live rows, which only the device
+ * knows; the longest cache is taken to hold params.budget rows, which decode uses for nothing else, so a
+ * caller whose caches have grown (or hold fewer) may say so there.
  */
 int calidrop_decode(const calidrop_params* p, const void* q_t, const void* k_c, const void* v_c,
                     const int32_t* cache_offsets, const int32_t* cache_lens,
@@ -239,7 +243,7 @@ int calidrop_decode(const calidrop_params* p, const void* q_t, const void* k_c, 
  *
  * Same arguments (minus workspace / workspace_bytes), same validation, same kernels and bit-identical
  * results.  The scratch of the call - the per-split partial outputs of the form of the step that spreads
- * a long cache over several workgroups - lives in a fixed array of CALIDROP_STATIC_SCRATCH_BYTES of
+ * a cache over several workgroups - lives in a fixed array of CALIDROP_STATIC_SCRATCH_BYTES of
  * device memory inside the library, one copy per GPU, held from the library's load until the process
  * ends.  The call allocates nothing and frees nothing.
  *   - A call whose scratch need, calidrop_decode_workspace_bytes(p, max_cache_len), exceeds

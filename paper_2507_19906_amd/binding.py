@@ -496,15 +496,21 @@ class CompressBuffers:
             calidrop_compress_workspace_bytes(p, self.total_tokens, self.max_seq_len),
             dtype=torch.uint8, device=device)
         self.max_cache_len = cap
+        self._compressed()
         self.ws_decode = torch.empty(calidrop_decode_workspace_bytes(p, cap), dtype=torch.uint8,
                                      device=device)
         self.out = torch.zeros((nb, Hq, D), dtype=dt, device=device)
         self.a_lse = torch.zeros((nb, Hq), dtype=torch.float32, device=device)
         self.flags = torch.zeros((nb, Hq), dtype=torch.uint8, device=device)
 
+    def _compressed(self):
+        # live rows of the longest cache as far as the host knows: what compress leaves, plus one per append
+        self.live_rows = min(self.p.budget, self.max_seq_len)
+
     def compress(self, q_win, k, v, seq_offsets, q_cal=None, stream=None, win_lse=None):
         """win_lse: [batch][Hq][w] fp32 log-sum-exp of the window rows from the caller's prefill
         attention (natural log); None = the library computes it."""
+        self._compressed()
         if win_lse is None:
             calidrop_compress(self.p, q_win, k, v, seq_offsets, self.total_tokens, self.max_seq_len,
                               q_cal, self.k_c, self.v_c, self.cache_offsets, self.cache_lens,
@@ -518,6 +524,7 @@ class CompressBuffers:
 
     def compress_given(self, q_cal, k, v, seq_offsets, stream=None):
         """Alg. 1 steps 4-8 for the retained lists already in self.indices."""
+        self._compressed()
         if getattr(self, "ws_given", None) is None:
             self.ws_given = torch.empty(calidrop_compress_given_workspace_bytes(self.p, self.max_seq_len),
                                         dtype=torch.uint8, device=self.out.device)
@@ -527,6 +534,7 @@ class CompressBuffers:
 
     def compress_h2o(self, q_full, k, v, seq_offsets, n_local=0, stream=None):
         """Alg. 1 with H2O as the eviction strategy; the workspace (self.ws_h2o) keeps the votes."""
+        self._compressed()
         if getattr(self, "ws_h2o", None) is None:
             self.ws_h2o = torch.empty(
                 calidrop_compress_h2o_workspace_bytes(self.p, n_local, self.total_tokens, self.max_seq_len),
@@ -553,11 +561,18 @@ class CompressBuffers:
         if not pass_offsets and (mcl != self.cap or not self.uniform):
             raise ValueError("the offsets can only be left out when every capacity equals max_cache_len")
         offs = self.cache_offsets if pass_offsets else None
-        calidrop_decode(self.p, q_t, self.k_c, self.v_c, offs, self.cache_lens, mcl, self.c_q, self.c_out,
+        p = self.p
+        if self.live_rows != p.budget:
+            # the library takes the budget for the rows the longest cache holds when it chooses between two forms of the step
+            # (which give the same result): 8 KV heads of 1500 appended rows 19 us as one workgroup each, 8 split
+            p = Params.from_buffer_copy(p)
+            p.budget = min(max(self.live_rows, p.window + 1), 1 << 24)
+        calidrop_decode(p, q_t, self.k_c, self.v_c, offs, self.cache_lens, mcl, self.c_q, self.c_out,
                         self.c_lse, self.out, self.a_lse, self.flags, self.ws_decode, stream)
 
     def append(self, k_new, v_new, stream=None):
         """Append the K/V rows of the token just generated ([batch][Hkv][D]) to every sequence."""
+        self.live_rows = min(self.live_rows + 1, self.cap)
         calidrop_append(self.p, k_new, v_new, self.k_c, self.v_c, self.cache_offsets, self.cache_lens, stream)
 
     def recalibrate(self, q_t, k, v, seq_offsets, stream=None):

@@ -99,23 +99,33 @@ float logit_scale(const calidrop_params* p) {
 }
 
 // Decode runs as one workgroup per (sequence, KV head) - one launch, no workspace - or with the rows of a pair split over
-// workgroups and a second launch that merges them.  One workgroup moves some 40 GB/s, so what it costs is its rows, nearly twice that where the fullest of the 256 compute units has two of
-// them, and a share of the memory traffic of all; the split form costs its two launches and the traffic, and no less than
-// 8 to 9.3 us from the host, process by process (9.4 below: at 512 rows, two tiles for each of 8 waves, the estimate for one workgroup is high).
-// us per call, one workgroup / split: 8 pairs of 512 rows, bf16, D = 128 7.7 / 7.5 (from the host 8.2 / 8.8), of 1022 12.5 /
-// 7.5, of 2044 27.3 / 8.0; 64 pairs of 1026 18.1 / 12.7; 184 pairs of 1026 20.5 / 22.9; 296 pairs of 809 30.2 / 26.3; fp32, 8
-// pairs of 1002 29.6 / 10.2.  The constants are fitted to 730 calls (2 to 512 pairs, 90 to 4500 rows, both types and head
-// dimensions): the form taken is 0.3 % slower than the better one on average, 14 % at most.  Rows are the longest cache's.
-struct DecodeCost { float fused, row, pair_row, split, split_pair_row; };      // us; per row, per (pair, row)
+// workgroups and a second launch that merges them.
+// One workgroup moves some 40 GB/s, so what it costs is its rows, nearly twice that where the fullest of the 256 compute units
+// has two of them, and a share of the memory traffic of all.  The split form costs its two launches, the traffic and the
+// workgroups whose rows hold nothing yet, and no less than 8 to 9.3 us from the host, process by process (9.4 below: at 512
+// rows, two tiles for each of 8 waves, the estimate for one workgroup is high).
+// Examples, us per call, one workgroup / split: 8 pairs of 512 rows, bf16, D = 128 7.7 / 7.5 (from the host 8.2 / 8.8), of
+// 1022 12.5 / 7.5, of 2044 27.3 / 8.0; 64 pairs of 1026 18.1 / 12.7; 184 pairs of 1026 20.5 / 22.9; 296 pairs of 809 30.2 /
+// 26.3; fp32, 8 pairs of 1002 29.6 / 10.2.
+// Both follow the rows that live, which only the device knows, and max_cache_len may be far above them: with room for 2048
+// rows, 64 pairs of 200 live ones take 6.0 in one workgroup and 10.5 split, 184 pairs in fp32 12.0 and 25.8.  The longest cache
+// is therefore taken to hold `budget` rows, what a compressed prompt starts with; from there on the split form gains on the
+// other with every row.  Few pairs with room for more than 2048 rows are priced full: one workgroup would take 25 to 70 us for
+// what the split form does in 8 to 30, and loses up to 4 while it is empty.
+struct DecodeCost { float fused, row, pair_row, split, split_pair_row, split_room; };      // us; per row, per (pair, row)
+int live_rows(const calidrop_params* p, int max_cache_len) { return std::min(p->budget, max_cache_len); }
 bool decode_splits(const calidrop_params* p, int max_cache_len) {
   const int64_t pairs = static_cast<int64_t>(p->batch) * p->n_kv_heads;
   if (pairs > 512) return false;
-  constexpr DecodeCost kCost[2][2] = {{{3.83f, .00615f, 1.58e-5f, 6.9f, 4.24e-5f}, {3.09f, .01196f, 3.09e-5f, 7.16f, 8.54e-5f}},
-                                      {{3.99f, .01229f, 3.12e-5f, 7.1f, 8.20e-5f}, {5.14f, .02457f, 6.77e-5f, 9.1f, 1.78e-4f}}};
+  constexpr DecodeCost kCost[2][2] = {
+      {{3.83f, .00615f, 1.58e-5f, 6.9f, 4.24e-5f, 4.05e-6f}, {3.09f, .01196f, 3.09e-5f, 7.16f, 8.54e-5f, 5.48e-6f}},
+      {{3.99f, .01229f, 3.12e-5f, 7.1f, 8.20e-5f, 6.09e-6f}, {5.14f, .02457f, 6.77e-5f, 9.1f, 1.78e-4f, 1.15e-5f}}};
   const DecodeCost& c = kCost[p->dtype == CALIDROP_FP32][p->head_dim == 128];
-  const float rows = static_cast<float>(max_cache_len), all = rows * static_cast<float>(pairs);
+  const bool priced_full = pairs < 192 && max_cache_len > 2048;
+  const float rows = static_cast<float>(priced_full ? max_cache_len : live_rows(p, max_cache_len));
+  const float all = rows * static_cast<float>(pairs), room = static_cast<float>(max_cache_len) * static_cast<float>(pairs) - all;
   const float fused = c.fused + c.row * rows * (pairs > 256 ? 1.82f : 1.f) + c.pair_row * all;
-  return std::max(9.4f, c.split + c.split_pair_row * all) < fused;
+  return std::max(9.4f, c.split + c.split_pair_row * all + c.split_room * room) < fused;
 }
 
 // How the rows of a streaming-attention pass are split over workgroups.
@@ -581,8 +591,11 @@ int decode_impl(const calidrop_params* p, const void* q_t, const void* k_c, cons
     // 31.0 / 35.3, D = 64 15.6 / 16.6, 16.8 / 18.7) and in bf16 with D = 128 where the pairs fill the chip (12.8 / 13.0 at 512
     // rows; 40.5 / 42.0 at 2048, where three such workgroups share a compute unit and one's merge overlaps the others'
     // streaming; with D = 64, 256 pairs of 500 rows, 9.5 / 8.5).
+    // Where the pairs fill the chip it is the rows that live which count: 1024 pairs of 64 rows, D = 64, with room for 512, 8.6
+    // with 4 waves, 9.7 with 8.
     const int pairs = p->batch * p->n_kv_heads;
-    int nw = tiles <= 4 || sizeof(T) == 4 || (pairs >= 192 && D == 128) ? 4 : 8;
+    const int held = pairs < 192 ? tiles : ceil_div(live_rows(p, max_cache_len), cd::kTileRows);
+    int nw = held <= 4 || sizeof(T) == 4 || (pairs >= 192 && D == 128) ? 4 : 8;
     while (nw > 4 && nw * lds_per_wave > 48 * 1024) nw /= 2;     // what a launch may use without raising the limit
     fa.xcd_blocks = (tiles >= 32 && p->batch % 8 == 0) ? 1 : 0;
     const dim3 grid(p->n_kv_heads, p->batch);

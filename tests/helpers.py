@@ -2,6 +2,8 @@
 compare with the stated tolerances and the tie-band protocol for retained indices."""
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 import torch
 
@@ -28,6 +30,36 @@ def params_for(wl: synth.Workload, **over) -> cd.Params:
               theta1=wl.theta1, theta2=wl.theta2)
     kw.update(over)
     return cd.make_params(**kw)
+
+
+class _Dim3(ctypes.Structure):
+    _fields_ = [("x", ctypes.c_uint32), ("y", ctypes.c_uint32), ("z", ctypes.c_uint32)]
+
+
+class _KernelNode(ctypes.Structure):                      # hipKernelNodeParams
+    _fields_ = [("block", _Dim3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", _Dim3),
+                ("params", ctypes.c_void_p), ("lds", ctypes.c_uint32)]
+
+
+def captured_launches(call):
+    """(grid x, y, z, threads) of every kernel `call` enqueues, in order: read from a graph it is captured into, which
+    is never run."""
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        call()
+    hip = ctypes.CDLL("libamdhip64.so.7")                 # the one that is loaded
+    handle, n = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(handle, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(handle, nodes, ctypes.byref(n)) == 0
+    launches = []
+    for node in nodes[:n.value]:
+        kind, par = ctypes.c_int(), _KernelNode()
+        assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0 and kind.value == 0      # a kernel
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(par)) == 0
+        launches.append((par.grid.x, par.grid.y, par.grid.z, par.block.x))
+    return launches
 
 
 def to64(t: torch.Tensor) -> np.ndarray:

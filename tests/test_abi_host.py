@@ -452,3 +452,35 @@ def test_decode_marshals_tensors_addresses_and_nothing_alike(absent, as_ints, mo
     (got,) = seen
     w = [want[k] for k in names]
     assert list(got[1:]) == w[:5] + [77] + w[5:] + [size, 5]
+
+
+def test_decode_is_told_how_many_rows_live(monkeypatch):
+    # params.budget of the decode call: what a compressed cache holds at least, as far as the host knows
+    p = good(batch=2, budget=300)
+    bufs = cd.CompressBuffers(p, [1000, 200], "cpu", extra_capacity=10)
+    short = cd.CompressBuffers(p, [150, 10], "cpu", extra_capacity=10)
+    tiny = cd.CompressBuffers(p, [5, 5], "cpu")
+    seen = []
+    fake = type("Lib", (), {name: staticmethod(lambda par, *a, n=name: seen.append((n, par._obj.budget, par._obj.theta1)) or cd.OK)
+                            for name in ("calidrop_decode", "calidrop_append", "calidrop_compress")})
+    monkeypatch.setattr(cd, "_lib", fake)
+    q = torch.zeros(2, 32, 128, dtype=torch.bfloat16)
+
+    def told(b):
+        seen.clear()
+        b.decode(q, stream=5)
+        return seen[-1][1]
+
+    assert told(bufs) == 300 and told(short) == 150
+    for _ in range(3):
+        bufs.append(q, q, stream=5)
+        short.append(q, q, stream=5)
+    assert told(bufs) == 303 and told(short) == 153
+    p.theta1 = 0.25                                       # whatever else the caller sets later still arrives
+    assert told(bufs) == 303 and seen[-1][2] == 0.25
+    for _ in range(9):
+        bufs.append(q, q, stream=5)
+    assert told(bufs) == 310                              # full
+    bufs.compress(q, q, q, q, stream=5)
+    assert told(bufs) == 300 and p.budget == 300
+    assert told(tiny) == p.window + 1                     # a budget within the window would be refused

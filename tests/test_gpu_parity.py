@@ -625,6 +625,43 @@ def test_decode_forms_at_their_borders(dtype, Hq, Hkv, D, batch, budget):
             H.check_decode_step(wl, bufs, x["q_dec"][t], b, report=rep)
 
 
+@pytest.mark.parametrize("dtype,Hq,Hkv,D,batch,budget,room,appended,launches", [
+    ("bf16", 32, 8, 128, 8, 200, 824, 0, 1),       # 64 pairs, 200 of 1024 rows live: 6.0 us in one workgroup each, 9.1 split
+    ("bf16", 32, 8, 128, 1, 200, 1848, 0, 1),      # 8 pairs, 200 of 2048: 5.2 / 7.4
+    ("bf16", 16, 4, 64, 16, 200, 1848, 0, 1),      # 64 pairs, D = 64: 5.3 / 9.3
+    ("fp32", 8, 2, 64, 32, 200, 824, 0, 1),        # fp32: 7.0 / 11.7
+    ("bf16", 32, 8, 128, 1, 400, 800, 0, 1),       # 8 pairs: as compressed ...
+    ("bf16", 32, 8, 128, 1, 400, 800, 600, 2),     # ... and grown to 1000 rows: 12.5 / 7.5
+    ("bf16", 32, 8, 128, 1, 1500, 100, 0, 1),      # prompts of 100 tokens below the budget (lens): 100 of 1600 rows live
+    ("bf16", 32, 8, 128, 1, 200, 3000, 0, 2)])     # 8 pairs with room beyond 2048 rows
+def test_decode_form_follows_the_rows_that_live(dtype, Hq, Hkv, D, batch, budget, room, appended, launches):
+    lens = [100] if budget == 1500 else [budget + 1 + b % 7 for b in range(batch)]
+    wl = small(dtype, Hq, Hkv, D, lens, 16, budget, 5, T=1, name=f"room_{budget}+{room}")
+    x = to_dev(synth.make_inputs(wl, 58))
+    bufs = H.gpu_compress(wl, x, extra_capacity=room)
+    rows = torch.randn((2, batch, Hkv, D), generator=torch.Generator().manual_seed(3)).to(bufs.out.dtype).to(DEV)
+    for _ in range(appended):
+        bufs.append(rows[0], rows[1])
+    assert len(H.captured_launches(lambda: bufs.decode(x["q_dec"][0]))) == launches
+    bufs.decode(x["q_dec"][0])
+    torch.cuda.synchronize()
+    for b in {0, batch - 1}:
+        H.check_decode_step(wl, bufs, x["q_dec"][0], b)
+
+
+@pytest.mark.parametrize("D,budget,threads", [(64, 128, 256), (64, 129, 512), (128, 129, 256)])
+def test_waves_of_many_short_caches_with_room(D, budget, threads):
+    # 512 pairs with room for 400 rows more: D = 64 has 4 waves for up to 128 live rows, 8 beyond
+    wl = small("bf16", 8, 4, D, [budget + 1 + b % 5 for b in range(128)], 16, budget, 5, T=1, name=f"many_room_{budget}")
+    x = to_dev(synth.make_inputs(wl, 59))
+    bufs = H.gpu_compress(wl, x, extra_capacity=400)
+    assert H.captured_launches(lambda: bufs.decode(x["q_dec"][0])) == [(4, 128, 1, threads)]
+    bufs.decode(x["q_dec"][0])
+    torch.cuda.synchronize()
+    for b in (0, 127):
+        H.check_decode_step(wl, bufs, x["q_dec"][0], b)
+
+
 @pytest.mark.parametrize("dtype,D,lens,budget", [
     ("bf16", 128, [12288, 60], 300),       # splits of 384 rows: the gather rides in the streaming pass
     ("bf16", 128, [12289, 299], 300),      # of 512: in the launch that merges; a prompt within the budget beside it
