@@ -110,7 +110,8 @@ enum { CALIDROP_OPT_WRITE_SCORES = 1u, CALIDROP_OPT_WIDE_SELECTION = 2u };
 size_t calidrop_compress_workspace_bytes(const calidrop_params* p, int64_t total_tokens,
                                          int32_t max_seq_len);
 
-/* Bytes of device workspace calidrop_decode needs (0 on invalid params).                     */
+/* Bytes of device workspace calidrop_decode needs for caches of up to max_cache_len rows (0 on
+ * invalid params): it does not fall as max_cache_len grows.                                  */
 size_t calidrop_decode_workspace_bytes(const calidrop_params* p, int32_t max_cache_len);
 
 /* Named regions inside the compress workspace, for inspection by tests and tools after the
@@ -246,9 +247,10 @@ int calidrop_decode(const calidrop_params* p, const void* q_t, const void* k_c, 
  * a cache over several workgroups - lives in a fixed array of CALIDROP_STATIC_SCRATCH_BYTES of
  * device memory inside the library, one copy per GPU, held from the library's load until the process
  * ends.  The call allocates nothing and frees nothing.
- *   - A call whose scratch need, calidrop_decode_workspace_bytes(p, max_cache_len), exceeds
- *     CALIDROP_STATIC_SCRATCH_BYTES returns CALIDROP_EWORKSPACE and enqueues nothing: use
- *     calidrop_decode with a workspace for such shapes.
+ *   - A call whose scratch need - a (D + 2)-float partial per query head and split of its rows, no more
+ *     than calidrop_decode_workspace_bytes(p, max_cache_len) - exceeds CALIDROP_STATIC_SCRATCH_BYTES
+ *     returns CALIDROP_EWORKSPACE and enqueues nothing: use calidrop_decode with a workspace for such
+ *     shapes.
  *   - Every call on a GPU shares that GPU's array, which keeps the previous call's contents.  Nothing in
  *     it needs to start at zero (every partial a call reads, it has written before), so consecutive
  *     calls on one stream are safe; calls that overlap in time on one GPU (different streams, or

@@ -151,8 +151,8 @@ SplitPlan plan_splits(int heads_kv_total, int max_rows, int few = 0) {
   return SplitPlan{rps, ceil_div(max_rows, rps)};
 }
 
-// The most splits any prompt of up to max_rows plans: a number that does not fall as prompts grow, unlike a plan's own, so that a
-// workspace sized for a long prompt serves the shorter ones.  (A plan starts from at most `want` splits and halves only
+// The most splits any prompt or cache of up to max_rows plans: a number that does not fall as they grow, unlike a plan's own, so
+// that a workspace sized for a long one serves the shorter ones.  (A plan starts from at most `want` splits and halves only
 // prompts of up to 32 * 512 rows, to at most twice the splits that `few` allows.)
 int most_splits(int heads_kv_total, int max_rows, int few) {
   const int want = std::min(std::max(ceil_div(4096, heads_kv_total), 1), 32);
@@ -273,16 +273,22 @@ CompressLayout compress_layout(const calidrop_params* p, int64_t total_tokens, i
   return L;
 }
 
-struct DecodeLayout { size_t part_o, part_ml, total; SplitPlan sp; };
+// `total`: what a workspace for caches of up to these rows holds, the most splits of any of them (4096 rows are cut into 32,
+// 4097 into 17); `used`: what this call writes of it.
+struct DecodeLayout { size_t part_o, part_ml, used, total; SplitPlan sp; };
 
 DecodeLayout decode_layout(const calidrop_params* p, int32_t max_cache_len) {
   DecodeLayout L{};
-  L.sp = plan_splits(p->batch * p->n_kv_heads, max_cache_len);
-  const size_t slots = static_cast<size_t>(p->batch) * p->n_q_heads * L.sp.NS;
-  size_t off = 0;
-  L.part_o = off;  off += round256(slots * p->head_dim * sizeof(float));
-  L.part_ml = off; off += round256(slots * sizeof(float2));
-  L.total = off;
+  const int pairs = p->batch * p->n_kv_heads;
+  L.sp = plan_splits(pairs, max_cache_len);
+  const size_t heads = static_cast<size_t>(p->batch) * p->n_q_heads;
+  const auto out_bytes = [&](int splits) { return round256(heads * splits * p->head_dim * sizeof(float)); };
+  const auto ml_bytes = [&](int splits) { return round256(heads * splits * sizeof(float2)); };
+  const int most = most_splits(pairs, max_cache_len, 0);
+  L.part_o = 0;
+  L.part_ml = out_bytes(L.sp.NS);
+  L.used = L.part_ml + ml_bytes(L.sp.NS);
+  L.total = out_bytes(most) + ml_bytes(most);
   return L;
 }
 
@@ -1095,9 +1101,9 @@ int decode_entry(const calidrop_params* p_in, const void* q_t, const void* k_c, 
   const DecodeLayout L = decode_layout(p, max_cache_len);
   char* ws = static_cast<char*>(workspace);
   if (fixed_scratch) {
-    if (L.total > kStaticScratchBytes)
+    if (L.used > kStaticScratchBytes)
       return fail(CALIDROP_EWORKSPACE, "this call needs %zu bytes of scratch and the fixed array holds %zu: use "
-                  "calidrop_decode with a workspace", L.total, kStaticScratchBytes);
+                  "calidrop_decode with a workspace", L.used, kStaticScratchBytes);
     if ((rc = static_scratch_ptr(&ws))) return rc;       // the first HIP call, after all validation
   } else {
     if (!workspace || workspace_bytes < L.total)

@@ -75,6 +75,17 @@ def test_a_workspace_for_long_prompts_serves_shorter_ones(kw):
         assert cd.calidrop_compress_workspace_bytes(p, tot_small, small) <= cd.calidrop_compress_workspace_bytes(p, tot_big, big)
 
 
+@pytest.mark.parametrize("kw", [dict(batch=1), dict(batch=1, dtype=cd.FP32, head_dim=64), dict(batch=3, n_q_heads=40), dict(batch=16),
+                                dict(batch=64), dict(batch=1, n_q_heads=2, n_kv_heads=1)])
+def test_a_workspace_for_long_caches_serves_shorter_ones(kw):
+    # 8 KV heads: 4096 rows are 32 splits of 128, 4097 are 17 of 256
+    p = good(**kw)
+    rows = sorted({*range(1, 9000, 7), *range(4090, 4300), *range(9000, 140000, 501)})
+    for size in (cd.calidrop_decode_workspace_bytes, cd.calidrop_recalibrate_packed_workspace_bytes):
+        got = [size(p, n) for n in rows]
+        assert got == sorted(got) and got[0] > 0
+
+
 @pytest.mark.parametrize("lens,budget", [([1024] * 512, 512), ([600] * 4096, 512), ([8192], 512), ([32768 + 32], 2000)])
 def test_short_prompts_carry_no_histograms(lens, budget):
     # the multi-workgroup selection's histograms (50 KiB per KV head, 2 KiB per 8192 positions of one) belong to the calls

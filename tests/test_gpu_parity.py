@@ -649,6 +649,16 @@ def test_decode_form_follows_the_rows_that_live(dtype, Hq, Hkv, D, batch, budget
         H.check_decode_step(wl, bufs, x["q_dec"][0], b)
 
 
+def test_decode_of_fewer_rows_than_the_workspace_is_for():
+    # room for 4224 rows (17 splits of 256), told that 4000 are the most (32 splits of 128)
+    wl = small("bf16", 32, 8, 128, [4300], 16, 4000, 5, T=1, name="tighter_bound")
+    x = to_dev(synth.make_inputs(wl, 60))
+    bufs = H.gpu_compress(wl, x, extra_capacity=224)
+    bufs.decode(x["q_dec"][0], max_cache_len=4000)
+    torch.cuda.synchronize()
+    H.check_decode_step(wl, bufs, x["q_dec"][0], 0)
+
+
 @pytest.mark.parametrize("D,budget,threads", [(64, 128, 256), (64, 129, 512), (128, 129, 256)])
 def test_waves_of_many_short_caches_with_room(D, budget, threads):
     # 512 pairs with room for 400 rows more: D = 64 has 4 waves for up to 128 live rows, 8 beyond

@@ -64,6 +64,24 @@ def test_static_scratch_decode_one_workgroup_form_and_fp32():
     decode_both_ways(wl, x, bufs, 1)
 
 
+def test_static_scratch_decode_counts_the_partials_of_the_call():
+    # 512 query heads with caches of 4224 rows: 17 splits, 4.5 MB of partials, fit the array; a workspace for caches of up to
+    # these rows holds the 32 splits of 4096 rows, 8.5 MB
+    wl = synth.Workload("static_grown", 8, 64, 8, 128, [4300] * 8, 16, 4200, 5, "bf16", 1)
+    x = {k: v.to(DEV) for k, v in synth.make_inputs(wl, 74).items()}
+    bufs = H.gpu_compress(wl, x, extra_capacity=24)
+    assert cd.calidrop_decode_workspace_bytes(bufs.p, 4224) > cd.STATIC_SCRATCH_BYTES
+    q_t = x["q_dec"][0]
+    bufs.decode(q_t, pass_offsets=True)
+    torch.cuda.synchronize()
+    want = (bufs.out.clone(), bufs.a_lse.clone(), bufs.flags.clone())
+    bufs.out.zero_(); bufs.a_lse.zero_(); bufs.flags.fill_(9)
+    cd.calidrop_decode_static(bufs.p, q_t, bufs.k_c, bufs.v_c, bufs.cache_offsets, bufs.cache_lens, 4224,
+                              bufs.c_q, bufs.c_out, bufs.c_lse, bufs.out, bufs.a_lse, bufs.flags)
+    torch.cuda.synchronize()
+    assert torch.equal(bufs.out, want[0]) and torch.equal(bufs.a_lse, want[1]) and torch.equal(bufs.flags, want[2])
+
+
 def test_static_scratch_decode_rejects_what_does_not_fit():
     # 150 sequences x 16 query heads with 32 splits each: more partials than the fixed array holds.
     # Refused on the host, before any HIP call, with a clear message; bad arguments are refused as by
