@@ -838,13 +838,16 @@ int recal_packed_impl(const calidrop_params* p, const void* q_t, const void* k_e
 // D = 64 (288) 136 -> 115 -> 98, 64 x 3000 (1536) 777 -> 731 -> 701.  So four shares of fp32 streams (long ones, for the
 // matrix cores run at an eighth) and of few heads, two otherwise; beyond 2560 blocks 2 to 3 % are left and the planes grow.
 constexpr int64_t kH2oSplitBlocks = 2560;
-constexpr int kH2oMaxSplits = 4;
 int64_t h2o_blocks(const calidrop_params* p, int32_t max_seq_len) {
   return static_cast<int64_t>(ceil_div(max_seq_len, cd::h2o_block(2))) * p->batch * p->n_q_heads;
 }
+// What the calls of these heads are cut into whatever their prompts: the room a workspace has for shares.
+int h2o_most_splits(const calidrop_params* p) {
+  if (h2o_blocks(p, 1) > kH2oSplitBlocks) return 1;
+  return p->dtype == CALIDROP_FP32 || p->batch * p->n_q_heads < 32 ? 4 : 2;
+}
 int h2o_splits(const calidrop_params* p, int32_t max_seq_len) {
-  if (h2o_blocks(p, max_seq_len) > kH2oSplitBlocks) return 1;
-  return p->dtype == CALIDROP_FP32 || p->batch * p->n_q_heads < 32 ? kH2oMaxSplits : 2;
+  return h2o_blocks(p, max_seq_len) > kH2oSplitBlocks ? 1 : h2o_most_splits(p);
 }
 
 struct H2oLayout {
@@ -868,12 +871,16 @@ H2oLayout h2o_layout(const calidrop_params* p, int64_t total_tokens, int32_t max
   {
     // What splits needs, for this and any shorter prompts, so that sizes do not fall as prompts grow: a call with more than one
     // share has at most kH2oSplitBlocks blocks, so no more than `few` tokens.
+    const int most = h2o_most_splits(p);
     const int64_t few = std::min<int64_t>(total_tokens, kH2oSplitBlocks * cd::h2o_block(2) / p->n_q_heads + 1);
-    const int64_t plane = std::max(vote_plane(total_tokens, p->n_kv_heads), kH2oMaxSplits * vote_plane(few, p->n_kv_heads));
+    const int64_t plane = std::max(vote_plane(total_tokens, p->n_kv_heads), most * vote_plane(few, p->n_kv_heads));
     off += round256(static_cast<size_t>(plane) * (p->n_q_heads / p->n_kv_heads) * sizeof(float));
-    const int64_t heads = static_cast<int64_t>(p->batch) * p->n_q_heads;
-    const int64_t rows = std::min(heads * L.lse_stride, kH2oSplitBlocks * cd::h2o_block(2) + heads * 256);
-    L.row_part = off; off += round256(static_cast<size_t>(rows) * kH2oMaxSplits * sizeof(float2));
+    L.row_part = off;
+    if (most > 1) {
+      const int64_t heads = static_cast<int64_t>(p->batch) * p->n_q_heads;
+      const int64_t rows = std::min(heads * L.lse_stride, kH2oSplitBlocks * cd::h2o_block(2) + heads * 256);
+      off += round256(static_cast<size_t>(rows) * most * sizeof(float2));
+    }
   }
   L.score = off;   off += round256(toks * sizeof(float));
   L.bitmap = off;  off += round256(static_cast<size_t>(p->batch) * p->n_kv_heads * L.W32 * sizeof(uint32_t));

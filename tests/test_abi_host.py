@@ -86,6 +86,19 @@ def test_a_workspace_for_long_caches_serves_shorter_ones(kw):
         assert got == sorted(got) and got[0] > 0
 
 
+@pytest.mark.parametrize("kw,most", [(dict(batch=1), 2), (dict(batch=1, dtype=cd.FP32), 4), (dict(batch=1, n_q_heads=16), 4), (dict(batch=96), 1)])
+def test_h2o_workspace_has_room_for_the_shares_its_heads_can_have(kw, most):
+    # streams of up to 2560 blocks of 128 rows are shared, by two workgroups in bf16 from 32 heads on: that many planes for the
+    # tokens of such a call, or one for all tokens, and row partials (8 bytes) for its rows
+    p = good(**kw)
+    heads, n = p.batch * p.n_q_heads, 32768
+    votes, _ = cd.calidrop_compress_h2o_workspace_region(p, 0, n * p.batch, n, cd.REGION_VOTE_PLANES)
+    score, _ = cd.calidrop_compress_h2o_workspace_region(p, 0, n * p.batch, n, cd.REGION_SCORE)
+    plane = max(n * p.batch, most * (2560 * 128 // p.n_q_heads + 1)) * 4 * p.n_q_heads
+    parts = most * 8 * (2560 * 128 + heads * 256) if most > 1 else 0
+    assert score - votes <= plane + parts + 4096 * p.n_q_heads
+
+
 @pytest.mark.parametrize("lens,budget", [([1024] * 512, 512), ([600] * 4096, 512), ([8192], 512), ([32768 + 32], 2000)])
 def test_short_prompts_carry_no_histograms(lens, budget):
     # the multi-workgroup selection's histograms (50 KiB per KV head, 2 KiB per 8192 positions of one) belong to the calls
