@@ -301,10 +301,10 @@ __device__ __forceinline__ void radix_select(uint32_t* hist, SelectShared& sh, u
   need_eq = remaining;
 }
 
-// s / k for an odd k up to kSelMaxPool, rounded as the division rounds it: two corrections of s times the rounded reciprocal
-// (checked over every 24-bit significand for every such k).  Sums outside 2^-100 .. 2^100 other than 0 - their
+// s / k for an odd k up to kSelMaxPool, rounded as the division rounds it: one correction of s times the rounded reciprocal
+// (a test compares every 24-bit significand for every such k).  Sums outside 2^-100 .. 2^100 other than 0 - their
 // remainders may leave the range - and what is no number are for the division itself.
-__device__ __forceinline__ float divide_small(float s, float k, float rk) {
+__host__ __device__ __forceinline__ float divide_small(float s, float k, float rk) {
   const float q = s * rk;
   return fmaf(fmaf(-k, q, s), rk, q);
 }

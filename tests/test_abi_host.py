@@ -168,6 +168,48 @@ def test_streamed_rows_bypass_the_caches(tmp_path):
     assert seen == 32
 
 
+@pytest.mark.skipif(not os.path.exists("/opt/rocm/bin/hipcc"), reason="needs hipcc")
+def test_short_division_rounds_as_the_division_does(tmp_path):
+    # the pooled score is sum / k: every significand, for every pooling width of the single-workgroup selection, at 1 and at both
+    # ends of the range in which it divides so; without the correction, from a reciprocal one ulp off, some must differ
+    src, exe = tmp_path / "divide.hip", tmp_path / "divide"
+    src.write_text(f'''
+#include "{ROOT}/paper_2507_19906_amd/csrc/cd_select.h"
+#include <cstdio>
+#include <cstring>
+#include <thread>
+#include <vector>
+static long wrong[cd::kSelMaxPool + 1][2];
+static void check(int width) {{
+  const float k = static_cast<float>(width), rk = 1.f / k;
+  uint32_t bits;
+  memcpy(&bits, &rk, 4);
+  bits += 1;
+  float off;
+  memcpy(&off, &bits, 4);
+  for (uint32_t base : {{cd::kDivideLow, 127u << 23, cd::kDivideHigh - (1u << 23)}})
+    for (uint32_t i = 0; i < (1u << 23); ++i) {{
+      const uint32_t u = base + i;
+      float s;
+      memcpy(&s, &u, 4);
+      wrong[width][0] += cd::divide_small(s, k, rk) != s / k;
+      wrong[width][1] += base == (127u << 23) && s * off != s / k;
+    }}
+}}
+int main() {{
+  std::vector<std::thread> t;
+  for (int width = 1; width <= cd::kSelMaxPool; width += 2) t.emplace_back(check, width);
+  for (auto& x : t) x.join();
+  for (int width = 1; width <= cd::kSelMaxPool; width += 2) printf("%d %ld %ld\\n", width, wrong[width][0], wrong[width][1]);
+}}
+''')
+    subprocess.run(["/opt/rocm/bin/hipcc", "--offload-arch=gfx950", "-O2", "-std=c++17", "-pthread", "-Xarch_host", "-mfma", "-Xarch_host",
+                    "-ffp-contract=off", "-w", str(src), "-o", str(exe)], check=True)
+    rows = [[int(x) for x in l.split()] for l in subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.splitlines()]
+    assert [r[0] for r in rows] == list(range(1, 16, 2))
+    assert all(r[1] == 0 and r[2] > 0 for r in rows), rows
+
+
 @pytest.mark.parametrize("lens,heads,w,dtype", [
     ([131072], 8, 64, "bf16"), ([131200], 8, 64, "bf16"), ([140000], 8, 64, "bf16"), ([8192], 8, 32, "bf16"), ([500], 2, 16, "fp32"),
     ([32768] * 32, 8, 32, "bf16"), ([13804] * 13, 2, 32, "fp32"), ([3000] * 20, 8, 64, "fp32"), ([2816, 2816, 2816], 1, 8, "fp32"), ([20000] * 4, 8, 32, "fp32"),
