@@ -98,34 +98,69 @@ float logit_scale(const calidrop_params* p) {
   return p->scale > 0.f ? p->scale : 1.0f / std::sqrt(static_cast<float>(p->head_dim));
 }
 
+int live_rows(const calidrop_params* p, int max_cache_len) { return std::min(p->budget, max_cache_len); }
+
+// Waves of a decode workgroup that has a whole (sequence, KV head).  8, so that its compute unit has more rows in flight, but 4
+//   - for caches of at most 4 tiles (one tile a wave);
+//   - in fp32, where a lane has two pieces of every row in flight (8 pairs of 1002 rows, D = 128 29.6 us with 4 waves, 33.4
+//     with 8, 512 pairs of 308 31.0 / 35.3, D = 64 15.6 / 16.6, 16.8 / 18.7);
+//   - in bf16 with D = 128 where the pairs fill the chip (12.8 / 13.0 at 512 rows; 40.5 / 42.0 at 2048, where three such
+//     workgroups share a compute unit and one's merge overlaps the others' streaming; with D = 64, 256 pairs of 500 rows,
+//     9.5 / 8.5);
+//   - where the partial outputs of 8 do not fit what a launch may use of LDS without raising the limit.
+// Where the pairs fill the chip it is the rows that live which count: 1024 pairs of 64 rows, D = 64, with room for 512, 8.6
+// with 4 waves, 9.7 with 8.
+size_t decode_wave_lds(const calidrop_params* p) {
+  return static_cast<size_t>(p->n_q_heads / p->n_kv_heads) * (p->head_dim + 2) * sizeof(float);
+}
+int decode_waves(const calidrop_params* p, int max_cache_len) {
+  const int64_t pairs = static_cast<int64_t>(p->batch) * p->n_kv_heads;
+  const int tiles = ceil_div(pairs < 192 ? max_cache_len : live_rows(p, max_cache_len), cd::kTileRows);
+  return tiles <= 4 || p->dtype == CALIDROP_FP32 || (pairs >= 192 && p->head_dim == 128) || 8 * decode_wave_lds(p) > 48 * 1024 ? 4 : 8;
+}
+
 // Decode runs as one workgroup per (sequence, KV head) - one launch, no workspace - or with the rows of a pair split over
-// workgroups and a second launch that merges them.
-// One workgroup moves some 40 GB/s, so what it costs is its rows, nearly twice that where the fullest of the 256 compute units
-// has two of them, and a share of the memory traffic of all.  The split form costs its two launches, the traffic and the
-// workgroups whose rows hold nothing yet, and no less than 8 to 9.3 us from the host, process by process (9.4 below: at 512
-// rows, two tiles for each of 8 waves, the estimate for one workgroup is high).
-// Examples, us per call, one workgroup / split: 8 pairs of 512 rows, bf16, D = 128 7.7 / 7.5 (from the host 8.2 / 8.8), of
-// 1022 12.5 / 7.5, of 2044 27.3 / 8.0; 64 pairs of 1026 18.1 / 12.7; 184 pairs of 1026 20.5 / 22.9; 296 pairs of 809 30.2 /
-// 26.3; fp32, 8 pairs of 1002 29.6 / 10.2.
+// workgroups and a second launch that merges them.  The form that is expected to take less time is taken.
+//
+// One workgroup: a start, its rows, the tiles of its fullest wave (a step every 32 x waves rows: fp32, D = 64, 8 pairs of
+// 384 rows 7.8 us, of 400 8.9) and a share of the traffic of all.  Where the fullest of the 256 compute units has two, rows and
+// tiles cost nearly twice that; where every XCD has at most one (8 pairs), its L2 still has rows of the call before if that
+// read the same caches, and they cost less (bf16, D = 128, 512 rows: 8 pairs 7.5 us, 16 pairs 8.8; all from memory 9.8, 9.9).
+// Split: the two launches, which the host does not issue faster than in `host` us, the traffic of all, and workgroups whose
+// rows hold nothing yet.
+//
+// us per call, one workgroup / split, from the host: bf16, D = 128, 8 pairs of 512 rows 7.5 / 7.7, of 520 7.8 / 7.7, of 1016
+// 12.2 / 7.7, of 2044 28.3 / 8.1; 64 pairs of 384 8.2 / 7.9, of 1016 17.4 / 9.9; 184 pairs of 1016 20.4 / 21.7; 320 pairs of
+// 776 28.6 / 25.6; D = 64, 8 pairs of 768 7.3 / 7.4, of 900 9.0 / 7.4; fp32, D = 64, 64 pairs of 384 9.4 / 8.2; D = 128, 8
+// pairs of 200 9.7 / 10.3, of 1016 30.4 / 10.6.
+// Fitted to 3500 calls (2 to 512 pairs, 48 to 4090 rows, both types and head dimensions), caches that were just read and, from
+// 9 pairs on, caches that were not, those in which the forms are close counting most: the form taken is 0.1 to 0.4 % (fp32,
+// D = 128: 0.8 %) slower on average than the better one, 27 % at most (8 pairs of 512 rows from memory, 9.8 / 7.9).
+//
 // Both follow the rows that live, which only the device knows, and max_cache_len may be far above them: with room for 2048
 // rows, 64 pairs of 200 live ones take 6.0 in one workgroup and 10.5 split, 184 pairs in fp32 12.0 and 25.8.  The longest cache
 // is therefore taken to hold `budget` rows, what a compressed prompt starts with; from there on the split form gains on the
 // other with every row.  Few pairs with room for more than 2048 rows are priced full: one workgroup would take 25 to 70 us for
 // what the split form does in 8 to 30, and loses up to 4 while it is empty.
-struct DecodeCost { float fused, row, pair_row, split, split_pair_row, split_room; };      // us; per row, per (pair, row)
-int live_rows(const calidrop_params* p, int max_cache_len) { return std::min(p->budget, max_cache_len); }
+struct DecodeCost {
+  float start, row, tile, pair_row, near, crowded;      // one workgroup; near, crowded: factors of row and tile
+  float host, split, split_pair_row, split_room;        // us; the latter two per (pair, row)
+};
 bool decode_splits(const calidrop_params* p, int max_cache_len) {
   const int64_t pairs = static_cast<int64_t>(p->batch) * p->n_kv_heads;
   if (pairs > 512) return false;
-  constexpr DecodeCost kCost[2][2] = {
-      {{3.83f, .00615f, 1.58e-5f, 6.9f, 4.24e-5f, 4.05e-6f}, {3.09f, .01196f, 3.09e-5f, 7.16f, 8.54e-5f, 5.48e-6f}},
-      {{3.99f, .01229f, 3.12e-5f, 7.1f, 8.20e-5f, 6.09e-6f}, {5.14f, .02457f, 6.77e-5f, 9.1f, 1.78e-4f, 1.15e-5f}}};
+  constexpr DecodeCost kCost[2][2] = {{{3.57f, .00512f, .286f, 1.24e-5f, .805f, 1.87f, 7.7f, 6.48f, 3.91e-5f, 2.98e-6f},
+                                       {3.21f, .01159f, .12f, 2.34e-5f, .689f, 1.87f, 7.7f, 6.98f, 7.68e-5f, 3.95e-6f}},
+                                      {{3.56f, .00569f, 1.02f, 1.88e-5f, .855f, 1.87f, 8.2f, 7.34f, 7.59e-5f, 4.58e-6f},
+                                       {5.14f, .02457f, 0.f, 6.77e-5f, 1.f, 1.82f, 9.4f, 9.1f, 1.78e-4f, 1.15e-5f}}};
   const DecodeCost& c = kCost[p->dtype == CALIDROP_FP32][p->head_dim == 128];
   const bool priced_full = pairs < 192 && max_cache_len > 2048;
-  const float rows = static_cast<float>(priced_full ? max_cache_len : live_rows(p, max_cache_len));
-  const float all = rows * static_cast<float>(pairs), room = static_cast<float>(max_cache_len) * static_cast<float>(pairs) - all;
-  const float fused = c.fused + c.row * rows * (pairs > 256 ? 1.82f : 1.f) + c.pair_row * all;
-  return std::max(9.4f, c.split + c.split_pair_row * all + c.split_room * room) < fused;
+  const int rows = priced_full ? max_cache_len : live_rows(p, max_cache_len);
+  const float all = static_cast<float>(rows) * static_cast<float>(pairs), room = static_cast<float>(max_cache_len) * static_cast<float>(pairs) - all;
+  const int tiles = ceil_div(rows, cd::kTileRows * decode_waves(p, max_cache_len));
+  const float factor = pairs <= 8 ? c.near : pairs > 256 ? c.crowded : 1.f;
+  const float one = c.start + (c.row * static_cast<float>(rows) + c.tile * static_cast<float>(tiles)) * factor + c.pair_row * all;
+  return std::max(c.host, c.split + c.split_pair_row * all + c.split_room * room) < one;
 }
 
 // How the rows of a streaming-attention pass are split over workgroups.
@@ -591,21 +626,10 @@ int decode_impl(const calidrop_params* p, const void* q_t, const void* k_c, cons
     fa.sl2 = logit_scale(p) * cd::kLog2e; fa.theta1 = p->theta1; fa.theta2 = p->theta2;
     fa.c_q = c_q; fa.c_out = c_out; fa.c_lse = c_lse; fa.out = out; fa.a_lse = a_lse; fa.flags = flags;
     const int tiles = ceil_div(max_cache_len, cd::kTileRows);
-    const size_t lds_per_wave = static_cast<size_t>(G) * (D + 2) * sizeof(float);
-    // 8 waves per workgroup, so that its compute unit has more rows in flight, but 4 for caches of at most 4 tiles, in fp32 (two
-    // pieces of every row in flight per lane: 8 pairs of 1002 rows, D = 128 29.6 us with 4 waves, 33.4 with 8, 512 pairs of 308
-    // 31.0 / 35.3, D = 64 15.6 / 16.6, 16.8 / 18.7) and in bf16 with D = 128 where the pairs fill the chip (12.8 / 13.0 at 512
-    // rows; 40.5 / 42.0 at 2048, where three such workgroups share a compute unit and one's merge overlaps the others'
-    // streaming; with D = 64, 256 pairs of 500 rows, 9.5 / 8.5).
-    // Where the pairs fill the chip it is the rows that live which count: 1024 pairs of 64 rows, D = 64, with room for 512, 8.6
-    // with 4 waves, 9.7 with 8.
-    const int pairs = p->batch * p->n_kv_heads;
-    const int held = pairs < 192 ? tiles : ceil_div(live_rows(p, max_cache_len), cd::kTileRows);
-    int nw = held <= 4 || sizeof(T) == 4 || (pairs >= 192 && D == 128) ? 4 : 8;
-    while (nw > 4 && nw * lds_per_wave > 48 * 1024) nw /= 2;     // what a launch may use without raising the limit
+    const int nw = decode_waves(p, max_cache_len);
     fa.xcd_blocks = (tiles >= 32 && p->batch % 8 == 0) ? 1 : 0;
     const dim3 grid(p->n_kv_heads, p->batch);
-    const size_t lds = nw * lds_per_wave;
+    const size_t lds = nw * decode_wave_lds(p);
     if constexpr (sizeof(T) == 2) {
       if (nw == 8) {
         hipLaunchKernelGGL((cd::decode_fused_kernel<T, D, 8>), grid, dim3(512), lds, st, fa);

@@ -604,19 +604,24 @@ def test_chunk_partials_merged_in_pass_2_or_ahead(dtype, D, w, lens):
             off += n
 
 
-@pytest.mark.parametrize("dtype,Hq,Hkv,D,batch,budget", [
-    ("bf16", 16, 4, 128, 2, 516),       # the last number of rows one workgroup takes and the first that are split: 8 pairs,
-    ("bf16", 16, 4, 128, 2, 517),       # where the two launches cost the host 8.8 us
-    ("fp32", 8, 2, 64, 20, 399), ("fp32", 8, 2, 64, 20, 400),
-    ("bf16", 4, 4, 64, 66, 750),        # more pairs than compute units: 264
-    ("fp32", 8, 4, 128, 70, 287),       # 280 pairs, split
-    ("bf16", 8, 8, 64, 24, 1200)])      # 192 pairs, 8 waves
-def test_decode_forms_at_their_borders(dtype, Hq, Hkv, D, batch, budget):
+@pytest.mark.parametrize("dtype,Hq,Hkv,D,batch,budget,launches", [
+    ("bf16", 16, 4, 128, 2, 516, 1), ("bf16", 16, 4, 128, 2, 517, 1),
+    ("bf16", 16, 4, 128, 2, 519, 1),       # the last number of rows one workgroup takes and the first that are split: 8 pairs,
+    ("bf16", 16, 4, 128, 2, 520, 2),       # 7.75 us / 7.73 with rows that were just read
+    ("bf16", 16, 4, 128, 4, 355, 1), ("bf16", 16, 4, 128, 4, 356, 2),      # 16 pairs: more than one on an XCD
+    ("fp32", 8, 2, 64, 20, 256, 1), ("fp32", 8, 2, 64, 20, 257, 2),        # two tiles a wave, and three
+    ("fp32", 8, 2, 64, 20, 399, 2), ("fp32", 8, 2, 64, 20, 400, 2),
+    ("bf16", 4, 4, 64, 66, 516, 1), ("bf16", 4, 4, 64, 66, 517, 2),        # more pairs than compute units: 264
+    ("bf16", 4, 4, 64, 66, 750, 2),
+    ("fp32", 8, 4, 128, 70, 286, 1), ("fp32", 8, 4, 128, 70, 287, 2),      # 280 pairs
+    ("bf16", 8, 8, 64, 24, 1200, 1)])      # 192 pairs, 8 waves
+def test_decode_forms_at_their_borders(dtype, Hq, Hkv, D, batch, budget, launches):
     lens = [budget + 40, budget - 5, 60] + [budget + 1 + b for b in range(batch - 3)]
     lens = lens[:batch]
     wl = small(dtype, Hq, Hkv, D, lens, 16, budget, 5, T=2, name=f"forms_{batch}x{budget}")
     x = to_dev(synth.make_inputs(wl, 57))
     bufs = H.gpu_compress(wl, x)
+    assert len(H.captured_launches(lambda: bufs.decode(x["q_dec"][0]))) == launches
     rep = {}
     for t in range(wl.decode_steps):
         bufs.decode(x["q_dec"][t])
