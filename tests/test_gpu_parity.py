@@ -92,12 +92,13 @@ def test_scoring_at_the_edges_of_its_key_stages(dtype, Hq, Hkv, D, w):
 @pytest.mark.parametrize("dtype,D,budget", [("bf16", 128, 64), ("fp32", 64, 200), ("bf16", 64, 300),
                                             ("bf16", 128, 600)])
 def test_many_sequences_single_workgroup_decode(dtype, D, budget):
-    # >= 192 (sequence, KV head) pairs: decode runs as one workgroup per pair (4, 8 or 16 waves)
+    # 200 (sequence, KV head) pairs of short caches: decode runs as one workgroup per pair, with 4 or 8 waves
     g = torch.Generator().manual_seed(budget)
     lens = torch.randint(budget // 2, 3 * budget, (100,), generator=g).tolist()
     wl = small(dtype, 8, 2, D, lens, 16, budget, 5, T=3, name=f"many_seqs_{dtype}_{D}_{budget}")
     x = to_dev(synth.make_inputs(wl, 17))
     bufs = H.gpu_compress(wl, x, extra_capacity=8)
+    assert len(H.captured_launches(lambda: bufs.decode(x["q_dec"][0]))) == 1
     rep = {}
     seqs = [0, 1, 37, 99, int(np.argmin(lens)), int(np.argmax(lens))]
     for b in seqs:
@@ -556,21 +557,38 @@ def test_exact_ties_with_multi_workgroup_selection(wide_selection):
     test_exact_ties_lower_index_wins(20016, 1, 3000, 2500)
 
 
+def gathered_in(wl):
+    """Where a compress call of few heads gathers the retained rows, read from its launches."""
+    x = to_dev(synth.make_inputs(wl, 1))
+    bufs = H.gpu_compress(wl, x)
+    launches = H.captured_launches(lambda: bufs.compress(x["q_win"], x["k"], x["v"], x["seq_offsets"]))
+    pass_, merge = launches[-2:]
+    assert merge[1:3] == (wl.batch, 1)
+    if merge[0] > wl.n_q_heads:                  # more workgroups a sequence than query heads
+        return "merge"
+    assert merge[0] == wl.n_q_heads and pass_[1] == wl.n_kv_heads
+    return "pass" if pass_[2] > wl.batch else "elsewhere"
+
+
 @pytest.mark.parametrize("dtype,budget", [("fp32", 64), ("fp32", 700), ("fp32", 2688), ("fp32", 2690), ("bf16", 1500),
                                           ("fp32", 10912), ("fp32", 10913)])
 def test_gather_workgroups_behind_the_streaming_ones(dtype, budget):
     # 256 pieces of 16 bytes per gathering workgroup, 16 rows in fp32 and 32 in bf16 here.  Budget 64: 12 of them per KV head,
     # less than one plane of the streaming pass's 23 splits; 700, 2688, 2690 and 1500: 132, 504, 507 and 141, several planes
     # with a partial last one; 10912: 4092 for the six (sequence, KV head) pairs, the pass still carries them; 10913: 4098,
-    # a launch of their own
+    # in the launch that merges the partials
     lens = [2900, budget - 1, 2850] if budget < 2800 else [11500, budget - 1, 10990]
-    run_case(small(dtype, 4, 2, 64, lens, 16, budget, 5, T=1, name=f"gather_{budget}"))
+    wl = small(dtype, 4, 2, 64, lens, 16, budget, 5, T=1, name=f"gather_{budget}")
+    run_case(wl)
+    assert gathered_in(wl) == ("pass" if budget < 10913 else "merge")
 
 
 @pytest.mark.parametrize("n", [28672, 28673])
 def test_gather_beside_short_and_long_splits(n):
-    # splits of 896 rows: the streaming pass carries the gather; of 1024: it has a launch of its own
-    run_case(small("bf16", 8, 2, 128, [n], 16, 200, 5, T=1, name=f"gather_n{n}"))
+    # splits of 896 and of 1024 rows: the launch that merges the partials carries the gather
+    wl = small("bf16", 8, 2, 128, [n], 16, 200, 5, T=1, name=f"gather_n{n}")
+    run_case(wl)
+    assert gathered_in(wl) == "merge"
 
 
 @pytest.mark.parametrize("dtype,D,w,lens", [
@@ -677,13 +695,15 @@ def test_waves_of_many_short_caches_with_room(D, budget, threads):
         H.check_decode_step(wl, bufs, x["q_dec"][0], b)
 
 
-@pytest.mark.parametrize("dtype,D,lens,budget", [
-    ("bf16", 128, [12288, 60], 300),       # splits of 384 rows: the gather rides in the streaming pass
-    ("bf16", 128, [12289, 299], 300),      # of 512: in the launch that merges; a prompt within the budget beside it
-    ("fp32", 64, [200, 150], 260)])        # nothing to evict, no pass: in the merging launch as well
-def test_gather_in_the_pass_and_in_the_merge(dtype, D, lens, budget):
+@pytest.mark.parametrize("dtype,D,lens,budget,place", [
+    ("bf16", 128, [12288, 60], 300, "pass"),       # splits of 384 rows: the gather rides in the streaming pass
+    ("bf16", 128, [12289, 299], 300, "merge"),     # of 512: in the launch that merges; a prompt within the budget beside it
+    ("fp32", 64, [200, 150], 260, "merge")])       # nothing to evict, no pass: in the merging launch as well
+def test_gather_in_the_pass_and_in_the_merge(dtype, D, lens, budget, place):
     # 16 (sequence, KV head) pairs; 512 and 256 threads a workgroup, so that 16-byte pieces end inside one
-    run_case(small(dtype, 16, 8, D, lens, 16, budget, 5, T=1, name=f"gather_after_{lens[0]}"))
+    wl = small(dtype, 16, 8, D, lens, 16, budget, 5, T=1, name=f"gather_after_{lens[0]}")
+    run_case(wl)
+    assert gathered_in(wl) == place
 
 
 @pytest.mark.parametrize("batch", [96, 97])

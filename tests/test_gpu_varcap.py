@@ -118,7 +118,7 @@ def test_packed_caches_one_workgroup_decode(dtype, D):
 
 @pytest.mark.parametrize("dtype,D", [("bf16", 64), ("fp32", 64), ("bf16", 128)])
 def test_packed_caches_split_decode(dtype, D):
-    # few pairs and caches above 2048 rows: the decode step splits the rows over workgroups (two launches)
+    # few pairs and caches of 2100 rows: the decode step splits the rows over workgroups (two launches)
     lens = [2600, 1000, 3100, 2101]
     extras = [5, 12, 0, 40]
     wl = small(dtype, 4, 2, D, lens, 16, 2100, 5, 3, f"varcap_split_{dtype}_{D}")
@@ -127,7 +127,7 @@ def test_packed_caches_split_decode(dtype, D):
 
 @pytest.mark.parametrize("dtype,budget", [("bf16", 64), ("bf16", 600), ("fp32", 200)])
 def test_packed_caches_many_sequences(dtype, budget):
-    # >= 192 (sequence, KV head) pairs: one workgroup per pair with 4 or 8 waves; 100 different capacities
+    # 200 (sequence, KV head) pairs of short caches: one workgroup per pair with 4 or 8 waves; 100 different capacities
     rng = np.random.default_rng(budget)
     lens = rng.integers(budget // 2, 3 * budget, 100).tolist()
     extras = rng.integers(0, 41, 100).tolist()

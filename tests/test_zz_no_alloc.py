@@ -2,7 +2,7 @@
 scratch is a fixed per-GPU array inside the library) - against calidrop_decode on the same inputs:
 same kernels, so the results must agree bit for bit, and with the oracle to the stated tolerance.
 Two calls in a row, the second with a smaller input, both in the form of the step that uses the
-scratch (few (sequence, KV head) pairs, cache above 2048 rows: rows split over workgroups)."""
+scratch (few (sequence, KV head) pairs of thousands of rows: rows split over workgroups)."""
 import ctypes
 
 import numpy as np
@@ -24,9 +24,10 @@ def prepared(lens, budget, seed, dtype="bf16", D=128):
     return wl, x, bufs
 
 
-def decode_both_ways(wl, x, bufs, t):
+def decode_both_ways(wl, x, bufs, t, launches=2):
     q_t = x["q_dec"][t]
     p = bufs.p
+    assert len(H.captured_launches(lambda: bufs.decode(q_t, pass_offsets=True))) == launches      # split rows: two
     need = cd.calidrop_decode_workspace_bytes(p, bufs.max_cache_len)
     assert 0 < need <= cd.STATIC_SCRATCH_BYTES
     bufs.decode(q_t, pass_offsets=True)                      # the existing entry point, caller's workspace
@@ -60,8 +61,8 @@ def test_static_scratch_decode_matches_the_workspace_entry_point_twice_in_a_row(
 def test_static_scratch_decode_one_workgroup_form_and_fp32():
     # the form of the step that needs no scratch goes through the same entry point unchanged
     wl, x, bufs = prepared([700, 60, 900], 96, seed=73, dtype="fp32", D=64)
-    decode_both_ways(wl, x, bufs, 0)
-    decode_both_ways(wl, x, bufs, 1)
+    decode_both_ways(wl, x, bufs, 0, launches=1)
+    decode_both_ways(wl, x, bufs, 1, launches=1)
 
 
 def test_static_scratch_decode_counts_the_partials_of_the_call():
