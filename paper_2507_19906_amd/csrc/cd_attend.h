@@ -255,8 +255,9 @@ struct AttendWave {
       }
     }
     for (int row0 = row_first; row0 < row_end; row0 += row_step) {
-      // V of this tile first, then K of the next tile: both in flight during the QK product.  (In fp32 V used to be fetched row by
-      // row inside the PV product, its latency in every tile: given set of 2 prompts of 60000 tokens, 8 KV heads, D = 128 192 ->
+      // V of this tile is in flight during the QK product, K of the next tile, requested behind it, during the softmax; whether
+      // there is a next tile is a branch, so the wait ahead of PV is for all of both.  (In fp32 V used to be fetched row by row
+      // inside the PV product, its latency in every tile: given set of 2 prompts of 60000 tokens, 8 KV heads, D = 128 192 ->
       // 160 us, D = 64 94 -> 83; one cache of 100 rows 9.8 -> 6.9.  The registers of a second tile of both, in the decode kernel
       // where a workgroup has a compute unit to itself, gain nothing: bf16, 8 heads of 512 rows 7.9 -> 8.3 us.)
       u32x4 vf[8 * NVP];
