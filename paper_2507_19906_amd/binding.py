@@ -504,8 +504,10 @@ class CompressBuffers:
         self.flags = torch.zeros((nb, Hq), dtype=torch.uint8, device=device)
 
     def _compressed(self):
-        # live rows of the longest cache as far as the host knows: what compress leaves, plus one per append
+        # live rows of the longest cache as far as the host knows: what compress leaves, plus one per append.  decode says so in
+        # the budget of its call, hence no fewer than a budget may be.
         self.live_rows = min(self.p.budget, self.max_seq_len)
+        self._told_rows = max(self.live_rows, self.p.window + 1)
 
     def compress(self, q_win, k, v, seq_offsets, q_cal=None, stream=None, win_lse=None):
         """win_lse: [batch][Hq][w] fp32 log-sum-exp of the window rows from the caller's prefill
@@ -561,18 +563,20 @@ class CompressBuffers:
         if not pass_offsets and (mcl != self.cap or not self.uniform):
             raise ValueError("the offsets can only be left out when every capacity equals max_cache_len")
         offs = self.cache_offsets if pass_offsets else None
-        p = self.p
-        if self.live_rows != p.budget:
+        p, rows = self.p, self._told_rows
+        if rows != p.budget:
             # the library takes the budget for the rows the longest cache holds when it chooses between two forms of the step
-            # (which give the same result): 8 KV heads of 1500 appended rows 19 us as one workgroup each, 8 split
+            # (which give the same result): 8 KV heads of 1500 appended rows 19 us as one workgroup each, 8 split.  A copy of
+            # the caller's params as they are now, 0.2 us.
             p = Params.from_buffer_copy(p)
-            p.budget = min(max(self.live_rows, p.window + 1), 1 << 24)
+            p.budget = rows
         calidrop_decode(p, q_t, self.k_c, self.v_c, offs, self.cache_lens, mcl, self.c_q, self.c_out,
                         self.c_lse, self.out, self.a_lse, self.flags, self.ws_decode, stream)
 
     def append(self, k_new, v_new, stream=None):
         """Append the K/V rows of the token just generated ([batch][Hkv][D]) to every sequence."""
         self.live_rows = min(self.live_rows + 1, self.cap)
+        self._told_rows = max(min(self.live_rows, 1 << 24), self.p.window + 1)
         calidrop_append(self.p, k_new, v_new, self.k_c, self.v_c, self.cache_offsets, self.cache_lens, stream)
 
     def recalibrate(self, q_t, k, v, seq_offsets, stream=None):
